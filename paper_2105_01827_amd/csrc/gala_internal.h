@@ -207,6 +207,8 @@ int static_scratch_init();
 int launch_ntt(const gala_ctx *ctx, void *stream, const u64 *src, u64 *dst, size_t count, int inverse);
 // the same with the tables of another modulus of the context (dev_q, dev_p or dev_P)
 int launch_ntt_mod(const gala_ctx *ctx, void *stream, const u64 *src, u64 *dst, size_t count, int inverse, const NttDev &T);
+// the n = 2048 radix-8 form of launch_ntt, modulo q or modulo the special prime (uses_fast_perm contexts only)
+int launch_ntt_2048(const gala_ctx *ctx, void *stream, const u64 *src, u64 *dst, size_t count, int inverse, bool special);
 
 // Batched client steps on internal-form ciphertexts (one workgroup per ciphertext).
 int launch_encrypt(const gala_ctx *ctx, void *stream, const u64 *s_hat, const u64 *slots, const u64 *seeds, int count,

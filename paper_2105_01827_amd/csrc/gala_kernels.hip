@@ -853,6 +853,9 @@ inline int last_error() { return (int)hipGetLastError(); }
 // ---------------------------------------------------------------------------
 int launch_ntt_mod(const gala_ctx *c, void *stream, const u64 *src, u64 *dst, size_t count, int inverse, const NttDev &T) {
     if (!count) return 0;
+    // both ciphertext-side moduli of a context on the n = 2048 kernels have their tables
+    if (uses_fast_perm(c) && (&T == &c->dev_q || (c->special && &T == &c->dev_P)))
+        return launch_ntt_2048(c, stream, src, dst, count, inverse, &T != &c->dev_q);
     hipStream_t st = (hipStream_t)stream;
     const size_t lds = sizeof(u64) * c->n;
     by_threads(c->n, [&](auto nt) {

@@ -827,6 +827,40 @@ __global__ __launch_bounds__(NT) void hstperm_pack_2048(const u64 *ct_in, const 
 }
 
 
+// ---- plain transforms (import, export, key upload) ------------------------------------------------------------
+// One workgroup per polynomial, forward or inverse, canonical results, in place or not (a polynomial is read whole
+// before its first word is written).  Few polynomials: bound by one workgroup's chain of passes, so three exchanges
+// instead of the any-n kernel's eleven barriers; many: by the butterflies.  Against that kernel: encrypting and
+// exporting 1024 ciphertexts 83.7 -> 68.2 us, a 16x128 FC layer with one ciphertext imported and one exported
+// 41.7 -> 28.8 us.
+// Inputs as the any-n kernel takes them: below 4q forward, below 2q inverse.
+template <bool INVERSE>
+__global__ __launch_bounds__(NT) void ntt_2048(const u64 *src, u64 *dst, Tables2048 T) {
+    __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
+    const int tid = threadIdx.x;
+    src += (size_t)blockIdx.x * N;
+    dst += (size_t)blockIdx.x * N;
+    u64 a[PER];
+    if (INVERSE) {
+        // coalesced reads, then through LDS to the eight consecutive coefficients a thread starts from
+#pragma unroll
+        for (int k = 0; k < PER; ++k) bufB[pad(tid + k * NT)] = src[tid + k * NT];
+        __syncthreads();
+        const u64 *pi = bufB + pad(tid << 3);
+#pragma unroll
+        for (int k = 0; k < PER; ++k) a[k] = pi[k];
+        inverse_in_regs(a, bufA, bufB, T, tid);       // LDS phases A B A; the reads of bufB above precede its barriers
+#pragma unroll
+        for (int k = 0; k < PER; ++k) dst[tid + k * NT] = a[k];
+    } else {
+#pragma unroll
+        for (int k = 0; k < PER; ++k) a[k] = csub_dev(src[tid + k * NT], T.mod.q2);
+        forward_to_lds(a, bufA, bufB, T, tid);
+#pragma unroll
+        for (int k = 0; k < PER; ++k) dst[tid + k * NT] = reduce64(bufA[pad(tid + k * NT)], T.mod);
+    }
+}
+
 // ---- the client's two steps with the radix-8 transforms (one workgroup per ciphertext) ------------------------
 // ct = (-a s + e + delta m, a) (Sec. II-C(1)), bit for bit the any-n kernel: m = the plaintext polynomial of the
 // slots, a uniform, e Gaussian, all drawn from the ciphertext's seed by coefficient index.
@@ -1369,6 +1403,15 @@ int launch_hstperm_pack_2048(const gala_ctx *c, void *stream, const u64 *ct_in, 
         hipLaunchKernelGGL((hstperm_pack_2048<3, true>), grid, dim3(NT), 0, st, ct_in, digits, terms, kblocks, keys2, out, T, c->ndigits, batch);
     else
         hipLaunchKernelGGL((hstperm_pack_2048<0, true>), grid, dim3(NT), 0, st, ct_in, digits, terms, kblocks, keys2, out, T, c->ndigits, batch);
+    return (int)hipGetLastError();
+}
+
+int launch_ntt_2048(const gala_ctx *c, void *stream, const u64 *src, u64 *dst, size_t count, int inverse, bool special) {
+    if (!count) return 0;
+    const Tables2048 T = special ? make_tables(c, c->d_tw2P, c->dev_P) : make_tables(c, c->d_tw2, c->dev_q);
+    hipStream_t st = (hipStream_t)stream;
+    if (inverse) hipLaunchKernelGGL(ntt_2048<true>, dim3((unsigned)count), dim3(NT), 0, st, src, dst, T);
+    else hipLaunchKernelGGL(ntt_2048<false>, dim3((unsigned)count), dim3(NT), 0, st, src, dst, T);
     return (int)hipGetLastError();
 }
 
