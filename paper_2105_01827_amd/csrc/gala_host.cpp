@@ -526,7 +526,7 @@ extern "C" int gala_galois_keygen(gala_ctx *c, const gala_sk *sk, const gala_rot
     }
     if (!rc && uses_fast_perm(c)) {
         if (hipMalloc((void **)&gk->d_keys2, 2 * nkeys * kw * sizeof(u64)) != hipSuccess) rc = GALA_ENOMEM;
-        if (!rc && launch_pair_pack(c, nullptr, gk->d_keys, gk->d_keys2, nkeys * kw, polys)) rc = GALA_EHIP;
+        if (!rc && launch_key_pack(c, nullptr, gk->d_keys, gk->d_keys2, nkeys)) rc = GALA_EHIP;
     }
     if (!rc && hipDeviceSynchronize() != hipSuccess) rc = GALA_EHIP;
     hipFree(d_s);
@@ -718,7 +718,7 @@ extern "C" int gala_fc_plan_create(gala_ctx *c, const uint64_t *W, int n_o, int 
     if (!rc && uses_fast_perm(c)) {
         // pairs in natural order, then once more in the order the Perm kernel's threads own them
         if (hipMalloc((void **)&pl->d_w2, 4 * wsize * sizeof(u64)) != hipSuccess) rc = GALA_ENOMEM;
-        if (!rc && (launch_pair_pack(c, nullptr, pl->d_w, pl->d_w2, wsize, 2) ||
+        if (!rc && (launch_pair_pack(c, nullptr, pl->d_w, pl->d_w2, wsize) ||
                     launch_owner_order_2048(nullptr, pl->d_w2, pl->d_w2 + 2 * wsize, (size_t)G) ||
                     hipDeviceSynchronize() != hipSuccess))
             rc = GALA_EHIP;

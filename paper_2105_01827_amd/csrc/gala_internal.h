@@ -112,7 +112,7 @@ struct gala_gk {
     std::map<int, int> index_of;       // Galois element -> key index
     std::vector<int> elements;
     gala::u64 *d_keys = nullptr;       // nkeys x ndigits x polys x n, evaluation domain (b then a)
-    gala::u64 *d_keys2 = nullptr;      // same keys as (value, companion) pairs for the n = 2048 kernel, or null
+    gala::u64 *d_keys2 = nullptr;      // the folded keys as (value, companion) pairs for the n = 2048 kernels, or null
     int *d_elements = nullptr;         // nkeys Galois elements, device
     int *d_iota = nullptr;             // 0,1,2,... (key index of element k is k), device
     int *d_one = nullptr;              // the single value 1 (Galois element of the identity), device
@@ -250,9 +250,9 @@ int launch_unpack_share(const gala_ctx *ctx, void *stream, const u64 *slots, int
 int launch_key_finish(const gala_ctx *ctx, void *stream, u64 *pairs, const u64 *s_hat, size_t npairs, const Modulus &mod);
 // dst[i] = (src[i], floor(src[i] * 2^64 / q)) for i < count: constants with the precomputed quotient
 // that the n = 2048 kernel multiplies by.
-// With a special prime the polynomials alternate (b, a) mod q, (b, a) mod P: `polys` = 4 selects the modulus
-// by polynomial index, `polys` = 2 uses q throughout.
-int launch_pair_pack(const gala_ctx *ctx, void *stream, const u64 *src, u64 *dst, size_t count, int polys);
+int launch_pair_pack(const gala_ctx *ctx, void *stream, const u64 *src, u64 *dst, size_t count);
+// the same for nkeys whole key-switching keys, with the last digit's key folded into the others (key_pack_kernel)
+int launch_key_pack(const gala_ctx *ctx, void *stream, const u64 *src, u64 *dst, size_t nkeys);
 // dst[poly][512*(t/64) + 64*k + t%64] = src[poly][8*t + k] on 16-byte pairs of n = 2048 polynomials: the order in which
 // the threads of the Perm kernel read the 8 consecutive coefficients they own - one coalesced load per k, the eight of
 // a wavefront within 8 KiB

@@ -90,15 +90,7 @@ __global__ void key_finish_kernel(u64 *pairs, const u64 *s_hat, int n, size_t to
 }
 
 // companion of a constant w < q: floor(w * 2^64 / q), by 64 steps of binary long division
-// (polys = 4: polynomials 2 and 3 of every group of four are constants modulo the second modulus).  The
-// modulus differs from lane to lane; it is picked with a lane mask rather than a branch on purpose: hipcc 7.2
-// kept a branchy `cond ? q_second : q_first` in scalar registers and gave every lane q_second.
-__global__ void pair_pack_kernel(const u64 *src, u64 *dst, size_t count, u64 q_first, u64 q_second, int logn, int polys) {
-    const size_t id = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= count) return;
-    const u64 second = polys == 4 ? 0 - (u64)((id >> (logn + 1)) & 1) : 0;   // all ones on polynomials 2, 3 of 4
-    const u64 q = (q_first & ~second) | (q_second & second);
-    const u64 w = src[id];
+__device__ __forceinline__ u64 companion(u64 w, u64 q) {
     u64 rem = w, quot = 0;
     for (int b = 0; b < 64; ++b) {
         rem <<= 1;                       // rem < q < 2^61, no overflow
@@ -106,8 +98,35 @@ __global__ void pair_pack_kernel(const u64 *src, u64 *dst, size_t count, u64 q_f
         rem -= ge ? q : 0;
         quot = (quot << 1) | (ge ? 1 : 0);
     }
+    return quot;
+}
+__global__ void pair_pack_kernel(const u64 *src, u64 *dst, size_t count, u64 q) {
+    const size_t id = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (id >= count) return;
+    const u64 w = src[id];
     dst[2 * id] = w;
-    dst[2 * id + 1] = quot;
+    dst[2 * id + 1] = companion(w, q);
+}
+// Pair image of key-switching keys, folded: the digits D_j of X satisfy sum_j B^j D_j = X, so with F = B^(1-L) K_(L-1)
+//   sum_(j<L) K_j D_j = sum_(j<L-1) (K_j - B^j F) D_j + F X   (mod q)
+// and the image holds K_j - B^j F for j < L-1 and F for j = L-1.  Binv = B^(1-L) mod q.  With a special prime the
+// polynomials of a digit are (b, a) mod q and (b, a) mod P (polys = 4); those modulo P stay as they are, since X is
+// known modulo q only.  The modulus differs from lane to lane; it is picked with a lane mask rather than a branch on
+// purpose: hipcc 7.2 kept a branchy `cond ? q_second : q_first` in scalar registers and gave every lane q_second.
+__global__ void key_pack_kernel(const u64 *src, u64 *dst, size_t count, Modulus mod, u64 P, int logn, int polys, int ndigits,
+                                u64 B, u64 Binv) {
+    const size_t id = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (id >= count) return;
+    const size_t poly = id >> logn;
+    const int j = (int)(poly / polys % ndigits);
+    const u64 second = polys == 4 ? 0 - (u64)((poly >> 1) & 1) : 0;   // all ones on polynomials 2, 3 of 4
+    u64 F = mul_mod(src[id + ((size_t)(ndigits - 1 - j) * polys << logn)] & ~second, Binv, mod), BjF = F;
+    for (int t = 0; t < j; ++t) BjF = mul_mod(BjF, B, mod);
+    const u64 own = src[id];
+    const u64 folded = j == ndigits - 1 ? F : sub_mod(own & ~second, BjF, mod.q);
+    const u64 w = (folded & ~second) | (own & second);
+    dst[2 * id] = w;
+    dst[2 * id + 1] = companion(w, (mod.q & ~second) | (P & second));
 }
 
 // ---------------------------------------------------------------------------
@@ -956,10 +975,19 @@ int launch_owner_order_2048(void *stream, const u64 *src, u64 *dst, size_t npoly
                        reinterpret_cast<const ulonglong2 *>(src), reinterpret_cast<ulonglong2 *>(dst));
     return (int)hipGetLastError();
 }
-int launch_pair_pack(const gala_ctx *c, void *stream, const u64 *src, u64 *dst, size_t count, int polys) {
+int launch_pair_pack(const gala_ctx *c, void *stream, const u64 *src, u64 *dst, size_t count) {
     if (!count) return 0;
     hipLaunchKernelGGL(pair_pack_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, (hipStream_t)stream, src,
-                       dst, count, c->q, c->special, c->logn, polys);
+                       dst, count, c->q);
+    return last_error();
+}
+int launch_key_pack(const gala_ctx *c, void *stream, const u64 *src, u64 *dst, size_t nkeys) {
+    if (!nkeys) return 0;
+    const int polys = c->key_polys();
+    const size_t count = nkeys * c->ndigits * polys * c->n;
+    const u64 B = (1ull << c->gadget_bits) % c->q, Binv = inv_mod(pow_mod(B, (u64)(c->ndigits - 1), c->q), c->q);
+    hipLaunchKernelGGL(key_pack_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, (hipStream_t)stream, src, dst,
+                       count, c->dev_q.mod, c->special, c->logn, polys, c->ndigits, B, Binv);
     return last_error();
 }
 bool uses_fast_perm(const gala_ctx *c) {

@@ -482,6 +482,14 @@ __device__ __forceinline__ void item_and_chunk(const PermJob &job, int &item, in
     }
 }
 
+// Folded keys.  The digits of a coefficient x add up to it, x = sum_j B^j d_j, and the transform is linear, so the last
+// digit's transform is B^(1-L) (X - sum_(j<L-1) B^j D_j) with X = the transform of x, i.e. the very polynomial the
+// inverse transform started from.  The inner product sum_j K_j D_j is then sum_(j<L-1) (K_j - B^(j-L+1) K_(L-1)) D_j +
+// B^(1-L) K_(L-1) X modulo q: the pair image of the keys holds those combinations (key_pack_kernel), and a rotation
+// takes L-1 forward transforms instead of L, for one more product (c1 (.) w at the rotated index).
+// From wire to wire, three digits: he_fc 128x1024 at batch 64 209 -> 162 us, 1000x2048 2669 -> 2195 us (the share of the
+// import and export transforms in that is 12 us); two digits and a special prime, 100x784 at batch 7: 92 -> 80 us.
+//
 // Every product on this path is a multiplication by a constant that carries its precomputed
 // quotient (twiddles, encoded weights, key polynomials), so sums of products stay in 64-bit
 // registers: each product is below 2q, a running sum is kept below 8q and may take four more
@@ -568,18 +576,29 @@ __global__ __launch_bounds__(NT) void perm_accumulate_2048(PermJob job, Tables20
 #pragma unroll
         for (int k = 0; k < PER; ++k) stash[tid + k * NT] = a[k];
 
-        // the c0 part: permuted c0 (.) w
+        // the c0 part, permuted c0 (.) w, and the last digit's products: with the folded keys (FoldedKeys) they are
+        // products of the rotated c1 (.) w itself
+        {
+            const ulonglong2 *kb = key + (size_t)(2 * (ndigits - 1)) * N, *ka = kb + N;
 #pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            if (HAS_W) {
-                const ulonglong2 ww = w[src[k]];
-                sum0[k] = mul_const<false, true>(c0[src[k]], ww.x, ww.y, q, sum0[k]);
-            } else {
-                sum0[k] += at(c0, src[k]);
+            for (int k = 0; k < PER; ++k) {
+                const int i = tid + k * NT;
+                u64 d;
+                if (HAS_W) {
+                    const ulonglong2 ww = w[src[k]];
+                    sum0[k] = mul_const<false, true>(c0[src[k]], ww.x, ww.y, q, sum0[k]);
+                    d = mul_const(c1[src[k]], ww.x, ww.y, q);
+                } else {
+                    sum0[k] += at(c0, src[k]);
+                    d = at(c1, src[k]);
+                }
+                const ulonglong2 b = kb[i], aa = ka[i];
+                sum0[k] = mul_const<false, true>(d, b.x, b.y, q, sum0[k]);
+                sum1[k] = mul_const<false, true>(d, aa.x, aa.y, q, sum1[k]);
             }
         }
-        int pending = 1;   // products added to sum0 since it was last brought below 8q
-        for (int j = 0; j < ndigits; ++j) {
+        int pending = 2;   // products added to sum0 since it was last brought below 8q
+        for (int j = 0; j < ndigits - 1; ++j) {
 #pragma unroll
             for (int k = 0; k < PER; ++k) a[k] = (stash[tid + k * NT] >> (j * gadget_bits)) & digit_mask;
             // result in bufA, any 64-bit value below 16q.  The cheaper first stage for digits below 2^32 only where
@@ -622,15 +641,16 @@ __global__ __launch_bounds__(NT) void perm_accumulate_2048(PermJob job, Tables20
 // Hoisted rotations of the input ciphertexts (Sec. III-B: one DecPerm shared by all the taps of a kernel,
 // then one HstPerm per tap), as two launches so that both fill the chip at small batches.
 //
-// DecPerm: one workgroup per (ciphertext, digit); each repeats the inverse transform of c1 and runs the
+// DecPerm: one workgroup per (ciphertext, digit but the last); each repeats the inverse transform of c1 and runs the
 // forward transform of its digit.  digits[ct][j][i] holds lazy values (any 64-bit word below 16q), which is
-// what the constant multiplications of the inner product accept.
+// what the constant multiplications of the inner product accept.  In the place of the last digit the inner products
+// take c1 itself (folded keys).  stored: L-1 digits.
 constexpr int HOIST_DIGITS = 3;
 __global__ __launch_bounds__(NT) void decperm_2048(const u64 *ct_in, u64 *digits, Tables2048 T, int gadget_bits,
-                                                   int ndigits) {
+                                                   int stored) {
     __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
     const int tid = threadIdx.x;
-    const int ct = blockIdx.x / ndigits, j = blockIdx.x % ndigits;
+    const int ct = blockIdx.x / stored, j = blockIdx.x % stored;
     const u64 *c1 = ct_in + (size_t)ct * 2 * N + N;
     u64 a[PER];
     const ulonglong2 *c1v = reinterpret_cast<const ulonglong2 *>(c1 + 8 * tid);
@@ -645,7 +665,7 @@ __global__ __launch_bounds__(NT) void decperm_2048(const u64 *ct_in, u64 *digits
 #pragma unroll
     for (int k = 0; k < PER; ++k) a[k] = (a[k] >> (j * gadget_bits)) & digit_mask;
     forward_to_lds(a, bufA, bufB, T, tid, gadget_bits <= 32);       // LDS phases B A B A, ends on a barrier
-    u64 *out = digits + ((size_t)ct * ndigits + j) * N;
+    u64 *out = digits + ((size_t)ct * stored + j) * N;
 #pragma unroll
     for (int k = 0; k < PER; ++k) out[tid + k * NT] = bufA[pad(tid + k * NT)];
 }
@@ -671,7 +691,7 @@ __global__ __launch_bounds__(NT) void hstperm_taps_2048(const u64 *ct_in, const 
         return;
     }
     const NegQ q = T.nq;
-    const u64 *dsrc = digits + ct * ndigits * N;
+    const u64 *dsrc = digits + ct * (ndigits - 1) * N;
     const ulonglong2 *key = reinterpret_cast<const ulonglong2 *>(keys2) + (size_t)terms.key[e] * ndigits * 2 * N;
     // two batches of four coefficients keep the loads of a batch in flight together at a modest register count
 #pragma unroll 1
@@ -688,11 +708,12 @@ __global__ __launch_bounds__(NT) void hstperm_taps_2048(const u64 *ct_in, const 
         }
         for (int j = 0; j < ndigits; ++j) {
             const ulonglong2 *kb = key + (size_t)(2 * j) * N, *ka = kb + N;
+            const u64 *dj = j == ndigits - 1 ? c1 : dsrc + (size_t)j * N;      // folded keys: c1 for the last digit
             ulonglong2 b[H], aa[H];
             u64 d[H];
 #pragma unroll
             for (int k = 0; k < H; ++k) {
-                d[k] = dsrc[(size_t)j * N + src[k]];
+                d[k] = dj[src[k]];
                 b[k] = kb[idx[k]];
                 aa[k] = ka[idx[k]];
             }
@@ -768,19 +789,20 @@ __global__ __launch_bounds__(NT) void hstperm_pack_2048(const u64 *ct_in, const 
             v0 = c0[i];
             v1 = c0[N + i];
         } else {
-            const u64 *dsrc = digits + ct * ndigits * N;
+            const u64 *dsrc = digits + ct * (ndigits - 1) * N;
+            const u64 last = c0[N + src];         // folded keys: c1 in the place of the last digit
             u64 s0 = c0[src], s1 = 0;
             if (ND) {
 #pragma unroll
                 for (int j = 0; j < KD; ++j) {
-                    const u64 d = dsrc[(size_t)j * N + src];
+                    const u64 d = j == KD - 1 ? last : dsrc[(size_t)j * N + src];
                     const U64Pair r = mul_const_pair(d, kwb[j], d, kwa[j], q);      // each product is below 2q: at most 7q in all
                     s0 += r.a;
                     s1 += r.b;
                 }
             } else {
                 for (int j = 0; j < ndigits; ++j) {
-                    const u64 d = dsrc[(size_t)j * N + src];
+                    const u64 d = j == ndigits - 1 ? last : dsrc[(size_t)j * N + src];
                     const ulonglong2 wb = key[(size_t)(2 * j) * N + i], wa = key[(size_t)(2 * j + 1) * N + i];
                     s0 = mul_const<false, true>(d, wb.x, wb.y, q, s0);
                     s1 = mul_const<false, true>(d, wa.x, wa.y, q, s1);
@@ -1018,42 +1040,51 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_2048(PermJob jo
         inverse_in_regs<true>(a, bufA, bufB, T, tid);
 #pragma unroll
         for (int k = 0; k < PER; ++k) stash[tid + k * NT] = a[k];
-        // the c0 part, times P
+        // the c0 part, times P, and the last digit's products modulo q (folded keys: the rotated c1 (.) w itself)
+        {
+            const ulonglong2 *kb = key + (size_t)(4 * (ndigits - 1)) * N, *ka = kb + N;
 #pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            u64 x = at(c0, src[k]);
-            if (HAS_W) {
-                const ulonglong2 ww = w[src[k]];
-                x = mul_const<true>(x, ww.x, ww.y, q);
+            for (int k = 0; k < PER; ++k) {
+                const int i = tid + k * NT;
+                u64 x = at(c0, src[k]), d = at(c1, src[k]);
+                if (HAS_W) {
+                    const ulonglong2 ww = w[src[k]];
+                    x = mul_const<true>(x, ww.x, ww.y, q);
+                    d = mul_const<true>(d, ww.x, ww.y, q);
+                }
+                const ulonglong2 b = kb[i], aa = ka[i];
+                sum0[k] += mul_const<true>(x, S.Pq.x, S.Pq.y, q) + mul_const<true>(d, b.x, b.y, q);
+                sum1[k] += mul_const<true>(d, aa.x, aa.y, q);
             }
-            sum0[k] += mul_const<true>(x, S.Pq.x, S.Pq.y, q);
         }
-        int pending = 1, pendingP = 0;
+        int pending = 2, pendingP = 0;
         u64 tp0[PER], tp1[PER];   // this rotation's sums modulo P, below 8P between products
 #pragma unroll
         for (int k = 0; k < PER; ++k) tp0[k] = tp1[k] = 0;
         for (int j = 0; j < ndigits; ++j) {
-#pragma unroll
-            for (int k = 0; k < PER; ++k) a[k] = (stash[tid + k * NT] >> (j * gadget_bits)) & digit_mask;
-            forward_to_lds<true>(a, bufA, bufB, T, tid);
             const ulonglong2 *kb = key + (size_t)(4 * j) * N, *ka = kb + N;
-            if (pending == 4) {
+            if (j + 1 < ndigits) {
+#pragma unroll
+                for (int k = 0; k < PER; ++k) a[k] = (stash[tid + k * NT] >> (j * gadget_bits)) & digit_mask;
+                forward_to_lds<true>(a, bufA, bufB, T, tid);
+                if (pending == 4) {
+#pragma unroll
+                    for (int k = 0; k < PER; ++k) {
+                        sum0[k] = csub_dev(sum0[k], q8);
+                        sum1[k] = csub_dev(sum1[k], q8);
+                    }
+                    pending = 0;
+                }
 #pragma unroll
                 for (int k = 0; k < PER; ++k) {
-                    sum0[k] = csub_dev(sum0[k], q8);
-                    sum1[k] = csub_dev(sum1[k], q8);
+                    const int i = tid + k * NT;
+                    const u64 d = bufA[pad(src[k])];
+                    const ulonglong2 b = kb[i], aa = ka[i];
+                    sum0[k] += mul_const<true>(d, b.x, b.y, q);
+                    sum1[k] += mul_const<true>(d, aa.x, aa.y, q);
                 }
-                pending = 0;
+                ++pending;
             }
-#pragma unroll
-            for (int k = 0; k < PER; ++k) {
-                const int i = tid + k * NT;
-                const u64 d = bufA[pad(src[k])];
-                const ulonglong2 b = kb[i], aa = ka[i];
-                sum0[k] += mul_const<true>(d, b.x, b.y, q);
-                sum1[k] += mul_const<true>(d, aa.x, aa.y, q);
-            }
-            ++pending;
             // the same digit modulo P
 #pragma unroll
             for (int k = 0; k < PER; ++k) a[k] = (stash[tid + k * NT] >> (j * gadget_bits)) & digit_mask;
@@ -1128,11 +1159,13 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_2048(PermJob jo
 
 // ---- hoisted input rotations with a special prime ----------------------------------------------------------
 // DecPerm: one workgroup per (ciphertext, digit, modulus); digits[ct][j][modulus][i], lazy values of that modulus.
+// The last digit modulo q is not needed (folded keys), its place stays empty.
 __global__ __launch_bounds__(NT) void decperm_special_2048(const u64 *ct_in, u64 *digits, Tables2048 T, Tables2048 TP,
                                                            int gadget_bits, int ndigits) {
     __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
     const int tid = threadIdx.x;
-    const int m = blockIdx.x & 1, j = (blockIdx.x >> 1) % ndigits, ct = (blockIdx.x >> 1) / ndigits;
+    const int per_ct = 2 * ndigits - 1, ct = blockIdx.x / per_ct, v = blockIdx.x % per_ct;
+    const int m = v == per_ct - 1 ? 1 : v & 1, j = v >> 1;
     const u64 *c1 = ct_in + (size_t)ct * 2 * N + N;
     u64 a[PER];
     const ulonglong2 *c1v = reinterpret_cast<const ulonglong2 *>(c1 + 8 * tid);
@@ -1156,7 +1189,7 @@ __global__ __launch_bounds__(NT) void decperm_special_2048(const u64 *ct_in, u64
 // HstPerm: one workgroup per (ciphertext, tap): inner products in both moduli from the stored digits, the sums
 // modulo P back to coefficients, lifted, reduced modulo q and transformed forward again, then
 // out = (P c0(X^g) + t_b - NTT(r_b)) / P, (t_a - NTT(r_a)) / P.  Output: xrot[ct][tap][c0|c1][i], canonical.
-__global__ __launch_bounds__(NT) void hstperm_special_2048(const u64 *ct_in, const u64 *digits, TermList terms,
+__global__ __launch_bounds__(NT, 4) void hstperm_special_2048(const u64 *ct_in, const u64 *digits, TermList terms,
                                                            const u64 *keys2, u64 *xrot, Tables2048 T, SpecialJob S,
                                                            int ndigits) {
     __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
@@ -1194,10 +1227,11 @@ __global__ __launch_bounds__(NT) void hstperm_special_2048(const u64 *ct_in, con
         }
         for (int j = 0; j < ndigits; ++j) {
             const ulonglong2 *kq = key + (size_t)(4 * j + h) * N, *kP = key + (size_t)(4 * j + 2 + h) * N;
+            const u64 *djq = j == ndigits - 1 ? c1 : dsrc + (size_t)(2 * j) * N;       // folded keys modulo q
 #pragma unroll
             for (int k = 0; k < PER; ++k) {
                 const int i = tid + k * NT;
-                const u64 dq = dsrc[(size_t)(2 * j) * N + src[k]], dP = dsrc[(size_t)(2 * j + 1) * N + src[k]];
+                const u64 dq = djq[src[k]], dP = dsrc[(size_t)(2 * j + 1) * N + src[k]];
                 const ulonglong2 wq = kq[i], wP = kP[i];
                 sum[k] += mul_const(dq, wq.x, wq.y, q);
                 tp[k] += mul_const(dP, wP.x, wP.y, qP);
@@ -1362,7 +1396,7 @@ int launch_hoist_taps_2048(const gala_ctx *c, void *stream, const u64 *ct_in, in
         S.Pq = make_ulonglong2(c->Pq, c->Pq_s);
         S.Pinv = make_ulonglong2(c->Pinv, c->Pinv_s);
         if (any_rotation) {
-            hipLaunchKernelGGL(decperm_special_2048, dim3((unsigned)(count * c->ndigits * 2)), dim3(NT), 0, st, ct_in, digits,
+            hipLaunchKernelGGL(decperm_special_2048, dim3((unsigned)(count * (2 * c->ndigits - 1))), dim3(NT), 0, st, ct_in, digits,
                                T, S.TP, c->gadget_bits, c->ndigits);
             const int rc = (int)hipGetLastError();
             if (rc) return rc;
@@ -1370,9 +1404,9 @@ int launch_hoist_taps_2048(const gala_ctx *c, void *stream, const u64 *ct_in, in
         hipLaunchKernelGGL(hstperm_special_2048, per_term, dim3(NT), 0, st, ct_in, digits, terms, keys2, xrot, T, S, c->ndigits);
         return (int)hipGetLastError();
     }
-    if (any_rotation) {
-        hipLaunchKernelGGL(decperm_2048, dim3((unsigned)(count * c->ndigits)), dim3(NT), 0, st, ct_in, digits, T,
-                           c->gadget_bits, c->ndigits);
+    if (any_rotation && c->ndigits > 1) {
+        hipLaunchKernelGGL(decperm_2048, dim3((unsigned)(count * (c->ndigits - 1))), dim3(NT), 0, st, ct_in, digits, T,
+                           c->gadget_bits, c->ndigits - 1);
         const int rc = (int)hipGetLastError();
         if (rc) return rc;
     }
@@ -1386,9 +1420,9 @@ int launch_hstperm_pack_2048(const gala_ctx *c, void *stream, const u64 *ct_in, 
     if (batch <= 0 || terms.nterm <= 0) return 0;
     const Tables2048 T = make_tables(c, c->d_tw2, c->dev_q);
     hipStream_t st = (hipStream_t)stream;
-    if (any_rotation) {
-        hipLaunchKernelGGL(decperm_2048, dim3((unsigned)((size_t)batch * terms.nin * c->ndigits)), dim3(NT), 0, st, ct_in,
-                           digits, T, c->gadget_bits, c->ndigits);
+    if (any_rotation && c->ndigits > 1) {
+        hipLaunchKernelGGL(decperm_2048, dim3((unsigned)((size_t)batch * terms.nin * (c->ndigits - 1))), dim3(NT), 0, st, ct_in,
+                           digits, T, c->gadget_bits, c->ndigits - 1);
         const int rc = (int)hipGetLastError();
         if (rc) return rc;
     }
