@@ -103,6 +103,10 @@ void NttHost::init(int n_, u64 q, u64 psi_) {
     }
     ninv = inv_mod((u64)n, q);           ninvs = shoup_companion(ninv, q);
     itw1n = mulmod_slow(itw[1], ninv, q); itw1ns = shoup_companion(itw1n, q);
+    for (int e = 0; e < 3; ++e) {
+        w8[e] = ipw[(size_t)(e + 1) * n / 4];      // psi^-(2n/8) to the power e + 1
+        w8s[e] = shoup_companion(w8[e], q);
+    }
 }
 void NttHost::forward(u64 *a) const {
     const u64 q = mod.q, q2 = mod.q2;
@@ -323,37 +327,49 @@ extern "C" int gala_ctx_create(const gala_params *par, gala_ctx **out) {
         std::copy(hs[k]->itw.begin(), hs[k]->itw.end(), base + 2 * n);
         std::copy(hs[k]->itws.begin(), hs[k]->itws.end(), base + 3 * n);
     }
-    // pass-major twiddle blocks for the n = 2048 kernel: block T (1 <= T < 512) holds the pairs
-    // tw[T], tw[2T], tw[2T+1], tw[4T..4T+3] and one unused pair; forward table then inverse table
+    // twiddle pairs for the n = 2048 kernels.  Forward: block T (1 <= T < 512) of a radix-8 pass is tw[T], tw[2T],
+    // tw[2T+1], tw[4T..4T+3]; level c (blocks c .. 2c-1, c = 1, 8, 64, 256) is stored [e][j] = constant e of block c + j,
+    // so that a wavefront's load of constant e reads neighbouring pairs.  Inverse: a stage of half-length t multiplies
+    // by w(t, j) = psi^(-j n / t), j the index modulo t; the passes on bits 3-5 and 6-8 (first half-length h = 8, 64)
+    // are [7][h]: w(h, l), w(2h, l), w(2h, l + h), w(4h, l + e h) for e = 0 .. 3; bits 9-10 are [6][256]:
+    // w(512, l), w(512, l + 256), w(1024, l + 256 e); then psi^-j / n for every coefficient j.
     std::vector<u64> pairs, pairs_p, pairs_P, hostP;
     if (n == 2048) {
         auto build = [&](const NttHost &h, std::vector<u64> &out) {
-            // ... followed, for each direction, by the same pairs level by level with the constant's number before
-            // the block's: level c (blocks c .. 2c-1, c = 1, 4, 8, 32, 64, 256) is [e][j] = block (c + j), pair e, so
-            // that a wavefront's load of constant e reads neighbouring pairs (2555 pairs per direction)
-            static const int kLevels[6] = {1, 4, 8, 32, 64, 256};
-            const size_t blocks_words = 2 * 2 * 8 * (size_t)512, level_pairs = 7 * (1 + 4 + 8 + 32 + 64 + 256);
-            out.assign(blocks_words + 2 * 2 * level_pairs, 0);
-            for (int inv = 0; inv < 2; ++inv) {
-                const std::vector<u64> &w = inv ? h.itw : h.tw, &ws = inv ? h.itws : h.tws;
-                u64 *base = out.data() + (size_t)inv * 2 * 8 * 512;
-                for (int T = 1; T < 512; ++T) {
-                    const int idx[7] = {T, 2 * T, 2 * T + 1, 4 * T, 4 * T + 1, 4 * T + 2, 4 * T + 3};
-                    for (int e = 0; e < 7; ++e) {
-                        base[2 * (8 * T + e)] = w[idx[e]];
-                        base[2 * (8 * T + e) + 1] = ws[idx[e]];
+            const u64 m = h.mod.q;
+            out.clear();
+            auto put = [&](u64 w, u64 ws) {
+                out.push_back(w);
+                out.push_back(ws);
+            };
+            for (int cnt : {1, 8, 64, 256})
+                for (int e = 0; e < 7; ++e)
+                    for (int j = 0; j < cnt; ++j) {
+                        const int T = cnt + j, idx[7] = {T, 2 * T, 2 * T + 1, 4 * T, 4 * T + 1, 4 * T + 2, 4 * T + 3};
+                        put(h.tw[idx[e]], h.tws[idx[e]]);
                     }
-                }
-                u64 *lev = out.data() + blocks_words + (size_t)inv * 2 * level_pairs;
-                for (int L = 0; L < 6; ++L) {
-                    const int cnt = kLevels[L];
-                    for (int e = 0; e < 7; ++e)
-                        for (int j = 0; j < cnt; ++j) {
-                            lev[2 * ((size_t)e * cnt + j)] = base[2 * (8 * (cnt + j) + e)];
-                            lev[2 * ((size_t)e * cnt + j) + 1] = base[2 * (8 * (cnt + j) + e) + 1];
-                        }
-                    lev += 2 * 7 * (size_t)cnt;
-                }
+            std::vector<u64> ipw(2 * (size_t)n);     // powers of psi^-1
+            const u64 ipsi = inv_mod(h.psi, m);
+            ipw[0] = 1;
+            for (int i = 1; i < 2 * n; ++i) ipw[i] = mulmod_slow(ipw[i - 1], ipsi, m);
+            auto w = [&](int t, int j) {
+                const u64 v = ipw[(size_t)j * (n / t)];
+                put(v, shoup_companion(v, m));
+            };
+            for (int half : {8, 64}) {
+                for (int l = 0; l < half; ++l) w(half, l);
+                for (int e = 0; e < 2; ++e)
+                    for (int l = 0; l < half; ++l) w(2 * half, l + e * half);
+                for (int e = 0; e < 4; ++e)
+                    for (int l = 0; l < half; ++l) w(4 * half, l + e * half);
+            }
+            for (int e = 0; e < 2; ++e)
+                for (int l = 0; l < 256; ++l) w(512, l + 256 * e);
+            for (int e = 0; e < 4; ++e)
+                for (int l = 0; l < 256; ++l) w(1024, l + 256 * e);
+            for (int j = 0; j < n; ++j) {
+                const u64 v = mulmod_slow(ipw[j], h.ninv, m);
+                put(v, shoup_companion(v, m));
             }
         };
         build(c->ntt_q, pairs);

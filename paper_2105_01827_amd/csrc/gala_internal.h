@@ -46,6 +46,7 @@ struct NttHost {
     u64 psi = 0;
     std::vector<u64> tw, tws, itw, itws;
     u64 ninv = 0, ninvs = 0, itw1n = 0, itw1ns = 0;
+    u64 w8[3] = {0, 0, 0}, w8s[3] = {0, 0, 0};   // powers 1, 2, 3 of psi^(-2n/8)
 
     void init(int n, u64 q, u64 psi);
     void forward(u64 *a) const;   // in place, canonical in -> canonical out
@@ -88,10 +89,10 @@ struct gala_ctx {
     bool has_device = false;           // tables uploaded; false on a host without a HIP device
     gala::u64 *d_tables = nullptr;     // 8*n words: tw,tws,itw,itws for q then for p
     int *d_slot_to_idx = nullptr;
-    gala::u64 *d_tw2 = nullptr;        // n = 2048 only: pass-major (w, companion) twiddle blocks, forward then inverse
+    gala::u64 *d_tw2 = nullptr;        // n = 2048 only: (w, companion) twiddle pairs in the order of the radix-8 passes, forward then inverse
     gala::u64 *d_tw2p = nullptr;       // the same for the plaintext modulus
     gala::u64 *d_tablesP = nullptr;    // 4*n words: tw,tws,itw,itws for the special prime
-    gala::u64 *d_tw2P = nullptr;       // pass-major blocks for the special prime (n = 2048)
+    gala::u64 *d_tw2P = nullptr;       // the same for the special prime
     gala::NttDev dev_q{}, dev_p{}, dev_P{};
     int key_polys() const { return special ? 4 : 2; }
     // measurement aid: event pairs recorded around rotate-and-accumulate launches
