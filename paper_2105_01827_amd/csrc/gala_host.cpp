@@ -33,6 +33,10 @@ int bit_length(u64 v) {
     for (; v; v >>= 1) ++l;
     return l;
 }
+Reciprocal make_reciprocal(u64 q) {
+    const u64 hi = shoup_companion(1, q);
+    return {hi, shoup_companion(0 - hi * q, q)};      // 2^64 = hi q + remainder
+}
 Modulus make_modulus(u64 q) {
     Modulus m;
     m.q = q;
@@ -92,14 +96,16 @@ void NttHost::init(int n_, u64 q, u64 psi_) {
     tw.assign(n, 0); tws.assign(n, 0); itw.assign(n, 0); itws.assign(n, 0);
     std::vector<u64> pw(n), ipw(n);
     pw[0] = ipw[0] = 1;
+    const Reciprocal rec = make_reciprocal(q);
+    const u64 psi_s = companion(psi, q, rec), ipsi_s = companion(ipsi, q, rec);
     for (int i = 1; i < n; ++i) {
-        pw[i] = mulmod_slow(pw[i - 1], psi, q);
-        ipw[i] = mulmod_slow(ipw[i - 1], ipsi, q);
+        pw[i] = mul_shoup(pw[i - 1], psi, psi_s, q);
+        ipw[i] = mul_shoup(ipw[i - 1], ipsi, ipsi_s, q);
     }
     for (int k = 0; k < n; ++k) {
         int r = brev(k, logn);
-        tw[k] = pw[r];   tws[k] = shoup_companion(tw[k], q);
-        itw[k] = ipw[r]; itws[k] = shoup_companion(itw[k], q);
+        tw[k] = pw[r];   tws[k] = companion(tw[k], q, rec);
+        itw[k] = ipw[r]; itws[k] = companion(itw[k], q, rec);
     }
     ninv = inv_mod((u64)n, q);           ninvs = shoup_companion(ninv, q);
     itw1n = mulmod_slow(itw[1], ninv, q); itw1ns = shoup_companion(itw1n, q);
@@ -348,13 +354,14 @@ extern "C" int gala_ctx_create(const gala_params *par, gala_ctx **out) {
                         const int T = cnt + j, idx[7] = {T, 2 * T, 2 * T + 1, 4 * T, 4 * T + 1, 4 * T + 2, 4 * T + 3};
                         put(h.tw[idx[e]], h.tws[idx[e]]);
                     }
-            std::vector<u64> ipw(2 * (size_t)n);     // powers of psi^-1
-            const u64 ipsi = inv_mod(h.psi, m);
+            std::vector<u64> ipw(n);     // powers of psi^-1
+            const Reciprocal rec = make_reciprocal(m);
+            const u64 ipsi = inv_mod(h.psi, m), ipsi_s = companion(ipsi, m, rec);
             ipw[0] = 1;
-            for (int i = 1; i < 2 * n; ++i) ipw[i] = mulmod_slow(ipw[i - 1], ipsi, m);
+            for (int i = 1; i < n; ++i) ipw[i] = mul_shoup(ipw[i - 1], ipsi, ipsi_s, m);
             auto w = [&](int t, int j) {
                 const u64 v = ipw[(size_t)j * (n / t)];
-                put(v, shoup_companion(v, m));
+                put(v, companion(v, m, rec));
             };
             for (int half : {8, 64}) {
                 for (int l = 0; l < half; ++l) w(half, l);
@@ -368,8 +375,8 @@ extern "C" int gala_ctx_create(const gala_params *par, gala_ctx **out) {
             for (int e = 0; e < 4; ++e)
                 for (int l = 0; l < 256; ++l) w(1024, l + 256 * e);
             for (int j = 0; j < n; ++j) {
-                const u64 v = mulmod_slow(ipw[j], h.ninv, m);
-                put(v, shoup_companion(v, m));
+                const u64 v = mul_shoup(ipw[j], h.ninv, h.ninvs, m);
+                put(v, companion(v, m, rec));
             }
         };
         build(c->ntt_q, pairs);

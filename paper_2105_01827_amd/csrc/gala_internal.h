@@ -63,6 +63,7 @@ struct NttDev {
 u64 pow_mod(u64 b, u64 e, u64 m);
 u64 inv_mod(u64 a, u64 m);
 u64 shoup_companion(u64 w, u64 q);
+Reciprocal make_reciprocal(u64 q);
 Modulus make_modulus(u64 q);
 bool is_prime_u64(u64 v);
 int bit_length(u64 v);

@@ -34,6 +34,22 @@ GALA_HD u64 csub(u64 a, u64 q) { return a >= q ? a - q : a; }
 GALA_HD u64 mul_shoup_lazy(u64 a, u64 w, u64 ws, u64 q) { return a * w - mulhi64(a, ws) * q; }
 GALA_HD u64 mul_shoup(u64 a, u64 w, u64 ws, u64 q) { return csub(mul_shoup_lazy(a, w, ws, q), q); }
 
+// floor(2^128 / q) in two words, for companion()
+struct Reciprocal {
+    u64 hi, lo;
+};
+// floor(w * 2^64 / q) for w < q < 2^61: the estimate from the reciprocal is at most two below, and the remainder
+// w 2^64 - estimate * q, below 3q, is what its low word says
+GALA_HD u64 companion(u64 w, u64 q, const Reciprocal &r) {
+    u64 quot = w * r.hi + mulhi64(w, r.lo), rem = 0 - quot * q;
+    for (int t = 0; t < 2; ++t) {
+        const u64 over = rem >= q ? 1 : 0;
+        rem -= over * q;
+        quot += over;
+    }
+    return quot;
+}
+
 // What a kernel needs to know about a modulus (passed by value).
 struct Modulus {
     u64 q;       // the modulus
