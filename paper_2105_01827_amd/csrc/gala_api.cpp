@@ -29,16 +29,20 @@ int choose_chunks(const gala_ctx *ctx, int items, int G) {
     // With a special prime the kernel holds two workgroups per CU, not three, and a rotation is twice the work:
     // one round of 512 workgroups was the fastest cut for short and long sums alike (he_fc 128x1024: 0.43 ms
     // against 0.48 ms with 2048 workgroups and 0.58 ms with 768).
+    // Other rings with kernels of their own hold more or fewer workgroups in the same proportion (LDS, registers), at
+    // least one per CU.
+    const int n = uses_fast_perm(ctx) ? ctx->n : 2048;
+    auto scaled = [n](int wgs) { return std::max(256, wgs * 2048 / n); };
     if (G < 32 || ctx->special) {
-        const int c = ((ctx->special ? 512 : 768) + items - 1) / items;
+        const int c = (scaled(ctx->special ? 512 : 768) + items - 1) / items;
         return std::max(1, std::min(c, G - 1));     // G-1 entries cost a key switch (chunk_range)
     }
     // a power of two (it divides the padded G, and from 8 on it keeps the XCD mapping): 1280 to 2560 workgroups,
     // halved while a workgroup would be left with a single term and a round of the chip is still filled
     int c = 1;
-    while (2 * c * items <= 2560) c *= 2;
+    while (2 * c * items <= scaled(2560)) c *= 2;
     c = std::min(c, G);
-    while (c > 1 && G / c < 2 && items * (c / 2) >= 768) c /= 2;
+    while (c > 1 && G / c < 2 && items * (c / 2) >= scaled(768)) c /= 2;
     return std::max(1, c);
 }
 size_t align_up(size_t v) { return (v + 255) & ~(size_t)255; }
@@ -183,7 +187,7 @@ int hoist_terms(const gala_ctx *c, void *stream, const u64 *ct_in, int batch, co
                 const u64 *keys, const u64 *keys2, u64 *digits, u64 *xrot) {
     const int n = c->n;
     const bool fast = uses_fast_hoist(c) && (!rotates || keys2);
-    if (fast) return launch_hoist_taps_2048(c, stream, ct_in, batch, terms, rotates, keys2, digits, xrot);
+    if (fast) return ring_ops(c)->hoist_taps(c, stream, ct_in, batch, terms, rotates, keys2, digits, xrot);
     if (c->special) {
         // every term as a Perm of its own: one workgroup per (item, term)
         PermJob taps{};
@@ -391,13 +395,13 @@ extern "C" int gala_he_conv(const gala_ctx *c, void *stream, const gala_conv_pla
     // The n = 2048 Perm kernels read the product's sums in their own blocks of eight coefficients: no transposition
     // pass in between.  With one-prime keys the rotated inputs also go straight into the product's column image.
     const bool direct = ws.mfma && fast_hoist && !c->special;
-    const bool in8 = ws.mfma && uses_fast_perm(c);      // both n = 2048 Perm kernels read the blocks of eight
+    const bool in8 = ws.mfma && uses_fast_perm(c);      // the ring's Perm kernels read the blocks of eight
     const u64 *perm_in = acc;
     if (direct) {
         // the rotated inputs go straight into the column image of the matrix-core product
         u64 *xl = (u64 *)(base + ws.xl), *tmp = (u64 *)(base + ws.tmp);
         mark_as(2, 0);
-        if (launch_hstperm_pack_2048(c, stream, ct_in, digits, batch, terms, rotates, keys2, xl))
+        if (ring_ops(c)->hstperm_pack(c, stream, ct_in, digits, batch, terms, rotates, keys2, xl))
             return GALA_EHIP;
         mark_as(2, 1);
         mark(0);

@@ -333,14 +333,15 @@ extern "C" int gala_ctx_create(const gala_params *par, gala_ctx **out) {
         std::copy(hs[k]->itw.begin(), hs[k]->itw.end(), base + 2 * n);
         std::copy(hs[k]->itws.begin(), hs[k]->itws.end(), base + 3 * n);
     }
-    // twiddle pairs for the n = 2048 kernels.  Forward: block T (1 <= T < 512) of a radix-8 pass is tw[T], tw[2T],
-    // tw[2T+1], tw[4T..4T+3]; level c (blocks c .. 2c-1, c = 1, 8, 64, 256) is stored [e][j] = constant e of block c + j,
-    // so that a wavefront's load of constant e reads neighbouring pairs.  Inverse: a stage of half-length t multiplies
-    // by w(t, j) = psi^(-j n / t), j the index modulo t; the passes on bits 3-5 and 6-8 (first half-length h = 8, 64)
-    // are [7][h]: w(h, l), w(2h, l), w(2h, l + h), w(4h, l + e h) for e = 0 .. 3; bits 9-10 are [6][256]:
-    // w(512, l), w(512, l + 256), w(1024, l + 256 e); then psi^-j / n for every coefficient j.
+    // twiddle pairs for the ring kernels.  Forward: block T (1 <= T < n/4) of a radix-8 pass is tw[T], tw[2T],
+    // tw[2T+1], tw[4T..4T+3]; level c (blocks c .. 2c-1, c = 1, 8, 64, .. below n/8, and n/8) is stored [e][j] = constant e
+    // of block c + j, so that a wavefront's load of constant e reads neighbouring pairs.  Inverse: a stage of half-length
+    // t multiplies by w(t, j) = psi^(-j n / t), j the index modulo t; the passes on three whole bits from bit 3 on (first
+    // half-length h = 8, 64, 512) are [7][h]: w(h, l), w(2h, l), w(2h, l + h), w(4h, l + e h) for e = 0 .. 3; the last
+    // pass of two stages or one is [6] or [4][n/8]: w(n/4, l), w(n/4, l + n/8) and w(n/2, l + e n/8), or the latter alone;
+    // then psi^-j / n for every coefficient j.
     std::vector<u64> pairs, pairs_p, pairs_P, hostP;
-    if (n == 2048) {
+    if (uses_fast_perm(c)) {
         auto build = [&](const NttHost &h, std::vector<u64> &out) {
             const u64 m = h.mod.q;
             out.clear();
@@ -348,12 +349,15 @@ extern "C" int gala_ctx_create(const gala_params *par, gala_ctx **out) {
                 out.push_back(w);
                 out.push_back(ws);
             };
-            for (int cnt : {1, 8, 64, 256})
+            auto level = [&](int cnt) {
                 for (int e = 0; e < 7; ++e)
                     for (int j = 0; j < cnt; ++j) {
                         const int T = cnt + j, idx[7] = {T, 2 * T, 2 * T + 1, 4 * T, 4 * T + 1, 4 * T + 2, 4 * T + 3};
                         put(h.tw[idx[e]], h.tws[idx[e]]);
                     }
+            };
+            for (int cnt = 1; cnt < n / 8; cnt *= 8) level(cnt);
+            level(n / 8);
             std::vector<u64> ipw(n);     // powers of psi^-1
             const Reciprocal rec = make_reciprocal(m);
             const u64 ipsi = inv_mod(h.psi, m), ipsi_s = companion(ipsi, m, rec);
@@ -363,17 +367,19 @@ extern "C" int gala_ctx_create(const gala_params *par, gala_ctx **out) {
                 const u64 v = ipw[(size_t)j * (n / t)];
                 put(v, companion(v, m, rec));
             };
-            for (int half : {8, 64}) {
-                for (int l = 0; l < half; ++l) w(half, l);
-                for (int e = 0; e < 2; ++e)
-                    for (int l = 0; l < half; ++l) w(2 * half, l + e * half);
-                for (int e = 0; e < 4; ++e)
-                    for (int l = 0; l < half; ++l) w(4 * half, l + e * half);
+            // `count` constants of half-length t, each for the l below step
+            auto stage = [&](int t, int count, int step) {
+                for (int e = 0; e < count; ++e)
+                    for (int l = 0; l < step; ++l) w(t, l + e * step);
+            };
+            int half = 8;
+            for (; 4 * half < n; half *= 8) {
+                stage(half, 1, half);
+                stage(2 * half, 2, half);
+                stage(4 * half, 4, half);
             }
-            for (int e = 0; e < 2; ++e)
-                for (int l = 0; l < 256; ++l) w(512, l + 256 * e);
-            for (int e = 0; e < 4; ++e)
-                for (int l = 0; l < 256; ++l) w(1024, l + 256 * e);
+            if (2 * half < n) stage(n / 4, 2, n / 8);
+            if (half < n) stage(n / 2, 4, n / 8);
             for (int j = 0; j < n; ++j) {
                 const u64 v = mul_shoup(ipw[j], h.ninv, h.ninvs, m);
                 put(v, companion(v, m, rec));
@@ -742,7 +748,7 @@ extern "C" int gala_fc_plan_create(gala_ctx *c, const uint64_t *W, int n_o, int 
         // pairs in natural order, then once more in the order the Perm kernel's threads own them
         if (hipMalloc((void **)&pl->d_w2, 4 * wsize * sizeof(u64)) != hipSuccess) rc = GALA_ENOMEM;
         if (!rc && (launch_pair_pack(c, nullptr, pl->d_w, pl->d_w2, wsize) ||
-                    launch_owner_order_2048(nullptr, pl->d_w2, pl->d_w2 + 2 * wsize, (size_t)G) ||
+                    launch_owner_order(nullptr, pl->d_w2, pl->d_w2 + 2 * wsize, (size_t)G, n) ||
                     hipDeviceSynchronize() != hipSuccess))
             rc = GALA_EHIP;
     }

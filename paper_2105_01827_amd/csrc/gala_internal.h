@@ -11,7 +11,7 @@
 namespace gala {
 
 constexpr int kMaxDigits = 32;
-constexpr int kMaxN = 8192;   // rings above 2048 run on the any-n kernels (512 or 1024 threads per polynomial)
+constexpr int kMaxN = 8192;   // rings outside 1024 .. 8192 and moduli from 2^60 on run on the any-n kernels
 constexpr int kGaussBound = 19;
 
 // Cumulative table of the discrete Gaussian (passed to kernels by value) and the draw from it: one 64-bit word
@@ -90,7 +90,7 @@ struct gala_ctx {
     bool has_device = false;           // tables uploaded; false on a host without a HIP device
     gala::u64 *d_tables = nullptr;     // 8*n words: tw,tws,itw,itws for q then for p
     int *d_slot_to_idx = nullptr;
-    gala::u64 *d_tw2 = nullptr;        // n = 2048 only: (w, companion) twiddle pairs in the order of the radix-8 passes, forward then inverse
+    gala::u64 *d_tw2 = nullptr;        // ring kernels only: (w, companion) twiddle pairs in the order of the radix-8 passes, forward then inverse
     gala::u64 *d_tw2p = nullptr;       // the same for the plaintext modulus
     gala::u64 *d_tablesP = nullptr;    // 4*n words: tw,tws,itw,itws for the special prime
     gala::u64 *d_tw2P = nullptr;       // the same for the special prime
@@ -114,7 +114,7 @@ struct gala_gk {
     std::map<int, int> index_of;       // Galois element -> key index
     std::vector<int> elements;
     gala::u64 *d_keys = nullptr;       // nkeys x ndigits x polys x n, evaluation domain (b then a)
-    gala::u64 *d_keys2 = nullptr;      // the folded keys as (value, companion) pairs for the n = 2048 kernels, or null
+    gala::u64 *d_keys2 = nullptr;      // the folded keys as (value, companion) pairs for the ring kernels, or null
     int *d_elements = nullptr;         // nkeys Galois elements, device
     int *d_iota = nullptr;             // 0,1,2,... (key index of element k is k), device
     int *d_one = nullptr;              // the single value 1 (Galois element of the identity), device
@@ -148,7 +148,7 @@ struct gala_fc_plan {
     std::vector<int> slot_row;         // padded row of each slot, -1 if it carries no weight
     std::vector<int> gal;              // Galois element of rotation g (gal[0] = 1)
     gala::u64 *d_w = nullptr;          // G x n encoded weights, evaluation domain
-    gala::u64 *d_w2 = nullptr;         // the same as (value, companion) pairs for the n = 2048 kernel, or null: G polynomials in
+    gala::u64 *d_w2 = nullptr;         // the same as (value, companion) pairs for the ring kernels, or null: G polynomials in
                                        // natural order, then the same G in the threads' ownership order
     int *d_gal = nullptr;              // G Galois elements
     int *d_key_idx = nullptr;          // G key indices (valid once bound)
@@ -209,19 +209,11 @@ int static_scratch_init();
 int launch_ntt(const gala_ctx *ctx, void *stream, const u64 *src, u64 *dst, size_t count, int inverse);
 // the same with the tables of another modulus of the context (dev_q, dev_p or dev_P)
 int launch_ntt_mod(const gala_ctx *ctx, void *stream, const u64 *src, u64 *dst, size_t count, int inverse, const NttDev &T);
-// the n = 2048 radix-8 form of launch_ntt, modulo q or modulo the special prime (uses_fast_perm contexts only)
-int launch_ntt_2048(const gala_ctx *ctx, void *stream, const u64 *src, u64 *dst, size_t count, int inverse, bool special);
-
 // Batched client steps on internal-form ciphertexts (one workgroup per ciphertext).
 int launch_encrypt(const gala_ctx *ctx, void *stream, const u64 *s_hat, const u64 *slots, const u64 *seeds, int count,
                    u64 *ct_out);
 int launch_decrypt(const gala_ctx *ctx, void *stream, const u64 *s_hat, const u64 *ct_in, int count, u64 *slots);
 const u64 *gauss_cdf_table();
-// the same two steps with the radix-8 transforms of the n = 2048 kernels
-int launch_encrypt_2048(const gala_ctx *ctx, void *stream, const u64 *s_hat, const u64 *slots, const u64 *seeds, int count,
-                        u64 *ct_out);
-int launch_decrypt_2048(const gala_ctx *ctx, void *stream, const u64 *s_hat, const u64 *ct_in, int count, u64 *slots);
-
 // Stand-alone Add / ScMult / plaintext operations on internal-form buffers (op: 0 add ct, 1 scmult, 2 sub plain, 3 add plain).
 int launch_encode_plain(const gala_ctx *ctx, void *stream, const u64 *slots, int count, int mode, u64 *plain);
 int launch_ct_op(const gala_ctx *ctx, void *stream, int op, const u64 *a, const u64 *b, size_t b_stride, int count, u64 *out);
@@ -251,15 +243,15 @@ int launch_unpack_share(const gala_ctx *ctx, void *stream, const u64 *slots, int
 // polynomials: t_hat <- t_hat - a_hat * s_hat in place (s_hat shared by all pairs).
 int launch_key_finish(const gala_ctx *ctx, void *stream, u64 *pairs, const u64 *s_hat, size_t npairs, const Modulus &mod);
 // dst[i] = (src[i], floor(src[i] * 2^64 / q)) for i < count: constants with the precomputed quotient
-// that the n = 2048 kernel multiplies by.
+// that the ring kernels multiply by.
 int launch_pair_pack(const gala_ctx *ctx, void *stream, const u64 *src, u64 *dst, size_t count);
 // the same for nkeys whole key-switching keys, with the last digit's key folded into the others (key_pack_kernel)
 int launch_key_pack(const gala_ctx *ctx, void *stream, const u64 *src, u64 *dst, size_t nkeys);
-// dst[poly][512*(t/64) + 64*k + t%64] = src[poly][8*t + k] on 16-byte pairs of n = 2048 polynomials: the order in which
+// dst[poly][512*(t/64) + 64*k + t%64] = src[poly][8*t + k] on 16-byte pairs of polynomials: the order in which
 // the threads of the Perm kernel read the 8 consecutive coefficients they own - one coalesced load per k, the eight of
 // a wavefront within 8 KiB
-int launch_owner_order_2048(void *stream, const u64 *src_pairs, u64 *dst_pairs, size_t npolys);
-// whether launch_perm_accumulate will use the n = 2048 kernel for this context
+int launch_owner_order(void *stream, const u64 *src_pairs, u64 *dst_pairs, size_t npolys, int n);
+// whether the context has kernels of its ring's own (ring_ops)
 bool uses_fast_perm(const gala_ctx *ctx);
 
 // One job of the rotate-and-accumulate kernel.  For item in [0,items), chunk in [0,nchunks):
@@ -272,9 +264,9 @@ struct PermJob {
     const u64 *w;
     const int *gal, *key_idx;
     const u64 *keys;
-    const u64 *w2, *keys2;   // (value, companion) pair images of w and keys (n = 2048 kernel only)
+    const u64 *w2, *keys2;   // (value, companion) pair images of w and keys (ring kernels only)
     const int *in_g_index;   // optional: rotation g reads input number in_g_index[g] instead of g
-    // n = 2048 kernel only, in8_S != 0: the inputs are the matrix-core product's sums in blocks of eight coefficients,
+    // ring kernels only, in8_S != 0: the inputs are the matrix-core product's sums in blocks of eight coefficients,
     // word (i/8)*in8_S + i%8 of a polynomial, c1 eight words after c0; item = b*in8_nout + O starts at
     // ct_in + O*in8_o_stride + 16*b and rotation g in_g_stride words further.
     size_t in8_S, in8_o_stride;
@@ -284,8 +276,6 @@ struct PermJob {
     u64 *partial;            // items x slots x 2n
 };
 int launch_perm_accumulate(const gala_ctx *ctx, void *stream, const PermJob &job);
-// the n = 2048, q < 2^60 specialisation (gala_perm2048.hip); launch_perm_accumulate dispatches to it
-int launch_perm_accumulate_2048(const gala_ctx *ctx, void *stream, const PermJob &job);
 
 // out[item] = sum_chunk partial[item][chunk] - mask(item) ; mask built from r and the generator.
 struct FinalizeJob {
@@ -300,12 +290,11 @@ struct FinalizeJob {
     u64 *ct_out;             // items x 2n
 };
 int launch_finalize(const gala_ctx *ctx, void *stream, const FinalizeJob &job);
-// Rotate-and-accumulate followed by share generation.  With the n = 2048 kernel the mask of every
+// Rotate-and-accumulate followed by share generation.  With the ring kernels the mask of every
 // item is built by extra workgroups of the same launch (as one more partial ciphertext, slot
 // `nchunks`, so job.slots must be >= nchunks + 1) and a light kernel adds the partials up;
 // otherwise this is launch_perm_accumulate + launch_finalize.
 int launch_perm_finalize(const gala_ctx *ctx, void *stream, const PermJob &job, const FinalizeJob &fin);
-int launch_perm_accumulate_2048_masked(const gala_ctx *ctx, void *stream, const PermJob &job, const FinalizeJob &fin);
 
 // DecPerm of `count` ciphertexts: digits[c][j] = forward(digit_j(inverse(c1))), j < ndigits.
 int launch_decperm(const gala_ctx *ctx, void *stream, const u64 *ct_in, size_t count, u64 *digits);
@@ -330,14 +319,27 @@ void conv_mfma_geometry(int groups, int cols, int nterm, int *mtiles, int *ntile
 size_t conv_mfma_image_bytes(int n, int tiles, int kblocks);
 int launch_limb_pack(const gala_ctx *ctx, void *stream, const u64 *src, int mode, int rows, int nterm, u64 *dst);
 bool uses_fast_hoist(const gala_ctx *ctx);
-int launch_hoist_taps_2048(const gala_ctx *ctx, void *stream, const u64 *ct_in, int batch, const TermList &terms,
-                           bool any_rotation, const u64 *keys2, u64 *digits, u64 *xrot);
 size_t conv_mfma_tmp_bytes(int n, int mtiles, int ntiles);
 // blocks_of_eight: tmp[(i/8)][row][column][i%8] instead of tmp[i][row][column] (what PermJob::in8_S describes)
 int launch_conv_mfma(const gala_ctx *ctx, void *stream, const u64 *wl, const u64 *xl, int batch, int groups,
                      int nterm, u64 *tmp, bool blocks_of_eight = false);
 int launch_conv_untranspose(const gala_ctx *ctx, void *stream, const u64 *tmp, int batch, int groups, u64 *acc);
-int launch_hstperm_pack_2048(const gala_ctx *ctx, void *stream, const u64 *ct_in, u64 *digits, int batch,
-                             const TermList &terms, bool any_rotation, const u64 *keys2, u64 *xl);
+
+// The launchers of one ring's own kernels (gala_ring_impl.h): rings of 1024 to 8192 slots, q < 2^60.
+struct RingOps {
+    // transform modulo q or modulo the special prime
+    int (*ntt)(const gala_ctx *, void *stream, const u64 *src, u64 *dst, size_t count, int inverse, bool special);
+    int (*perm)(const gala_ctx *, void *stream, const PermJob &);
+    int (*perm_masked)(const gala_ctx *, void *stream, const PermJob &, const FinalizeJob &);
+    // DecPerm (when any term rotates) and HstPerm of every term: as ciphertexts, or as the product's column image
+    int (*hoist_taps)(const gala_ctx *, void *stream, const u64 *ct_in, int batch, const TermList &, bool any_rotation,
+                      const u64 *keys2, u64 *digits, u64 *xrot);
+    int (*hstperm_pack)(const gala_ctx *, void *stream, const u64 *ct_in, u64 *digits, int batch, const TermList &,
+                        bool any_rotation, const u64 *keys2, u64 *xl);
+    int (*encrypt)(const gala_ctx *, void *stream, const u64 *s_hat, const u64 *slots, const u64 *seeds, int count, u64 *ct_out);
+    int (*decrypt)(const gala_ctx *, void *stream, const u64 *s_hat, const u64 *ct_in, int count, u64 *slots);
+};
+// the context's, or nullptr: its ring size or moduli have none and the any-n kernels serve it
+const RingOps *ring_ops(const gala_ctx *ctx);
 
 }  // namespace gala

@@ -862,9 +862,10 @@ inline int last_error() { return (int)hipGetLastError(); }
 // ---------------------------------------------------------------------------
 int launch_ntt_mod(const gala_ctx *c, void *stream, const u64 *src, u64 *dst, size_t count, int inverse, const NttDev &T) {
     if (!count) return 0;
-    // both ciphertext-side moduli of a context on the n = 2048 kernels have their tables
-    if (uses_fast_perm(c) && (&T == &c->dev_q || (c->special && &T == &c->dev_P)))
-        return launch_ntt_2048(c, stream, src, dst, count, inverse, &T != &c->dev_q);
+    // both ciphertext-side moduli of a context on the ring kernels have their tables
+    const RingOps *ops = ring_ops(c);
+    if (ops && (&T == &c->dev_q || (c->special && &T == &c->dev_P)))
+        return ops->ntt(c, stream, src, dst, count, inverse, &T != &c->dev_q);
     hipStream_t st = (hipStream_t)stream;
     const size_t lds = sizeof(u64) * c->n;
     by_threads(c->n, [&](auto nt) {
@@ -919,7 +920,7 @@ int launch_unpack_share(const gala_ctx *c, void *stream, const u64 *slots, int c
 int launch_encrypt(const gala_ctx *c, void *stream, const u64 *s_hat, const u64 *slots, const u64 *seeds, int count,
                    u64 *ct_out) {
     if (!count) return 0;
-    if (uses_fast_perm(c)) return launch_encrypt_2048(c, stream, s_hat, slots, seeds, count, ct_out);
+    if (const RingOps *ops = ring_ops(c)) return ops->encrypt(c, stream, s_hat, slots, seeds, count, ct_out);
     GaussCdf cdf;
     for (int i = 0; i < 2 * kGaussBound; ++i) cdf.t[i] = gauss_cdf_table()[i];
     const size_t lds = sizeof(u64) * c->n;
@@ -933,7 +934,7 @@ int launch_encrypt(const gala_ctx *c, void *stream, const u64 *s_hat, const u64 
 }
 int launch_decrypt(const gala_ctx *c, void *stream, const u64 *s_hat, const u64 *ct_in, int count, u64 *slots) {
     if (!count) return 0;
-    if (uses_fast_perm(c)) return launch_decrypt_2048(c, stream, s_hat, ct_in, count, slots);
+    if (const RingOps *ops = ring_ops(c)) return ops->decrypt(c, stream, s_hat, ct_in, count, slots);
     u64 inv = c->q;                                   // Newton's iteration for q^-1 mod 2^64 (q is odd)
     for (int i = 0; i < 6; ++i) inv *= 2 - c->q * inv;
     const size_t lds = sizeof(u64) * c->n;
@@ -952,17 +953,17 @@ int launch_key_finish(const gala_ctx *c, void *stream, u64 *pairs, const u64 *s_
                        s_hat, c->n, total, mod);
     return last_error();
 }
-__global__ void owner_order_2048_kernel(const ulonglong2 *src, ulonglong2 *dst) {
-    const size_t base = (size_t)blockIdx.x * 2048;
-    for (int j = threadIdx.x; j < 2048; j += blockDim.x) {
+__global__ void owner_order_kernel(const ulonglong2 *src, ulonglong2 *dst, int n) {
+    const size_t base = (size_t)blockIdx.x * n;
+    for (int j = threadIdx.x; j < n; j += blockDim.x) {
         const int t = j >> 3, k = j & 7;      // owner thread t, its k-th coefficient
         dst[base + (size_t)(t >> 6) * 512 + k * 64 + (t & 63)] = src[base + j];
     }
 }
-int launch_owner_order_2048(void *stream, const u64 *src, u64 *dst, size_t npolys) {
+int launch_owner_order(void *stream, const u64 *src, u64 *dst, size_t npolys, int n) {
     if (!npolys) return 0;
-    hipLaunchKernelGGL(owner_order_2048_kernel, dim3((unsigned)npolys), dim3(256), 0, (hipStream_t)stream,
-                       reinterpret_cast<const ulonglong2 *>(src), reinterpret_cast<ulonglong2 *>(dst));
+    hipLaunchKernelGGL(owner_order_kernel, dim3((unsigned)npolys), dim3(256), 0, (hipStream_t)stream,
+                       reinterpret_cast<const ulonglong2 *>(src), reinterpret_cast<ulonglong2 *>(dst), n);
     return (int)hipGetLastError();
 }
 int launch_pair_pack(const gala_ctx *c, void *stream, const u64 *src, u64 *dst, size_t count) {
@@ -981,10 +982,25 @@ int launch_key_pack(const gala_ctx *c, void *stream, const u64 *src, u64 *dst, s
                        c->logn, polys, c->ndigits, B, Binv);
     return last_error();
 }
-bool uses_fast_perm(const gala_ctx *c) {
-    return c->n == 2048 && c->q < (1ull << 60) &&
-           (!c->special || (c->special < (1ull << 60) && c->special < 2 * c->q));
+const RingOps *ring_ops_10();
+const RingOps *ring_ops_11();
+const RingOps *ring_ops_12();
+const RingOps *ring_ops_13();
+const RingOps *ring_ops(const gala_ctx *c) {
+    // lazy residues reach 16q, and P's are lifted modulo q by one subtraction
+    if (c->q >= (1ull << 60) || (c->special && (c->special >= (1ull << 60) || c->special >= 2 * c->q))) return nullptr;
+    switch (c->logn) {
+        case 10: return ring_ops_10();
+        case 11: return ring_ops_11();
+        case 12: return ring_ops_12();
+        case 13: return c->special ? nullptr : ring_ops_13();     // the two-modulus kernels need more LDS than there is
+        default: return nullptr;
+    }
 }
+bool uses_fast_perm(const gala_ctx *c) { return ring_ops(c) != nullptr; }
+// the hoisted inner products add a rotation's terms without corrections: at most 2q for each digit and q for c0
+constexpr int kHoistDigits = 3;
+bool uses_fast_hoist(const gala_ctx *c) { return ring_ops(c) && c->ndigits <= kHoistDigits; }
 int launch_perm_accumulate(const gala_ctx *c, void *stream, const PermJob &job) {
     if (job.items <= 0 || job.nchunks <= 0) return 0;
     hipStream_t st = (hipStream_t)stream;
@@ -992,8 +1008,9 @@ int launch_perm_accumulate(const gala_ctx *c, void *stream, const PermJob &job) 
     const dim3 grid((unsigned)(job.items * job.nchunks));
     const bool timed = c->prof_which == 0 && (size_t)(2 * c->prof_used + 1) < c->prof_events.size();
     if (timed) (void)hipEventRecord((hipEvent_t)c->prof_events[2 * c->prof_used], st);
-    if (uses_fast_perm(c) && !job.in_g_index) {   // the n = 2048 kernels take consecutive inputs only
-        const int rc = launch_perm_accumulate_2048(c, stream, job);
+    const RingOps *ops = ring_ops(c);
+    if (ops && !job.in_g_index) {   // the ring kernels take consecutive inputs only
+        const int rc = ops->perm(c, stream, job);
         if (timed) (void)hipEventRecord((hipEvent_t)c->prof_events[2 * c->prof_used++ + 1], st);
         return rc;
     }
@@ -1022,8 +1039,9 @@ int launch_finalize(const gala_ctx *c, void *stream, const FinalizeJob &job) {
     return last_error();
 }
 int launch_perm_finalize(const gala_ctx *c, void *stream, const PermJob &job, const FinalizeJob &fin) {
-    if (uses_fast_perm(c) && fin.r && job.slots > job.nchunks) return launch_perm_accumulate_2048_masked(c, stream, job, fin);
-    if (job.in8_S) return (int)hipErrorInvalidValue;     // only the n = 2048 kernel reads blocks of eight
+    const RingOps *ops = ring_ops(c);
+    if (ops && fin.r && job.slots > job.nchunks) return ops->perm_masked(c, stream, job, fin);
+    if (job.in8_S) return (int)hipErrorInvalidValue;     // only the ring kernels read blocks of eight
     const int rc = launch_perm_accumulate(c, stream, job);
     return rc ? rc : launch_finalize(c, stream, fin);
 }

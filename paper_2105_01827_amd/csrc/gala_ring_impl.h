@@ -1,21 +1,30 @@
-// Rotate-and-accumulate kernel specialised for n = 2048 and q < 2^60.
+// Kernels on the transforms of one ring size, n = 2^GALA_LOGN (1024 to 8192), for q < 2^60: Perm and its hoisted halves,
+// share masks, import and export, the client's steps.  Included once per ring by gala_ring1024.hip ... gala_ring8192.hip,
+// which define GALA_LOGN; the launchers leave through the RingOps table at the end.
 //
-// One 256-thread workgroup (four wavefronts) owns one polynomial; every thread
+// One workgroup of n / 8 threads (four wavefronts at n = 2048) owns one polynomial; every thread
 // keeps 8 coefficients in registers and runs radix-8 passes (three butterfly
 // stages each) on them, so a 2048-point transform is 3 + 3 + 3 + 2 stages with
 // only three exchanges through LDS.  The LDS image is padded by one word every
-// 32 so that all exchange patterns are bank-conflict free, and two buffers
+// 32 so that the exchange patterns are bank-conflict free at n = 2048, and two buffers
 // alternate so that each exchange needs a single barrier.
 //
-// Index ownership of register k of thread t in each pass (bits of the
-// coefficient index the pass works on):
-//   forward:  A bits 8-10: t + 256k | B bits 5-7 | C bits 2-4 | D bits 0-1: 8t + k
-//   inverse:  1 bits 0-2: 8t + k    | 2 bits 3-5 | 3 bits 6-8 | 4 bits 9-10: t + 256k
+// Index ownership of register k of thread t in a pass on bits B .. B+2 of the coefficient index: those three bits are
+// k, the bits below are t's low B bits, the bits above the rest of t.
+//   forward:  from the top bits down in threes; the last pass (what is left of the bits, one or two stages, none at
+//             n = 4096) owns 8t + k          n = 2048: 8-10 | 5-7 | 2-4 | 0-1
+//   inverse:  from bit 0 up in threes, the last pass owns t + (n/8) k      n = 2048: 0-2 | 3-5 | 6-8 | 9-10
 // so the inverse transform of c1 ends exactly where the forward transforms of
 // its digits begin, and the digits never leave registers.
 //
 // Forward butterflies are fully lazy: no conditional subtraction at all except
-// one (of 8q) after the seventh stage; values stay below 16q < 2^64.
+// one (of 8q) after the seventh stage and after the eleventh; values stay below 16q < 2^64.
+//
+// Rings of 4096 slots on these kernels instead of the any-n ones: he_fc 500x1024 at batch 8 706 -> 140 us from wire to
+// wire (there a lone workgroup per item also added the 256 partial sums one after the other).
+#ifndef GALA_LOGN
+#error "define GALA_LOGN before including this file"
+#endif
 #include <hip/hip_runtime.h>
 
 #include "gala_internal.h"
@@ -23,14 +32,21 @@
 namespace gala {
 namespace {
 
-constexpr int N = 2048, LOGN = 11, NT = 256, PER = 8;
+constexpr int LOGN = GALA_LOGN, N = 1 << LOGN, PER = 8, NT = N / PER;
+// a wavefront's 64 threads own the same 512 consecutive indices in every pass on bits at or below this one
+constexpr int LOCAL_BITS = 6;
 constexpr int LDS_WORDS = N + N / 32;
 
 __device__ __forceinline__ int pad(int i) { return i + (i >> 5); }
-__device__ __forceinline__ int bitrev11(int v) { return (int)(__brev((unsigned)v) >> 21); }
-__device__ __forceinline__ int galois_index11(int i, int gal) {
-    const int e = ((2 * bitrev11(i) + 1) * gal) & (2 * N - 1);
-    return bitrev11((e - 1) >> 1);
+__device__ __forceinline__ int bitrev(int v) { return (int)(__brev((unsigned)v) >> (32 - LOGN)); }
+__device__ __forceinline__ int galois_index(int i, int gal) {
+    const int e = ((2 * bitrev(i) + 1) * gal) & (2 * N - 1);
+    return bitrev((e - 1) >> 1);
+}
+// index of register 0 of thread t in the pass on bits B .. B+2
+template <int B>
+__device__ __forceinline__ int owner(int t) {
+    return ((t >> B) << (B + 3)) | (t & ((1 << B) - 1));
 }
 
 // ---- 64-bit modular primitives shaped for the gfx950 VALU ---------------------------------------
@@ -200,7 +216,7 @@ __device__ __forceinline__ void bf_one(u64 &x, u64 &y, u64 off) {
 
 // The seven constants one thread needs for a radix-8 pass on index bits B..B+2 are tw[T], tw[2T], tw[2T+1],
 // tw[4T..4T+3] of the natural table order, with T = (n >> (B+3)) + (index >> (B+3)): "block" T.  A pass uses the
-// blocks c .. 2c-1 of one level c (1, 8, 64, 256).  The table is stored level by
+// blocks c .. 2c-1 of one level c = n >> (B+3) (1, 8, 64, 256 at n = 2048).  The table is stored level by
 // level with the constant's number before the block's: level c is [e][j] = constant e of block c + j.  Constant e
 // of the 64 lanes of a wavefront is then 16 to 1024 contiguous bytes; stored block by block (128 bytes per block)
 // the same load touched up to 64 different lines, and the twiddles were two thirds of all the lines the Perm
@@ -213,10 +229,13 @@ __device__ __forceinline__ void bf_one(u64 &x, u64 &y, u64 off) {
 struct Tw7 {
     ulonglong2 t[7];
 };
-// offset, in pairs, of level c inside the forward table (levels 1, 8, 64, 256 in this order)
-__device__ __forceinline__ constexpr int level_offset(int c) {
-    return 7 * (c > 1 ? 1 : 0) + 7 * (c > 8 ? 8 : 0) + 7 * (c > 64 ? 64 : 0);
+// offset, in pairs, of level c inside the forward table (levels 1, 8, 64, (512,) n/8 in this order, each once)
+__host__ __device__ constexpr int level_offset(int c) {
+    int at = 0;
+    for (int l = 1; l < c; l *= 8) at += 7 * l;
+    return at;
 }
+constexpr int FWD_PAIRS = level_offset(N / 8) + 7 * (N / 8);
 // constants of block COUNT + j: the level's start is uniform, j*16 a 32-bit offset
 template <int COUNT>
 __device__ __forceinline__ Tw7 tw_level(const ulonglong2 *__restrict__ table, unsigned j) {
@@ -227,11 +246,14 @@ __device__ __forceinline__ Tw7 tw_level(const ulonglong2 *__restrict__ table, un
     for (int e = 0; e < 7; ++e) w.t[e] = *reinterpret_cast<const ulonglong2 *>(level + (size_t)(e * COUNT * 16) + off);
     return w;
 }
+// STAGE: the first of the three stages to run.  CORRECT: the stage (of 0, 1, 2) before which the operands that it
+// does not multiply are brought from below 16q to below 8q, or -1.
 // small_in (the same for every thread): all eight inputs are below 2^32, as gadget digits are; the first stage then
 // multiplies with mul_const_small.
-template <bool FIRST, bool CORRECT, bool CM = false>
+template <int STAGE, int CORRECT, bool CM = false>
 __device__ __forceinline__ void fwd_pass(u64 (&a)[8], const Tw7 &w, NegQ q, u64 q2, bool small_in = false) {
-    if (FIRST) {
+    const u64 q8 = 4 * q2;
+    if (STAGE == 0) {
         if (!CM && small_in) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) bf_fwd_small(a[k], a[k + 4], w.t[0], q, q2);
@@ -240,17 +262,24 @@ __device__ __forceinline__ void fwd_pass(u64 (&a)[8], const Tw7 &w, NegQ q, u64 
             for (int k = 0; k < 4; ++k) bf_fwd<CM>(a[k], a[k + 4], w.t[0], q, q2);
         }
     }
-    if (CORRECT) {   // seven stages done: everything is below 16q; the operands that are not multiplied next to below 8q
-        const u64 q8 = 4 * q2;
-        a[0] = csub_dev(a[0], q8);
-        a[1] = csub_dev(a[1], q8);
-        a[4] = csub_dev(a[4], q8);
-        a[5] = csub_dev(a[5], q8);
+    if (STAGE <= 1) {
+        if (CORRECT == 1) {
+            a[0] = csub_dev(a[0], q8);
+            a[1] = csub_dev(a[1], q8);
+            a[4] = csub_dev(a[4], q8);
+            a[5] = csub_dev(a[5], q8);
+        }
+        bf_fwd<CM>(a[0], a[2], w.t[1], q, q2);
+        bf_fwd<CM>(a[1], a[3], w.t[1], q, q2);
+        bf_fwd<CM>(a[4], a[6], w.t[2], q, q2);
+        bf_fwd<CM>(a[5], a[7], w.t[2], q, q2);
     }
-    bf_fwd<CM>(a[0], a[2], w.t[1], q, q2);
-    bf_fwd<CM>(a[1], a[3], w.t[1], q, q2);
-    bf_fwd<CM>(a[4], a[6], w.t[2], q, q2);
-    bf_fwd<CM>(a[5], a[7], w.t[2], q, q2);
+    if (CORRECT == 2) {
+        a[0] = csub_dev(a[0], q8);
+        a[2] = csub_dev(a[2], q8);
+        a[4] = csub_dev(a[4], q8);
+        a[6] = csub_dev(a[6], q8);
+    }
     bf_fwd<CM>(a[0], a[1], w.t[3], q, q2);
     bf_fwd<CM>(a[2], a[3], w.t[4], q, q2);
     bf_fwd<CM>(a[4], a[5], w.t[5], q, q2);
@@ -311,9 +340,11 @@ __device__ __forceinline__ void inv_pass(u64 (&a)[8], const Tw7 &w, NegQ q, u64 
     bf_fwd<CM>(a[2], a[6], w.t[5], q, q2);
     bf_fwd<CM>(a[3], a[7], w.t[6], q, q2);
 }
-// The inverse table: bits 3-5 as [7][8], bits 6-8 as [7][64], bits 9-10 as [6][256] (constant, low bits of the index),
-// then psi^-j / n for j = 0 .. n-1.
-constexpr int INV_MID = 7 * 8, INV_TOP = INV_MID + 7 * 64, INV_TWIST = INV_TOP + 6 * 256;
+// The inverse table: bits 3-5 as [7][8], bits 6-8 as [7][64], from n = 4096 on bits 9-11 as [7][512], the last pass's one
+// or two stages as [4] or [6][n/8] (constant, low bits of the index), then psi^-j / n for j = 0 .. n-1.
+constexpr int TOP_STAGES = LOGN % 3, TOP_CONSTS = TOP_STAGES == 2 ? 6 : 4;
+constexpr int INV_MID = 7 * 8, INV_HIGH = INV_MID + 7 * 64, INV_TOP = INV_HIGH + (LOGN >= 12 ? 7 * 512 : 0),
+              INV_TWIST = INV_TOP + (TOP_STAGES ? TOP_CONSTS * NT : 0);
 template <int CONSTANTS, int COUNT>
 __device__ __forceinline__ void inv_level(ulonglong2 (&t)[CONSTANTS], const ulonglong2 *__restrict__ level, unsigned j) {
     const char *base = reinterpret_cast<const char *>(level);
@@ -322,35 +353,34 @@ __device__ __forceinline__ void inv_level(ulonglong2 (&t)[CONSTANTS], const ulon
     for (int e = 0; e < CONSTANTS; ++e) t[e] = *reinterpret_cast<const ulonglong2 *>(base + (size_t)(e * COUNT * 16) + off);
 }
 
-// Store the 8 registers at index(k) = base_out | (k << SH_OUT), barrier, load index(k) = base_in | (k << SH_IN).
-// The bases have zeros in the three bits the register number fills, so the padded address of
-// register k is pad(base) plus a compile-time offset.
+// Exchange between the pass on bits B_OUT .. B_OUT+2 and the one on B_IN .. B_IN+2: store, barrier, load.  The owned
+// indices have zeros in the three bits the register number fills, so the padded address of
+// register k is pad(owner) plus a compile-time offset.
 template <int SH>
 __device__ __forceinline__ constexpr int reg_offset(int k) { return (k << SH) + ((k << SH) >> 5); }
-// LOCAL: every word a thread loads was stored by a thread of its own wavefront (both index sets lie in the
-// wavefront's 512-word range of the buffer).  A wavefront's LDS instructions execute in order, so its loads see
-// its stores without a workgroup barrier; the fences only keep the compiler from moving the loads up.  Four of
-// the seven exchanges of an inverse + forward transform pair are of this kind: <5,2> and <2,0> move data inside
-// groups of 32 and 4 lanes, <0,3> and <3,6> inside groups of 8 and 64; <8,5>, <6,8> and the final store of the
-// forward transform cross wavefronts and keep the barrier.
-template <int SH_OUT, int SH_IN, bool LOCAL = false>
-__device__ __forceinline__ void exchange(u64 (&a)[8], u64 *buf, int base_out, int base_in) {
-    u64 *po = buf + pad(base_out);
+// Where every word a thread loads was stored by a thread of its own wavefront (both index sets lie in the
+// wavefront's 512-word range of the buffer), a wavefront's LDS instructions execute in order, so its loads see
+// its stores without a workgroup barrier; the fences only keep the compiler from moving the loads up.  At n = 2048
+// four of the seven exchanges of an inverse + forward transform pair are of this kind; <8,5>, <6,8> and the final
+// store of the forward transform cross wavefronts and keep the barrier.
+template <int B_OUT, int B_IN>
+__device__ __forceinline__ void exchange(u64 (&a)[8], u64 *buf, int tid) {
+    u64 *po = buf + pad(owner<B_OUT>(tid));
 #pragma unroll
-    for (int k = 0; k < 8; ++k) po[reg_offset<SH_OUT>(k)] = a[k];
-    if (LOCAL) {
+    for (int k = 0; k < 8; ++k) po[reg_offset<B_OUT>(k)] = a[k];
+    if (B_OUT <= LOCAL_BITS && B_IN <= LOCAL_BITS) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     } else {
         __syncthreads();
     }
-    const u64 *pi = buf + pad(base_in);
+    const u64 *pi = buf + pad(owner<B_IN>(tid));
 #pragma unroll
-    for (int k = 0; k < 8; ++k) a[k] = pi[reg_offset<SH_IN>(k)];
+    for (int k = 0; k < 8; ++k) a[k] = pi[reg_offset<B_IN>(k)];
 }
 
-struct Tables2048 {
+struct RingTables {
     const ulonglong2 *tw, *itw;   // (w, companion) pairs, forward (see tw_level) and inverse (see inv_level)
     ulonglong2 w8[3];             // w8, w8^2, w8^3 of the inverse transform's first pass
     Modulus mod;
@@ -364,58 +394,87 @@ __device__ __forceinline__ int fresh(int tid) {
     return tid;
 }
 
-// Forward transform of the 8 registers (ownership t + 256k, values below q); the result is left in
-// LDS buffer `res` (natural index, padded), values below 16q.  LDS phases: other, res, other, res.
+// Forward transform of the 8 registers (ownership t + (n/8) k, values below 2q); the result is left in
+// LDS buffer `res` (natural index, padded), values below 16q.  LDS phases: other, res, other, res; at n = 8192, where a
+// fifth phase would start and end on the same buffer, res, other, res, other, res behind a barrier.
 template <bool CM = false>
-__device__ __forceinline__ void forward_to_lds(u64 (&a)[8], u64 *res, u64 *other, const Tables2048 &T, int tid_,
+__device__ __forceinline__ void forward_to_lds(u64 (&a)[8], u64 *res, u64 *other, const RingTables &T, int tid_,
                                                bool small_in = false) {
     const int tid = fresh(tid_);
     const NegQ q = T.nq;
     const u64 q2 = T.mod.q2;
+    constexpr int B1 = LOGN - 3, B2 = LOGN - 6, B3 = LOGN - 9, B4 = LOGN >= 12 ? LOGN - 12 : 0;
+    u64 *first = LOGN == 13 ? res : other, *second = LOGN == 13 ? other : res;
+    if (LOGN == 13) __syncthreads();
     Tw7 w = tw_level<1>(T.tw, 0);
-    fwd_pass<true, false, CM>(a, w, q, q2, small_in);                                    // bits 8-10
-    w = tw_level<8>(T.tw, (unsigned)tid >> 5);
-    exchange<8, 5>(a, other, tid, ((tid >> 5) << 8) | (tid & 31));
-    fwd_pass<true, false, CM>(a, w, q, q2);                                              // bits 5-7
-    w = tw_level<64>(T.tw, (unsigned)tid >> 2);
-    exchange<5, 2, true>(a, res, ((tid >> 5) << 8) | (tid & 31), ((tid >> 2) << 5) | (tid & 3));
-    fwd_pass<true, true, CM>(a, w, q, q2);                                               // bits 2-4
-    w = tw_level<256>(T.tw, (unsigned)tid);
-    exchange<2, 0, true>(a, other, ((tid >> 2) << 5) | (tid & 3), tid << 3);
-    fwd_pass<false, false, CM>(a, w, q, q2);                                             // bits 0-1
+    fwd_pass<0, -1, CM>(a, w, q, q2, small_in);                                          // stages 1-3
+    w = tw_level<8>(T.tw, (unsigned)tid >> B2);
+    exchange<B1, B2>(a, first, tid);
+    fwd_pass<0, -1, CM>(a, w, q, q2);                                                    // stages 4-6
+    w = tw_level<64>(T.tw, (unsigned)tid >> B3);
+    exchange<B2, B3>(a, second, tid);
+    fwd_pass<0, 1, CM>(a, w, q, q2);                                                     // stages 7-9
+    if (LOGN < 12) {
+        w = tw_level<NT>(T.tw, (unsigned)tid);
+        exchange<B3, 0>(a, first, tid);
+        fwd_pass<3 - LOGN % 3, -1, CM>(a, w, q, q2);                                     // stages 10, 11
+    } else {
+        w = tw_level<512>(T.tw, (unsigned)tid >> B4);
+        exchange<B3, B4>(a, first, tid);
+        fwd_pass<0, 2, CM>(a, w, q, q2);                                                 // stages 10-12
+        if (LOGN == 13) {
+            w = tw_level<NT>(T.tw, (unsigned)tid);
+            exchange<B4, 0>(a, second, tid);
+            fwd_pass<2, -1, CM>(a, w, q, q2);                                            // stage 13
+        }
+    }
     u64 *po = res + pad(tid << 3);
 #pragma unroll
     for (int k = 0; k < 8; ++k) po[k] = a[k];
     __syncthreads();
 }
 
-// Inverse transform: registers hold index 8t + k (values below 2q) on entry and index t + 256k,
-// canonical, on return.
+// Inverse transform: registers hold index 8t + k (values below 2q) on entry and index t + (n/8) k,
+// canonical, on return.  LDS phases A B A, one more on B at n = 8192.
 template <bool CM = false>
-__device__ __forceinline__ void inverse_in_regs(u64 (&a)[8], u64 *bufA, u64 *bufB, const Tables2048 &T, int tid_) {
+__device__ __forceinline__ void inverse_in_regs(u64 (&a)[8], u64 *bufA, u64 *bufB, const RingTables &T, int tid_) {
     const int tid = fresh(tid_);
     const NegQ q = T.nq;
     const u64 q2 = T.mod.q2;
+    constexpr int TOP = LOGN - 3;
     Tw7 w;
     inv_level<7, 8>(w.t, T.itw, (unsigned)tid & 7);
     inv_first_pass<CM>(a, T.w8, q, q2);                                                  // bits 0-2: below 8q
-    exchange<0, 3, true>(a, bufA, tid << 3, ((tid >> 3) << 6) | (tid & 7));
+    exchange<0, 3>(a, bufA, tid);
     inv_pass<false, CM>(a, w, q, q2);                                                    // bits 3-5: below 14q
     inv_level<7, 64>(w.t, T.itw + INV_MID, (unsigned)tid & 63);
-    exchange<3, 6, true>(a, bufB, ((tid >> 3) << 6) | (tid & 7), ((tid >> 6) << 9) | (tid & 63));
+    exchange<3, 6>(a, bufB, tid);
     inv_pass<true, CM>(a, w, q, q2);                                                     // bits 6-8: below 12q
-    ulonglong2 t[6];
-    inv_level<6, 256>(t, T.itw + INV_TOP, (unsigned)tid);
-    exchange<6, 8>(a, bufA, ((tid >> 6) << 9) | (tid & 63), tid);
+    // requested right behind the last barrier and used after the last stages: asked for when they are needed, their
+    // latency cost he_fc 128x1024 at batch 64 10 us of 158
     ulonglong2 c[8];
-    inv_level<8, 256>(c, T.itw + INV_TWIST, (unsigned)tid);
-    // bits 9-10 (register bits 1,2; register bit 0 is index bit 8): below 16q
-    bf_fwd<CM>(a[0], a[2], t[0], q, q2);
-    bf_fwd<CM>(a[1], a[3], t[1], q, q2);
-    bf_fwd<CM>(a[4], a[6], t[0], q, q2);
-    bf_fwd<CM>(a[5], a[7], t[1], q, q2);
+    if (LOGN >= 12) {
+        inv_level<7, 512>(w.t, T.itw + INV_HIGH, (unsigned)tid & 511);
+        exchange<6, 9>(a, bufA, tid);
+        if (!TOP_STAGES) inv_level<8, NT>(c, T.itw + INV_TWIST, (unsigned)tid);
+        inv_pass<true, CM>(a, w, q, q2);                                                 // bits 9-11: below 12q
+    }
+    if (TOP_STAGES) {
+        // the last pass (register bit 2 is the top bit): below 16q
+        ulonglong2 t[TOP_CONSTS];
+        inv_level<TOP_CONSTS, NT>(t, T.itw + INV_TOP, (unsigned)tid);
+        if (LOGN >= 12) exchange<9, TOP>(a, bufB, tid);
+        else exchange<6, TOP>(a, bufA, tid);
+        inv_level<8, NT>(c, T.itw + INV_TWIST, (unsigned)tid);
+        if (TOP_STAGES == 2) {
+            bf_fwd<CM>(a[0], a[2], t[0], q, q2);
+            bf_fwd<CM>(a[1], a[3], t[1], q, q2);
+            bf_fwd<CM>(a[4], a[6], t[0], q, q2);
+            bf_fwd<CM>(a[5], a[7], t[1], q, q2);
+        }
 #pragma unroll
-    for (int k = 0; k < 4; ++k) bf_fwd<CM>(a[k], a[k + 4], t[2 + k], q, q2);
+        for (int k = 0; k < 4; ++k) bf_fwd<CM>(a[k], a[k + 4], t[TOP_CONSTS - 4 + k], q, q2);
+    }
 #pragma unroll
     for (int k = 0; k < PER; ++k) a[k] = csub_dev(mul_const<CM>(a[k], c[k].x, c[k].y, q), T.mod.q);
 }
@@ -437,10 +496,10 @@ struct MaskJob {
     const int *slot_to_idx;
     int pbits;
     ulonglong2 delta;           // delta = floor(q/p) and its companion mod q
-    Tables2048 Tp;              // inverse-transform tables of the plaintext modulus
+    RingTables Tp;              // inverse-transform tables of the plaintext modulus
 };
 
-__device__ __forceinline__ void mask_role(const PermJob &job, const Tables2048 &T, const MaskJob &mj, int item,
+__device__ __forceinline__ void mask_role(const PermJob &job, const RingTables &T, const MaskJob &mj, int item,
                                           u64 *bufA, u64 *bufB) {
     const int tid = threadIdx.x;
     const int b = item / mj.nout, O = item % mj.nout;
@@ -533,16 +592,24 @@ __device__ __forceinline__ void item_and_chunk(const PermJob &job, int &item, in
 // From wire to wire, three digits: he_fc 128x1024 at batch 64 209 -> 162 us, 1000x2048 2669 -> 2195 us (the share of the
 // import and export transforms in that is 12 us); two digits and a special prime, 100x784 at batch 7: 92 -> 80 us.
 //
+// Wavefronts per SIMD of the Perm kernel: what its LDS (two images and the parked coefficients) leaves room for, which
+// bounds the registers: three at n = 1024 and 2048, two at 4096 (one workgroup), the workgroup's own four at 8192.
+constexpr int PERM_WAVES = LOGN <= 11 ? 3 : LOGN == 12 ? 2 : 4;
+//
 // Every product on this path is a multiplication by a constant that carries its precomputed
 // quotient (twiddles, encoded weights, key polynomials), so sums of products stay in 64-bit
 // registers: each product is below 2q, a running sum is kept below 8q and may take four more
 // products before one conditional subtraction of 8q.
 // IN8: the inputs lie in blocks of eight coefficients (PermJob::in8_S), as the matrix-core product leaves them.
 template <bool HAS_W, bool IN8 = false>
-__global__ __launch_bounds__(NT, 3) void perm_accumulate_2048(PermJob job, Tables2048 T, MaskJob mj, int gadget_bits,
+__global__ __launch_bounds__(NT, PERM_WAVES) void perm_accumulate_ring(PermJob job, RingTables T, MaskJob mj, int gadget_bits,
                                                            int ndigits) {
     __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
-    __shared__ u64 stash[N];   // each thread parks its 8 coefficients here between digits (private slots, no barrier)
+    // each thread parks its 8 coefficients here between digits (private slots, no barrier); at n = 8192 there is no LDS
+    // left for them and they stay in registers
+    constexpr bool PARK = LOGN < 13;
+    __shared__ u64 stash[PARK ? N : 1];
+    u64 coef[PARK ? 1 : PER];
     const int tid = threadIdx.x;
     if ((int)blockIdx.x >= job.items * job.nchunks) {   // only launched when mj.enabled
         mask_role(job, T, mj, (int)blockIdx.x - job.items * job.nchunks, bufA, bufB);
@@ -593,9 +660,9 @@ __global__ __launch_bounds__(NT, 3) void perm_accumulate_2048(PermJob job, Table
         // A and the next one starts on A, so that one boundary needs a barrier of its own.
         __syncthreads();
         const ulonglong2 *key = reinterpret_cast<const ulonglong2 *>(job.keys2) + (size_t)job.key_idx[g] * key_pairs;
-        int src[PER];   // where the automorphism takes output index tid + 256k from
+        int src[PER];   // where the automorphism takes output index tid + (n/8) k from
 #pragma unroll
-        for (int k = 0; k < PER; ++k) src[k] = galois_index11(tid + k * NT, gal);
+        for (int k = 0; k < PER; ++k) src[k] = galois_index(tid + k * NT, gal);
 
         // ScMult of c1 (8 consecutive coefficients per thread), then the inverse transform
         u64 a[PER];
@@ -617,7 +684,7 @@ __global__ __launch_bounds__(NT, 3) void perm_accumulate_2048(PermJob job, Table
         }
         inverse_in_regs(a, bufA, bufB, T, tid);
 #pragma unroll
-        for (int k = 0; k < PER; ++k) stash[tid + k * NT] = a[k];
+        for (int k = 0; k < PER; ++k) (PARK ? stash[tid + k * NT] : coef[PARK ? 0 : k]) = a[k];
 
         // the c0 part, permuted c0 (.) w, and the last digit's products: with the folded keys (FoldedKeys) they are
         // products of the rotated c1 (.) w itself
@@ -643,7 +710,7 @@ __global__ __launch_bounds__(NT, 3) void perm_accumulate_2048(PermJob job, Table
         int pending = 2;   // products added to sum0 since it was last brought below 8q
         for (int j = 0; j < ndigits - 1; ++j) {
 #pragma unroll
-            for (int k = 0; k < PER; ++k) a[k] = (stash[tid + k * NT] >> (j * gadget_bits)) & digit_mask;
+            for (int k = 0; k < PER; ++k) a[k] = ((PARK ? stash[tid + k * NT] : coef[PARK ? 0 : k]) >> (j * gadget_bits)) & digit_mask;
             // result in bufA, any 64-bit value below 16q.  The cheaper first stage for digits below 2^32 only where
             // the registers allow it: in the variants without weights it pushes the count past three workgroups per CU
             forward_to_lds(a, bufA, bufB, T, tid, HAS_W && gadget_bits <= 32);
@@ -688,8 +755,7 @@ __global__ __launch_bounds__(NT, 3) void perm_accumulate_2048(PermJob job, Table
 // forward transform of its digit.  digits[ct][j][i] holds lazy values (any 64-bit word below 16q), which is
 // what the constant multiplications of the inner product accept.  In the place of the last digit the inner products
 // take c1 itself (folded keys).  stored: L-1 digits.
-constexpr int HOIST_DIGITS = 3;
-__global__ __launch_bounds__(NT) void decperm_2048(const u64 *ct_in, u64 *digits, Tables2048 T, int gadget_bits,
+__global__ __launch_bounds__(NT) void decperm_ring(const u64 *ct_in, u64 *digits, RingTables T, int gadget_bits,
                                                    int stored) {
     __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
     const int tid = threadIdx.x;
@@ -716,8 +782,8 @@ __global__ __launch_bounds__(NT) void decperm_2048(const u64 *ct_in, u64 *digits
 // HstPerm: one workgroup per (ciphertext, tap).  c0 and the digits are read through the automorphism's index
 // map straight from memory: the map sends every aligned block of 64 indices onto another such block, so a
 // wavefront's gather still touches whole cache lines.  Output: xrot[ct][tap][c0|c1][i], canonical.
-__global__ __launch_bounds__(NT) void hstperm_taps_2048(const u64 *ct_in, const u64 *digits, TermList terms,
-                                                        const u64 *keys2, u64 *xrot, Tables2048 T, int ndigits) {
+__global__ __launch_bounds__(NT) void hstperm_taps_ring(const u64 *ct_in, const u64 *digits, TermList terms,
+                                                        const u64 *keys2, u64 *xrot, RingTables T, int ndigits) {
     const int tid = threadIdx.x;
     const int b = blockIdx.x / terms.nterm, e = blockIdx.x % terms.nterm;
     const size_t ct = (size_t)b * terms.nin + terms.ct[e];
@@ -745,7 +811,7 @@ __global__ __launch_bounds__(NT) void hstperm_taps_2048(const u64 *ct_in, const 
 #pragma unroll
         for (int k = 0; k < H; ++k) {
             idx[k] = tid + (half * H + k) * NT;
-            src[k] = galois_index11(idx[k], gal);
+            src[k] = galois_index(idx[k], gal);
             s0[k] = c0[src[k]];
             s1[k] = 0;
         }
@@ -779,12 +845,13 @@ __global__ __launch_bounds__(NT) void hstperm_taps_2048(const u64 *ct_in, const 
 // base-256 digit of 16 consecutive terms per chunk).  One thread owns one coefficient of one input and 16
 // consecutive terms (input ciphertext, tap), so a chunk is assembled in registers and the eight digit
 // chunks of a coefficient leave as 128 contiguous bytes.
+constexpr int PACK_THREADS = 256;      // whatever the ring: a workgroup is 64 coefficients of 4 inputs
 typedef int v4i_t __attribute__((ext_vector_type(4)));
 // ND: the number of digits when it is 3 (unrolled), else 0 (run-time loop).  ANY_ROT false: no term rotates, there
 // are no keys and no digits to read.
 template <int ND, bool ANY_ROT>
-__global__ __launch_bounds__(NT) void hstperm_pack_2048(const u64 *ct_in, const u64 *digits, TermList terms, int kblocks,
-                                                        const u64 *keys2, v4i_t *xl, Tables2048 T, int ndigits_rt, int batch) {
+__global__ __launch_bounds__(PACK_THREADS) void hstperm_pack_ring(const u64 *ct_in, const u64 *digits, TermList terms, int kblocks,
+                                                        const u64 *keys2, v4i_t *xl, RingTables T, int ndigits_rt, int batch) {
     // a workgroup is 64 coefficients x 4 inputs: its wavefronts read the same key words, which then come out of
     // the vector cache for three of them
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -813,7 +880,7 @@ __global__ __launch_bounds__(NT) void hstperm_pack_2048(const u64 *ct_in, const 
         if (gal != cur_gal) {          // the same for every lane
             cur_gal = gal;
             ident = gal == 1;
-            src = ident ? i : galois_index11(i, gal);
+            src = ident ? i : galois_index(i, gal);
             if (ANY_ROT && !ident) {
                 key = reinterpret_cast<const ulonglong2 *>(keys2) + (size_t)terms.key[e] * key_pairs;
                 if (ND) {
@@ -863,7 +930,7 @@ __global__ __launch_bounds__(NT) void hstperm_pack_2048(const u64 *ct_in, const 
     // the registers, every store instruction would touch 64 different lines with 16 bytes each.  The chunks go
     // through LDS instead (row = lane, padded to 144 bytes), so that instruction k of a wavefront writes the
     // 1 KiB of coefficients 8k..8k+7.
-    __shared__ v4i_t tr[NT / 64][64][9];
+    __shared__ v4i_t tr[PACK_THREADS / 64][64][9];
     const int kb = eb >> 2, g = eb & 3;
     const int i_wave = blockIdx.x * 64;
 #pragma unroll
@@ -900,7 +967,7 @@ __global__ __launch_bounds__(NT) void hstperm_pack_2048(const u64 *ct_in, const 
 // 41.7 -> 28.8 us.
 // Inputs as the any-n kernel takes them: below 4q forward, below 2q inverse.
 template <bool INVERSE>
-__global__ __launch_bounds__(NT) void ntt_2048(const u64 *src, u64 *dst, Tables2048 T) {
+__global__ __launch_bounds__(NT) void ntt_ring(const u64 *src, u64 *dst, RingTables T) {
     __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
     const int tid = threadIdx.x;
     src += (size_t)blockIdx.x * N;
@@ -929,8 +996,8 @@ __global__ __launch_bounds__(NT) void ntt_2048(const u64 *src, u64 *dst, Tables2
 // ---- the client's two steps with the radix-8 transforms (one workgroup per ciphertext) ------------------------
 // ct = (-a s + e + delta m, a) (Sec. II-C(1)), bit for bit the any-n kernel: m = the plaintext polynomial of the
 // slots, a uniform, e Gaussian, all drawn from the ciphertext's seed by coefficient index.
-__global__ __launch_bounds__(NT, 4) void encrypt_2048(const u64 *slots, const u64 *seeds, const u64 *s_hat, u64 *ct_out,
-                                                   Tables2048 T, Tables2048 Tp, const int *slot_to_idx, GaussCdf cdf,
+__global__ __launch_bounds__(NT, 4) void encrypt_ring(const u64 *slots, const u64 *seeds, const u64 *s_hat, u64 *ct_out,
+                                                   RingTables T, RingTables Tp, const int *slot_to_idx, GaussCdf cdf,
                                                    int qbits, ulonglong2 delta) {
     __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
     const int tid = threadIdx.x;
@@ -945,7 +1012,7 @@ __global__ __launch_bounds__(NT, 4) void encrypt_2048(const u64 *slots, const u6
     u64 a[PER];
 #pragma unroll
     for (int k = 0; k < PER; ++k) a[k] = bufB[8 * tid + k];
-    inverse_in_regs(a, bufA, bufB, Tp, tid);          // m, coefficient tid + 256k, canonical mod p
+    inverse_in_regs(a, bufA, bufB, Tp, tid);          // m, coefficient tid + (n/8) k, canonical mod p
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         const int e = draw_gauss_cdf(cdf, seed, kStreamCtE, (u64)(tid + k * NT));
@@ -968,8 +1035,8 @@ __global__ __launch_bounds__(NT, 4) void encrypt_2048(const u64 *slots, const u6
     }
 }
 // slots = decode(round(p (c0 + c1 s) / q) mod p); the rounded quotient through the exact division by q (q^-1 mod 2^64).
-__global__ __launch_bounds__(NT) void decrypt_2048(const u64 *ct_in, const u64 *s_hat, u64 *slots, Tables2048 T,
-                                                   Tables2048 Tp, const int *slot_to_idx, u64 q_inv64) {
+__global__ __launch_bounds__(NT) void decrypt_ring(const u64 *ct_in, const u64 *s_hat, u64 *slots, RingTables T,
+                                                   RingTables Tp, const int *slot_to_idx, u64 q_inv64) {
     __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
     const int tid = threadIdx.x;
     const u64 q = T.mod.q, p = Tp.mod.q;
@@ -980,7 +1047,7 @@ __global__ __launch_bounds__(NT) void decrypt_2048(const u64 *ct_in, const u64 *
         const int i = 8 * tid + k;
         a[k] = add_mod(c0[i], mul_mod(c1[i], s_hat[i], T.mod), q);
     }
-    inverse_in_regs(a, bufA, bufB, T, tid);           // c0 + c1 s, coefficient tid + 256k, canonical
+    inverse_in_regs(a, bufA, bufB, T, tid);           // c0 + c1 s, coefficient tid + (n/8) k, canonical
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         const u128 t = (u128)p * a[k] + (q >> 1);
@@ -993,6 +1060,7 @@ __global__ __launch_bounds__(NT) void decrypt_2048(const u64 *ct_in, const u64 *
     for (int s = tid; s < N; s += NT) out[s] = reduce64(bufA[pad(slot_to_idx[s])], Tp.mod);
 }
 
+#if GALA_LOGN < 13   // at n = 8192 the remainder sums do not fit beside the images: the any-n kernels serve it
 // ---- key switching with a special prime P -------------------------------------------------------------
 // Keys hold four polynomials per digit ((b, a) modulo q, then modulo P).  Per rotation the digits are
 // transformed in both moduli and multiplied into sums modulo q and modulo P; the sums modulo P go back to
@@ -1001,17 +1069,17 @@ __global__ __launch_bounds__(NT) void decrypt_2048(const u64 *ct_in, const u64 *
 // (R0, R1) and transformed once at the end; terms that are not divided by P (the c0 part, rotations by zero)
 // enter the sums multiplied by P.  Needs P < 2^60 and P < 2q.
 struct SpecialJob {
-    Tables2048 TP;          // transform tables of P
+    RingTables TP;          // transform tables of P
     ulonglong2 Pq, Pinv;    // P mod q and P^-1 mod q with companions
 };
 
 // IN8: the inputs lie in blocks of eight coefficients (PermJob::in8_S), as the matrix-core product leaves them.
 template <bool HAS_W, bool IN8 = false>
-__global__ __launch_bounds__(NT, 2) void perm_accumulate_special_2048(PermJob job, Tables2048 T, SpecialJob S, MaskJob mj,
+__global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob job, RingTables T, SpecialJob S, MaskJob mj,
                                                                       int gadget_bits, int ndigits) {
     __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
     __shared__ u64 stash[N];
-    // Sums of the lifted remainders (coefficient domain modulo q, canonical, index tid + 256k): 15 of a thread's 16
+    // Sums of the lifted remainders (coefficient domain modulo q, canonical, index tid + (n/8) k): 15 of a thread's 16
     // words live in LDS slots of its own (no barrier), which is what two workgroups per CU leave room for.
     __shared__ u64 Rl[15 * NT];
     const int tid = threadIdx.x;
@@ -1063,7 +1131,7 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_2048(PermJob jo
         const ulonglong2 *key = reinterpret_cast<const ulonglong2 *>(job.keys2) + (size_t)job.key_idx[g] * key_pairs;
         int src[PER];
 #pragma unroll
-        for (int k = 0; k < PER; ++k) src[k] = galois_index11(tid + k * NT, gal);
+        for (int k = 0; k < PER; ++k) src[k] = galois_index(tid + k * NT, gal);
         u64 a[PER];
         {
             const ulonglong2 *c1v = reinterpret_cast<const ulonglong2 *>(IN8 ? c1 + (size_t)tid * S8 : c1 + 8 * tid);
@@ -1203,7 +1271,7 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_2048(PermJob jo
 // ---- hoisted input rotations with a special prime ----------------------------------------------------------
 // DecPerm: one workgroup per (ciphertext, digit, modulus); digits[ct][j][modulus][i], lazy values of that modulus.
 // The last digit modulo q is not needed (folded keys), its place stays empty.
-__global__ __launch_bounds__(NT) void decperm_special_2048(const u64 *ct_in, u64 *digits, Tables2048 T, Tables2048 TP,
+__global__ __launch_bounds__(NT) void decperm_special_ring(const u64 *ct_in, u64 *digits, RingTables T, RingTables TP,
                                                            int gadget_bits, int ndigits) {
     __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
     const int tid = threadIdx.x;
@@ -1232,8 +1300,8 @@ __global__ __launch_bounds__(NT) void decperm_special_2048(const u64 *ct_in, u64
 // HstPerm: one workgroup per (ciphertext, tap): inner products in both moduli from the stored digits, the sums
 // modulo P back to coefficients, lifted, reduced modulo q and transformed forward again, then
 // out = (P c0(X^g) + t_b - NTT(r_b)) / P, (t_a - NTT(r_a)) / P.  Output: xrot[ct][tap][c0|c1][i], canonical.
-__global__ __launch_bounds__(NT, 3) void hstperm_special_2048(const u64 *ct_in, const u64 *digits, TermList terms,
-                                                           const u64 *keys2, u64 *xrot, Tables2048 T, SpecialJob S,
+__global__ __launch_bounds__(NT, 3) void hstperm_special_ring(const u64 *ct_in, const u64 *digits, TermList terms,
+                                                           const u64 *keys2, u64 *xrot, RingTables T, SpecialJob S,
                                                            int ndigits) {
     __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
     const int tid = threadIdx.x;
@@ -1256,7 +1324,7 @@ __global__ __launch_bounds__(NT, 3) void hstperm_special_2048(const u64 *ct_in, 
     const ulonglong2 *key = reinterpret_cast<const ulonglong2 *>(keys2) + (size_t)terms.key[e] * ndigits * 4 * N;
     int src[PER];
 #pragma unroll
-    for (int k = 0; k < PER; ++k) src[k] = galois_index11(tid + k * NT, gal);
+    for (int k = 0; k < PER; ++k) src[k] = galois_index(tid + k * NT, gal);
     // The two output polynomials one after the other (the digits are read twice, out of the L2): half the sums
     // are alive at a time, and the products are formed four coefficients at a time so that no more than their
     // operands are in flight - the kernel fits three workgroups per CU instead of one.
@@ -1307,6 +1375,8 @@ __global__ __launch_bounds__(NT, 3) void hstperm_special_2048(const u64 *ct_in, 
     }
 }
 
+#endif
+
 // out[item] = sum over the first `used` partial ciphertexts of the item (mod q).  A workgroup owns 64 consecutive
 // words; its SG wavefronts each add every SG-th partial (independent loads, several in flight) and the SG sums
 // meet in LDS: with one input and a few hundred partials a single thread per word would wait for them one by one.
@@ -1342,10 +1412,10 @@ __global__ void sum_few_partials_kernel(const u64 *partial, int slots, int used,
 
 }  // namespace
 
-static Tables2048 make_tables(const u64 *pairs, const NttHost &h) {
-    Tables2048 T;
+static RingTables make_tables(const u64 *pairs, const NttHost &h) {
+    RingTables T;
     T.tw = reinterpret_cast<const ulonglong2 *>(pairs);
-    T.itw = T.tw + 7 * (1 + 8 + 64 + 256);
+    T.itw = T.tw + FWD_PAIRS;
     for (int e = 0; e < 3; ++e) T.w8[e] = make_ulonglong2(h.w8[e], h.w8s[e]);
     T.mod = h.mod;
     const u64 neg = 0 - h.mod.q;
@@ -1354,10 +1424,11 @@ static Tables2048 make_tables(const u64 *pairs, const NttHost &h) {
     return T;
 }
 
-static int launch_2048(const gala_ctx *c, void *stream, const PermJob &job, const MaskJob &mj) {
+static int launch_perm(const gala_ctx *c, void *stream, const PermJob &job, const MaskJob &mj) {
     hipStream_t st = (hipStream_t)stream;
-    const Tables2048 T = make_tables(c->d_tw2, c->ntt_q);
+    const RingTables T = make_tables(c->d_tw2, c->ntt_q);
     const dim3 grid((unsigned)(job.items * job.nchunks + (mj.enabled ? job.items : 0)));
+#if GALA_LOGN < 13
     if (c->special) {
         if (job.in8_S && job.w) return (int)hipErrorInvalidValue;
         SpecialJob S;
@@ -1365,31 +1436,32 @@ static int launch_2048(const gala_ctx *c, void *stream, const PermJob &job, cons
         S.Pq = make_ulonglong2(c->Pq, c->Pq_s);
         S.Pinv = make_ulonglong2(c->Pinv, c->Pinv_s);
         if (job.w)
-            hipLaunchKernelGGL(perm_accumulate_special_2048<true>, grid, dim3(NT), 0, st, job, T, S, mj, c->gadget_bits, c->ndigits);
+            hipLaunchKernelGGL(perm_accumulate_special_ring<true>, grid, dim3(NT), 0, st, job, T, S, mj, c->gadget_bits, c->ndigits);
         else if (job.in8_S)
-            hipLaunchKernelGGL((perm_accumulate_special_2048<false, true>), grid, dim3(NT), 0, st, job, T, S, mj, c->gadget_bits,
+            hipLaunchKernelGGL((perm_accumulate_special_ring<false, true>), grid, dim3(NT), 0, st, job, T, S, mj, c->gadget_bits,
                                c->ndigits);
         else
-            hipLaunchKernelGGL(perm_accumulate_special_2048<false>, grid, dim3(NT), 0, st, job, T, S, mj, c->gadget_bits, c->ndigits);
+            hipLaunchKernelGGL(perm_accumulate_special_ring<false>, grid, dim3(NT), 0, st, job, T, S, mj, c->gadget_bits, c->ndigits);
         return (int)hipGetLastError();
     }
+#endif
     if (job.in8_S && job.w) return (int)hipErrorInvalidValue;
     if (job.w)
-        hipLaunchKernelGGL(perm_accumulate_2048<true>, grid, dim3(NT), 0, st, job, T, mj, c->gadget_bits, c->ndigits);
+        hipLaunchKernelGGL(perm_accumulate_ring<true>, grid, dim3(NT), 0, st, job, T, mj, c->gadget_bits, c->ndigits);
     else if (job.in8_S)
-        hipLaunchKernelGGL((perm_accumulate_2048<false, true>), grid, dim3(NT), 0, st, job, T, mj, c->gadget_bits, c->ndigits);
+        hipLaunchKernelGGL((perm_accumulate_ring<false, true>), grid, dim3(NT), 0, st, job, T, mj, c->gadget_bits, c->ndigits);
     else
-        hipLaunchKernelGGL(perm_accumulate_2048<false>, grid, dim3(NT), 0, st, job, T, mj, c->gadget_bits, c->ndigits);
+        hipLaunchKernelGGL(perm_accumulate_ring<false>, grid, dim3(NT), 0, st, job, T, mj, c->gadget_bits, c->ndigits);
     return (int)hipGetLastError();
 }
 
-int launch_perm_accumulate_2048(const gala_ctx *c, void *stream, const PermJob &job) {
+static int perm(const gala_ctx *c, void *stream, const PermJob &job) {
     MaskJob mj{};
     mj.enabled = 0;
-    return launch_2048(c, stream, job, mj);
+    return launch_perm(c, stream, job, mj);
 }
 
-int launch_perm_accumulate_2048_masked(const gala_ctx *c, void *stream, const PermJob &job, const FinalizeJob &fin) {
+static int perm_masked(const gala_ctx *c, void *stream, const PermJob &job, const FinalizeJob &fin) {
     MaskJob mj{};
     mj.enabled = 1;
     mj.nout = fin.nout;
@@ -1404,7 +1476,7 @@ int launch_perm_accumulate_2048_masked(const gala_ctx *c, void *stream, const Pe
     hipStream_t st = (hipStream_t)stream;
     const bool timed = c->prof_which == 0 && (size_t)(2 * c->prof_used + 1) < c->prof_events.size();
     if (timed) (void)hipEventRecord((hipEvent_t)c->prof_events[2 * c->prof_used], st);
-    int rc = launch_2048(c, stream, job, mj);
+    int rc = launch_perm(c, stream, job, mj);
     if (timed) (void)hipEventRecord((hipEvent_t)c->prof_events[2 * c->prof_used++ + 1], st);
     if (rc) return rc;
     const size_t words = (size_t)job.items * 2 * N;
@@ -1421,46 +1493,47 @@ int launch_perm_accumulate_2048_masked(const gala_ctx *c, void *stream, const Pe
     return (int)hipGetLastError();
 }
 
-bool uses_fast_hoist(const gala_ctx *c) { return uses_fast_perm(c) && c->ndigits <= HOIST_DIGITS; }
-int launch_hoist_taps_2048(const gala_ctx *c, void *stream, const u64 *ct_in, int batch, const TermList &terms,
+static int hoist_taps(const gala_ctx *c, void *stream, const u64 *ct_in, int batch, const TermList &terms,
                            bool any_rotation, const u64 *keys2, u64 *digits, u64 *xrot) {
     if (batch <= 0 || terms.nterm <= 0) return 0;
     const size_t count = (size_t)batch * terms.nin;
-    const Tables2048 T = make_tables(c->d_tw2, c->ntt_q);
+    const RingTables T = make_tables(c->d_tw2, c->ntt_q);
     hipStream_t st = (hipStream_t)stream;
     const dim3 per_term((unsigned)((size_t)batch * terms.nterm));
+#if GALA_LOGN < 13
     if (c->special) {     // digits[ct][j][modulus][N]: twice the digit storage of the one-prime form
         SpecialJob S;
         S.TP = make_tables(c->d_tw2P, c->ntt_P);
         S.Pq = make_ulonglong2(c->Pq, c->Pq_s);
         S.Pinv = make_ulonglong2(c->Pinv, c->Pinv_s);
         if (any_rotation) {
-            hipLaunchKernelGGL(decperm_special_2048, dim3((unsigned)(count * (2 * c->ndigits - 1))), dim3(NT), 0, st, ct_in, digits,
+            hipLaunchKernelGGL(decperm_special_ring, dim3((unsigned)(count * (2 * c->ndigits - 1))), dim3(NT), 0, st, ct_in, digits,
                                T, S.TP, c->gadget_bits, c->ndigits);
             const int rc = (int)hipGetLastError();
             if (rc) return rc;
         }
-        hipLaunchKernelGGL(hstperm_special_2048, per_term, dim3(NT), 0, st, ct_in, digits, terms, keys2, xrot, T, S, c->ndigits);
+        hipLaunchKernelGGL(hstperm_special_ring, per_term, dim3(NT), 0, st, ct_in, digits, terms, keys2, xrot, T, S, c->ndigits);
         return (int)hipGetLastError();
     }
+#endif
     if (any_rotation && c->ndigits > 1) {
-        hipLaunchKernelGGL(decperm_2048, dim3((unsigned)(count * (c->ndigits - 1))), dim3(NT), 0, st, ct_in, digits, T,
+        hipLaunchKernelGGL(decperm_ring, dim3((unsigned)(count * (c->ndigits - 1))), dim3(NT), 0, st, ct_in, digits, T,
                            c->gadget_bits, c->ndigits - 1);
         const int rc = (int)hipGetLastError();
         if (rc) return rc;
     }
-    hipLaunchKernelGGL(hstperm_taps_2048, per_term, dim3(NT), 0, st, ct_in, digits, terms, keys2, xrot, T, c->ndigits);
+    hipLaunchKernelGGL(hstperm_taps_ring, per_term, dim3(NT), 0, st, ct_in, digits, terms, keys2, xrot, T, c->ndigits);
     return (int)hipGetLastError();
 }
 
 // DecPerm (when any term rotates) followed by the HstPerm of every term, written as the column image
-int launch_hstperm_pack_2048(const gala_ctx *c, void *stream, const u64 *ct_in, u64 *digits, int batch,
+static int hstperm_pack(const gala_ctx *c, void *stream, const u64 *ct_in, u64 *digits, int batch,
                              const TermList &terms, bool any_rotation, const u64 *keys2, u64 *xl) {
     if (batch <= 0 || terms.nterm <= 0) return 0;
-    const Tables2048 T = make_tables(c->d_tw2, c->ntt_q);
+    const RingTables T = make_tables(c->d_tw2, c->ntt_q);
     hipStream_t st = (hipStream_t)stream;
     if (any_rotation && c->ndigits > 1) {
-        hipLaunchKernelGGL(decperm_2048, dim3((unsigned)((size_t)batch * terms.nin * (c->ndigits - 1))), dim3(NT), 0, st, ct_in,
+        hipLaunchKernelGGL(decperm_ring, dim3((unsigned)((size_t)batch * terms.nin * (c->ndigits - 1))), dim3(NT), 0, st, ct_in,
                            digits, T, c->gadget_bits, c->ndigits - 1);
         const int rc = (int)hipGetLastError();
         if (rc) return rc;
@@ -1469,42 +1542,49 @@ int launch_hstperm_pack_2048(const gala_ctx *c, void *stream, const u64 *ct_in, 
     const dim3 grid(N / 64, (unsigned)eblocks, (unsigned)((batch + 3) / 4));
     v4i_t *out = reinterpret_cast<v4i_t *>(xl);
     if (!any_rotation)
-        hipLaunchKernelGGL((hstperm_pack_2048<0, false>), grid, dim3(NT), 0, st, ct_in, digits, terms, kblocks, keys2, out, T, c->ndigits, batch);
+        hipLaunchKernelGGL((hstperm_pack_ring<0, false>), grid, dim3(PACK_THREADS), 0, st, ct_in, digits, terms, kblocks, keys2, out, T, c->ndigits, batch);
     else if (!keys2)
         return (int)hipErrorInvalidValue;
     else if (c->ndigits == 3)
-        hipLaunchKernelGGL((hstperm_pack_2048<3, true>), grid, dim3(NT), 0, st, ct_in, digits, terms, kblocks, keys2, out, T, c->ndigits, batch);
+        hipLaunchKernelGGL((hstperm_pack_ring<3, true>), grid, dim3(PACK_THREADS), 0, st, ct_in, digits, terms, kblocks, keys2, out, T, c->ndigits, batch);
     else
-        hipLaunchKernelGGL((hstperm_pack_2048<0, true>), grid, dim3(NT), 0, st, ct_in, digits, terms, kblocks, keys2, out, T, c->ndigits, batch);
+        hipLaunchKernelGGL((hstperm_pack_ring<0, true>), grid, dim3(PACK_THREADS), 0, st, ct_in, digits, terms, kblocks, keys2, out, T, c->ndigits, batch);
     return (int)hipGetLastError();
 }
 
-int launch_ntt_2048(const gala_ctx *c, void *stream, const u64 *src, u64 *dst, size_t count, int inverse, bool special) {
+static int ntt(const gala_ctx *c, void *stream, const u64 *src, u64 *dst, size_t count, int inverse, bool special) {
     if (!count) return 0;
-    const Tables2048 T = special ? make_tables(c->d_tw2P, c->ntt_P) : make_tables(c->d_tw2, c->ntt_q);
+    const RingTables T = special ? make_tables(c->d_tw2P, c->ntt_P) : make_tables(c->d_tw2, c->ntt_q);
     hipStream_t st = (hipStream_t)stream;
-    if (inverse) hipLaunchKernelGGL(ntt_2048<true>, dim3((unsigned)count), dim3(NT), 0, st, src, dst, T);
-    else hipLaunchKernelGGL(ntt_2048<false>, dim3((unsigned)count), dim3(NT), 0, st, src, dst, T);
+    if (inverse) hipLaunchKernelGGL(ntt_ring<true>, dim3((unsigned)count), dim3(NT), 0, st, src, dst, T);
+    else hipLaunchKernelGGL(ntt_ring<false>, dim3((unsigned)count), dim3(NT), 0, st, src, dst, T);
     return (int)hipGetLastError();
 }
 
-int launch_encrypt_2048(const gala_ctx *c, void *stream, const u64 *s_hat, const u64 *slots, const u64 *seeds, int count,
+static int encrypt(const gala_ctx *c, void *stream, const u64 *s_hat, const u64 *slots, const u64 *seeds, int count,
                         u64 *ct_out) {
     if (!count) return 0;
     GaussCdf cdf;
     for (int i = 0; i < 2 * kGaussBound; ++i) cdf.t[i] = gauss_cdf_table()[i];
-    hipLaunchKernelGGL(encrypt_2048, dim3((unsigned)count), dim3(NT), 0, (hipStream_t)stream, slots, seeds, s_hat, ct_out,
+    hipLaunchKernelGGL(encrypt_ring, dim3((unsigned)count), dim3(NT), 0, (hipStream_t)stream, slots, seeds, s_hat, ct_out,
                        make_tables(c->d_tw2, c->ntt_q), make_tables(c->d_tw2p, c->ntt_p), c->d_slot_to_idx, cdf, c->qbits,
                        make_ulonglong2(c->delta, c->delta_s));
     return (int)hipGetLastError();
 }
-int launch_decrypt_2048(const gala_ctx *c, void *stream, const u64 *s_hat, const u64 *ct_in, int count, u64 *slots) {
+static int decrypt(const gala_ctx *c, void *stream, const u64 *s_hat, const u64 *ct_in, int count, u64 *slots) {
     if (!count) return 0;
     u64 inv = c->q;                                   // Newton's iteration for q^-1 mod 2^64 (q is odd)
     for (int i = 0; i < 6; ++i) inv *= 2 - c->q * inv;
-    hipLaunchKernelGGL(decrypt_2048, dim3((unsigned)count), dim3(NT), 0, (hipStream_t)stream, ct_in, s_hat, slots,
+    hipLaunchKernelGGL(decrypt_ring, dim3((unsigned)count), dim3(NT), 0, (hipStream_t)stream, ct_in, s_hat, slots,
                        make_tables(c->d_tw2, c->ntt_q), make_tables(c->d_tw2p, c->ntt_p), c->d_slot_to_idx, inv);
     return (int)hipGetLastError();
+}
+
+#define GALA_RING_OPS_(logn) ring_ops_##logn
+#define GALA_RING_OPS(logn) GALA_RING_OPS_(logn)
+const RingOps *GALA_RING_OPS(GALA_LOGN)() {
+    static const RingOps ops = {ntt, perm, perm_masked, hoist_taps, hstperm_pack, encrypt, decrypt};
+    return &ops;
 }
 
 }  // namespace gala
