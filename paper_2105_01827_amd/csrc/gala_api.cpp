@@ -29,10 +29,21 @@ int choose_chunks(const gala_ctx *ctx, int items, int G) {
     // With a special prime the kernel holds two workgroups per CU, not three, and a rotation is twice the work:
     // one round of 512 workgroups was the fastest cut for short and long sums alike (he_fc 128x1024: 0.43 ms
     // against 0.48 ms with 2048 workgroups and 0.58 ms with 768).
-    // Other rings with kernels of their own hold more or fewer workgroups in the same proportion (LDS, registers), at
-    // least one per CU.
+    // Other rings with kernels of their own hold more or fewer workgroups in the same proportion (LDS, registers).  From
+    // n = 4096 on it is one per CU, and what counts is rounds of the 256 CUs times the rotations of the longest chunk,
+    // a workgroup's start and its partial ciphertext taken as a fifth of a rotation (he_fc 500x1024 at n = 4096, batch
+    // 8: 32 chunks in one round 130 us, 64 in two 136, 24 that fill 192 CUs 149, 16 in half a round 190).
     const int n = uses_fast_perm(ctx) ? ctx->n : 2048;
-    auto scaled = [n](int wgs) { return std::max(256, wgs * 2048 / n); };
+    if (n >= 4096) {
+        int best = 1;
+        long cost = -1;
+        for (int c = 1; c <= std::max(1, G - 1); c += c < 64 ? 1 : c / 8) {
+            const long rounds = ((long)items * c + 255) / 256, t = rounds * (5 * ((G - 1 + c - 1) / c) + 1);
+            if (cost < 0 || t < cost) cost = t, best = c;
+        }
+        return best;
+    }
+    auto scaled = [n](int wgs) { return wgs * 2048 / n; };
     if (G < 32 || ctx->special) {
         const int c = (scaled(ctx->special ? 512 : 768) + items - 1) / items;
         return std::max(1, std::min(c, G - 1));     // G-1 entries cost a key switch (chunk_range)

@@ -20,7 +20,7 @@
 // Forward butterflies are fully lazy: no conditional subtraction at all except
 // one (of 8q) after the seventh stage and after the eleventh; values stay below 16q < 2^64.
 //
-// Rings of 4096 slots on these kernels instead of the any-n ones: he_fc 500x1024 at batch 8 706 -> 140 us from wire to
+// Rings of 4096 slots on these kernels instead of the any-n ones: he_fc 500x1024 at batch 8 706 -> 130 us from wire to
 // wire (there a lone workgroup per item also added the 256 partial sums one after the other).
 #ifndef GALA_LOGN
 #error "define GALA_LOGN before including this file"
@@ -397,9 +397,13 @@ __device__ __forceinline__ int fresh(int tid) {
 // Forward transform of the 8 registers (ownership t + (n/8) k, values below 2q); the result is left in
 // LDS buffer `res` (natural index, padded), values below 16q.  LDS phases: other, res, other, res; at n = 8192, where a
 // fifth phase would start and end on the same buffer, res, other, res, other, res behind a barrier.
-template <bool CM = false>
+// `ahead` runs before the last pass: loads of what is multiplied with the result can be issued there.
+struct NothingAhead {
+    __device__ __forceinline__ void operator()() const {}
+};
+template <bool CM = false, class Ahead = NothingAhead>
 __device__ __forceinline__ void forward_to_lds(u64 (&a)[8], u64 *res, u64 *other, const RingTables &T, int tid_,
-                                               bool small_in = false) {
+                                               bool small_in = false, Ahead ahead = Ahead{}) {
     const int tid = fresh(tid_);
     const NegQ q = T.nq;
     const u64 q2 = T.mod.q2;
@@ -417,14 +421,17 @@ __device__ __forceinline__ void forward_to_lds(u64 (&a)[8], u64 *res, u64 *other
     if (LOGN < 12) {
         w = tw_level<NT>(T.tw, (unsigned)tid);
         exchange<B3, 0>(a, first, tid);
+        ahead();
         fwd_pass<3 - LOGN % 3, -1, CM>(a, w, q, q2);                                     // stages 10, 11
     } else {
         w = tw_level<512>(T.tw, (unsigned)tid >> B4);
         exchange<B3, B4>(a, first, tid);
+        if (LOGN == 12) ahead();
         fwd_pass<0, 2, CM>(a, w, q, q2);                                                 // stages 10-12
         if (LOGN == 13) {
             w = tw_level<NT>(T.tw, (unsigned)tid);
             exchange<B4, 0>(a, second, tid);
+            ahead();
             fwd_pass<2, -1, CM>(a, w, q, q2);                                            // stage 13
         }
     }
@@ -610,6 +617,10 @@ __global__ __launch_bounds__(NT, PERM_WAVES) void perm_accumulate_ring(PermJob j
     constexpr bool PARK = LOGN < 13;
     __shared__ u64 stash[PARK ? N : 1];
     u64 coef[PARK ? 1 : PER];
+    // Key pairs of a digit requested before its transform's last pass, as many as the registers hold.  At n = 4096, two
+    // wavefronts per SIMD, three of eight: he_fc 500x1024 at batch 8 139.6 -> 135.7 us.  At three wavefronts per SIMD
+    // they gain nothing without weights and spill with them (he_fc 1000x2048 2185 -> 2270 us).
+    constexpr int AHEAD = LOGN == 12 ? 3 : 0;
     const int tid = threadIdx.x;
     if ((int)blockIdx.x >= job.items * job.nchunks) {   // only launched when mj.enabled
         mask_role(job, T, mj, (int)blockIdx.x - job.items * job.nchunks, bufA, bufB);
@@ -713,8 +724,15 @@ __global__ __launch_bounds__(NT, PERM_WAVES) void perm_accumulate_ring(PermJob j
             for (int k = 0; k < PER; ++k) a[k] = ((PARK ? stash[tid + k * NT] : coef[PARK ? 0 : k]) >> (j * gadget_bits)) & digit_mask;
             // result in bufA, any 64-bit value below 16q.  The cheaper first stage for digits below 2^32 only where
             // the registers allow it: in the variants without weights it pushes the count past three workgroups per CU
-            forward_to_lds(a, bufA, bufB, T, tid, HAS_W && gadget_bits <= 32);
             const ulonglong2 *kb = key + (size_t)(2 * j) * N, *ka = kb + N;
+            ulonglong2 kbv[AHEAD ? AHEAD : 1], kav[AHEAD ? AHEAD : 1];
+            forward_to_lds(a, bufA, bufB, T, tid, HAS_W && gadget_bits <= 32, [&] {
+#pragma unroll
+                for (int k = 0; k < AHEAD; ++k) {
+                    kbv[k] = kb[tid + k * NT];
+                    kav[k] = ka[tid + k * NT];
+                }
+            });
             if (pending == 4) {
 #pragma unroll
                 for (int k = 0; k < PER; ++k) {
@@ -727,7 +745,7 @@ __global__ __launch_bounds__(NT, PERM_WAVES) void perm_accumulate_ring(PermJob j
             for (int k = 0; k < PER; ++k) {
                 const int i = tid + k * NT;
                 const u64 d = bufA[pad(src[k])];
-                const ulonglong2 b = kb[i], aa = ka[i];
+                const ulonglong2 b = k < AHEAD ? kbv[k < AHEAD ? k : 0] : kb[i], aa = k < AHEAD ? kav[k < AHEAD ? k : 0] : ka[i];
                 sum0[k] = mul_const<false, true>(d, b.x, b.y, q, sum0[k]);       // the sum rides on the product
                 sum1[k] = mul_const<false, true>(d, aa.x, aa.y, q, sum1[k]);
             }
