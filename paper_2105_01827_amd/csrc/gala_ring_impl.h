@@ -608,9 +608,14 @@ constexpr int PERM_WAVES = LOGN <= 11 ? 3 : LOGN == 12 ? 2 : 4;
 // registers: each product is below 2q, a running sum is kept below 8q and may take four more
 // products before one conditional subtraction of 8q.
 // IN8: the inputs lie in blocks of eight coefficients (PermJob::in8_S), as the matrix-core product leaves them.
-template <bool HAS_W, bool IN8 = false>
-__global__ __launch_bounds__(NT, PERM_WAVES) void perm_accumulate_ring(PermJob job, RingTables T, MaskJob mj, int gadget_bits,
-                                                           int ndigits) {
+// FEW: the launch leaves a CU at most two workgroups, so what counts is one workgroup's chain of dependent steps, not the
+// chip's issue rate: it takes up to 256 registers and requests all key pairs of a digit before its transform's last
+// pass.  A convolution of 13x11x24 to 40 channels at batch 5 (175 workgroups) 86.7 -> 82.8 us, he_fc 1000x512 on one
+// input (257) 40.7 -> 40.2 us.  Sharing a rotation's two digits out to two workgroups as well lost: 45.8 us, the inverse
+// transforms and the partial ciphertexts double.
+template <bool HAS_W, bool IN8 = false, bool FEW = false>
+__global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring(PermJob job, RingTables T, MaskJob mj,
+                                                                                 int gadget_bits, int ndigits) {
     __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
     // each thread parks its 8 coefficients here between digits (private slots, no barrier); at n = 8192 there is no LDS
     // left for them and they stay in registers
@@ -620,7 +625,7 @@ __global__ __launch_bounds__(NT, PERM_WAVES) void perm_accumulate_ring(PermJob j
     // Key pairs of a digit requested before its transform's last pass, as many as the registers hold.  At n = 4096, two
     // wavefronts per SIMD, three of eight: he_fc 500x1024 at batch 8 139.6 -> 135.7 us.  At three wavefronts per SIMD
     // they gain nothing without weights and spill with them (he_fc 1000x2048 2185 -> 2270 us).
-    constexpr int AHEAD = LOGN == 12 ? 3 : 0;
+    constexpr int AHEAD = FEW ? PER : LOGN == 12 ? 3 : 0;
     const int tid = threadIdx.x;
     if ((int)blockIdx.x >= job.items * job.nchunks) {   // only launched when mj.enabled
         mask_role(job, T, mj, (int)blockIdx.x - job.items * job.nchunks, bufA, bufB);
@@ -1464,12 +1469,21 @@ static int launch_perm(const gala_ctx *c, void *stream, const PermJob &job, cons
     }
 #endif
     if (job.in8_S && job.w) return (int)hipErrorInvalidValue;
-    if (job.w)
-        hipLaunchKernelGGL(perm_accumulate_ring<true>, grid, dim3(NT), 0, st, job, T, mj, c->gadget_bits, c->ndigits);
-    else if (job.in8_S)
-        hipLaunchKernelGGL((perm_accumulate_ring<false, true>), grid, dim3(NT), 0, st, job, T, mj, c->gadget_bits, c->ndigits);
-    else
-        hipLaunchKernelGGL(perm_accumulate_ring<false>, grid, dim3(NT), 0, st, job, T, mj, c->gadget_bits, c->ndigits);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(NT), 0, st, job, T, mj, c->gadget_bits, c->ndigits);
+    };
+#if GALA_LOGN < 13
+    // at most two wavefronts per SIMD in all: two workgroups per CU at n = 2048
+    if ((size_t)grid.x * NT <= (size_t)256 * 4 * 2 * 64) {
+        if (job.w) go(perm_accumulate_ring<true, false, true>);
+        else if (job.in8_S) go(perm_accumulate_ring<false, true, true>);
+        else go(perm_accumulate_ring<false, false, true>);
+        return (int)hipGetLastError();
+    }
+#endif
+    if (job.w) go(perm_accumulate_ring<true>);
+    else if (job.in8_S) go(perm_accumulate_ring<false, true>);
+    else go(perm_accumulate_ring<false>);
     return (int)hipGetLastError();
 }
 
