@@ -24,7 +24,7 @@
 namespace gala {
 namespace {
 
-typedef int v4i __attribute__((ext_vector_type(4)));
+typedef digit_chunk_t v4i;
 
 // term blocks of 64 between two reductions of the running sums (conv_mfma_kernel); q < 2^60 is required
 constexpr int kFoldBlocks = 3;
@@ -33,19 +33,6 @@ constexpr int kFoldBlocks = 3;
 __device__ __forceinline__ u64 balanced_digits(u64 x) {
     const u64 k = 0x8080808080808080ull;
     return (x + k) ^ k;
-}
-
-// the 16 bytes of digit `limb` of 16 balanced-digit words
-__device__ __forceinline__ v4i digit_chunk(const u64 (&d)[16], int limb) {
-    v4i c;
-#pragma unroll
-    for (int t = 0; t < 4; ++t) {
-        u32 wd = 0;
-#pragma unroll
-        for (int b = 0; b < 4; ++b) wd |= (u32)((d[4 * t + b] >> (8 * limb)) & 0xff) << (8 * b);
-        c[t] = (int)wd;
-    }
-    return c;
 }
 
 // Builds the digit-plane image of 16 rows x 16 terms x 16 coefficients per workgroup.  Phase 1 reads the
@@ -74,13 +61,15 @@ __global__ __launch_bounds__(256) void limb_pack_kernel(const u64 *src, int mode
     u64 d[16];
 #pragma unroll
     for (int j = 0; j < 16; ++j) d[j] = stage[(rl * 16 + j) * 17 + il];
+    v4i chunk[8];
+    digit_chunks(d, chunk);
     const size_t lane = (size_t)(g * 16 + rl);
     if (mode == 0) {
         if (!live) return;
         // 16 threads (the rows of a tile) write 256 contiguous bytes per digit
         const size_t base = ((((size_t)(i0 + il) * tiles + tile) * kblocks + kb) * 8) * 64 + lane;
 #pragma unroll
-        for (int limb = 0; limb < 8; ++limb) dst[base + (size_t)limb * 64] = digit_chunk(d, limb);
+        for (int limb = 0; limb < 8; ++limb) dst[base + (size_t)limb * 64] = chunk[limb];
         return;
     }
     // mode 1: a row's 16 coefficients x 8 digits are 2 KiB contiguous in the image, but a thread owns the 128
@@ -89,7 +78,7 @@ __global__ __launch_bounds__(256) void limb_pack_kernel(const u64 *src, int mode
     __syncthreads();                                   // everybody has read its digits out of `stage`
     v4i *tr = reinterpret_cast<v4i *>(stage);          // [row][coefficient][digit], 32 KiB
 #pragma unroll
-    for (int limb = 0; limb < 8; ++limb) tr[(rl * 16 + il) * 8 + limb] = digit_chunk(d, limb);
+    for (int limb = 0; limb < 8; ++limb) tr[(rl * 16 + il) * 8 + limb] = chunk[limb];
     __syncthreads();
     const size_t base = ((((size_t)tile * kblocks + kb) * 64 + lane) * n + i0) * 8;
 #pragma unroll

@@ -298,6 +298,34 @@ int launch_perm_finalize(const gala_ctx *ctx, void *stream, const PermJob &job, 
 
 // DecPerm of `count` ciphertexts: digits[c][j] = forward(digit_j(inverse(c1))), j < ndigits.
 int launch_decperm(const gala_ctx *ctx, void *stream, const u64 *ct_in, size_t count, u64 *digits);
+#if defined(__HIPCC__)
+// The digit planes of four balanced-digit words: out[u] = byte u of words a, b, c, d, in eight byte permutations.
+__device__ __forceinline__ void transpose_bytes4(u32 a, u32 b, u32 c, u32 d, u32 (&out)[4]) {
+    const u32 ab01 = __builtin_amdgcn_perm(b, a, 0x05010400), ab23 = __builtin_amdgcn_perm(b, a, 0x07030602);
+    const u32 cd01 = __builtin_amdgcn_perm(d, c, 0x05010400), cd23 = __builtin_amdgcn_perm(d, c, 0x07030602);
+    out[0] = __builtin_amdgcn_perm(cd01, ab01, 0x05040100);
+    out[1] = __builtin_amdgcn_perm(cd01, ab01, 0x07060302);
+    out[2] = __builtin_amdgcn_perm(cd23, ab23, 0x05040100);
+    out[3] = __builtin_amdgcn_perm(cd23, ab23, 0x07060302);
+}
+// 16 balanced-digit words -> their eight digit chunks: chunk u holds byte u of every word
+typedef int digit_chunk_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void digit_chunks(const u64 (&d)[16], digit_chunk_t (&c)[8]) {
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        const u64 *t = d + 4 * w;
+        u32 lo[4], hi[4];
+        transpose_bytes4((u32)t[0], (u32)t[1], (u32)t[2], (u32)t[3], lo);
+        transpose_bytes4((u32)(t[0] >> 32), (u32)(t[1] >> 32), (u32)(t[2] >> 32), (u32)(t[3] >> 32), hi);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            c[u][w] = (int)lo[u];
+            c[4 + u][w] = (int)hi[u];
+        }
+    }
+}
+#endif
+
 // The convolution's rotated inputs, one per (batch element, term): the description of the terms of a plan.
 struct TermList {
     int nin, nterm;               // input ciphertexts per batch element, terms

@@ -490,6 +490,15 @@ __device__ __forceinline__ void inverse_in_regs(u64 (&a)[8], u64 *bufA, u64 *buf
 __device__ __forceinline__ u64 reduce64(u64 x, const Modulus &m) {
     return csub(x - mulhi64(x, m.one_s) * m.q, m.q);
 }
+// below BOUND q (8 or 16) -> canonical, by three or four conditional subtractions: 12 or 16 instructions instead of 24,
+// but four constants more to keep.  Faster in the hoisted inner products (the 16x16x128 convolution at batch 16 294.8
+// -> 293.5 us), slower in encryption (70.6 -> 71.7 us), which stays with the product.
+template <int BOUND>
+__device__ __forceinline__ u64 reduce_below(u64 x, u64 q) {
+    static_assert(BOUND == 8 || BOUND == 16, "");
+    if (BOUND == 16) x = csub_dev(x, 8 * q);
+    return csub_dev(csub_dev(csub_dev(x, 4 * q), 2 * q), q);
+}
 
 // Share generation inside the same launch: the workgroups after the last (item, chunk) pair build the
 // negated mask of one output ciphertext each and store it as one more partial ciphertext.
@@ -857,8 +866,8 @@ __global__ __launch_bounds__(NT) void hstperm_taps_ring(const u64 *ct_in, const 
         }
 #pragma unroll
         for (int k = 0; k < H; ++k) {
-            out[idx[k]] = reduce64(s0[k], T.mod);
-            out[N + idx[k]] = reduce64(s1[k], T.mod);
+            out[idx[k]] = reduce_below<8>(s0[k], T.mod.q);
+            out[N + idx[k]] = reduce_below<8>(s1[k], T.mod.q);
         }
     }
 }
@@ -869,7 +878,7 @@ __global__ __launch_bounds__(NT) void hstperm_taps_ring(const u64 *ct_in, const 
 // consecutive terms (input ciphertext, tap), so a chunk is assembled in registers and the eight digit
 // chunks of a coefficient leave as 128 contiguous bytes.
 constexpr int PACK_THREADS = 256;      // whatever the ring: a workgroup is 64 coefficients of 4 inputs
-typedef int v4i_t __attribute__((ext_vector_type(4)));
+typedef digit_chunk_t v4i_t;
 // ND: the number of digits when it is 3 (unrolled), else 0 (run-time loop).  ANY_ROT false: no term rotates, there
 // are no keys and no digits to read.
 template <int ND, bool ANY_ROT>
@@ -941,8 +950,8 @@ __global__ __launch_bounds__(PACK_THREADS) void hstperm_pack_ring(const u64 *ct_
                     s1 = mul_const<false, true>(d, wa.x, wa.y, q, s1);
                 }
             }
-            v0 = reduce64(s0, T.mod);
-            v1 = reduce64(s1, T.mod);
+            v0 = reduce_below<8>(s0, T.mod.q);
+            v1 = reduce_below<8>(s1, T.mod.q);
         }
         if (!live) v0 = v1 = 0;
         const u64 k80 = 0x8080808080808080ull;   // bytes of x + 0x80..80 are the balanced digits plus 128
@@ -959,19 +968,10 @@ __global__ __launch_bounds__(PACK_THREADS) void hstperm_pack_ring(const u64 *ct_
 #pragma unroll
     for (int poly = 0; poly < 2; ++poly) {
         const int col = 2 * b + poly, row = g * 16 + (col & 15);
+        v4i_t c[8];
+        digit_chunks(poly ? D1 : D0, c);
 #pragma unroll
-        for (int limb = 0; limb < 8; ++limb) {
-            v4i_t c;
-#pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                u32 wd = 0;
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    wd |= (u32)(((poly ? D1[4 * w + t] : D0[4 * w + t]) >> (8 * limb)) & 0xff) << (8 * t);
-                c[w] = (int)wd;
-            }
-            tr[wave][lane][limb] = c;
-        }
+        for (int limb = 0; limb < 8; ++limb) tr[wave][lane][limb] = c[limb];
         __syncthreads();
         v4i_t *dst = xl + ((((size_t)(col >> 4) * kblocks + kb) * 64 + row) * N + i_wave) * 8;
         if (b_live)
@@ -1376,7 +1376,7 @@ __global__ __launch_bounds__(NT, 3) void hstperm_special_ring(const u64 *ct_in, 
         u64 a[PER];
         // LDS phases: B (ownership change), A B A (inverse), B A B A (forward), then reads of A
 #pragma unroll
-        for (int k = 0; k < PER; ++k) bufB[pad(tid + k * NT)] = reduce64(tp[k], S.TP.mod);
+        for (int k = 0; k < PER; ++k) bufB[pad(tid + k * NT)] = reduce_below<8>(tp[k], S.TP.mod.q);
         __syncthreads();
         {
             const u64 *pi = bufB + pad(tid << 3);
@@ -1390,8 +1390,8 @@ __global__ __launch_bounds__(NT, 3) void hstperm_special_ring(const u64 *ct_in, 
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
             const int i = tid + k * NT;
-            const u64 x = reduce64(bufA[pad(i)], T.mod);
-            const u64 t = reduce64(sum[k], T.mod);
+            const u64 x = reduce_below<16>(bufA[pad(i)], T.mod.q);
+            const u64 t = reduce_below<8>(sum[k], T.mod.q);
             const u64 dlt = t >= x ? t - x : t + T.mod.q - x;
             out[h * N + i] = csub_dev(mul_const(dlt, S.Pinv.x, S.Pinv.y, q), T.mod.q);
         }
