@@ -515,30 +515,40 @@ struct MaskJob {
     RingTables Tp;              // inverse-transform tables of the plaintext modulus
 };
 
-__device__ __forceinline__ void mask_role(const PermJob &job, const RingTables &T, const MaskJob &mj, int item,
-                                          u64 *bufA, u64 *bufB) {
+// store(k, i, m): mask word i = tid + k NT of the evaluation domain, canonical.
+template <class Store>
+__device__ __forceinline__ void mask_role(const RingTables &T, const MaskJob &mj, int item, u64 *bufA, u64 *bufB, Store store) {
     const int tid = threadIdx.x;
     const int b = item / mj.nout, O = item % mj.nout;
     const u64 p = mj.Tp.mod.q, q = T.mod.q;
     const int *row_ptr = mj.layout.row_ptr + (size_t)O * (N + 1);
     const int *row_rindex = mj.layout.row_rindex + (size_t)O * N;
     const unsigned char *is_first = mj.layout.is_first + (size_t)O * N;
+    // Everything read from the layout is requested before the draws: the chain of dependent steps is what a mask takes
+    const int nrows = mj.layout.nrows[O];
+    const int *first_idx = mj.layout.first_idx + (size_t)O * N;
+    const int4 *entries = reinterpret_cast<const int4 *>(mj.layout.entry_row + (size_t)O * N + PER * tid),
+               *places = reinterpret_cast<const int4 *>(mj.layout.entry_idx + (size_t)O * N + PER * tid);
+    const int4 e_lo = entries[0], e_hi = entries[1], p_lo = places[0], p_hi = places[1];
+    const int entry_row[PER] = {e_lo.x, e_lo.y, e_lo.z, e_lo.w, e_hi.x, e_hi.y, e_hi.z, e_hi.w};
+    const int entry_idx[PER] = {p_lo.x, p_lo.y, p_lo.z, p_lo.w, p_hi.x, p_hi.y, p_hi.z, p_hi.w};
+    const int nent = row_ptr[nrows];
+    // the first of this thread's rows
+    const bool has_row = tid < nrows && row_ptr[tid + 1] > row_ptr[tid];
+    const u64 row_r = has_row ? mj.r[(size_t)b * mj.r_stride + row_rindex[tid]] : 0;
+    const int row_place = has_row ? first_idx[tid] : 0;
     // every slot but the first of each real output is a draw from the mask stream; values go to the
     // position the mod-p transform expects them at
     for (int s = tid; s < N; s += NT) {
         u64 v = 0;
         if (!is_first[s]) v = draw_uniform(p, mj.pbits, mj.mask_seed, kStreamMask, ((u64)b << 32) + ((u64)O << 16) + (u64)s);
-        bufB[mj.slot_to_idx[s]] = v;
+        bufB[pad(mj.slot_to_idx[s])] = v;
     }
     __syncthreads();
     // the first slot of every real row absorbs r minus the row's other slots.  The row sums are formed by all
     // threads: a thread adds up its strip of consecutive entries and flushes to the row's cell in LDS whenever the
     // row changes (plain integer sums of values below p: at most n of them, far from 64 bits).
-    const int nrows = mj.layout.nrows[O];
-    const int *entry_row = mj.layout.entry_row + (size_t)O * N, *entry_idx = mj.layout.entry_idx + (size_t)O * N;
-    const int *first_idx = mj.layout.first_idx + (size_t)O * N;
     unsigned long long *rowsum = reinterpret_cast<unsigned long long *>(bufA);
-    const int nent = row_ptr[nrows];
     const bool sums = nent > nrows;      // rows of a single slot (convolutions) have nothing to add up
     if (sums) {
         for (int t = tid; t < nrows; t += NT) rowsum[t] = 0;
@@ -548,41 +558,83 @@ __device__ __forceinline__ void mask_role(const PermJob &job, const RingTables &
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
             const int e = PER * tid + k;
-            const int t = e < nent ? entry_row[e] : -1;
+            const int t = e < nent ? entry_row[k] : -1;
             if (t < 0) continue;
             if (t != cur) {
                 if (cur >= 0) atomicAdd(&rowsum[cur], acc);
                 cur = t;
                 acc = 0;
             }
-            acc += bufB[entry_idx[e]];
+            acc += bufB[pad(entry_idx[k])];
         }
         if (cur >= 0) atomicAdd(&rowsum[cur], acc);
         __syncthreads();
     }
     for (int t = tid; t < nrows; t += NT) {
-        if (row_ptr[t + 1] <= row_ptr[t]) continue;
-        u64 rv = mj.r[(size_t)b * mj.r_stride + row_rindex[t]];
+        const bool first = t == tid;
+        if (first ? !has_row : row_ptr[t + 1] <= row_ptr[t]) continue;
+        u64 rv = first ? row_r : mj.r[(size_t)b * mj.r_stride + row_rindex[t]];
         if (rv >= p) rv %= p;
-        bufB[first_idx[t]] = sub_mod(rv, sums ? rowsum[t] % p : 0, p);
+        bufB[pad(first ? row_place : first_idx[t])] = sub_mod(rv, sums ? rowsum[t] % p : 0, p);
     }
     __syncthreads();
     // slots -> plaintext polynomial (inverse transform mod p) -> delta * m mod q -> evaluation domain mod q
+    // (padded like an exchange's image: a wavefront reads the words it then writes in the second exchange, which no
+    // barrier separates from the other wavefronts' reads)
     u64 a[PER];
 #pragma unroll
-    for (int k = 0; k < PER; ++k) a[k] = bufB[8 * tid + k];
-    inverse_in_regs(a, bufA, bufB, mj.Tp, tid);        // LDS phases A B A; the reads of bufB above precede the first barrier
+    for (int k = 0; k < PER; ++k) a[k] = bufB[pad(8 * tid) + k];
+    inverse_in_regs(a, bufA, bufB, mj.Tp, tid);        // LDS phases A B A
 #pragma unroll
     for (int k = 0; k < PER; ++k) a[k] = csub_dev(mul_const(a[k], mj.delta.x, mj.delta.y, T.nq), q);
     forward_to_lds(a, bufA, bufB, T, tid);             // LDS phases B A B A, result in bufA (below 16q)
-    u64 *out = job.partial + ((size_t)item * job.slots + job.nchunks) * 2 * N;
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         const int i = tid + k * NT;
-        const u64 m = reduce64(bufA[pad(i)], T.mod);
-        out[i] = m ? q - m : 0;       // minus the mask on c0
-        out[N + i] = 0;
+        store(k, i, reduce64(bufA[pad(i)], T.mod));
     }
+}
+// ... as one more partial ciphertext of the item: minus the mask on c0
+__device__ __forceinline__ void mask_partial(const PermJob &job, const RingTables &T, const MaskJob &mj, int item, u64 *bufA,
+                                             u64 *bufB) {
+    u64 *out = job.partial + ((size_t)item * job.slots + job.nchunks) * 2 * N;
+    const u64 q = T.mod.q;
+    mask_role(T, mj, item, bufA, bufB, [&](int, int i, u64 m) {
+        out[i] = m ? q - m : 0;
+        out[N + i] = 0;
+    });
+}
+// A layer without rotations (G = 1: a matrix that fits one ciphertext, a convolution of one channel a ciphertext) is one
+// product and the mask: the workgroup that builds an item's mask forms its output at once, in one launch and without
+// partial ciphertexts.
+// From wire to wire (with the layout's loads requested ahead of the draws): 16x128 on one input 27.5 -> 24.1 us; that
+// and he_fc 1000x512 on one input, where a mask is the longest workgroup, 40.9 -> 39.6 us.
+template <bool HAS_W, bool IN8>
+__global__ __launch_bounds__(NT) void scmult_masked_ring(PermJob job, RingTables T, MaskJob mj, u64 *ct_out) {
+    __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
+    const int item = blockIdx.x;
+    const u64 *c0 = IN8 ? job.ct_in + (size_t)(item % job.in8_nout) * job.in8_o_stride + (size_t)(item / job.in8_nout) * 16
+                        : job.ct_in + (size_t)item * job.in_item_stride;
+    const u64 *c1 = IN8 ? c0 + 8 : c0 + N;
+    auto at = [&](const u64 *poly, int i) -> u64 { return IN8 ? poly[(size_t)(i >> 3) * job.in8_S + (i & 7)] : poly[i]; };
+    const ulonglong2 *w = reinterpret_cast<const ulonglong2 *>(job.w2);
+    u64 x0[PER], x1[PER];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int i = threadIdx.x + k * NT;
+        x0[k] = at(c0, i);
+        x1[k] = at(c1, i);
+        if (HAS_W) {
+            const ulonglong2 ww = w[i];
+            x0[k] = csub_dev(mul_const(x0[k], ww.x, ww.y, T.nq), T.mod.q);
+            x1[k] = csub_dev(mul_const(x1[k], ww.x, ww.y, T.nq), T.mod.q);
+        }
+    }
+    u64 *out = ct_out + (size_t)item * 2 * N;
+    mask_role(T, mj, item, bufA, bufB, [&](int k, int i, u64 m) {
+        out[i] = sub_mod(x0[k], m, T.mod.q);
+        out[N + i] = x1[k];
+    });
 }
 
 // Workgroup -> (item, chunk).  Consecutive workgroup ids go to the eight XCDs in turn, each with an L2 of its own.
@@ -637,7 +689,7 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
     constexpr int AHEAD = FEW ? PER : LOGN == 12 ? 3 : 0;
     const int tid = threadIdx.x;
     if ((int)blockIdx.x >= job.items * job.nchunks) {   // only launched when mj.enabled
-        mask_role(job, T, mj, (int)blockIdx.x - job.items * job.nchunks, bufA, bufB);
+        mask_partial(job, T, mj, (int)blockIdx.x - job.items * job.nchunks, bufA, bufB);
         return;
     }
     int item, chunk;
@@ -1029,12 +1081,12 @@ __global__ __launch_bounds__(NT, 4) void encrypt_ring(const u64 *slots, const u6
     u64 *c0 = ct_out + (size_t)blockIdx.x * 2 * N, *c1 = c0 + N;
     for (int s = tid; s < N; s += NT) {
         const u64 v = sl[s];
-        bufB[slot_to_idx[s]] = v >= p ? v % p : v;
+        bufB[pad(slot_to_idx[s])] = v >= p ? v % p : v;       // padded: see mask_role
     }
     __syncthreads();
     u64 a[PER];
 #pragma unroll
-    for (int k = 0; k < PER; ++k) a[k] = bufB[8 * tid + k];
+    for (int k = 0; k < PER; ++k) a[k] = bufB[pad(8 * tid) + k];
     inverse_in_regs(a, bufA, bufB, Tp, tid);          // m, coefficient tid + (n/8) k, canonical mod p
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
@@ -1107,7 +1159,7 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
     __shared__ u64 Rl[15 * NT];
     const int tid = threadIdx.x;
     if ((int)blockIdx.x >= job.items * job.nchunks) {   // only launched when mj.enabled
-        mask_role(job, T, mj, (int)blockIdx.x - job.items * job.nchunks, bufA, bufB);
+        mask_partial(job, T, mj, (int)blockIdx.x - job.items * job.nchunks, bufA, bufB);
         return;
     }
     int item, chunk;
@@ -1508,10 +1560,26 @@ static int perm_masked(const gala_ctx *c, void *stream, const PermJob &job, cons
     hipStream_t st = (hipStream_t)stream;
     const bool timed = c->prof_which == 0 && (size_t)(2 * c->prof_used + 1) < c->prof_events.size();
     if (timed) (void)hipEventRecord((hipEvent_t)c->prof_events[2 * c->prof_used], st);
-    int rc = launch_perm(c, stream, job, mj);
+    int rc;
+    // in place, or with the inputs and outputs apart: items are written as soon as they are done
+    const size_t span = (size_t)job.items * 2 * N;
+    const bool apart = fin.ct_out == job.ct_in || fin.ct_out + span <= job.ct_in || job.ct_in + span <= fin.ct_out;
+    const bool alone = job.identity_only && (job.in8_S ? !job.w : apart);
+    if (alone) {
+        const RingTables T = make_tables(c->d_tw2, c->ntt_q);
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)job.items), dim3(NT), 0, st, job, T, mj, fin.ct_out);
+        };
+        if (job.w) go(scmult_masked_ring<true, false>);
+        else if (job.in8_S) go(scmult_masked_ring<false, true>);
+        else go(scmult_masked_ring<false, false>);
+        rc = (int)hipGetLastError();
+    } else {
+        rc = launch_perm(c, stream, job, mj);
+    }
     if (timed) (void)hipEventRecord((hipEvent_t)c->prof_events[2 * c->prof_used++ + 1], st);
-    if (rc) return rc;
-    const size_t words = (size_t)job.items * 2 * N;
+    if (rc || alone) return rc;
+    const size_t words = span;
     // many partials of few items: more wavefronts per word
     if (job.nchunks + 1 <= 8)
         hipLaunchKernelGGL(sum_few_partials_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, st, job.partial, job.slots,
