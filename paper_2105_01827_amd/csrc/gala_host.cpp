@@ -341,6 +341,7 @@ extern "C" int gala_ctx_create(const gala_params *par, gala_ctx **out) {
     // pass of two stages or one is [6] or [4][n/8]: w(n/4, l), w(n/4, l + n/8) and w(n/2, l + e n/8), or the latter alone;
     // then psi^-j / n for every coefficient j.
     std::vector<u64> pairs, pairs_p, pairs_P, hostP;
+    std::vector<u32> small_p;
     if (uses_fast_perm(c)) {
         auto build = [&](const NttHost &h, std::vector<u64> &out) {
             const u64 m = h.mod.q;
@@ -387,6 +388,13 @@ extern "C" int gala_ctx_create(const gala_params *par, gala_ctx **out) {
         };
         build(c->ntt_q, pairs);
         build(c->ntt_p, pairs_p);
+        if (p < (1ull << 26)) {       // 13 lazy stages stay below 2^32 (gala_ring_impl.h)
+            small_p.resize(pairs_p.size());
+            for (size_t k = 0; k < pairs_p.size(); k += 2) {
+                small_p[k] = (u32)pairs_p[k];
+                small_p[k + 1] = (u32)(pairs_p[k + 1] >> 32);     // floor(floor(w 2^64 / p) / 2^32)
+            }
+        }
         if (P) build(c->ntt_P, pairs_P);
     }
     if (P) {
@@ -397,7 +405,7 @@ extern "C" int gala_ctx_create(const gala_params *par, gala_ctx **out) {
         std::copy(c->ntt_P.itws.begin(), c->ntt_P.itws.end(), hostP.begin() + 3 * n);
     }
     if (upload(&c->d_tables, host) || upload(&c->d_slot_to_idx, c->slot_to_idx) ||
-        upload(&c->d_tw2, pairs) || upload(&c->d_tw2p, pairs_p) || upload(&c->d_tablesP, hostP) ||
+        upload(&c->d_tw2, pairs) || upload(&c->d_tw2p, pairs_p) || upload(&c->d_tw32p, small_p) || upload(&c->d_tablesP, hostP) ||
         upload(&c->d_tw2P, pairs_P)) {
         gala_ctx_destroy(c);
         return GALA_EHIP;
@@ -434,6 +442,7 @@ extern "C" void gala_ctx_destroy(gala_ctx *c) {
         hipFree(c->d_slot_to_idx);
         hipFree(c->d_tw2);
         hipFree(c->d_tw2p);
+        hipFree(c->d_tw32p);
         hipFree(c->d_tablesP);
         hipFree(c->d_tw2P);
     }

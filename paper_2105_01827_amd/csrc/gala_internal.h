@@ -92,6 +92,7 @@ struct gala_ctx {
     int *d_slot_to_idx = nullptr;
     gala::u64 *d_tw2 = nullptr;        // ring kernels only: (w, companion) twiddle pairs in the order of the radix-8 passes, forward then inverse
     gala::u64 *d_tw2p = nullptr;       // the same for the plaintext modulus
+    gala::u32 *d_tw32p = nullptr;      // ... with 32-bit words and companions floor(w 2^32 / p), when p < 2^26; else null
     gala::u64 *d_tablesP = nullptr;    // 4*n words: tw,tws,itw,itws for the special prime
     gala::u64 *d_tw2P = nullptr;       // the same for the special prime
     gala::NttDev dev_q{}, dev_p{}, dev_P{};

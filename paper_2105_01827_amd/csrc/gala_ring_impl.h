@@ -486,6 +486,190 @@ __device__ __forceinline__ void inverse_in_regs(u64 (&a)[8], u64 *bufA, u64 *buf
     for (int k = 0; k < PER; ++k) a[k] = csub_dev(mul_const<CM>(a[k], c[k].x, c[k].y, q), T.mod.q);
 }
 
+// ---- transforms modulo a small plaintext prime -------------------------------------------------------------------
+// Below 2^26 the plaintext modulus leaves 32-bit words room for every stage without corrections (at most 36p after 13
+// stages), and a product by a constant is three 32-bit multiplies instead of nine: the slots of masks and messages are
+// transformed this way, half the LDS words included.  Same passes, ownership and tables as above, with (constant,
+// floor(constant 2^32 / p)) pairs of eight bytes; larger plaintext primes keep the 64-bit transforms.
+// From wire to wire: 16x128 on one input 24.1 -> 22.4 us, 1000x512 39.6 -> 37.2 us; 1024 encryptions 67.5 -> 62.4 us, 256
+// decryptions 28.2 -> 26.0 us.
+struct SmallTables {
+    const uint2 *tw, *itw;        // null: the plaintext modulus is not below 2^26
+    uint2 w8[3];
+    u32 p, one_s;                 // the modulus and floor(2^32 / p)
+};
+__device__ __forceinline__ u32 mul_small(u32 y, uint2 w, u32 p) { return y * w.x - __umulhi(y, w.y) * p; }     // below 2p
+__device__ __forceinline__ void bf_small(u32 &x, u32 &y, uint2 w, u32 p) {
+    const u32 t = mul_small(y, w, p);
+    y = x - t + 2 * p;
+    x += t;
+}
+__device__ __forceinline__ void bf_small_one(u32 &x, u32 &y, u32 off) {
+    const u32 s = x + y;
+    y = x - y + off;
+    x = s;
+}
+template <int CONSTANTS, int COUNT>
+__device__ __forceinline__ void small_level(uint2 (&t)[CONSTANTS], const uint2 *__restrict__ level, unsigned j) {
+#pragma unroll
+    for (int e = 0; e < CONSTANTS; ++e) t[e] = level[e * COUNT + j];
+}
+template <int B_OUT, int B_IN>
+__device__ __forceinline__ void exchange_small(u32 (&a)[8], u32 *buf, int tid) {
+    u32 *po = buf + pad(owner<B_OUT>(tid));
+#pragma unroll
+    for (int k = 0; k < 8; ++k) po[reg_offset<B_OUT>(k)] = a[k];
+    if (B_OUT <= LOCAL_BITS && B_IN <= LOCAL_BITS) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    } else {
+        __syncthreads();
+    }
+    const u32 *pi = buf + pad(owner<B_IN>(tid));
+#pragma unroll
+    for (int k = 0; k < 8; ++k) a[k] = pi[reg_offset<B_IN>(k)];
+}
+template <int STAGE>
+__device__ __forceinline__ void fwd_pass_small(u32 (&a)[8], const uint2 (&w)[7], u32 p) {
+    if (STAGE == 0) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) bf_small(a[k], a[k + 4], w[0], p);
+    }
+    if (STAGE <= 1) {
+        bf_small(a[0], a[2], w[1], p);
+        bf_small(a[1], a[3], w[1], p);
+        bf_small(a[4], a[6], w[2], p);
+        bf_small(a[5], a[7], w[2], p);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) bf_small(a[2 * k], a[2 * k + 1], w[3 + k], p);
+}
+__device__ __forceinline__ void inv_pass_small(u32 (&a)[8], const uint2 (&w)[7], u32 p) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) bf_small(a[2 * k], a[2 * k + 1], w[0], p);
+    bf_small(a[0], a[2], w[1], p);
+    bf_small(a[1], a[3], w[2], p);
+    bf_small(a[4], a[6], w[1], p);
+    bf_small(a[5], a[7], w[2], p);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) bf_small(a[k], a[k + 4], w[3 + k], p);
+}
+// as forward_to_lds; inputs canonical, the result in `res` canonical up to reduce_small()
+__device__ __forceinline__ u32 reduce_small(u32 x, const SmallTables &T) {
+    const u32 r = x - __umulhi(x, T.one_s) * T.p;      // below 2p
+    return r >= T.p ? r - T.p : r;
+}
+__device__ __forceinline__ void forward_small_to_lds(u32 (&a)[8], u32 *res, u32 *other, const SmallTables &T, int tid) {
+    constexpr int B1 = LOGN - 3, B2 = LOGN - 6, B3 = LOGN - 9, B4 = LOGN >= 12 ? LOGN - 12 : 0;
+    u32 *first = LOGN == 13 ? res : other, *second = LOGN == 13 ? other : res;
+    if (LOGN == 13) __syncthreads();
+    uint2 w[7];
+    small_level<7, 1>(w, T.tw, 0);
+    fwd_pass_small<0>(a, w, T.p);
+    small_level<7, 8>(w, T.tw + level_offset(8), (unsigned)tid >> B2);
+    exchange_small<B1, B2>(a, first, tid);
+    fwd_pass_small<0>(a, w, T.p);
+    small_level<7, 64>(w, T.tw + level_offset(64), (unsigned)tid >> B3);
+    exchange_small<B2, B3>(a, second, tid);
+    fwd_pass_small<0>(a, w, T.p);
+    if (LOGN < 12) {
+        small_level<7, NT>(w, T.tw + level_offset(NT), (unsigned)tid);
+        exchange_small<B3, 0>(a, first, tid);
+        fwd_pass_small<3 - LOGN % 3>(a, w, T.p);
+    } else {
+        small_level<7, 512>(w, T.tw + level_offset(512), (unsigned)tid >> B4);
+        exchange_small<B3, B4>(a, first, tid);
+        fwd_pass_small<0>(a, w, T.p);
+        if (LOGN == 13) {
+            small_level<7, NT>(w, T.tw + level_offset(NT), (unsigned)tid);
+            exchange_small<B4, 0>(a, second, tid);
+            fwd_pass_small<2>(a, w, T.p);
+        }
+    }
+    u32 *po = res + pad(tid << 3);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) po[k] = a[k];
+    __syncthreads();
+}
+// as inverse_in_regs: canonical in, canonical out
+__device__ __forceinline__ void inverse_small_in_regs(u32 (&a)[8], u32 *bufA, u32 *bufB, const SmallTables &T, int tid) {
+    constexpr int TOP = LOGN - 3;
+    const u32 p = T.p;
+    uint2 w[7];
+    small_level<7, 8>(w, T.itw, (unsigned)tid & 7);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) bf_small_one(a[2 * k], a[2 * k + 1], p);                 // below 2p
+    bf_small_one(a[0], a[2], 2 * p);
+    bf_small_one(a[4], a[6], 2 * p);                                                     // below 4p
+    bf_small(a[1], a[3], T.w8[1], p);
+    bf_small(a[5], a[7], T.w8[1], p);
+    bf_small_one(a[0], a[4], 4 * p);                                                     // below 8p
+    bf_small(a[1], a[5], T.w8[0], p);
+    bf_small(a[2], a[6], T.w8[1], p);
+    bf_small(a[3], a[7], T.w8[2], p);
+    exchange_small<0, 3>(a, bufA, tid);
+    inv_pass_small(a, w, p);
+    small_level<7, 64>(w, T.itw + INV_MID, (unsigned)tid & 63);
+    exchange_small<3, 6>(a, bufB, tid);
+    inv_pass_small(a, w, p);
+    if (LOGN >= 12) {
+        small_level<7, 512>(w, T.itw + INV_HIGH, (unsigned)tid & 511);
+        exchange_small<6, 9>(a, bufA, tid);
+        inv_pass_small(a, w, p);
+    }
+    uint2 c[8];
+    if (TOP_STAGES) {
+        uint2 t[TOP_CONSTS];
+        small_level<TOP_CONSTS, NT>(t, T.itw + INV_TOP, (unsigned)tid);
+        if (LOGN >= 12) exchange_small<9, TOP>(a, bufB, tid);
+        else exchange_small<6, TOP>(a, bufA, tid);
+        small_level<8, NT>(c, T.itw + INV_TWIST, (unsigned)tid);
+        if (TOP_STAGES == 2) {
+            bf_small(a[0], a[2], t[0], p);
+            bf_small(a[1], a[3], t[1], p);
+            bf_small(a[4], a[6], t[0], p);
+            bf_small(a[5], a[7], t[1], p);
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) bf_small(a[k], a[k + 4], t[TOP_CONSTS - 4 + k], p);
+    } else {
+        small_level<8, NT>(c, T.itw + INV_TWIST, (unsigned)tid);
+    }
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const u32 r = mul_small(a[k], c[k], p);
+        a[k] = r >= p ? r - p : r;
+    }
+}
+
+// The plaintext polynomial of a slot image: slot values sit at pad(position) of bufB, as 32-bit words when the plaintext
+// modulus is small (put_slot); coefficients t + (n/8) k come back in registers.  The image is padded like an exchange's,
+// because a wavefront reads the words it then writes in the second exchange, and no barrier separates those writes from
+// the other wavefronts' reads.
+__device__ __forceinline__ void put_slot(u64 *bufB, int position, u64 v, bool small) {
+    if (small) reinterpret_cast<u32 *>(bufB)[pad(position)] = (u32)v;
+    else bufB[pad(position)] = v;
+}
+__device__ __forceinline__ u64 get_slot(const u64 *bufB, int position, bool small) {
+    return small ? reinterpret_cast<const u32 *>(bufB)[pad(position)] : bufB[pad(position)];
+}
+__device__ __forceinline__ void slots_to_coefficients(u64 (&a)[8], u64 *bufA, u64 *bufB, const RingTables &Tp,
+                                                      const SmallTables &small, int tid) {
+    if (small.tw) {
+        u32 *A = reinterpret_cast<u32 *>(bufA), *B = reinterpret_cast<u32 *>(bufB), v[8];
+#pragma unroll
+        for (int k = 0; k < PER; ++k) v[k] = B[pad(8 * tid) + k];
+        inverse_small_in_regs(v, A, B, small, tid);
+#pragma unroll
+        for (int k = 0; k < PER; ++k) a[k] = v[k];
+    } else {
+#pragma unroll
+        for (int k = 0; k < PER; ++k) a[k] = bufB[pad(8 * tid) + k];
+        inverse_in_regs(a, bufA, bufB, Tp, tid);
+    }
+}
+
 // below 16q -> canonical
 __device__ __forceinline__ u64 reduce64(u64 x, const Modulus &m) {
     return csub(x - mulhi64(x, m.one_s) * m.q, m.q);
@@ -513,6 +697,7 @@ struct MaskJob {
     int pbits;
     ulonglong2 delta;           // delta = floor(q/p) and its companion mod q
     RingTables Tp;              // inverse-transform tables of the plaintext modulus
+    SmallTables small;
 };
 
 // store(k, i, m): mask word i = tid + k NT of the evaluation domain, canonical.
@@ -521,6 +706,7 @@ __device__ __forceinline__ void mask_role(const RingTables &T, const MaskJob &mj
     const int tid = threadIdx.x;
     const int b = item / mj.nout, O = item % mj.nout;
     const u64 p = mj.Tp.mod.q, q = T.mod.q;
+    const bool small = mj.small.tw != nullptr;
     const int *row_ptr = mj.layout.row_ptr + (size_t)O * (N + 1);
     const int *row_rindex = mj.layout.row_rindex + (size_t)O * N;
     const unsigned char *is_first = mj.layout.is_first + (size_t)O * N;
@@ -542,7 +728,7 @@ __device__ __forceinline__ void mask_role(const RingTables &T, const MaskJob &mj
     for (int s = tid; s < N; s += NT) {
         u64 v = 0;
         if (!is_first[s]) v = draw_uniform(p, mj.pbits, mj.mask_seed, kStreamMask, ((u64)b << 32) + ((u64)O << 16) + (u64)s);
-        bufB[pad(mj.slot_to_idx[s])] = v;
+        put_slot(bufB, mj.slot_to_idx[s], v, small);
     }
     __syncthreads();
     // the first slot of every real row absorbs r minus the row's other slots.  The row sums are formed by all
@@ -565,7 +751,7 @@ __device__ __forceinline__ void mask_role(const RingTables &T, const MaskJob &mj
                 cur = t;
                 acc = 0;
             }
-            acc += bufB[pad(entry_idx[k])];
+            acc += get_slot(bufB, entry_idx[k], small);
         }
         if (cur >= 0) atomicAdd(&rowsum[cur], acc);
         __syncthreads();
@@ -575,16 +761,12 @@ __device__ __forceinline__ void mask_role(const RingTables &T, const MaskJob &mj
         if (first ? !has_row : row_ptr[t + 1] <= row_ptr[t]) continue;
         u64 rv = first ? row_r : mj.r[(size_t)b * mj.r_stride + row_rindex[t]];
         if (rv >= p) rv %= p;
-        bufB[pad(first ? row_place : first_idx[t])] = sub_mod(rv, sums ? rowsum[t] % p : 0, p);
+        put_slot(bufB, first ? row_place : first_idx[t], sub_mod(rv, sums ? rowsum[t] % p : 0, p), small);
     }
     __syncthreads();
     // slots -> plaintext polynomial (inverse transform mod p) -> delta * m mod q -> evaluation domain mod q
-    // (padded like an exchange's image: a wavefront reads the words it then writes in the second exchange, which no
-    // barrier separates from the other wavefronts' reads)
     u64 a[PER];
-#pragma unroll
-    for (int k = 0; k < PER; ++k) a[k] = bufB[pad(8 * tid) + k];
-    inverse_in_regs(a, bufA, bufB, mj.Tp, tid);        // LDS phases A B A
+    slots_to_coefficients(a, bufA, bufB, mj.Tp, mj.small, tid);        // LDS phases A B A
 #pragma unroll
     for (int k = 0; k < PER; ++k) a[k] = csub_dev(mul_const(a[k], mj.delta.x, mj.delta.y, T.nq), q);
     forward_to_lds(a, bufA, bufB, T, tid);             // LDS phases B A B A, result in bufA (below 16q)
@@ -1072,7 +1254,7 @@ __global__ __launch_bounds__(NT) void ntt_ring(const u64 *src, u64 *dst, RingTab
 // ct = (-a s + e + delta m, a) (Sec. II-C(1)), bit for bit the any-n kernel: m = the plaintext polynomial of the
 // slots, a uniform, e Gaussian, all drawn from the ciphertext's seed by coefficient index.
 __global__ __launch_bounds__(NT, 4) void encrypt_ring(const u64 *slots, const u64 *seeds, const u64 *s_hat, u64 *ct_out,
-                                                   RingTables T, RingTables Tp, const int *slot_to_idx, GaussCdf cdf,
+                                                   RingTables T, RingTables Tp, SmallTables small, const int *slot_to_idx, GaussCdf cdf,
                                                    int qbits, ulonglong2 delta) {
     __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
     const int tid = threadIdx.x;
@@ -1081,13 +1263,11 @@ __global__ __launch_bounds__(NT, 4) void encrypt_ring(const u64 *slots, const u6
     u64 *c0 = ct_out + (size_t)blockIdx.x * 2 * N, *c1 = c0 + N;
     for (int s = tid; s < N; s += NT) {
         const u64 v = sl[s];
-        bufB[pad(slot_to_idx[s])] = v >= p ? v % p : v;       // padded: see mask_role
+        put_slot(bufB, slot_to_idx[s], v >= p ? v % p : v, small.tw != nullptr);
     }
     __syncthreads();
     u64 a[PER];
-#pragma unroll
-    for (int k = 0; k < PER; ++k) a[k] = bufB[pad(8 * tid) + k];
-    inverse_in_regs(a, bufA, bufB, Tp, tid);          // m, coefficient tid + (n/8) k, canonical mod p
+    slots_to_coefficients(a, bufA, bufB, Tp, small, tid);      // m, coefficient tid + (n/8) k, canonical mod p
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         const int e = draw_gauss_cdf(cdf, seed, kStreamCtE, (u64)(tid + k * NT));
@@ -1111,7 +1291,7 @@ __global__ __launch_bounds__(NT, 4) void encrypt_ring(const u64 *slots, const u6
 }
 // slots = decode(round(p (c0 + c1 s) / q) mod p); the rounded quotient through the exact division by q (q^-1 mod 2^64).
 __global__ __launch_bounds__(NT) void decrypt_ring(const u64 *ct_in, const u64 *s_hat, u64 *slots, RingTables T,
-                                                   RingTables Tp, const int *slot_to_idx, u64 q_inv64) {
+                                                   RingTables Tp, SmallTables small, const int *slot_to_idx, u64 q_inv64) {
     __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
     const int tid = threadIdx.x;
     const u64 q = T.mod.q, p = Tp.mod.q;
@@ -1130,9 +1310,18 @@ __global__ __launch_bounds__(NT) void decrypt_ring(const u64 *ct_in, const u64 *
         const u64 quot = ((u64)t - r) * q_inv64;      // t - r is a multiple of q and the quotient is at most p
         a[k] = quot >= p ? quot - p : quot;
     }
-    forward_to_lds(a, bufA, bufB, Tp, tid);           // the slots' values at their transform positions, in bufA
     u64 *out = slots + (size_t)blockIdx.x * N;
-    for (int s = tid; s < N; s += NT) out[s] = reduce64(bufA[pad(slot_to_idx[s])], Tp.mod);
+    // the slots' values at their transform positions, in bufA
+    if (small.tw) {
+        u32 v[PER], *A = reinterpret_cast<u32 *>(bufA);
+#pragma unroll
+        for (int k = 0; k < PER; ++k) v[k] = (u32)a[k];
+        forward_small_to_lds(v, A, reinterpret_cast<u32 *>(bufB), small, tid);
+        for (int s = tid; s < N; s += NT) out[s] = reduce_small(A[pad(slot_to_idx[s])], small);
+    } else {
+        forward_to_lds(a, bufA, bufB, Tp, tid);
+        for (int s = tid; s < N; s += NT) out[s] = reduce64(bufA[pad(slot_to_idx[s])], Tp.mod);
+    }
 }
 
 #if GALA_LOGN < 13   // at n = 8192 the remainder sums do not fit beside the images: the any-n kernels serve it
@@ -1499,6 +1688,17 @@ static RingTables make_tables(const u64 *pairs, const NttHost &h) {
     return T;
 }
 
+static SmallTables make_small(const gala_ctx *c) {
+    SmallTables S{};
+    if (!c->d_tw32p) return S;
+    S.tw = reinterpret_cast<const uint2 *>(c->d_tw32p);
+    S.itw = S.tw + FWD_PAIRS;
+    S.p = (u32)c->p;
+    S.one_s = (u32)((1ull << 32) / c->p);
+    for (int e = 0; e < 3; ++e) S.w8[e] = make_uint2((u32)c->ntt_p.w8[e], (u32)((c->ntt_p.w8[e] << 32) / c->p));
+    return S;
+}
+
 static int launch_perm(const gala_ctx *c, void *stream, const PermJob &job, const MaskJob &mj) {
     hipStream_t st = (hipStream_t)stream;
     const RingTables T = make_tables(c->d_tw2, c->ntt_q);
@@ -1557,6 +1757,7 @@ static int perm_masked(const gala_ctx *c, void *stream, const PermJob &job, cons
     mj.pbits = c->pbits;
     mj.delta = make_ulonglong2(c->delta, c->delta_s);
     mj.Tp = make_tables(c->d_tw2p, c->ntt_p);
+    mj.small = make_small(c);
     hipStream_t st = (hipStream_t)stream;
     const bool timed = c->prof_which == 0 && (size_t)(2 * c->prof_used + 1) < c->prof_events.size();
     if (timed) (void)hipEventRecord((hipEvent_t)c->prof_events[2 * c->prof_used], st);
@@ -1667,7 +1868,7 @@ static int encrypt(const gala_ctx *c, void *stream, const u64 *s_hat, const u64 
     GaussCdf cdf;
     for (int i = 0; i < 2 * kGaussBound; ++i) cdf.t[i] = gauss_cdf_table()[i];
     hipLaunchKernelGGL(encrypt_ring, dim3((unsigned)count), dim3(NT), 0, (hipStream_t)stream, slots, seeds, s_hat, ct_out,
-                       make_tables(c->d_tw2, c->ntt_q), make_tables(c->d_tw2p, c->ntt_p), c->d_slot_to_idx, cdf, c->qbits,
+                       make_tables(c->d_tw2, c->ntt_q), make_tables(c->d_tw2p, c->ntt_p), make_small(c), c->d_slot_to_idx, cdf, c->qbits,
                        make_ulonglong2(c->delta, c->delta_s));
     return (int)hipGetLastError();
 }
@@ -1676,7 +1877,7 @@ static int decrypt(const gala_ctx *c, void *stream, const u64 *s_hat, const u64 
     u64 inv = c->q;                                   // Newton's iteration for q^-1 mod 2^64 (q is odd)
     for (int i = 0; i < 6; ++i) inv *= 2 - c->q * inv;
     hipLaunchKernelGGL(decrypt_ring, dim3((unsigned)count), dim3(NT), 0, (hipStream_t)stream, ct_in, s_hat, slots,
-                       make_tables(c->d_tw2, c->ntt_q), make_tables(c->d_tw2p, c->ntt_p), c->d_slot_to_idx, inv);
+                       make_tables(c->d_tw2, c->ntt_q), make_tables(c->d_tw2p, c->ntt_p), make_small(c), c->d_slot_to_idx, inv);
     return (int)hipGetLastError();
 }
 
