@@ -404,7 +404,7 @@ extern "C" int gala_he_conv(const gala_ctx *c, void *stream, const gala_conv_pla
         if (end) ++c->prof_used;
     };
     auto mark = [&](int end) { mark_as(1, end); };
-    // The n = 2048 Perm kernels read the product's sums in their own blocks of eight coefficients: no transposition
+    // The ring's Perm kernels read the product's sums in their own blocks of eight coefficients: no transposition
     // pass in between.  With one-prime keys the rotated inputs also go straight into the product's column image.
     const bool direct = ws.mfma && fast_hoist && !c->special;
     const bool in8 = ws.mfma && uses_fast_perm(c);      // the ring's Perm kernels read the blocks of eight

@@ -343,6 +343,11 @@ int launch_hstperm_taps(const gala_ctx *ctx, void *stream, const u64 *ct_in, con
 int launch_conv_mac(const gala_ctx *ctx, void *stream, const u64 *w, const u64 *xrot, int batch, int nout, int cn,
                     int nterm, u64 *acc, const int *seg_ptr = nullptr, const int *seg_terms = nullptr, int nseg = 1);
 
+// Whether operands of this size, read once a launch, are worth keeping out of the caches: past the 256 MB of the
+// last-level cache nothing of them is left for the next launch.  Below it they may be (13x11x24 to 40 channels at batch
+// 5, 24 MB of kernels' digit planes: 81.2 us kept, 83.0 us not).
+inline bool streams_past_cache(size_t bytes) { return bytes > ((size_t)256 << 20); }
+
 // Matrix-core path of the convolution's multiply-accumulate (gala_conv_mfma.hip): digit-plane images of the
 // encoded kernels (built once per plan) and of the rotated inputs (built per call), then one MFMA kernel.
 void conv_mfma_geometry(int groups, int cols, int nterm, int *mtiles, int *ntiles, int *kblocks);
