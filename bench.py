@@ -40,8 +40,7 @@ HBM_PEAK_GBS = 8000.0   # MI355X HBM3E, published
 #     (multiply-adds, adds with carry, selects; no address arithmetic, no register moves):
 OPS_CONST_MUL = 13      # y*w mod q, w with precomputed quotient: 6 for the high product, 6 + 1 for y*w - h*q
 OPS_CSUB = 4            # conditional subtraction: sub, subb, two selects on the borrow
-OPS_BF_FWD = OPS_CONST_MUL + 1 + 3             # lazy forward butterfly: x + v, x + 2q - v
-OPS_BF_INV = OPS_CONST_MUL + 1 + 3 + OPS_CSUB  # inverse butterfly: x + y reduced, (x - y + 2q) * w
+OPS_BF = OPS_CONST_MUL + 3                     # lazy butterfly: x + v rides on the product, 2x + 2q - (x + v)
 OPS_MAC128 = 10         # 64x64 product added into a 128-bit sum: 4 multiply-adds and 6 carry additions
 OPS_REDUCE128 = 2 * OPS_CONST_MUL + 2 * OPS_CSUB + 1
 # (2) 32x32-bit multiplies only, 10 per modular multiplication (a 64x64 high product and two 64x64 low products
@@ -50,27 +49,31 @@ MUL32_PER_MODMUL = 10
 
 
 def transform_ops(n, logn):
+    """Both directions are decimation-in-time transforms of lazy butterflies.  The inverse's first pass has seven constants
+    of one in twelve butterflies and corrects eight of a thread's values twice, then twists and scales every word; the
+    forward transform corrects half of its words once."""
     half = n // 2
-    inverse = half * (logn - 1) * OPS_BF_INV + half * (2 * OPS_CONST_MUL + 2 * OPS_CSUB + 4)   # n^-1 folded in
-    forward = half * logn * OPS_BF_FWD + n * OPS_CSUB           # one conditional subtraction per coefficient
+    inverse = half * logn * OPS_BF - n // 8 * 7 * OPS_CONST_MUL + n * OPS_CSUB + n * (OPS_CONST_MUL + OPS_CSUB)
+    forward = half * logn * OPS_BF + half * OPS_CSUB
     return inverse, forward
 
 
 def ops_per_fused_perm(n, logn, ndigits):
-    """Integer operations of one ScMult + Perm + Add on one ciphertext (one 'fused unit')."""
+    """Integer operations of one ScMult + Perm + Add on one ciphertext (one 'fused unit').  The last digit is folded into
+    the keys: one forward transform fewer, one product of c1 (.) w at the rotated index instead."""
     inverse, forward = transform_ops(n, logn)
     scmult_c1 = n * OPS_CONST_MUL                               # c1 (.) w before the inverse transform
-    c0_term = n * (OPS_CONST_MUL + 1)                           # permuted c0 (.) w added to the sum
-    digits = ndigits * n * 2                                    # shift and mask
-    key_mac = 2 * ndigits * n * (OPS_CONST_MUL + 1)             # inner product with (b_j, a_j)
+    c0_term = n * 2 * OPS_CONST_MUL                             # permuted c0 (.) w, on the sum, and c1 (.) w
+    digits = (ndigits - 1) * n * 2                              # shift and mask
+    key_mac = 2 * ndigits * n * OPS_CONST_MUL                   # inner product with (b_j, a_j), on the sums
     accumulate = 2 * n * OPS_CSUB                               # keep the running sums below 8q
-    return inverse + ndigits * forward + scmult_c1 + c0_term + digits + key_mac + accumulate
+    return inverse + (ndigits - 1) * forward + scmult_c1 + c0_term + digits + key_mac + accumulate
 
 
 def modmuls_per_fused_perm(n, logn, ndigits, scmult=True):
-    """Modular multiplications of the same unit: butterflies of 1 + ndigits transforms, the key inner product and
-    (scmult) the two products with the encoded weight."""
-    return (1 + ndigits) * (n // 2) * logn + 2 * ndigits * n + (2 * n if scmult else 0)
+    """Modular multiplications of the same unit: butterflies of ndigits transforms, the inverse's twist, the key inner
+    product and (scmult) the three products with the encoded weight."""
+    return ndigits * (n // 2) * logn - n // 8 * 7 + n + 2 * ndigits * n + (3 * n if scmult else 0)
 
 
 def ops_per_fused_perm_special(n, logn, ndigits):
@@ -79,25 +82,25 @@ def ops_per_fused_perm_special(n, logn, ndigits):
     summed remainders happen once per workgroup and are not counted."""
     inverse, forward = transform_ops(n, logn)
     scmult_c1 = n * OPS_CONST_MUL
-    c0_term = n * (2 * OPS_CONST_MUL + 1)                       # permuted c0 (.) w, times P
-    digits = 2 * ndigits * n * 2
+    c0_term = n * (3 * OPS_CONST_MUL + 1)                       # permuted c0 (.) w, times P, and c1 (.) w
+    digits = (2 * ndigits - 1) * n * 2
     key_mac = 4 * ndigits * n * (OPS_CONST_MUL + 1)             # (b_j, a_j) modulo q and modulo P
     accumulate = 2 * n * OPS_CSUB
     remainders = 2 * n * (OPS_CONST_MUL + OPS_CSUB + 2 * OPS_CSUB + 1)   # canonical mod P, lift, reduce mod q, add
-    return 3 * inverse + 2 * ndigits * forward + scmult_c1 + c0_term + digits + key_mac + accumulate + remainders
+    return 3 * inverse + (2 * ndigits - 1) * forward + scmult_c1 + c0_term + digits + key_mac + accumulate + remainders
 
 
 def modmuls_per_fused_perm_special(n, logn, ndigits):
-    return (3 + 2 * ndigits) * (n // 2) * logn + 4 * ndigits * n + 2 * n + 4 * n
+    return (2 + 2 * ndigits) * (n // 2) * logn - 3 * (n // 8 * 7) + 3 * n + 4 * ndigits * n + 3 * n + 4 * n
 
 
 def ops_decperm(n, logn, ndigits):
     inverse, forward = transform_ops(n, logn)
-    return inverse + ndigits * forward + ndigits * n * 2
+    return inverse + (ndigits - 1) * (forward + n * 2)          # the last digit is c1 itself
 
 
 def ops_hstperm(n, ndigits):
-    return 2 * ndigits * n * (OPS_CONST_MUL + 1) + n + 2 * n * OPS_CSUB
+    return 2 * ndigits * n * OPS_CONST_MUL + n + 2 * n * 3 * OPS_CSUB
 
 
 # ---- timing helpers --------------------------------------------------------------------------------------------
@@ -229,10 +232,10 @@ def fc_config(ctx, sk, D, torch, par, shape, steps, prewarm_s, cpu_sample, cpu_r
     G = plan.G
     if special:
         unit_ops, unit_mm = ops_per_fused_perm_special(par.n, 11, ctx.ndigits), modmuls_per_fused_perm_special(par.n, 11, ctx.ndigits)
-        kernel = "perm_accumulate_special_2048"
+        kernel = "perm_accumulate_special_ring"
     else:
         unit_ops, unit_mm = ops_per_fused_perm(par.n, 11, ctx.ndigits), modmuls_per_fused_perm(par.n, 11, ctx.ndigits)
-        kernel = "perm_accumulate_2048"
+        kernel = "perm_accumulate_ring"
     if G > 1:
         roof = alu_roofline(kernel, kms, batch * (G - 1), unit_ops, unit_mm,      # the g = 0 unit has no Perm: not counted
                             traffic_file=f"perm_accumulate_{shape.name}_hbm_traffic.txt" if not special else None)
@@ -330,11 +333,11 @@ def conv_config(ctx, sk, D, torch, par, shape, steps, prewarm_s, cpu_blocks, spe
     kernels = []
     # input rotations: one DecPerm per input ciphertext, one HstPerm per rotating term (written as the digit-plane image)
     hoist_ops = cnt["decperm_in"] * ops_decperm(n, 11, nd) + cnt["hstperm_in"] * ops_hstperm(n, nd)
-    hoist_mm = cnt["decperm_in"] * (1 + nd) * (n // 2) * 11 + cnt["hstperm_in"] * 2 * nd * n
+    hoist_mm = cnt["decperm_in"] * (nd * (n // 2) * 11 - n // 8 * 7 + n) + cnt["hstperm_in"] * 2 * nd * n
     if not special:
-        kernels.append(alu_roofline("decperm_2048 + hstperm_pack_2048", k_hoist, 1, hoist_ops, hoist_mm))
+        kernels.append(alu_roofline("decperm_ring + hstperm_pack_ring", k_hoist, 1, hoist_ops, hoist_mm))
     else:
-        kernels.append(dict({"kernel": "decperm_special_2048 + hstperm_special_2048", "bound": "alu"}, **stats(k_hoist)))
+        kernels.append(dict({"kernel": "decperm_special_ring + hstperm_special_ring", "bound": "alu"}, **stats(k_hoist)))
     if vector_mac:
         kernels.append(alu_roofline("conv_mac_kernel", k_mac, 1, macs * OPS_MAC128 + batch * groups * 2 * n * OPS_REDUCE128,
                                     macs))
@@ -348,12 +351,12 @@ def conv_config(ctx, sk, D, torch, par, shape, steps, prewarm_s, cpu_blocks, spe
                                     extra={"units_per_launch": macs, "bytes_per_unit": alg_bytes / macs,
                                            "int8_mfma_top_s": macs * 64 * 2 / ((st["kernel_ms_avg"] or float("nan")) * 1e-3) / 1e12}))
     if special:
-        kernels.append(alu_roofline("perm_accumulate_special_2048", k_perm, cnt["perm"],
-                                    ops_per_fused_perm_special(n, 11, nd) - n * OPS_CONST_MUL,
-                                    modmuls_per_fused_perm_special(n, 11, nd) - 2 * n))
+        kernels.append(alu_roofline("perm_accumulate_special_ring", k_perm, cnt["perm"],
+                                    ops_per_fused_perm_special(n, 11, nd) - 3 * n * OPS_CONST_MUL,
+                                    modmuls_per_fused_perm_special(n, 11, nd) - 3 * n))
     else:
-        kernels.append(alu_roofline("perm_accumulate_2048", k_perm, cnt["perm"],
-                                    ops_per_fused_perm(n, 11, nd) - 2 * n * OPS_CONST_MUL,      # no ScMult in these units
+        kernels.append(alu_roofline("perm_accumulate_ring", k_perm, cnt["perm"],
+                                    ops_per_fused_perm(n, 11, nd) - 3 * n * OPS_CONST_MUL,      # no ScMult in these units
                                     modmuls_per_fused_perm(n, 11, nd, scmult=False)))
     gazelle = None
     if compare:
