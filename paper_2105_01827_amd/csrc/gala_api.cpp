@@ -29,12 +29,11 @@ int choose_chunks(const gala_ctx *ctx, int items, int G) {
     // With a special prime the kernel holds two workgroups per CU, not three, and a rotation is twice the work:
     // one round of 512 workgroups was the fastest cut for short and long sums alike (he_fc 128x1024: 0.43 ms
     // against 0.48 ms with 2048 workgroups and 0.58 ms with 768).
-    // Other rings with kernels of their own hold more or fewer workgroups in the same proportion (LDS, registers).  From
-    // n = 4096 on it is one per CU, and what counts is rounds of the 256 CUs times the rotations of the longest chunk,
+    // Smaller rings keep n = 2048's targets (a static call's fixed scratch is sized by them).  From n = 4096 on a CU holds
+    // one workgroup, and what counts is rounds of the 256 CUs times the rotations of the longest chunk,
     // a workgroup's start and its partial ciphertext taken as a fifth of a rotation (he_fc 500x1024 at n = 4096, batch
     // 8: 32 chunks in one round 130 us, 64 in two 136, 24 that fill 192 CUs 149, 16 in half a round 190).
-    const int n = uses_fast_perm(ctx) ? ctx->n : 2048;
-    if (n >= 4096) {
+    if (uses_fast_perm(ctx) && ctx->n >= 4096) {
         int best = 1;
         long cost = -1;
         for (int c = 1; c <= std::max(1, G - 1); c += c < 64 ? 1 : c / 8) {
@@ -43,17 +42,16 @@ int choose_chunks(const gala_ctx *ctx, int items, int G) {
         }
         return best;
     }
-    auto scaled = [n](int wgs) { return wgs * 2048 / n; };
     if (G < 32 || ctx->special) {
-        const int c = (scaled(ctx->special ? 512 : 768) + items - 1) / items;
+        const int c = ((ctx->special ? 512 : 768) + items - 1) / items;
         return std::max(1, std::min(c, G - 1));     // G-1 entries cost a key switch (chunk_range)
     }
     // a power of two (it divides the padded G, and from 8 on it keeps the XCD mapping): 1280 to 2560 workgroups,
     // halved while a workgroup would be left with a single term and a round of the chip is still filled
     int c = 1;
-    while (2 * c * items <= scaled(2560)) c *= 2;
+    while (2 * c * items <= 2560) c *= 2;
     c = std::min(c, G);
-    while (c > 1 && G / c < 2 && items * (c / 2) >= scaled(768)) c /= 2;
+    while (c > 1 && G / c < 2 && items * (c / 2) >= 768) c /= 2;
     return std::max(1, c);
 }
 size_t align_up(size_t v) { return (v + 255) & ~(size_t)255; }
