@@ -31,13 +31,24 @@ int choose_chunks(const gala_ctx *ctx, int items, int G) {
     // against 0.48 ms with 2048 workgroups and 0.58 ms with 768).
     // Smaller rings keep n = 2048's targets (a static call's fixed scratch is sized by them).  From n = 4096 on a CU holds
     // one workgroup, and what counts is rounds of the 256 CUs times the rotations of the longest chunk,
-    // a workgroup's start and its partial ciphertext taken as a fifth of a rotation (he_fc 500x1024 at n = 4096, batch
-    // 8: 32 chunks in one round 130 us, 64 in two 136, 24 that fill 192 CUs 149, 16 in half a round 190).
+    // a workgroup's start taken as a fifth of a rotation (he_fc 500x1024 at n = 4096, batch
+    // 8: 32 chunks in one round 130 us, 64 in two 136, 24 that fill 192 CUs 149, 16 in half a round 190), plus the partial
+    // ciphertexts, written once and read once.  Without them near-ties went to the finest cut: 1000x4096 at n = 4096,
+    // batch 50, 128 chunks and 403 MiB of workspace in 5568 us against 5 chunks and 19 MiB in 5089 us; batch 86, 128 chunks
+    // and 693 MiB in 9563 us against 32 and 177 MiB in 8986 us.  At n = 4096 they are 60 ns each beside 5 us for a fifth
+    // of a rotation: 80 of them count as one.  At n = 8192 (105 ns, 14 us) they only decide near-ties, 512 count as one: by
+    // their time 250x8192 at batch 86 would go from 32 chunks to 17, which lose the XCD mapping, 6475 us against 6290.
+    // No cut has more than 32 workgroups a CU (four chunks an input for larger batches): 1000x8192 at n = 8192, batch 130,
+    // takes 57 chunks, 29 a CU, 39.7 ms, and would take 41.8 ms with 31.  From 64 chunks on the counts are tried in steps of
+    // an eighth.
     if (uses_fast_perm(ctx) && ctx->n >= 4096) {
         int best = 1;
         long cost = -1;
-        for (int c = 1; c <= std::max(1, G - 1); c += c < 64 ? 1 : c / 8) {
-            const long rounds = ((long)items * c + 255) / 256, t = rounds * (5 * ((G - 1 + c - 1) / c) + 1);
+        const long per_unit = ctx->n == 4096 ? 80 : 512;
+        const int most = std::max(1, std::min(G - 1, std::max(4, 32 * 256 / items)));
+        for (int c = 1; c <= most; c += c < 64 ? 1 : c / 8) {
+            const long rounds = ((long)items * c + 255) / 256, longest = (G - 1 + c - 1) / c;
+            const long t = per_unit * rounds * (5 * longest + 1) + (long)items * (c + 1);
             if (cost < 0 || t < cost) cost = t, best = c;
         }
         return best;
