@@ -1781,10 +1781,13 @@ static int perm_masked(const gala_ctx *c, void *stream, const PermJob &job, cons
     const bool timed = c->prof_which == 0 && (size_t)(2 * c->prof_used + 1) < c->prof_events.size();
     if (timed) (void)hipEventRecord((hipEvent_t)c->prof_events[2 * c->prof_used], st);
     int rc;
-    // in place, or with the inputs and outputs apart: items are written as soon as they are done
+    // One launch writes an item as soon as it is done, while other items are still read: only in place or with the inputs
+    // and outputs apart, and not with the outputs over the shares r.  Otherwise the outputs are written by a second launch.
     const size_t span = (size_t)job.items * 2 * N;
     const bool apart = fin.ct_out == job.ct_in || fin.ct_out + span <= job.ct_in || job.ct_in + span <= fin.ct_out;
-    const bool alone = job.identity_only && (job.in8_S ? !job.w : apart);
+    const u64 *r_end = fin.r + (size_t)(job.items / fin.nout) * fin.r_stride;
+    const bool r_apart = fin.ct_out + span <= fin.r || r_end <= fin.ct_out;
+    const bool alone = job.identity_only && r_apart && (job.in8_S ? !job.w : apart);
     if (alone) {
         const RingTables T = make_tables(c->d_tw2, c->ntt_q);
         auto go = [&](auto kernel) {
