@@ -276,7 +276,7 @@ extern "C" int gala_he_fc(const gala_ctx *c, void *stream, const gala_fc_plan *p
     job.keys2 = pl->bound ? pl->bound->d_keys2 : nullptr;
     job.w2 = pl->d_w2;
     job.G = pl->G; job.items = batch; job.nchunks = chunks; job.slots = chunks + 1;
-    job.identity_only = pl->G == 1;
+    job.product_only = pl->G == 1;
     job.partial = (u64 *)workspace;
     FinalizeJob fin{};
     fin.partial = job.partial;
@@ -467,7 +467,6 @@ extern "C" int gala_he_conv(const gala_ctx *c, void *stream, const gala_conv_pla
     job.keys = keys;
     job.keys2 = pl->bound ? pl->bound->d_keys2 : nullptr;
     job.G = pl->cn; job.items = batch * pl->nout; job.nchunks = ws.chunks; job.slots = ws.chunks + 1;
-    job.identity_only = pl->cn == 1;
     job.partial = partial;
     FinalizeJob fin{};
     fin.partial = partial;

@@ -275,7 +275,7 @@ struct PermJob {
     int G, items, nchunks;
     int slots;               // partial ciphertexts reserved per item (>= nchunks)
     u64 *partial;            // items x slots x 2n
-    bool identity_only;      // G = 1 and gal[0] = 1: no rotation at all
+    bool product_only;       // G = 1, gal[0] = 1 and weights: no rotation at all
 };
 int launch_perm_accumulate(const gala_ctx *ctx, void *stream, const PermJob &job);
 

@@ -786,31 +786,23 @@ __device__ __forceinline__ void mask_partial(const PermJob &job, const RingTable
         out[N + i] = 0;
     });
 }
-// A layer without rotations (G = 1: a matrix that fits one ciphertext, a convolution of one channel a ciphertext) is one
-// product and the mask: the workgroup that builds an item's mask forms its output at once, in one launch and without
-// partial ciphertexts.
+// A layer without rotations (he_fc with G = 1: a matrix that fits one ciphertext; a convolution always has two kernel
+// orders at least) is one product and the mask: the workgroup that builds an item's mask forms its output at once, in one
+// launch and without partial ciphertexts.
 // From wire to wire (with the layout's loads requested ahead of the draws): 16x128 on one input 27.5 -> 24.1 us; that
 // and he_fc 1000x512 on one input, where a mask is the longest workgroup, 40.9 -> 39.6 us.
-template <bool HAS_W, bool IN8>
 __global__ __launch_bounds__(NT) void scmult_masked_ring(PermJob job, RingTables T, MaskJob mj, u64 *ct_out) {
     __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
     const int item = blockIdx.x;
-    const u64 *c0 = IN8 ? job.ct_in + (size_t)(item % job.in8_nout) * job.in8_o_stride + (size_t)(item / job.in8_nout) * 16
-                        : job.ct_in + (size_t)item * job.in_item_stride;
-    const u64 *c1 = IN8 ? c0 + 8 : c0 + N;
-    auto at = [&](const u64 *poly, int i) -> u64 { return IN8 ? poly[(size_t)(i >> 3) * job.in8_S + (i & 7)] : poly[i]; };
+    const u64 *c0 = job.ct_in + (size_t)item * job.in_item_stride, *c1 = c0 + N;
     const ulonglong2 *w = reinterpret_cast<const ulonglong2 *>(job.w2);
     u64 x0[PER], x1[PER];
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         const int i = threadIdx.x + k * NT;
-        x0[k] = at(c0, i);
-        x1[k] = at(c1, i);
-        if (HAS_W) {
-            const ulonglong2 ww = w[i];
-            x0[k] = csub_dev(mul_const(x0[k], ww.x, ww.y, T.nq), T.mod.q);
-            x1[k] = csub_dev(mul_const(x1[k], ww.x, ww.y, T.nq), T.mod.q);
-        }
+        const ulonglong2 ww = w[i];
+        x0[k] = csub_dev(mul_const(c0[i], ww.x, ww.y, T.nq), T.mod.q);
+        x1[k] = csub_dev(mul_const(c1[i], ww.x, ww.y, T.nq), T.mod.q);
     }
     u64 *out = ct_out + (size_t)item * 2 * N;
     mask_role(T, mj, item, bufA, bufB, [&](int k, int i, u64 m) {
@@ -1787,15 +1779,10 @@ static int perm_masked(const gala_ctx *c, void *stream, const PermJob &job, cons
     const bool apart = fin.ct_out == job.ct_in || fin.ct_out + span <= job.ct_in || job.ct_in + span <= fin.ct_out;
     const u64 *r_end = fin.r + (size_t)(job.items / fin.nout) * fin.r_stride;
     const bool r_apart = fin.ct_out + span <= fin.r || r_end <= fin.ct_out;
-    const bool alone = job.identity_only && r_apart && (job.in8_S ? !job.w : apart);
+    const bool alone = job.product_only && apart && r_apart;
     if (alone) {
-        const RingTables T = make_tables(c->d_tw2, c->ntt_q);
-        auto go = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, dim3((unsigned)job.items), dim3(NT), 0, st, job, T, mj, fin.ct_out);
-        };
-        if (job.w) go(scmult_masked_ring<true, false>);
-        else if (job.in8_S) go(scmult_masked_ring<false, true>);
-        else go(scmult_masked_ring<false, false>);
+        hipLaunchKernelGGL(scmult_masked_ring, dim3((unsigned)job.items), dim3(NT), 0, st, job, make_tables(c->d_tw2, c->ntt_q), mj,
+                           fin.ct_out);
         rc = (int)hipGetLastError();
     } else {
         rc = launch_perm(c, stream, job, mj);
