@@ -1,5 +1,6 @@
-"""Rings above the paper's n = 2048 (n = 4096 and 8192, one 60-bit prime) on the any-n kernels: the same parity as
-everywhere else, the library against the oracle bit for bit through the C ABI."""
+"""Rings above the paper's n = 2048 (n = 4096 and 8192, q below 2^60): the same parity as everywhere else, the library
+against the oracle bit for bit through the C ABI.  These parameters run on the rings' own kernels, except n = 8192 with a
+special prime; the any-n kernels at these sizes have test_gpu_any_n_large_rings."""
 import dataclasses
 
 import numpy as np
