@@ -358,7 +358,7 @@ ConvWorkspace conv_workspace(const gala_conv_plan *pl, int batch) {
     ConvWorkspace ws{};
     ws.chunks = choose_chunks(c, batch * pl->nout, pl->cn);
     ws.mfma = pl->d_wl && batch >= 2;    // from two inputs on (4 of a workgroup's 32 columns) the matrix cores win
-    // the one-prime n = 2048 path writes the rotated inputs straight into the product's column image and the Perm
+    // with one-prime keys the ring kernels write the rotated inputs straight into the product's column image and the Perm
     // kernel reads the product in place: neither the rotated inputs nor the per-ciphertext sums are materialised
     const bool rotates = pl->nrot_terms > 0;
     const bool direct = ws.mfma && !c->special && uses_fast_hoist(c) && (!rotates || (pl->bound && pl->bound->d_keys2));

@@ -223,7 +223,7 @@ __device__ __forceinline__ void bf_one(u64 &x, u64 &y, u64 off) {
 // kernel asked its vector cache for.
 //
 // Radix-8 forward pass on the three index bits held in the register number (bit 2 of k first).
-// FIRST = false skips the first stage (the last pass of the transform has only two stages).
+// STAGE > 0 skips the first stage or two (the last pass of a transform has what is left of the bits).
 // The seven constants of a pass are fetched with tw_level() BEFORE the exchange that precedes the pass: a load
 // cannot move across the exchange's barrier, and issued after it its latency is fully exposed, pass after pass.
 struct Tw7 {
@@ -835,7 +835,8 @@ __device__ __forceinline__ void item_and_chunk(const PermJob &job, int &item, in
 // import and export transforms in that is 12 us); two digits and a special prime, 100x784 at batch 7: 92 -> 80 us.
 //
 // Wavefronts per SIMD of the Perm kernel: what its LDS (two images and the parked coefficients) leaves room for, which
-// bounds the registers: three at n = 1024 and 2048, two at 4096 (one workgroup), the workgroup's own four at 8192.
+// bounds the registers: three at n = 1024 and 2048 (168 registers; with weights at n = 2048 the compiler spills two of them,
+// 12 bytes a lane), two at 4096 (one workgroup), the workgroup's own four at 8192.
 constexpr int PERM_WAVES = LOGN <= 11 ? 3 : LOGN == 12 ? 2 : 4;
 //
 // Every product on this path is a multiplication by a constant that carries its precomputed
@@ -853,7 +854,9 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
                                                                                  int gadget_bits, int ndigits) {
     __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
     // each thread parks its 8 coefficients here between digits (private slots, no barrier); at n = 8192 there is no LDS
-    // left for them and they stay in registers
+    // left for them and they are variables: the workgroup's four wavefronts per SIMD leave 128 registers, and the
+    // compiler spills 97 with weights, 60 on blocks of eight and 46 on whole ciphertexts (300, 240 and 180 bytes of
+    // scratch a lane).  Against the any-n kernel he_fc 200x8192 at batch 40 takes 2904 us instead of 5562 all the same.
     constexpr bool PARK = LOGN < 13;
     __shared__ u64 stash[PARK ? N : 1];
     u64 coef[PARK ? 1 : PER];
@@ -937,8 +940,8 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
 #pragma unroll
         for (int k = 0; k < PER; ++k) (PARK ? stash[tid + k * NT] : coef[PARK ? 0 : k]) = a[k];
 
-        // the c0 part, permuted c0 (.) w, and the last digit's products: with the folded keys (FoldedKeys) they are
-        // products of the rotated c1 (.) w itself
+        // the c0 part, permuted c0 (.) w, and the last digit's products: with the folded keys
+        // (key_pack_kernel) they are products of the rotated c1 (.) w itself
         {
             const ulonglong2 *kb = key + (size_t)(2 * (ndigits - 1)) * N, *ka = kb + N;
 #pragma unroll
