@@ -242,9 +242,9 @@ def fc_config(ctx, sk, D, torch, par, shape, steps, prewarm_s, cpu_sample, cpu_r
     else:
         # no rotation at all: one ScMult and the mask's encoding (a transform mod p and one mod q) per input
         inverse, forward = transform_ops(par.n, 11)
-        roof = alu_roofline(kernel, kms, batch, 2 * par.n * OPS_CONST_MUL + inverse + forward + par.n * OPS_CONST_MUL,
+        roof = alu_roofline("scmult_masked_ring", kms, batch, 2 * par.n * OPS_CONST_MUL + inverse + forward + par.n * OPS_CONST_MUL,
                             11 * par.n + 3 * par.n,
-                            note="latency-bound: one input is two workgroups of work; the figure is the launch's duration")
+                            note="latency-bound: one input is one workgroup of work; the figure is the launch's duration")
     gazelle = None
     if compare:
         # the paper's comparison schedule (hybrid method, Sec. III-A(2)) on the same kernels and inputs
