@@ -855,7 +855,7 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
     __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
     // each thread parks its 8 coefficients here between digits (private slots, no barrier); at n = 8192 there is no LDS
     // left for them and they are variables: the workgroup's four wavefronts per SIMD leave 128 registers, and the
-    // compiler spills 97 with weights, 60 on blocks of eight and 46 on whole ciphertexts (300, 240 and 180 bytes of
+    // compiler spills 97 with weights, 60 on blocks of eight and 46 on whole ciphertexts (304, 244 and 180 bytes of
     // scratch a lane).  Against the any-n kernel he_fc 200x8192 at batch 40 takes 2904 us instead of 5562 all the same.
     constexpr bool PARK = LOGN < 13;
     __shared__ u64 stash[PARK ? N : 1];
