@@ -37,6 +37,10 @@ Reciprocal make_reciprocal(u64 q) {
     const u64 hi = shoup_companion(1, q);
     return {hi, shoup_companion(0 - hi * q, q)};      // 2^64 = hi q + remainder
 }
+MontMaker make_mont(u64 m) {
+    const u64 r = (u64)((1ull << 32) % m);
+    return {m, r, shoup_companion(r, m)};
+}
 Modulus make_modulus(u64 q) {
     Modulus m;
     m.q = q;
@@ -109,10 +113,12 @@ void NttHost::init(int n_, u64 q, u64 psi_) {
     }
     ninv = inv_mod((u64)n, q);           ninvs = shoup_companion(ninv, q);
     itw1n = mulmod_slow(itw[1], ninv, q); itw1ns = shoup_companion(itw1n, q);
+    const MontMaker mont = make_mont(q);
     for (int e = 0; e < 3; ++e) {
         w8[e] = ipw[(size_t)(e + 1) * n / 4];      // psi^-(2n/8) to the power e + 1
-        w8s[e] = shoup_companion(w8[e], q);
+        w8m[e] = mont_pair(w8[e], mont);
     }
+    one_m = mont_pair(1, mont);
 }
 void NttHost::forward(u64 *a) const {
     const u64 q = mod.q, q2 = mod.q2;
@@ -295,6 +301,7 @@ extern "C" int gala_ctx_create(const gala_params *par, gala_ctx **out) {
     c->gadget_bits = par->gadget_bits; c->ndigits = ndigits;
     c->qbits = bit_length(q); c->pbits = bit_length(p);
     c->delta = q / p; c->delta_s = shoup_companion(c->delta, q);
+    c->delta_m = mont_pair(c->delta, make_mont(q));
     c->zeta = least_primitive_2n_root(p, n);
     c->ntt_q.init(n, q, primitive_2n_root(q, n));
     c->ntt_p.init(n, p, c->zeta);
@@ -303,6 +310,8 @@ extern "C" int gala_ctx_create(const gala_params *par, gala_ctx **out) {
         c->ntt_P.init(n, P, primitive_2n_root(P, n));
         c->Pq = P % q; c->Pq_s = shoup_companion(c->Pq, q);
         c->Pinv = inv_mod(c->Pq, q); c->Pinv_s = shoup_companion(c->Pinv, q);
+        c->Pq_m = mont_pair(c->Pq, make_mont(q));
+        c->minus_Pinv_m = mont_pair(q - c->Pinv, make_mont(q));
     }
     // slot (h,k) is the value at zeta^(+-3^k); the transform puts the value at
     // zeta^(2 r + 1) at index brev(r)
@@ -333,28 +342,26 @@ extern "C" int gala_ctx_create(const gala_params *par, gala_ctx **out) {
         std::copy(hs[k]->itw.begin(), hs[k]->itw.end(), base + 2 * n);
         std::copy(hs[k]->itws.begin(), hs[k]->itws.end(), base + 3 * n);
     }
-    // twiddle pairs for the ring kernels.  Forward: block T (1 <= T < n/4) of a radix-8 pass is tw[T], tw[2T],
+    // twiddles for the ring kernels.  Forward: block T (1 <= T < n/4) of a radix-8 pass is tw[T], tw[2T],
     // tw[2T+1], tw[4T..4T+3]; level c (blocks c .. 2c-1, c = 1, 8, 64, .. below n/8, and n/8) is stored [e][j] = constant e
     // of block c + j, so that a wavefront's load of constant e reads neighbouring pairs.  Inverse: a stage of half-length
     // t multiplies by w(t, j) = psi^(-j n / t), j the index modulo t; the passes on three whole bits from bit 3 on (first
     // half-length h = 8, 64, 512) are [7][h]: w(h, l), w(2h, l), w(2h, l + h), w(4h, l + e h) for e = 0 .. 3; the last
     // pass of two stages or one is [6] or [4][n/8]: w(n/4, l), w(n/4, l + n/8) and w(n/2, l + e n/8), or the latter alone;
     // then psi^-j / n for every coefficient j.
-    std::vector<u64> pairs, pairs_p, pairs_P, hostP;
+    std::vector<MontPair> pairs, pairs_p, pairs_P;
+    std::vector<u64> hostP;
     std::vector<u32> small_p;
     if (uses_fast_perm(c)) {
-        auto build = [&](const NttHost &h, std::vector<u64> &out) {
+        auto build = [&](const NttHost &h) {
             const u64 m = h.mod.q;
-            out.clear();
-            auto put = [&](u64 w, u64 ws) {
-                out.push_back(w);
-                out.push_back(ws);
-            };
+            std::vector<u64> out;
+            auto put = [&](u64 w) { out.push_back(w); };
             auto level = [&](int cnt) {
                 for (int e = 0; e < 7; ++e)
                     for (int j = 0; j < cnt; ++j) {
                         const int T = cnt + j, idx[7] = {T, 2 * T, 2 * T + 1, 4 * T, 4 * T + 1, 4 * T + 2, 4 * T + 3};
-                        put(h.tw[idx[e]], h.tws[idx[e]]);
+                        put(h.tw[idx[e]]);
                     }
             };
             for (int cnt = 1; cnt < n / 8; cnt *= 8) level(cnt);
@@ -364,14 +371,10 @@ extern "C" int gala_ctx_create(const gala_params *par, gala_ctx **out) {
             const u64 ipsi = inv_mod(h.psi, m), ipsi_s = companion(ipsi, m, rec);
             ipw[0] = 1;
             for (int i = 1; i < n; ++i) ipw[i] = mul_shoup(ipw[i - 1], ipsi, ipsi_s, m);
-            auto w = [&](int t, int j) {
-                const u64 v = ipw[(size_t)j * (n / t)];
-                put(v, companion(v, m, rec));
-            };
             // `count` constants of half-length t, each for the l below step
             auto stage = [&](int t, int count, int step) {
                 for (int e = 0; e < count; ++e)
-                    for (int l = 0; l < step; ++l) w(t, l + e * step);
+                    for (int l = 0; l < step; ++l) put(ipw[(size_t)(l + e * step) * (n / t)]);
             };
             int half = 8;
             for (; 4 * half < n; half *= 8) {
@@ -381,21 +384,28 @@ extern "C" int gala_ctx_create(const gala_params *par, gala_ctx **out) {
             }
             if (2 * half < n) stage(n / 4, 2, n / 8);
             if (half < n) stage(n / 2, 4, n / 8);
-            for (int j = 0; j < n; ++j) {
-                const u64 v = mul_shoup(ipw[j], h.ninv, h.ninvs, m);
-                put(v, companion(v, m, rec));
-            }
+            for (int j = 0; j < n; ++j) put(mul_shoup(ipw[j], h.ninv, h.ninvs, m));
+            return out;
         };
-        build(c->ntt_q, pairs);
-        build(c->ntt_p, pairs_p);
+        auto pack = [&](const std::vector<u64> &w, u64 m) {
+            const MontMaker mont = make_mont(m);
+            std::vector<MontPair> out(w.size());
+            for (size_t k = 0; k < w.size(); ++k) out[k] = mont_pair(w[k], mont);
+            return out;
+        };
+        pairs = pack(build(c->ntt_q), q);
+        const std::vector<u64> plain_p = build(c->ntt_p);
         if (p < (1ull << 26)) {       // 13 lazy stages stay below 2^32 (gala_ring_impl.h)
-            small_p.resize(pairs_p.size());
-            for (size_t k = 0; k < pairs_p.size(); k += 2) {
-                small_p[k] = (u32)pairs_p[k];
-                small_p[k + 1] = (u32)(pairs_p[k + 1] >> 32);     // floor(floor(w 2^64 / p) / 2^32)
+            const Reciprocal rec = make_reciprocal(p);
+            small_p.resize(2 * plain_p.size());
+            for (size_t k = 0; k < plain_p.size(); ++k) {
+                small_p[2 * k] = (u32)plain_p[k];
+                small_p[2 * k + 1] = (u32)(companion(plain_p[k], p, rec) >> 32);     // floor(floor(w 2^64 / p) / 2^32)
             }
+        } else {
+            pairs_p = pack(plain_p, p);
         }
-        if (P) build(c->ntt_P, pairs_P);
+        if (P) pairs_P = pack(build(c->ntt_P), P);
     }
     if (P) {
         hostP.resize(4 * (size_t)n);

@@ -46,7 +46,8 @@ struct NttHost {
     u64 psi = 0;
     std::vector<u64> tw, tws, itw, itws;
     u64 ninv = 0, ninvs = 0, itw1n = 0, itw1ns = 0;
-    u64 w8[3] = {0, 0, 0}, w8s[3] = {0, 0, 0};   // powers 1, 2, 3 of psi^(-2n/8)
+    u64 w8[3] = {0, 0, 0};                       // powers 1, 2, 3 of psi^(-2n/8)
+    MontPair w8m[3] = {}, one_m{};               // ... and the constant 1 for the ring kernels
 
     void init(int n, u64 q, u64 psi);
     void forward(u64 *a) const;   // in place, canonical in -> canonical out
@@ -64,6 +65,7 @@ u64 pow_mod(u64 b, u64 e, u64 m);
 u64 inv_mod(u64 a, u64 m);
 u64 shoup_companion(u64 w, u64 q);
 Reciprocal make_reciprocal(u64 q);
+MontMaker make_mont(u64 m);
 Modulus make_modulus(u64 q);
 bool is_prime_u64(u64 v);
 int bit_length(u64 v);
@@ -85,16 +87,17 @@ struct gala_ctx {
     // special prime of key switching (0: keys modulo q only)
     gala::u64 special = 0, Pq = 0, Pq_s = 0, Pinv = 0, Pinv_s = 0;   // P mod q and P^-1 mod q with companions
     gala::NttHost ntt_P;
+    gala::MontPair delta_m{}, Pq_m{}, minus_Pinv_m{};   // delta, P and -P^-1 mod q for the ring kernels
     std::vector<int> slot_to_idx;      // slot s -> index of its value in the mod-p transform
     int device = 0;
     bool has_device = false;           // tables uploaded; false on a host without a HIP device
     gala::u64 *d_tables = nullptr;     // 8*n words: tw,tws,itw,itws for q then for p
     int *d_slot_to_idx = nullptr;
-    gala::u64 *d_tw2 = nullptr;        // ring kernels only: (w, companion) twiddle pairs in the order of the radix-8 passes, forward then inverse
-    gala::u64 *d_tw2p = nullptr;       // the same for the plaintext modulus
+    gala::MontPair *d_tw2 = nullptr;        // ring kernels only: twiddles (MontPair) in the order of the radix-8 passes, forward then inverse
+    gala::MontPair *d_tw2p = nullptr;       // the same for the plaintext modulus, or null when p < 2^26
     gala::u32 *d_tw32p = nullptr;      // ... with 32-bit words and companions floor(w 2^32 / p), when p < 2^26; else null
     gala::u64 *d_tablesP = nullptr;    // 4*n words: tw,tws,itw,itws for the special prime
-    gala::u64 *d_tw2P = nullptr;       // the same for the special prime
+    gala::MontPair *d_tw2P = nullptr;       // the same for the special prime
     gala::NttDev dev_q{}, dev_p{}, dev_P{};
     int key_polys() const { return special ? 4 : 2; }
     // measurement aid: event pairs recorded around rotate-and-accumulate launches
@@ -115,7 +118,7 @@ struct gala_gk {
     std::map<int, int> index_of;       // Galois element -> key index
     std::vector<int> elements;
     gala::u64 *d_keys = nullptr;       // nkeys x ndigits x polys x n, evaluation domain (b then a)
-    gala::u64 *d_keys2 = nullptr;      // the folded keys as (value, companion) pairs for the ring kernels, or null
+    gala::u64 *d_keys2 = nullptr;      // the folded keys as MontPairs for the ring kernels, or null
     int *d_elements = nullptr;         // nkeys Galois elements, device
     int *d_iota = nullptr;             // 0,1,2,... (key index of element k is k), device
     int *d_one = nullptr;              // the single value 1 (Galois element of the identity), device
@@ -149,7 +152,7 @@ struct gala_fc_plan {
     std::vector<int> slot_row;         // padded row of each slot, -1 if it carries no weight
     std::vector<int> gal;              // Galois element of rotation g (gal[0] = 1)
     gala::u64 *d_w = nullptr;          // G x n encoded weights, evaluation domain
-    gala::u64 *d_w2 = nullptr;         // the same as (value, companion) pairs for the ring kernels, or null: G polynomials in
+    gala::u64 *d_w2 = nullptr;         // the same as MontPairs for the ring kernels, or null: G polynomials in
                                        // natural order, then the same G in the threads' ownership order
     int *d_gal = nullptr;              // G Galois elements
     int *d_key_idx = nullptr;          // G key indices (valid once bound)
@@ -243,8 +246,7 @@ int launch_unpack_share(const gala_ctx *ctx, void *stream, const u64 *slots, int
 // key generation helper on `npairs` consecutive (t_hat, a_hat) pairs of n-word evaluation-domain
 // polynomials: t_hat <- t_hat - a_hat * s_hat in place (s_hat shared by all pairs).
 int launch_key_finish(const gala_ctx *ctx, void *stream, u64 *pairs, const u64 *s_hat, size_t npairs, const Modulus &mod);
-// dst[i] = (src[i], floor(src[i] * 2^64 / q)) for i < count: constants with the precomputed quotient
-// that the ring kernels multiply by.
+// dst[i] = the MontPair of src[i] mod q for i < count: the constants that the ring kernels multiply by.
 int launch_pair_pack(const gala_ctx *ctx, void *stream, const u64 *src, u64 *dst, size_t count);
 // the same for nkeys whole key-switching keys, with the last digit's key folded into the others (key_pack_kernel)
 int launch_key_pack(const gala_ctx *ctx, void *stream, const u64 *src, u64 *dst, size_t nkeys);
@@ -265,7 +267,7 @@ struct PermJob {
     const u64 *w;
     const int *gal, *key_idx;
     const u64 *keys;
-    const u64 *w2, *keys2;   // (value, companion) pair images of w and keys (ring kernels only)
+    const u64 *w2, *keys2;   // MontPair images of w and keys (ring kernels only)
     const int *in_g_index;   // optional: rotation g reads input number in_g_index[g] instead of g
     // ring kernels only, in8_S != 0: the inputs are the matrix-core product's sums in blocks of eight coefficients,
     // word (i/8)*in8_S + i%8 of a polynomial, c1 eight words after c0; item = b*in8_nout + O starts at

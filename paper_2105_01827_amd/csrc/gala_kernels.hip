@@ -89,12 +89,12 @@ __global__ void key_finish_kernel(u64 *pairs, const u64 *s_hat, int n, size_t to
     t[i] = sub_mod(t[i], mul_mod(a[i], s_hat[i], mod), mod.q);
 }
 
-__global__ void pair_pack_kernel(const u64 *src, u64 *dst, size_t count, u64 q, Reciprocal r) {
+__global__ void pair_pack_kernel(const u64 *src, u64 *dst, size_t count, MontMaker mont) {
     const size_t id = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (id >= count) return;
-    const u64 w = src[id];
-    dst[2 * id] = w;
-    dst[2 * id + 1] = companion(w, q, r);
+    const MontPair w = mont_pair(src[id], mont);
+    dst[2 * id] = w.a;
+    dst[2 * id + 1] = w.b;
 }
 // Pair image of key-switching keys, folded: the digits D_j of X satisfy sum_j B^j D_j = X, so with F = B^(1-L) K_(L-1)
 //   sum_(j<L) K_j D_j = sum_(j<L-1) (K_j - B^j F) D_j + F X   (mod q)
@@ -102,7 +102,7 @@ __global__ void pair_pack_kernel(const u64 *src, u64 *dst, size_t count, u64 q, 
 // polynomials of a digit are (b, a) mod q and (b, a) mod P (polys = 4); those modulo P stay as they are, since X is
 // known modulo q only.  The modulus differs from lane to lane; it is picked with a lane mask rather than a branch on
 // purpose: hipcc 7.2 kept a branchy `cond ? q_second : q_first` in scalar registers and gave every lane q_second.
-__global__ void key_pack_kernel(const u64 *src, u64 *dst, size_t count, Modulus mod, Reciprocal rq, u64 P, Reciprocal rP, int logn,
+__global__ void key_pack_kernel(const u64 *src, u64 *dst, size_t count, Modulus mod, MontMaker kq, MontMaker kP, int logn,
                                 int polys, int ndigits, u64 B, u64 Binv) {
     const size_t id = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (id >= count) return;
@@ -114,9 +114,10 @@ __global__ void key_pack_kernel(const u64 *src, u64 *dst, size_t count, Modulus 
     const u64 own = src[id];
     const u64 folded = j == ndigits - 1 ? F : sub_mod(own & ~second, BjF, mod.q);
     const u64 w = (folded & ~second) | (own & second);
-    dst[2 * id] = w;
-    const Reciprocal r{(rq.hi & ~second) | (rP.hi & second), (rq.lo & ~second) | (rP.lo & second)};
-    dst[2 * id + 1] = companion(w, (mod.q & ~second) | (P & second), r);
+    const MontMaker mont{(kq.m & ~second) | (kP.m & second), (kq.r & ~second) | (kP.r & second), (kq.rs & ~second) | (kP.rs & second)};
+    const MontPair pair = mont_pair(w, mont);
+    dst[2 * id] = pair.a;
+    dst[2 * id + 1] = pair.b;
 }
 
 // ---------------------------------------------------------------------------
@@ -971,7 +972,7 @@ int launch_owner_order(void *stream, const u64 *src, u64 *dst, size_t npolys, in
 int launch_pair_pack(const gala_ctx *c, void *stream, const u64 *src, u64 *dst, size_t count) {
     if (!count) return 0;
     hipLaunchKernelGGL(pair_pack_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, (hipStream_t)stream, src,
-                       dst, count, c->q, make_reciprocal(c->q));
+                       dst, count, make_mont(c->q));
     return last_error();
 }
 int launch_key_pack(const gala_ctx *c, void *stream, const u64 *src, u64 *dst, size_t nkeys) {
@@ -980,8 +981,7 @@ int launch_key_pack(const gala_ctx *c, void *stream, const u64 *src, u64 *dst, s
     const size_t count = nkeys * c->ndigits * polys * c->n;
     const u64 B = (1ull << c->gadget_bits) % c->q, Binv = inv_mod(pow_mod(B, (u64)(c->ndigits - 1), c->q), c->q);
     hipLaunchKernelGGL(key_pack_kernel, dim3((unsigned)((count + 255) / 256)), dim3(256), 0, (hipStream_t)stream, src, dst,
-                       count, c->dev_q.mod, make_reciprocal(c->q), c->special, c->special ? make_reciprocal(c->special) : Reciprocal{0, 0},
-                       c->logn, polys, c->ndigits, B, Binv);
+                       count, c->dev_q.mod, make_mont(c->q), c->special ? make_mont(c->special) : MontMaker{0, 0, 0}, c->logn, polys, c->ndigits, B, Binv);
     return last_error();
 }
 const RingOps *ring_ops_10();

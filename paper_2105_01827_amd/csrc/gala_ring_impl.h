@@ -17,8 +17,8 @@
 // so the inverse transform of c1 ends exactly where the forward transforms of
 // its digits begin, and the digits never leave registers.
 //
-// Forward butterflies are fully lazy: no conditional subtraction at all except
-// one (of 8q) after the seventh stage and after the eleventh; values stay below 16q < 2^64.
+// Butterflies are lazy: residues are signed 64-bit words (below), and a transform brings only a few values near the
+// modulus on its way.
 //
 // Rings of 4096 slots on these kernels instead of the any-n ones: he_fc 500x1024 at batch 8 706 -> 130 us from wire to
 // wire (there a lone workgroup per item also added the 256 partial sums one after the other).
@@ -26,6 +26,8 @@
 #error "define GALA_LOGN before including this file"
 #endif
 #include <hip/hip_runtime.h>
+
+#include <type_traits>
 
 #include "gala_internal.h"
 
@@ -50,140 +52,105 @@ __device__ __forceinline__ int owner(int t) {
 }
 
 // ---- 64-bit modular primitives shaped for the gfx950 VALU ---------------------------------------
-// v_mad_u64_u32 (32x32 + 64 -> 64 with carry-out) issues at the full VALU rate, so everything is built
-// from it.  The compiler's own lowering of 64x64 products spends a quarter of its instructions on
-// register moves; the sequences below are written out so that it cannot re-associate them.
-// CM = true writes the multiply-adds in C instead: the compiler then knows the instruction and leaves out the wait
-// state it puts after every inline-asm result, at the price of choosing the registers and the order itself.  The
-// special-prime kernels are faster that way, the one-prime kernels are not.
-template <bool CM = false>
-__device__ __forceinline__ u64 mad_u64(u32 a, u32 b, u64 c) {
-    if (CM) return (u64)a * b + c;
-    u64 r, carry;
-    asm("v_mad_u64_u32 %0, %1, %2, %3, %4" : "=v"(r), "=s"(carry) : "v"(a), "v"(b), "v"(c));
-    return r;
+// Residues are signed 64-bit words v, |v| < 2^63, that stand for v mod m; a bound of c below means |v| <= c 2^60.
+// 32x32+64-bit multiply-adds issue at the full rate of the vector ALU, so the cost of a product is their number.  A
+// product by a constant w is a Montgomery product: with y = y1 2^32 + y0, both words signed, and the MontPair
+// (A, B) = (w 2^32, w 2^64) mod m, also in signed words,
+//     L = y0 A0 + y1 B0,   H = y0 A1 + y1 B1,   k = L m^-1 mod 2^32 (signed),   w y = H + (L - k m0) / 2^32 - k m1   (mod m)
+// Nothing needs a quotient of its own: seven multiply-adds and one 32-bit product, against thirteen instructions with a
+// precomputed quotient, and the constants take the same 16 bytes.  x + w y costs no more: x is the addend of H.
+// |w y| <= (y0 A + y1 B - k m) / 2^32 in absolute values <= (0.75 + c/32) m for |y| <= c 2^60: tight enough that a
+// transform corrects a few values once.
+// The words of y have to be signed: y1 is the high word of y + 2^31.  Transforms therefore run on biased values,
+// v + 2^31 in place of v: the high word is then y1 and the low one, its top bit flipped, y0.  A butterfly hands the bias of
+// its x on to both results.
+// L - k m0 must fit 64 bits: |y0 A0| + |k m0| + |y1 B0| <= 2^62 + 2^31 |m0| + 2^31 |y1|.  With |m0| <= 2^28 that holds up
+// to |y| <= 7 2^60 (WIDE = false).  Otherwise the high words of L and k m0 are added one by one, for one multiply-add
+// more, and |y| only has to stay below 2^63 - 2^31 (WIDE = true).
+// Measured alone (registers only, three wavefronts per SIMD): 1.27 times the butterflies of the form with precomputed
+// quotients a second, 1.18 times with WIDE.  From wire to wire: he_fc 128x1024 at batch 64 159 -> 150 us, 500x1024 at n = 4096
+// (WIDE), batch 8, 128 -> 114 us, 100x784 at batch 7 with the special prime 74 -> 67 us, the 16x16x128 convolution at batch 16
+// 288 -> 269 us.
+constexpr u64 BIAS = 0x80000000ull;
+struct MontQ {
+    u32 inv;              // m^-1 mod 2^32
+    int nlo, nhi, lo;     // the signed words of -m, and the low one of m
+};
+struct Words { u32 lo, hi; };     // y0, y1
+__device__ __forceinline__ Words biased_words(u64 y) { return {(u32)y ^ (u32)BIAS, (u32)(y >> 32)}; }
+__device__ __forceinline__ Words plain_words(u64 y) { return {(u32)y, (u32)((y + BIAS) >> 32)}; }
+// The instructions of a product are written in blocks: the compiler keeps a wait state between an inline-asm statement and
+// the next one that reads its result, inside a block there is none.  A block ends where the next step needs one half
+// of a 64-bit result (halves cannot be named inside a block).
+template <bool WIDE>
+__device__ __forceinline__ u64 mont_reduce(u64 L, u64 H, const MontQ &q) {
+    int k;
+    if (WIDE) {
+        asm("v_mul_lo_u32 %1, %2, %3\n\t"
+            "v_mad_i64_i32 %0, vcc, %1, %4, %0\n\t"
+            "v_mul_hi_i32 %1, %1, %5\n\t"
+            "v_mad_i64_i32 %0, vcc, %6, 1, %0\n\t"
+            "v_mad_i64_i32 %0, vcc, %1, -1, %0"
+            : "+v"(H), "=&v"(k)
+            : "v"((u32)L), "s"(q.inv), "s"(q.nhi), "s"(q.lo), "v"((u32)(L >> 32))
+            : "vcc");
+    } else {
+        asm("v_mul_lo_u32 %2, %3, %4\n\t"
+            "v_mad_i64_i32 %0, vcc, %2, %5, %0\n\t"
+            "v_mad_i64_i32 %1, vcc, %2, %6, %1"
+            : "+v"(L), "+v"(H), "=&v"(k)
+            : "v"((u32)L), "s"(q.inv), "s"(q.nlo), "s"(q.nhi)
+            : "vcc");
+        asm("v_mad_i64_i32 %0, vcc, %1, 1, %0" : "+v"(H) : "v"((u32)(L >> 32)) : "vcc");
+    }
+    return H;
 }
-template <bool CM = false>
-__device__ __forceinline__ u64 mul_u64(u32 a, u32 b) {
-    if (CM) return (u64)a * b;
-    u64 r, carry;
-    asm("v_mad_u64_u32 %0, %1, %2, %3, 0" : "=v"(r), "=s"(carry) : "v"(a), "v"(b));
-    return r;
+// w y, or x + w y.  UNIFORM: the constant is the same for all lanes and sits in scalar registers.
+template <bool WIDE, bool ADD = false, bool UNIFORM = false>
+__device__ __forceinline__ u64 mont(Words y, const ulonglong2 w, const MontQ &q, u64 x = 0) {
+    const u32 a0 = (u32)w.x, a1 = (u32)(w.x >> 32), b0 = (u32)w.y, b1 = (u32)(w.y >> 32);
+    u64 L, H;
+#define GALA_MONT(X, WHERE, ...)                                                                                       \
+    asm("v_mad_i64_i32 %0, vcc, %2, %4, 0\n\t"                                                                       \
+        "v_mad_i64_i32 %1, vcc, %2, %5, " X "\n\t"                                                                    \
+        "v_mad_i64_i32 %0, vcc, %3, %6, %0\n\t"                                                                       \
+        "v_mad_i64_i32 %1, vcc, %3, %7, %1"                                                                           \
+        : "=&v"(L), "=&v"(H)                                                                                          \
+        : "v"(y.lo), "v"(y.hi), WHERE(a0), WHERE(a1), WHERE(b0), WHERE(b1) __VA_ARGS__                                \
+        : "vcc")
+    if (UNIFORM) {
+        if (ADD) GALA_MONT("%8", "s", , "v"(x));
+        else GALA_MONT("0", "s");
+    } else {
+        if (ADD) GALA_MONT("%8", "v", , "v"(x));
+        else GALA_MONT("0", "v");
+    }
+#undef GALA_MONT
+    return mont_reduce<WIDE>(L, H, q);
 }
-// high 64 bits of y*s in 6 instructions: with A1 = hi32(y0 s0), B = y0 s1 + A1 and
-// S = y1 s0 + B (65 bits: C plus the carry-out), the result is y1 s1 + floor(S / 2^32).
-template <bool CM = false>
-__device__ __forceinline__ u64 mulhi64_dev(u64 y, u64 s) {
-    const u32 y0 = (u32)y, y1 = (u32)(y >> 32), s0 = (u32)s, s1 = (u32)(s >> 32);
-    const u64 B = mad_u64<CM>(y0, s1, (u64)__umulhi(y0, s0));
-    u64 C, carry;
-    asm("v_mad_u64_u32 %0, %1, %2, %3, %4" : "=v"(C), "=s"(carry) : "v"(y1), "v"(s0), "v"(B));
-    u32 top;
-    asm("v_cndmask_b32_e64 %0, 0, 1, %1" : "=v"(top) : "s"(carry));
-    return mad_u64<CM>(y1, s1, ((u64)top << 32) | (u32)(C >> 32));
-}
-// negated modulus split in two VGPR words, set up once per kernel
-struct NegQ { u32 lo, hi; };
-// y*w mod q up to one extra q (a value in [0,2q)) for any 64-bit y, w a constant with companion ws:
-// y*w - h*q = y*w + h*(-q) mod 2^64 as one chain for the low word and one for the high word.
-// ADD: x is added to the product in the same instructions (the first multiply-add of the low chain takes it as its
-// addend), so x + (y*w mod q) costs no more than the product; the sum is exact modulo 2^64.
-template <bool CM = false, bool ADD = false>
-__device__ __forceinline__ u64 mul_const(u64 y, u64 w, u64 ws, NegQ nq, u64 x = 0) {
-    const u64 h = mulhi64_dev<CM>(y, ws);
-    const u32 y0 = (u32)y, y1 = (u32)(y >> 32), w0 = (u32)w, w1 = (u32)(w >> 32);
-    const u32 h0 = (u32)h, h1 = (u32)(h >> 32);
-    u64 u = mul_u64<CM>(y0, w1);          // only the low word of this chain is used
-    u = mad_u64<CM>(y1, w0, u);
-    u = mad_u64<CM>(h0, nq.hi, u);
-    u = mad_u64<CM>(h1, nq.lo, u);
-    u64 t = ADD ? mad_u64<CM>(y0, w0, x) : mul_u64<CM>(y0, w0);
-    t = mad_u64<CM>(h0, nq.lo, t);
-    u32 hi;
-    asm("v_add_u32 %0, %1, %2" : "=v"(hi) : "v"((u32)(t >> 32)), "v"((u32)u));
-    return ((u64)hi << 32) | (u32)t;
-}
-// The same for y below 2^32 (a gadget digit): the quotient estimate floor(y*ws / 2^64) is the high word of
-// y*ws1 + hi32(y*ws0) and fits one word, so five of the twelve instructions have nothing to do.  Same value as mul_const.
-template <bool ADD = false>
-__device__ __forceinline__ u64 mul_const_small(u32 y, u64 w, u64 ws, NegQ nq, u64 x = 0) {
-    const u32 w0 = (u32)w, w1 = (u32)(w >> 32), s0 = (u32)ws, s1 = (u32)(ws >> 32);
-    const u32 h = (u32)(mad_u64(y, s1, (u64)__umulhi(y, s0)) >> 32);
-    u64 u = mul_u64(y, w1);
-    u = mad_u64(h, nq.hi, u);
-    u64 t = ADD ? mad_u64(y, w0, x) : mul_u64(y, w0);
-    t = mad_u64(h, nq.lo, t);
-    u32 hi;
-    asm("v_add_u32 %0, %1, %2" : "=v"(hi) : "v"((u32)(t >> 32)), "v"((u32)u));
-    return ((u64)hi << 32) | (u32)t;
-}
-// Two independent constant multiplications, written as three blocks of instructions instead of one statement per
-// instruction.  The compiler cannot know that v_mad_u64_u32 forwards its result without a hazard, so it puts a
-// wait state between an inline-asm statement and any statement that reads one of its results; inside a block
-// there is none.  A block ends where the next step needs one half of a 64-bit result (halves cannot be named
-// inside a block).  The two chains alternate, so no instruction reads the result of the one before it.  Carry-outs
-// go to vcc except the one that is read through a scalar pair; each of the two carries that are used is read two
-// wait states after the multiply-add that wrote it (the spacing the compiler itself keeps between a vector
-// instruction that writes a scalar register and one that reads it).
-// Measured, this form is 4.5 % faster where both constants already sit in registers (the packed convolution's
-// key products), makes no difference in the transforms, and is a tenth slower where each product waits for its
-// own loads (the Perm kernel's key products): only the first kind uses it.
-__device__ __forceinline__ void mul_const2(u64 &ra, u64 &rb, u64 ya, const ulonglong2 ca, u64 yb, const ulonglong2 cb,
-                                           NegQ nq) {
-    const u32 a0 = (u32)ya, a1 = (u32)(ya >> 32), b0 = (u32)yb, b1 = (u32)(yb >> 32);
-    const u32 wa0 = (u32)ca.x, wa1 = (u32)(ca.x >> 32), sa0 = (u32)ca.y, sa1 = (u32)(ca.y >> 32);
-    const u32 wb0 = (u32)cb.x, wb1 = (u32)(cb.x >> 32), sb0 = (u32)cb.y, sb1 = (u32)(cb.y >> 32);
-    const u64 A1a = __umulhi(a0, sa0), A1b = __umulhi(b0, sb0);
-    u64 Ca, Cb, ua, ub, ta, tb, kb;   // C holds B, then C of mulhi64_dev
-    u32 topa, topb;
-    asm("v_mad_u64_u32 %[Ca], vcc, %[a0], %[sa1], %[A1a]\n\t"
-        "v_mad_u64_u32 %[Cb], vcc, %[b0], %[sb1], %[A1b]\n\t"
-        "v_mad_u64_u32 %[Ca], vcc, %[a1], %[sa0], %[Ca]\n\t"
-        "v_mad_u64_u32 %[Cb], %[kb], %[b1], %[sb0], %[Cb]\n\t"
-        "s_nop 0\n\t"
-        "v_cndmask_b32_e64 %[topa], 0, 1, vcc\n\t"
-        "v_cndmask_b32_e64 %[topb], 0, 1, %[kb]"
-        : [Ca] "=&v"(Ca), [Cb] "=&v"(Cb), [topa] "=v"(topa), [topb] "=v"(topb), [kb] "=&s"(kb)
-        : [a0] "v"(a0), [a1] "v"(a1), [b0] "v"(b0), [b1] "v"(b1), [sa0] "v"(sa0), [sa1] "v"(sa1), [sb0] "v"(sb0),
-          [sb1] "v"(sb1), [A1a] "v"(A1a), [A1b] "v"(A1b)
+// x + w y for 0 <= y < 2^31 (a gadget digit, not biased): half of the products have nothing to do
+template <bool WIDE>
+__device__ __forceinline__ u64 mont_small(u32 y, const ulonglong2 w, const MontQ &q, u64 x) {
+    u64 L, H;
+    asm("v_mad_i64_i32 %0, vcc, %2, %3, 0\n\t"
+        "v_mad_i64_i32 %1, vcc, %2, %4, %5"
+        : "=&v"(L), "=&v"(H)
+        : "v"(y), "v"((u32)w.x), "v"((u32)(w.x >> 32)), "v"(x)
         : "vcc");
-    u64 ha = ((u64)topa << 32) | (u32)(Ca >> 32), hb = ((u64)topb << 32) | (u32)(Cb >> 32);
-    asm("v_mad_u64_u32 %[ha], vcc, %[a1], %[sa1], %[ha]\n\t"
-        "v_mad_u64_u32 %[hb], vcc, %[b1], %[sb1], %[hb]"
-        : [ha] "+v"(ha), [hb] "+v"(hb)
-        : [a1] "v"(a1), [sa1] "v"(sa1), [b1] "v"(b1), [sb1] "v"(sb1)
-        : "vcc");
-    asm("v_mad_u64_u32 %[ua], vcc, %[a0], %[wa1], 0\n\t"
-        "v_mad_u64_u32 %[ub], vcc, %[b0], %[wb1], 0\n\t"
-        "v_mad_u64_u32 %[ta], vcc, %[a0], %[wa0], 0\n\t"
-        "v_mad_u64_u32 %[tb], vcc, %[b0], %[wb0], 0\n\t"
-        "v_mad_u64_u32 %[ua], vcc, %[a1], %[wa0], %[ua]\n\t"
-        "v_mad_u64_u32 %[ub], vcc, %[b1], %[wb0], %[ub]\n\t"
-        "v_mad_u64_u32 %[ta], vcc, %[ha0], %[ql], %[ta]\n\t"
-        "v_mad_u64_u32 %[tb], vcc, %[hb0], %[ql], %[tb]\n\t"
-        "v_mad_u64_u32 %[ua], vcc, %[ha0], %[qh], %[ua]\n\t"
-        "v_mad_u64_u32 %[ub], vcc, %[hb0], %[qh], %[ub]\n\t"
-        "v_mad_u64_u32 %[ua], vcc, %[ha1], %[ql], %[ua]\n\t"
-        "v_mad_u64_u32 %[ub], vcc, %[hb1], %[ql], %[ub]"
-        : [ua] "=&v"(ua), [ub] "=&v"(ub), [ta] "=&v"(ta), [tb] "=&v"(tb)
-        : [a0] "v"(a0), [a1] "v"(a1), [b0] "v"(b0), [b1] "v"(b1), [wa0] "v"(wa0), [wa1] "v"(wa1), [wb0] "v"(wb0),
-          [wb1] "v"(wb1), [ha0] "v"((u32)ha), [ha1] "v"((u32)(ha >> 32)), [hb0] "v"((u32)hb), [hb1] "v"((u32)(hb >> 32)),
-          [ql] "v"(nq.lo), [qh] "v"(nq.hi)
-        : "vcc");
-    u32 hia, hib;
-    asm("v_add_u32 %0, %1, %2" : "=v"(hia) : "v"((u32)(ta >> 32)), "v"((u32)ua));
-    asm("v_add_u32 %0, %1, %2" : "=v"(hib) : "v"((u32)(tb >> 32)), "v"((u32)ub));
-    ra = ((u64)hia << 32) | (u32)ta;
-    rb = ((u64)hib << 32) | (u32)tb;
+    return mont_reduce<WIDE>(L, H, q);
 }
-struct U64Pair { u64 a, b; };
-__device__ __forceinline__ U64Pair mul_const_pair(u64 ya, const ulonglong2 ca, u64 yb, const ulonglong2 cb, NegQ nq) {
-    U64Pair r;
-    mul_const2(r.a, r.b, ya, ca, yb, cb, nq);
-    return r;
+// x - h m with h = floor(x / 2^60), biased or not: at most 1 + h (1 - m / 2^60), so never above 3 for |x| <= 8 m and close
+// to 1 when m is close to 2^60
+__device__ __forceinline__ u64 shrink(u64 x, const MontQ &q) {
+    const int h = (int)(x >> 32) >> 28;
+    u64 r;
+    asm("v_mad_i64_i32 %0, vcc, %1, %2, %3" : "=v"(r) : "v"(h), "s"(q.nlo), "v"(x) : "vcc");
+    return r + ((u64)((u32)h * (u32)q.nhi) << 32);
 }
+// a product, in (-m, m), to [0, m)
+__device__ __forceinline__ u64 unsign(u64 r, u64 m) { return r + ((u64)((i64)r >> 63) & m); }
 // x - c if x >= c else x, in 4 instructions (the borrow of the subtraction selects);
-// needs x - c < 2^63 when x >= c, which holds for every use here (x < 2c, c <= 8q < 2^63).
+// needs x - c < 2^63 when x >= c, which holds for every use here (x < 2c, c < 2^61).
 __device__ __forceinline__ u64 csub_dev(u64 x, u64 c) {
     u32 r0, r1;
     asm("v_sub_co_u32 %0, vcc, %2, %4\n\tv_subb_co_u32 %1, vcc, %3, %5, vcc\n\t"
@@ -194,23 +161,31 @@ __device__ __forceinline__ u64 csub_dev(u64 x, u64 c) {
     return ((u64)r1 << 32) | r0;
 }
 
-// x,y -> x + w*y, x - w*y + 2q  without any correction (bound grows by 2q per stage)
-template <bool CM = false>
-__device__ __forceinline__ void bf_fwd(u64 &x, u64 &y, const ulonglong2 t, NegQ nq, u64 q2) {
-    const u64 s = mul_const<CM, true>(y, t.x, t.y, nq, x);      // x + w*y
-    y = (x << 1) + q2 - s;                                      // x - w*y + 2q = 2x + 2q - (x + w*y)
+// x, y -> x + w y, x - w y without any correction; the bound grows by 0.75 + c/32, c the bound of y.  Both biased.
+template <bool WIDE>
+__device__ __forceinline__ void bf(u64 &x, u64 &y, const ulonglong2 w, const MontQ &q) {
+    const u64 s = mont<WIDE, true>(biased_words(y), w, q, x);
+    y = (x << 1) - s;
     x = s;
 }
-// the forward butterfly when y is below 2^32
-__device__ __forceinline__ void bf_fwd_small(u64 &x, u64 &y, const ulonglong2 t, NegQ nq, u64 q2) {
-    const u64 s = mul_const_small<true>((u32)y, t.x, t.y, nq, x);
-    y = (x << 1) + q2 - s;
+// y not biased, the constant in scalar registers
+template <bool WIDE>
+__device__ __forceinline__ void bf_plain(u64 &x, u64 &y, const ulonglong2 w, const MontQ &q) {
+    const u64 s = mont<WIDE, true, true>(plain_words(y), w, q, x);
+    y = (x << 1) - s;
     x = s;
 }
-// x, y -> x + y, x - y + off: the butterfly whose constant is one; `off`, a multiple of q, is at least y's bound
-__device__ __forceinline__ void bf_one(u64 &x, u64 &y, u64 off) {
+// y below 2^31 and not biased
+template <bool WIDE>
+__device__ __forceinline__ void bf_digit(u64 &x, u64 &y, const ulonglong2 w, const MontQ &q) {
+    const u64 s = mont_small<WIDE>((u32)y, w, q, x);
+    y = (x << 1) - s;
+    x = s;
+}
+// the butterfly whose constant is one; y not biased
+__device__ __forceinline__ void bf_one(u64 &x, u64 &y) {
     const u64 s = x + y;
-    y = x - y + off;
+    y = x - y;
     x = s;
 }
 
@@ -246,99 +221,85 @@ __device__ __forceinline__ Tw7 tw_level(const ulonglong2 *__restrict__ table, un
     for (int e = 0; e < 7; ++e) w.t[e] = *reinterpret_cast<const ulonglong2 *>(level + (size_t)(e * COUNT * 16) + off);
     return w;
 }
-// STAGE: the first of the three stages to run.  CORRECT: the stage (of 0, 1, 2) before which the operands that it
-// does not multiply are brought from below 16q to below 8q, or -1.
-// small_in (the same for every thread): all eight inputs are below 2^32, as gadget digits are; the first stage then
-// multiplies with mul_const_small.
-template <int STAGE, int CORRECT, bool CM = false>
-__device__ __forceinline__ void fwd_pass(u64 (&a)[8], const Tw7 &w, NegQ q, u64 q2, bool small_in = false) {
-    const u64 q8 = 4 * q2;
-    if (STAGE == 0) {
-        if (!CM && small_in) {
+// STAGE: the first of the three stages to run.  CORRECT: the values that the first stage does not multiply are shrunk.
+// digits (the same for every thread): a[4..7], the values that the first stage multiplies, are below 2^31 and not biased,
+// as gadget digits are.
+template <bool WIDE, int STAGE, bool CORRECT = false>
+__device__ __forceinline__ void fwd_pass(u64 (&a)[8], const Tw7 &w, const MontQ &q, bool digits = false) {
+    if (CORRECT) {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) bf_fwd_small(a[k], a[k + 4], w.t[0], q, q2);
+        for (int k = 0; k < 4; ++k) a[k] = shrink(a[k], q);
+    }
+    if (STAGE == 0) {
+        if (digits) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) bf_digit<WIDE>(a[k], a[k + 4], w.t[0], q);
         } else {
 #pragma unroll
-            for (int k = 0; k < 4; ++k) bf_fwd<CM>(a[k], a[k + 4], w.t[0], q, q2);
+            for (int k = 0; k < 4; ++k) bf<WIDE>(a[k], a[k + 4], w.t[0], q);
         }
     }
     if (STAGE <= 1) {
-        if (CORRECT == 1) {
-            a[0] = csub_dev(a[0], q8);
-            a[1] = csub_dev(a[1], q8);
-            a[4] = csub_dev(a[4], q8);
-            a[5] = csub_dev(a[5], q8);
-        }
-        bf_fwd<CM>(a[0], a[2], w.t[1], q, q2);
-        bf_fwd<CM>(a[1], a[3], w.t[1], q, q2);
-        bf_fwd<CM>(a[4], a[6], w.t[2], q, q2);
-        bf_fwd<CM>(a[5], a[7], w.t[2], q, q2);
+        bf<WIDE>(a[0], a[2], w.t[1], q);
+        bf<WIDE>(a[1], a[3], w.t[1], q);
+        bf<WIDE>(a[4], a[6], w.t[2], q);
+        bf<WIDE>(a[5], a[7], w.t[2], q);
     }
-    if (CORRECT == 2) {
-        a[0] = csub_dev(a[0], q8);
-        a[2] = csub_dev(a[2], q8);
-        a[4] = csub_dev(a[4], q8);
-        a[6] = csub_dev(a[6], q8);
-    }
-    bf_fwd<CM>(a[0], a[1], w.t[3], q, q2);
-    bf_fwd<CM>(a[2], a[3], w.t[4], q, q2);
-    bf_fwd<CM>(a[4], a[5], w.t[5], q, q2);
-    bf_fwd<CM>(a[6], a[7], w.t[6], q, q2);
+    bf<WIDE>(a[0], a[1], w.t[3], q);
+    bf<WIDE>(a[2], a[3], w.t[4], q);
+    bf<WIDE>(a[4], a[5], w.t[5], q);
+    bf<WIDE>(a[6], a[7], w.t[6], q);
 }
 // Inverse transform.  The values sit in bit-reversed order, which is what a decimation-in-time transform starts from:
 // it evaluates the plain cyclic sum over the powers of psi^-2, and a multiplication of coefficient j by psi^-j / n at
 // the end makes it negacyclic (the separate scaling by 1/n costs as many products).  Against the usual inverse, whose
-// butterflies (x + y, (x - y) w) carry psi inside: a forward butterfly is three instructions shorter because its sum
-// rides on the product; seven of the first pass's twelve constants are one; and of its values only those that are added
-// need corrections, twice four per transform instead of twenty-nine.  About 780 instead of 960 instructions a thread.
-// Measured: the Perm stage of a 3x3 convolution of 16x16x128 to 128 channels, batch 16, 112 -> 104 us, with the special prime, which
-// has three inverse transforms a rotation, 212 -> 198 us; he_fc 1000x2048 at batch 64 2369 -> 2345 us.
+// butterflies (x + y, (x - y) w) carry psi inside: the sum rides on the product, seven of the first pass's twelve
+// constants are one, and only four values need shrinking after the first pass and four before the third.
 //
-// First pass, bits 0-2: the constants are 1, i, w8 and w8^3 with w8 = psi^(-2n/8), i = w8^2; inputs below 2q.
-template <bool CM = false>
-__device__ __forceinline__ void inv_first_pass(u64 (&a)[8], const ulonglong2 (&w8)[3], NegQ q, u64 q2) {
-    const u64 q4 = 2 * q2, q8 = 4 * q2;
-    bf_one(a[0], a[1], q2);
-    bf_one(a[2], a[3], q2);
-    bf_one(a[4], a[5], q2);
-    bf_one(a[6], a[7], q2);                          // below 4q
-    bf_one(a[0], a[2], q4);
-    bf_one(a[4], a[6], q4);                          // below 8q
-    bf_fwd<CM>(a[1], a[3], w8[1], q, q2);
-    bf_fwd<CM>(a[5], a[7], w8[1], q, q2);            // below 6q
-    bf_one(a[0], a[4], q8);                          // below 16q
-    bf_fwd<CM>(a[1], a[5], w8[0], q, q2);            // below 8q
-    bf_fwd<CM>(a[2], a[6], w8[1], q, q2);            // below 10q
-    bf_fwd<CM>(a[3], a[7], w8[2], q, q2);            // below 8q
-    a[0] = csub_dev(a[0], q8);
-    a[4] = csub_dev(a[4], q8);
-    a[2] = csub_dev(a[2], q8);
-    a[6] = csub_dev(a[6], q8);                       // all below 8q
+// First pass, bits 0-2: the constants are 1, i, w8 and w8^3 with w8 = psi^(-2n/8), i = w8^2.  Not biased on entry, |a| < m
+// (eight of them add up to less than 2^63, with no room for a bias), biased on return.
+template <bool WIDE>
+__device__ __forceinline__ void inv_first_pass(u64 (&a)[8], const ulonglong2 (&w8)[3], const MontQ &q) {
+    bf_one(a[0], a[1]);
+    bf_one(a[2], a[3]);
+    bf_one(a[4], a[5]);
+    bf_one(a[6], a[7]);                              // 2
+    bf_one(a[0], a[2]);
+    bf_one(a[4], a[6]);                              // 4
+    a[1] += BIAS;
+    a[2] += BIAS;
+    bf_plain<WIDE>(a[1], a[3], w8[1], q);
+    bf_plain<WIDE>(a[5], a[7], w8[1], q);            // 2.9
+    bf_one(a[0], a[4]);                              // 8
+    bf_plain<WIDE>(a[1], a[5], w8[0], q);            // 3.7
+    bf_plain<WIDE>(a[2], a[6], w8[1], q);            // 4.9
+    bf_plain<WIDE>(a[3], a[7], w8[2], q);            // 3.7
+#pragma unroll
+    for (int k = 0; k < 8; k += 2) a[k] = shrink(a[k], q);
+    a[0] += BIAS;
+    a[4] += BIAS;
 }
 // Radix-8 pass on bits B .. B+2 held in the register number (bit 0 first).  A stage of half-length t multiplies by
 // psi^(-2j n / 2t), j the index modulo t: one constant for bit B, two for B+1, four for B+2, of the thread's low bits.
-// CORRECT: the inputs are below 14q instead of 10q; the values that the second stage only adds are brought below 8q.
-template <bool CORRECT, bool CM = false>
-__device__ __forceinline__ void inv_pass(u64 (&a)[8], const Tw7 &w, NegQ q, u64 q2) {
-    bf_fwd<CM>(a[0], a[1], w.t[0], q, q2);
-    bf_fwd<CM>(a[2], a[3], w.t[0], q, q2);
-    bf_fwd<CM>(a[4], a[5], w.t[0], q, q2);
-    bf_fwd<CM>(a[6], a[7], w.t[0], q, q2);
+// CORRECT: the values that the first stage only adds are shrunk.
+template <bool WIDE, bool CORRECT>
+__device__ __forceinline__ void inv_pass(u64 (&a)[8], const Tw7 &w, const MontQ &q) {
     if (CORRECT) {
-        const u64 q8 = 4 * q2;
-        a[0] = csub_dev(a[0], q8);
-        a[1] = csub_dev(a[1], q8);
-        a[4] = csub_dev(a[4], q8);
-        a[5] = csub_dev(a[5], q8);
+#pragma unroll
+        for (int k = 0; k < 8; k += 2) a[k] = shrink(a[k], q);
     }
-    bf_fwd<CM>(a[0], a[2], w.t[1], q, q2);
-    bf_fwd<CM>(a[1], a[3], w.t[2], q, q2);
-    bf_fwd<CM>(a[4], a[6], w.t[1], q, q2);
-    bf_fwd<CM>(a[5], a[7], w.t[2], q, q2);
-    bf_fwd<CM>(a[0], a[4], w.t[3], q, q2);
-    bf_fwd<CM>(a[1], a[5], w.t[4], q, q2);
-    bf_fwd<CM>(a[2], a[6], w.t[5], q, q2);
-    bf_fwd<CM>(a[3], a[7], w.t[6], q, q2);
+    bf<WIDE>(a[0], a[1], w.t[0], q);
+    bf<WIDE>(a[2], a[3], w.t[0], q);
+    bf<WIDE>(a[4], a[5], w.t[0], q);
+    bf<WIDE>(a[6], a[7], w.t[0], q);
+    bf<WIDE>(a[0], a[2], w.t[1], q);
+    bf<WIDE>(a[1], a[3], w.t[2], q);
+    bf<WIDE>(a[4], a[6], w.t[1], q);
+    bf<WIDE>(a[5], a[7], w.t[2], q);
+    bf<WIDE>(a[0], a[4], w.t[3], q);
+    bf<WIDE>(a[1], a[5], w.t[4], q);
+    bf<WIDE>(a[2], a[6], w.t[5], q);
+    bf<WIDE>(a[3], a[7], w.t[6], q);
 }
 // The inverse table: bits 3-5 as [7][8], bits 6-8 as [7][64], from n = 4096 on bits 9-11 as [7][512], the last pass's one
 // or two stages as [4] or [6][n/8] (constant, low bits of the index), then psi^-j / n for j = 0 .. n-1.
@@ -381,11 +342,17 @@ __device__ __forceinline__ void exchange(u64 (&a)[8], u64 *buf, int tid) {
 }
 
 struct RingTables {
-    const ulonglong2 *tw, *itw;   // (w, companion) pairs, forward (see tw_level) and inverse (see inv_level)
+    const ulonglong2 *tw, *itw;   // MontPairs, forward (see tw_level) and inverse (see inv_level)
     ulonglong2 w8[3];             // w8, w8^2, w8^3 of the inverse transform's first pass
+    ulonglong2 one;               // the constant 1
     Modulus mod;
-    NegQ nq;                      // 2^64 - q
+    MontQ mont;
 };
+// |y| < 8 m (7 unless WIDE) -> [0, m)
+template <bool WIDE>
+__device__ __forceinline__ u64 canonical(Words y, const RingTables &T) {
+    return unsign(mont<WIDE, false, true>(y, T.one, T.mont), T.mod.q);
+}
 
 // The thread id goes through an empty asm so that the address arithmetic of a transform is redone
 // where it is used instead of being hoisted out of the rotation loop into long-lived registers.
@@ -394,45 +361,54 @@ __device__ __forceinline__ int fresh(int tid) {
     return tid;
 }
 
-// Forward transform of the 8 registers (ownership t + (n/8) k, values below 2q); the result is left in
-// LDS buffer `res` (natural index, padded), values below 16q.  LDS phases: other, res, other, res; at n = 8192, where a
+// Forward transform of the 8 registers (ownership t + (n/8) k); the result is left in LDS buffer `res` (natural index,
+// padded), biased, below 7.3 (5.4 at n = 2048).  LDS phases: other, res, other, res; at n = 8192, where a
 // fifth phase would start and end on the same buffer, res, other, res, other, res behind a barrier.
+// IN: what the registers hold on entry.  Digits are below 2^31.  Bounds from |a| < m: 1.8, 2.6, 3.5 | 4.3, 5.2, 6.1 |
+// shrunk, 2.0, 2.8, 3.6 | 4.5, 5.4, 6.3 | 7.2.
 // `ahead` runs before the last pass: loads of what is multiplied with the result can be issued there.
 struct NothingAhead {
     __device__ __forceinline__ void operator()() const {}
 };
-template <bool CM = false, class Ahead = NothingAhead>
+enum Entry { PLAIN, BIASED };
+template <bool WIDE, Entry IN = PLAIN, class Ahead = NothingAhead>
 __device__ __forceinline__ void forward_to_lds(u64 (&a)[8], u64 *res, u64 *other, const RingTables &T, int tid_,
-                                               bool small_in = false, Ahead ahead = Ahead{}) {
+                                               bool digits = false, Ahead ahead = Ahead{}) {
     const int tid = fresh(tid_);
-    const NegQ q = T.nq;
-    const u64 q2 = T.mod.q2;
+    const MontQ q = T.mont;
     constexpr int B1 = LOGN - 3, B2 = LOGN - 6, B3 = LOGN - 9, B4 = LOGN >= 12 ? LOGN - 12 : 0;
     u64 *first = LOGN == 13 ? res : other, *second = LOGN == 13 ? other : res;
     if (LOGN == 13) __syncthreads();
+    if (IN == PLAIN) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) a[k] += BIAS;
+        if (!digits)
+#pragma unroll
+            for (int k = 4; k < 8; ++k) a[k] += BIAS;
+    }
     Tw7 w = tw_level<1>(T.tw, 0);
-    fwd_pass<0, -1, CM>(a, w, q, q2, small_in);                                          // stages 1-3
+    fwd_pass<WIDE, 0>(a, w, q, digits);                                                  // stages 1-3
     w = tw_level<8>(T.tw, (unsigned)tid >> B2);
     exchange<B1, B2>(a, first, tid);
-    fwd_pass<0, -1, CM>(a, w, q, q2);                                                    // stages 4-6
+    fwd_pass<WIDE, 0>(a, w, q);                                                          // stages 4-6
     w = tw_level<64>(T.tw, (unsigned)tid >> B3);
     exchange<B2, B3>(a, second, tid);
-    fwd_pass<0, 1, CM>(a, w, q, q2);                                                     // stages 7-9
+    fwd_pass<WIDE, 0, true>(a, w, q);                                                    // stages 7-9
     if (LOGN < 12) {
         w = tw_level<NT>(T.tw, (unsigned)tid);
         exchange<B3, 0>(a, first, tid);
         ahead();
-        fwd_pass<3 - LOGN % 3, -1, CM>(a, w, q, q2);                                     // stages 10, 11
+        fwd_pass<WIDE, 3 - LOGN % 3>(a, w, q);                                           // stages 10, 11
     } else {
         w = tw_level<512>(T.tw, (unsigned)tid >> B4);
         exchange<B3, B4>(a, first, tid);
         if (LOGN == 12) ahead();
-        fwd_pass<0, 2, CM>(a, w, q, q2);                                                 // stages 10-12
+        fwd_pass<WIDE, 0>(a, w, q);                                                      // stages 10-12
         if (LOGN == 13) {
             w = tw_level<NT>(T.tw, (unsigned)tid);
             exchange<B4, 0>(a, second, tid);
             ahead();
-            fwd_pass<2, -1, CM>(a, w, q, q2);                                            // stage 13
+            fwd_pass<WIDE, 2>(a, w, q);                                                  // stage 13
         }
     }
     u64 *po = res + pad(tid << 3);
@@ -441,22 +417,21 @@ __device__ __forceinline__ void forward_to_lds(u64 (&a)[8], u64 *res, u64 *other
     __syncthreads();
 }
 
-// Inverse transform: registers hold index 8t + k (values below 2q) on entry and index t + (n/8) k,
-// canonical, on return.  LDS phases A B A, one more on B at n = 8192.
-template <bool CM = false>
+// Inverse transform: registers hold index 8t + k (not biased, |a| < m) on entry and index t + (n/8) k, canonical, on
+// return.  LDS phases A B A, one more on B at n = 8192.
+template <bool WIDE>
 __device__ __forceinline__ void inverse_in_regs(u64 (&a)[8], u64 *bufA, u64 *bufB, const RingTables &T, int tid_) {
     const int tid = fresh(tid_);
-    const NegQ q = T.nq;
-    const u64 q2 = T.mod.q2;
+    const MontQ q = T.mont;
     constexpr int TOP = LOGN - 3;
     Tw7 w;
     inv_level<7, 8>(w.t, T.itw, (unsigned)tid & 7);
-    inv_first_pass<CM>(a, T.w8, q, q2);                                                  // bits 0-2: below 8q
+    inv_first_pass<WIDE>(a, T.w8, q);                                                    // bits 0-2: 3.7
     exchange<0, 3>(a, bufA, tid);
-    inv_pass<false, CM>(a, w, q, q2);                                                    // bits 3-5: below 14q
+    inv_pass<WIDE, false>(a, w, q);                                                      // bits 3-5: 6.4
     inv_level<7, 64>(w.t, T.itw + INV_MID, (unsigned)tid & 63);
     exchange<3, 6>(a, bufB, tid);
-    inv_pass<true, CM>(a, w, q, q2);                                                     // bits 6-8: below 12q
+    inv_pass<WIDE, true>(a, w, q);                                                       // bits 6-8: 3.6
     // requested right behind the last barrier and used after the last stages: asked for when they are needed, their
     // latency cost he_fc 128x1024 at batch 64 10 us of 158
     ulonglong2 c[8];
@@ -464,26 +439,26 @@ __device__ __forceinline__ void inverse_in_regs(u64 (&a)[8], u64 *bufA, u64 *buf
         inv_level<7, 512>(w.t, T.itw + INV_HIGH, (unsigned)tid & 511);
         exchange<6, 9>(a, bufA, tid);
         if (!TOP_STAGES) inv_level<8, NT>(c, T.itw + INV_TWIST, (unsigned)tid);
-        inv_pass<true, CM>(a, w, q, q2);                                                 // bits 9-11: below 12q
+        inv_pass<WIDE, false>(a, w, q);                                                  // bits 9-11: 6.3
     }
     if (TOP_STAGES) {
-        // the last pass (register bit 2 is the top bit): below 16q
+        // the last pass (register bit 2 is the top bit): 5.4, 7.2 at n = 8192
         ulonglong2 t[TOP_CONSTS];
         inv_level<TOP_CONSTS, NT>(t, T.itw + INV_TOP, (unsigned)tid);
         if (LOGN >= 12) exchange<9, TOP>(a, bufB, tid);
         else exchange<6, TOP>(a, bufA, tid);
         inv_level<8, NT>(c, T.itw + INV_TWIST, (unsigned)tid);
         if (TOP_STAGES == 2) {
-            bf_fwd<CM>(a[0], a[2], t[0], q, q2);
-            bf_fwd<CM>(a[1], a[3], t[1], q, q2);
-            bf_fwd<CM>(a[4], a[6], t[0], q, q2);
-            bf_fwd<CM>(a[5], a[7], t[1], q, q2);
+            bf<WIDE>(a[0], a[2], t[0], q);
+            bf<WIDE>(a[1], a[3], t[1], q);
+            bf<WIDE>(a[4], a[6], t[0], q);
+            bf<WIDE>(a[5], a[7], t[1], q);
         }
 #pragma unroll
-        for (int k = 0; k < 4; ++k) bf_fwd<CM>(a[k], a[k + 4], t[TOP_CONSTS - 4 + k], q, q2);
+        for (int k = 0; k < 4; ++k) bf<WIDE>(a[k], a[k + 4], t[TOP_CONSTS - 4 + k], q);
     }
 #pragma unroll
-    for (int k = 0; k < PER; ++k) a[k] = csub_dev(mul_const<CM>(a[k], c[k].x, c[k].y, q), T.mod.q);
+    for (int k = 0; k < PER; ++k) a[k] = unsign(mont<WIDE>(biased_words(a[k]), c[k], q), T.mod.q);
 }
 
 // ---- transforms modulo a small plaintext prime -------------------------------------------------------------------
@@ -654,6 +629,7 @@ __device__ __forceinline__ void put_slot(u64 *bufB, int position, u64 v, bool sm
 __device__ __forceinline__ u64 get_slot(const u64 *bufB, int position, bool small) {
     return small ? reinterpret_cast<const u32 *>(bufB)[pad(position)] : bufB[pad(position)];
 }
+template <bool WIDE>
 __device__ __forceinline__ void slots_to_coefficients(u64 (&a)[8], u64 *bufA, u64 *bufB, const RingTables &Tp,
                                                       const SmallTables &small, int tid) {
     if (small.tw) {
@@ -666,22 +642,8 @@ __device__ __forceinline__ void slots_to_coefficients(u64 (&a)[8], u64 *bufA, u6
     } else {
 #pragma unroll
         for (int k = 0; k < PER; ++k) a[k] = bufB[pad(8 * tid) + k];
-        inverse_in_regs(a, bufA, bufB, Tp, tid);
+        inverse_in_regs<WIDE>(a, bufA, bufB, Tp, tid);
     }
-}
-
-// below 16q -> canonical
-__device__ __forceinline__ u64 reduce64(u64 x, const Modulus &m) {
-    return csub(x - mulhi64(x, m.one_s) * m.q, m.q);
-}
-// below BOUND q (8 or 16) -> canonical, by three or four conditional subtractions: 12 or 16 instructions instead of 24,
-// but four constants more to keep.  Faster in the hoisted inner products (the 16x16x128 convolution at batch 16 294.8
-// -> 293.5 us), slower in encryption (70.6 -> 71.7 us), which stays with the product.
-template <int BOUND>
-__device__ __forceinline__ u64 reduce_below(u64 x, u64 q) {
-    static_assert(BOUND == 8 || BOUND == 16, "");
-    if (BOUND == 16) x = csub_dev(x, 8 * q);
-    return csub_dev(csub_dev(csub_dev(x, 4 * q), 2 * q), q);
 }
 
 // Share generation inside the same launch: the workgroups after the last (item, chunk) pair build the
@@ -695,17 +657,17 @@ struct MaskJob {
     MaskLayoutDev layout;
     const int *slot_to_idx;
     int pbits;
-    ulonglong2 delta;           // delta = floor(q/p) and its companion mod q
+    ulonglong2 delta;           // delta = floor(q/p), a MontPair mod q
     RingTables Tp;              // inverse-transform tables of the plaintext modulus
     SmallTables small;
 };
 
 // store(k, i, m): mask word i = tid + k NT of the evaluation domain, canonical.
-template <class Store>
+template <bool WIDE, class Store>
 __device__ __forceinline__ void mask_role(const RingTables &T, const MaskJob &mj, int item, u64 *bufA, u64 *bufB, Store store) {
     const int tid = threadIdx.x;
     const int b = item / mj.nout, O = item % mj.nout;
-    const u64 p = mj.Tp.mod.q, q = T.mod.q;
+    const u64 p = mj.Tp.mod.q;
     const bool small = mj.small.tw != nullptr;
     const int *row_ptr = mj.layout.row_ptr + (size_t)O * (N + 1);
     const int *row_rindex = mj.layout.row_rindex + (size_t)O * N;
@@ -766,22 +728,23 @@ __device__ __forceinline__ void mask_role(const RingTables &T, const MaskJob &mj
     __syncthreads();
     // slots -> plaintext polynomial (inverse transform mod p) -> delta * m mod q -> evaluation domain mod q
     u64 a[PER];
-    slots_to_coefficients(a, bufA, bufB, mj.Tp, mj.small, tid);        // LDS phases A B A
+    slots_to_coefficients<WIDE>(a, bufA, bufB, mj.Tp, mj.small, tid);        // LDS phases A B A
 #pragma unroll
-    for (int k = 0; k < PER; ++k) a[k] = csub_dev(mul_const(a[k], mj.delta.x, mj.delta.y, T.nq), q);
-    forward_to_lds(a, bufA, bufB, T, tid);             // LDS phases B A B A, result in bufA (below 16q)
+    for (int k = 0; k < PER; ++k) a[k] = mont<WIDE, true, true>(plain_words(a[k]), mj.delta, T.mont, BIAS);
+    forward_to_lds<WIDE, BIASED>(a, bufA, bufB, T, tid);             // LDS phases B A B A, result in bufA
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         const int i = tid + k * NT;
-        store(k, i, reduce64(bufA[pad(i)], T.mod));
+        store(k, i, canonical<WIDE>(biased_words(bufA[pad(i)]), T));
     }
 }
 // ... as one more partial ciphertext of the item: minus the mask on c0
+template <bool WIDE>
 __device__ __forceinline__ void mask_partial(const PermJob &job, const RingTables &T, const MaskJob &mj, int item, u64 *bufA,
                                              u64 *bufB) {
     u64 *out = job.partial + ((size_t)item * job.slots + job.nchunks) * 2 * N;
     const u64 q = T.mod.q;
-    mask_role(T, mj, item, bufA, bufB, [&](int, int i, u64 m) {
+    mask_role<WIDE>(T, mj, item, bufA, bufB, [&](int, int i, u64 m) {
         out[i] = m ? q - m : 0;
         out[N + i] = 0;
     });
@@ -791,6 +754,7 @@ __device__ __forceinline__ void mask_partial(const PermJob &job, const RingTable
 // launch and without partial ciphertexts.
 // From wire to wire (with the layout's loads requested ahead of the draws): 16x128 on one input 27.5 -> 24.1 us; that
 // and he_fc 1000x512 on one input, where a mask is the longest workgroup, 40.9 -> 39.6 us.
+template <bool WIDE>
 __global__ __launch_bounds__(NT) void scmult_masked_ring(PermJob job, RingTables T, MaskJob mj, u64 *ct_out) {
     __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
     const int item = blockIdx.x;
@@ -801,11 +765,11 @@ __global__ __launch_bounds__(NT) void scmult_masked_ring(PermJob job, RingTables
     for (int k = 0; k < PER; ++k) {
         const int i = threadIdx.x + k * NT;
         const ulonglong2 ww = w[i];
-        x0[k] = csub_dev(mul_const(c0[i], ww.x, ww.y, T.nq), T.mod.q);
-        x1[k] = csub_dev(mul_const(c1[i], ww.x, ww.y, T.nq), T.mod.q);
+        x0[k] = unsign(mont<WIDE>(plain_words(c0[i]), ww, T.mont), T.mod.q);
+        x1[k] = unsign(mont<WIDE>(plain_words(c1[i]), ww, T.mont), T.mod.q);
     }
     u64 *out = ct_out + (size_t)item * 2 * N;
-    mask_role(T, mj, item, bufA, bufB, [&](int k, int i, u64 m) {
+    mask_role<WIDE>(T, mj, item, bufA, bufB, [&](int k, int i, u64 m) {
         out[i] = sub_mod(x0[k], m, T.mod.q);
         out[N + i] = x1[k];
     });
@@ -839,17 +803,16 @@ __device__ __forceinline__ void item_and_chunk(const PermJob &job, int &item, in
 // 12 bytes a lane), two at 4096 (one workgroup), the workgroup's own four at 8192.
 constexpr int PERM_WAVES = LOGN <= 11 ? 3 : LOGN == 12 ? 2 : 4;
 //
-// Every product on this path is a multiplication by a constant that carries its precomputed
-// quotient (twiddles, encoded weights, key polynomials), so sums of products stay in 64-bit
-// registers: each product is below 2q, a running sum is kept below 8q and may take four more
-// products before one conditional subtraction of 8q.
+// Every product on this path is a multiplication by a constant (twiddles, encoded weights, key polynomials), so sums of
+// products stay in 64-bit registers: each product is below 0.99, a running sum is shrunk to 5 at most (1.1 when m is close to 2^60) and may take four
+// more products before it is shrunk again.
 // IN8: the inputs lie in blocks of eight coefficients (PermJob::in8_S), as the matrix-core product leaves them.
 // FEW: the launch leaves a CU at most two workgroups, so what counts is one workgroup's chain of dependent steps, not the
 // chip's issue rate: it takes up to 256 registers and requests all key pairs of a digit before its transform's last
 // pass.  A convolution of 13x11x24 to 40 channels at batch 5 (175 workgroups) 86.7 -> 82.8 us, he_fc 1000x512 on one
 // input (257) 40.7 -> 40.2 us.  Sharing a rotation's two digits out to two workgroups as well lost: 45.8 us, the inverse
 // transforms and the partial ciphertexts double.
-template <bool HAS_W, bool IN8 = false, bool FEW = false>
+template <bool WIDE, bool HAS_W, bool IN8 = false, bool FEW = false>
 __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring(PermJob job, RingTables T, MaskJob mj,
                                                                                  int gadget_bits, int ndigits) {
     __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
@@ -866,19 +829,18 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
     constexpr int AHEAD = FEW ? PER : LOGN == 12 ? 3 : 0;
     const int tid = threadIdx.x;
     if ((int)blockIdx.x >= job.items * job.nchunks) {   // only launched when mj.enabled
-        mask_partial(job, T, mj, (int)blockIdx.x - job.items * job.nchunks, bufA, bufB);
+        mask_partial<WIDE>(job, T, mj, (int)blockIdx.x - job.items * job.nchunks, bufA, bufB);
         return;
     }
     int item, chunk;
     item_and_chunk(job, item, chunk);
     int g0, g1;
     chunk_range(chunk, job.nchunks, job.G, g0, g1);
-    const NegQ q = T.nq;
-    const u64 q8 = 8 * T.mod.q;
+    const MontQ q = T.mont;
     const u64 digit_mask = (1ull << gadget_bits) - 1;
     const size_t key_pairs = (size_t)ndigits * 2 * N;
 
-    u64 sum0[PER], sum1[PER];   // running sums over the rotations of this chunk, below 8q between products
+    u64 sum0[PER], sum1[PER];   // running sums over the rotations of this chunk, at most 5 between rotations
 #pragma unroll
     for (int k = 0; k < PER; ++k) sum0[k] = sum1[k] = 0;
 
@@ -900,11 +862,11 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
                 const int i = tid + k * NT;
                 if (HAS_W) {
                     const ulonglong2 ww = w[i];
-                    sum0[k] = csub_dev(mul_const<false, true>(c0[i], ww.x, ww.y, q, sum0[k]), q8);
-                    sum1[k] = csub_dev(mul_const<false, true>(c1[i], ww.x, ww.y, q, sum1[k]), q8);
+                    sum0[k] = shrink(mont<WIDE, true>(plain_words(c0[i]), ww, q, sum0[k]), q);
+                    sum1[k] = shrink(mont<WIDE, true>(plain_words(c1[i]), ww, q, sum1[k]), q);
                 } else {
-                    sum0[k] = csub_dev(sum0[k] + at(c0, i), q8);
-                    sum1[k] = csub_dev(sum1[k] + at(c1, i), q8);
+                    sum0[k] = shrink(sum0[k] + at(c0, i), q);
+                    sum1[k] = shrink(sum1[k] + at(c1, i), q);
                 }
             }
             continue;
@@ -928,15 +890,15 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
                 if (HAS_W) {     // the copy in ownership order: 64 lanes read 1 KiB of whole lines
                     const ulonglong2 wa = *reinterpret_cast<const ulonglong2 *>(wo + (wmid + (unsigned)((2 * k - 4) * 1024))),
                                      wb = *reinterpret_cast<const ulonglong2 *>(wo + (wmid + (unsigned)((2 * k - 3) * 1024)));
-                    a[2 * k] = mul_const(cv.x, wa.x, wa.y, q);
-                    a[2 * k + 1] = mul_const(cv.y, wb.x, wb.y, q);
+                    a[2 * k] = mont<WIDE>(plain_words(cv.x), wa, q);
+                    a[2 * k + 1] = mont<WIDE>(plain_words(cv.y), wb, q);
                 } else {
                     a[2 * k] = cv.x;
                     a[2 * k + 1] = cv.y;
                 }
             }
         }
-        inverse_in_regs(a, bufA, bufB, T, tid);
+        inverse_in_regs<WIDE>(a, bufA, bufB, T, tid);
 #pragma unroll
         for (int k = 0; k < PER; ++k) (PARK ? stash[tid + k * NT] : coef[PARK ? 0 : k]) = a[k];
 
@@ -950,26 +912,25 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
                 u64 d;
                 if (HAS_W) {
                     const ulonglong2 ww = w[src[k]];
-                    sum0[k] = mul_const<false, true>(c0[src[k]], ww.x, ww.y, q, sum0[k]);
-                    d = mul_const(c1[src[k]], ww.x, ww.y, q);
+                    sum0[k] = mont<WIDE, true>(plain_words(c0[src[k]]), ww, q, sum0[k]);
+                    d = mont<WIDE>(plain_words(c1[src[k]]), ww, q);
                 } else {
                     sum0[k] += at(c0, src[k]);
                     d = at(c1, src[k]);
                 }
                 const ulonglong2 b = kb[i], aa = ka[i];
-                sum0[k] = mul_const<false, true>(d, b.x, b.y, q, sum0[k]);
-                sum1[k] = mul_const<false, true>(d, aa.x, aa.y, q, sum1[k]);
+                const Words y = plain_words(d);
+                sum0[k] = mont<WIDE, true>(y, b, q, sum0[k]);
+                sum1[k] = mont<WIDE, true>(y, aa, q, sum1[k]);
             }
         }
-        int pending = 2;   // products added to sum0 since it was last brought below 8q
+        int pending = 2;   // products added to sum0 since it was last shrunk
         for (int j = 0; j < ndigits - 1; ++j) {
 #pragma unroll
             for (int k = 0; k < PER; ++k) a[k] = ((PARK ? stash[tid + k * NT] : coef[PARK ? 0 : k]) >> (j * gadget_bits)) & digit_mask;
-            // result in bufA, any 64-bit value below 16q.  The cheaper first stage for digits below 2^32 only where
-            // the registers allow it: in the variants without weights it pushes the count past three workgroups per CU
             const ulonglong2 *kb = key + (size_t)(2 * j) * N, *ka = kb + N;
             ulonglong2 kbv[AHEAD ? AHEAD : 1], kav[AHEAD ? AHEAD : 1];
-            forward_to_lds(a, bufA, bufB, T, tid, HAS_W && gadget_bits <= 32, [&] {
+            forward_to_lds<WIDE>(a, bufA, bufB, T, tid, gadget_bits <= 31, [&] {
 #pragma unroll
                 for (int k = 0; k < AHEAD; ++k) {
                     kbv[k] = kb[tid + k * NT];
@@ -979,33 +940,33 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
             if (pending == 4) {
 #pragma unroll
                 for (int k = 0; k < PER; ++k) {
-                    sum0[k] = csub_dev(sum0[k], q8);
-                    sum1[k] = csub_dev(sum1[k], q8);
+                    sum0[k] = shrink(sum0[k], q);
+                    sum1[k] = shrink(sum1[k], q);
                 }
                 pending = 0;
             }
 #pragma unroll
             for (int k = 0; k < PER; ++k) {
                 const int i = tid + k * NT;
-                const u64 d = bufA[pad(src[k])];
+                const Words d = biased_words(bufA[pad(src[k])]);
                 const ulonglong2 b = k < AHEAD ? kbv[k < AHEAD ? k : 0] : kb[i], aa = k < AHEAD ? kav[k < AHEAD ? k : 0] : ka[i];
-                sum0[k] = mul_const<false, true>(d, b.x, b.y, q, sum0[k]);       // the sum rides on the product
-                sum1[k] = mul_const<false, true>(d, aa.x, aa.y, q, sum1[k]);
+                sum0[k] = mont<WIDE, true>(d, b, q, sum0[k]);       // the sum rides on the product
+                sum1[k] = mont<WIDE, true>(d, aa, q, sum1[k]);
             }
             ++pending;
         }
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
-            sum0[k] = csub_dev(sum0[k], q8);
-            sum1[k] = csub_dev(sum1[k], q8);
+            sum0[k] = shrink(sum0[k], q);
+            sum1[k] = shrink(sum1[k], q);
         }
     }
     u64 *out = job.partial + ((size_t)item * job.slots + chunk) * 2 * N;
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         const int i = tid + k * NT;
-        out[i] = reduce64(sum0[k], T.mod);
-        out[N + i] = reduce64(sum1[k], T.mod);
+        out[i] = canonical<WIDE>(plain_words(sum0[k]), T);
+        out[N + i] = canonical<WIDE>(plain_words(sum1[k]), T);
     }
 }
 
@@ -1013,9 +974,10 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
 // then one HstPerm per tap), as two launches so that both fill the chip at small batches.
 //
 // DecPerm: one workgroup per (ciphertext, digit but the last); each repeats the inverse transform of c1 and runs the
-// forward transform of its digit.  digits[ct][j][i] holds lazy values (any 64-bit word below 16q), which is
-// what the constant multiplications of the inner product accept.  In the place of the last digit the inner products
+// forward transform of its digit.  digits[ct][j][i] holds the transform's biased values, which is
+// what the products of the inner product take.  In the place of the last digit the inner products
 // take c1 itself (folded keys).  stored: L-1 digits.
+template <bool WIDE>
 __global__ __launch_bounds__(NT) void decperm_ring(const u64 *ct_in, u64 *digits, RingTables T, int gadget_bits,
                                                    int stored) {
     __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
@@ -1030,11 +992,11 @@ __global__ __launch_bounds__(NT) void decperm_ring(const u64 *ct_in, u64 *digits
         a[2 * k] = cv.x;
         a[2 * k + 1] = cv.y;
     }
-    inverse_in_regs(a, bufA, bufB, T, tid);      // LDS phases A B A
+    inverse_in_regs<WIDE>(a, bufA, bufB, T, tid);      // LDS phases A B A
     const u64 digit_mask = (1ull << gadget_bits) - 1;
 #pragma unroll
     for (int k = 0; k < PER; ++k) a[k] = (a[k] >> (j * gadget_bits)) & digit_mask;
-    forward_to_lds(a, bufA, bufB, T, tid, gadget_bits <= 32);       // LDS phases B A B A, ends on a barrier
+    forward_to_lds<WIDE>(a, bufA, bufB, T, tid, gadget_bits <= 31);       // LDS phases B A B A, ends on a barrier
     u64 *out = digits + ((size_t)ct * stored + j) * N;
 #pragma unroll
     for (int k = 0; k < PER; ++k) out[tid + k * NT] = bufA[pad(tid + k * NT)];
@@ -1043,6 +1005,7 @@ __global__ __launch_bounds__(NT) void decperm_ring(const u64 *ct_in, u64 *digits
 // HstPerm: one workgroup per (ciphertext, tap).  c0 and the digits are read through the automorphism's index
 // map straight from memory: the map sends every aligned block of 64 indices onto another such block, so a
 // wavefront's gather still touches whole cache lines.  Output: xrot[ct][tap][c0|c1][i], canonical.
+template <bool WIDE>
 __global__ __launch_bounds__(NT) void hstperm_taps_ring(const u64 *ct_in, const u64 *digits, TermList terms,
                                                         const u64 *keys2, u64 *xrot, RingTables T, int ndigits) {
     const int tid = threadIdx.x;
@@ -1060,7 +1023,7 @@ __global__ __launch_bounds__(NT) void hstperm_taps_ring(const u64 *ct_in, const 
         }
         return;
     }
-    const NegQ q = T.nq;
+    const MontQ q = T.mont;
     const u64 *dsrc = digits + ct * (ndigits - 1) * N;
     const ulonglong2 *key = reinterpret_cast<const ulonglong2 *>(keys2) + (size_t)terms.key[e] * ndigits * 2 * N;
     // two batches of four coefficients keep the loads of a batch in flight together at a modest register count
@@ -1079,6 +1042,7 @@ __global__ __launch_bounds__(NT) void hstperm_taps_ring(const u64 *ct_in, const 
         for (int j = 0; j < ndigits; ++j) {
             const ulonglong2 *kb = key + (size_t)(2 * j) * N, *ka = kb + N;
             const u64 *dj = j == ndigits - 1 ? c1 : dsrc + (size_t)j * N;      // folded keys: c1 for the last digit
+            const u64 bias = j == ndigits - 1 ? BIAS : 0;
             ulonglong2 b[H], aa[H];
             u64 d[H];
 #pragma unroll
@@ -1089,14 +1053,15 @@ __global__ __launch_bounds__(NT) void hstperm_taps_ring(const u64 *ct_in, const 
             }
 #pragma unroll
             for (int k = 0; k < H; ++k) {
-                s0[k] += mul_const(d[k], b[k].x, b[k].y, q);    // each product is below 2q: at most 7q in all
-                s1[k] += mul_const(d[k], aa[k].x, aa[k].y, q);
+                const Words y = biased_words(d[k] + bias);
+                s0[k] += mont<WIDE>(y, b[k], q);    // each product is below 1: at most 4 in all
+                s1[k] += mont<WIDE>(y, aa[k], q);
             }
         }
 #pragma unroll
         for (int k = 0; k < H; ++k) {
-            out[idx[k]] = reduce_below<8>(s0[k], T.mod.q);
-            out[N + idx[k]] = reduce_below<8>(s1[k], T.mod.q);
+            out[idx[k]] = canonical<WIDE>(plain_words(s0[k]), T);
+            out[N + idx[k]] = canonical<WIDE>(plain_words(s1[k]), T);
         }
     }
 }
@@ -1110,7 +1075,7 @@ constexpr int PACK_THREADS = 256;      // whatever the ring: a workgroup is 64 c
 typedef digit_chunk_t v4i_t;
 // ND: the number of digits when it is 3 (unrolled), else 0 (run-time loop).  ANY_ROT false: no term rotates, there
 // are no keys and no digits to read.
-template <int ND, bool ANY_ROT>
+template <bool WIDE, int ND, bool ANY_ROT>
 __global__ __launch_bounds__(PACK_THREADS) void hstperm_pack_ring(const u64 *ct_in, const u64 *digits, TermList terms, int kblocks,
                                                         const u64 *keys2, v4i_t *xl, RingTables T, int ndigits_rt, int batch) {
     // a workgroup is 64 coefficients x 4 inputs: its wavefronts read the same key words, which then come out of
@@ -1120,7 +1085,7 @@ __global__ __launch_bounds__(PACK_THREADS) void hstperm_pack_ring(const u64 *ct_
     const bool b_live = (int)blockIdx.z * 4 + wave < batch;
     const int b = min((int)blockIdx.z * 4 + wave, batch - 1);
     const int nterm = terms.nterm, ndigits = ND ? ND : ndigits_rt;
-    const NegQ q = T.nq;
+    const MontQ q = T.mont;
     const size_t key_pairs = (size_t)ndigits * 2 * N;
     // Terms come in (tap, input ciphertext) order, so the sixteen terms of a thread share their rotation in runs: the
     // automorphism's source index and the key pairs of the tap are fetched when the rotation changes (a decision all
@@ -1166,21 +1131,20 @@ __global__ __launch_bounds__(PACK_THREADS) void hstperm_pack_ring(const u64 *ct_
             if (ND) {
 #pragma unroll
                 for (int j = 0; j < KD; ++j) {
-                    const u64 d = j == KD - 1 ? last : dsrc[(size_t)j * N + src];
-                    const U64Pair r = mul_const_pair(d, kwb[j], d, kwa[j], q);      // each product is below 2q: at most 7q in all
-                    s0 += r.a;
-                    s1 += r.b;
+                    const Words d = j == KD - 1 ? plain_words(last) : biased_words(dsrc[(size_t)j * N + src]);
+                    s0 = mont<WIDE, true>(d, kwb[j], q, s0);        // each product is below 1: at most 4 in all
+                    s1 = mont<WIDE, true>(d, kwa[j], q, s1);
                 }
             } else {
                 for (int j = 0; j < ndigits; ++j) {
-                    const u64 d = j == ndigits - 1 ? last : dsrc[(size_t)j * N + src];
+                    const Words d = biased_words(j == ndigits - 1 ? last + BIAS : dsrc[(size_t)j * N + src]);
                     const ulonglong2 wb = key[(size_t)(2 * j) * N + i], wa = key[(size_t)(2 * j + 1) * N + i];
-                    s0 = mul_const<false, true>(d, wb.x, wb.y, q, s0);
-                    s1 = mul_const<false, true>(d, wa.x, wa.y, q, s1);
+                    s0 = mont<WIDE, true>(d, wb, q, s0);
+                    s1 = mont<WIDE, true>(d, wa, q, s1);
                 }
             }
-            v0 = reduce_below<8>(s0, T.mod.q);
-            v1 = reduce_below<8>(s1, T.mod.q);
+            v0 = canonical<WIDE>(plain_words(s0), T);
+            v1 = canonical<WIDE>(plain_words(s1), T);
         }
         if (!live) v0 = v1 = 0;
         const u64 k80 = 0x8080808080808080ull;   // bytes of x + 0x80..80 are the balanced digits plus 128
@@ -1218,7 +1182,7 @@ __global__ __launch_bounds__(PACK_THREADS) void hstperm_pack_ring(const u64 *ct_
 // exporting 1024 ciphertexts 83.7 -> 68.2 us, a 16x128 FC layer with one ciphertext imported and one exported
 // 41.7 -> 28.8 us.
 // Inputs as the any-n kernel takes them: below 4q forward, below 2q inverse.
-template <bool INVERSE>
+template <bool WIDE, bool INVERSE>
 __global__ __launch_bounds__(NT) void ntt_ring(const u64 *src, u64 *dst, RingTables T) {
     __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
     const int tid = threadIdx.x;
@@ -1228,26 +1192,27 @@ __global__ __launch_bounds__(NT) void ntt_ring(const u64 *src, u64 *dst, RingTab
     if (INVERSE) {
         // coalesced reads, then through LDS to the eight consecutive coefficients a thread starts from
 #pragma unroll
-        for (int k = 0; k < PER; ++k) bufB[pad(tid + k * NT)] = src[tid + k * NT];
+        for (int k = 0; k < PER; ++k) bufB[pad(tid + k * NT)] = csub_dev(src[tid + k * NT], T.mod.q);
         __syncthreads();
         const u64 *pi = bufB + pad(tid << 3);
 #pragma unroll
         for (int k = 0; k < PER; ++k) a[k] = pi[k];
-        inverse_in_regs(a, bufA, bufB, T, tid);       // LDS phases A B A; the reads of bufB above precede its barriers
+        inverse_in_regs<WIDE>(a, bufA, bufB, T, tid);       // LDS phases A B A; the reads of bufB above precede its barriers
 #pragma unroll
         for (int k = 0; k < PER; ++k) dst[tid + k * NT] = a[k];
     } else {
 #pragma unroll
-        for (int k = 0; k < PER; ++k) a[k] = csub_dev(src[tid + k * NT], T.mod.q2);
-        forward_to_lds(a, bufA, bufB, T, tid);
+        for (int k = 0; k < PER; ++k) a[k] = shrink(src[tid + k * NT], T.mont);
+        forward_to_lds<WIDE>(a, bufA, bufB, T, tid);
 #pragma unroll
-        for (int k = 0; k < PER; ++k) dst[tid + k * NT] = reduce64(bufA[pad(tid + k * NT)], T.mod);
+        for (int k = 0; k < PER; ++k) dst[tid + k * NT] = canonical<WIDE>(biased_words(bufA[pad(tid + k * NT)]), T);
     }
 }
 
 // ---- the client's two steps with the radix-8 transforms (one workgroup per ciphertext) ------------------------
 // ct = (-a s + e + delta m, a) (Sec. II-C(1)), bit for bit the any-n kernel: m = the plaintext polynomial of the
 // slots, a uniform, e Gaussian, all drawn from the ciphertext's seed by coefficient index.
+template <bool WIDE>
 __global__ __launch_bounds__(NT, 4) void encrypt_ring(const u64 *slots, const u64 *seeds, const u64 *s_hat, u64 *ct_out,
                                                    RingTables T, RingTables Tp, SmallTables small, const int *slot_to_idx, GaussCdf cdf,
                                                    int qbits, ulonglong2 delta) {
@@ -1262,29 +1227,29 @@ __global__ __launch_bounds__(NT, 4) void encrypt_ring(const u64 *slots, const u6
     }
     __syncthreads();
     u64 a[PER];
-    slots_to_coefficients(a, bufA, bufB, Tp, small, tid);      // m, coefficient tid + (n/8) k, canonical mod p
+    slots_to_coefficients<WIDE>(a, bufA, bufB, Tp, small, tid);      // m, coefficient tid + (n/8) k, canonical mod p
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         const int e = draw_gauss_cdf(cdf, seed, kStreamCtE, (u64)(tid + k * NT));
-        const u64 el = e >= 0 ? (u64)e : q - (u64)(-e);
-        a[k] = csub_dev(el + csub_dev(mul_const(a[k], delta.x, delta.y, T.nq), q), q);
+        a[k] = mont<WIDE, true, true>(plain_words(a[k]), delta, T.mont, BIAS + (u64)(i64)e);
     }
-    forward_to_lds(a, bufA, bufB, T, tid);            // (e + delta m) in the evaluation domain, in bufA
+    forward_to_lds<WIDE, BIASED>(a, bufA, bufB, T, tid);            // (e + delta m) in the evaluation domain, in bufA
     u64 t0[PER];
 #pragma unroll
-    for (int k = 0; k < PER; ++k) t0[k] = reduce64(bufA[pad(tid + k * NT)], T.mod);
+    for (int k = 0; k < PER; ++k) t0[k] = canonical<WIDE>(biased_words(bufA[pad(tid + k * NT)]), T);
 #pragma unroll
     for (int k = 0; k < PER; ++k) a[k] = draw_uniform(q, qbits, seed, kStreamCtA, (u64)(tid + k * NT));
-    forward_to_lds(a, bufA, bufB, T, tid);            // its first barrier comes after every read of bufA above
+    forward_to_lds<WIDE>(a, bufA, bufB, T, tid);            // its first barrier comes after every read of bufA above
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         const int i = tid + k * NT;
-        const u64 ah = reduce64(bufA[pad(i)], T.mod);
+        const u64 ah = canonical<WIDE>(biased_words(bufA[pad(i)]), T);
         c1[i] = ah;
         c0[i] = sub_mod(t0[k], mul_mod(ah, s_hat[i], T.mod), q);
     }
 }
 // slots = decode(round(p (c0 + c1 s) / q) mod p); the rounded quotient through the exact division by q (q^-1 mod 2^64).
+template <bool WIDE>
 __global__ __launch_bounds__(NT) void decrypt_ring(const u64 *ct_in, const u64 *s_hat, u64 *slots, RingTables T,
                                                    RingTables Tp, SmallTables small, const int *slot_to_idx, u64 q_inv64) {
     __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
@@ -1297,7 +1262,7 @@ __global__ __launch_bounds__(NT) void decrypt_ring(const u64 *ct_in, const u64 *
         const int i = 8 * tid + k;
         a[k] = add_mod(c0[i], mul_mod(c1[i], s_hat[i], T.mod), q);
     }
-    inverse_in_regs(a, bufA, bufB, T, tid);           // c0 + c1 s, coefficient tid + (n/8) k, canonical
+    inverse_in_regs<WIDE>(a, bufA, bufB, T, tid);           // c0 + c1 s, coefficient tid + (n/8) k, canonical
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         const u128 t = (u128)p * a[k] + (q >> 1);
@@ -1314,8 +1279,8 @@ __global__ __launch_bounds__(NT) void decrypt_ring(const u64 *ct_in, const u64 *
         forward_small_to_lds(v, A, reinterpret_cast<u32 *>(bufB), small, tid);
         for (int s = tid; s < N; s += NT) out[s] = reduce_small(A[pad(slot_to_idx[s])], small);
     } else {
-        forward_to_lds(a, bufA, bufB, Tp, tid);
-        for (int s = tid; s < N; s += NT) out[s] = reduce64(bufA[pad(slot_to_idx[s])], Tp.mod);
+        forward_to_lds<WIDE>(a, bufA, bufB, Tp, tid);
+        for (int s = tid; s < N; s += NT) out[s] = canonical<WIDE>(biased_words(bufA[pad(slot_to_idx[s])]), Tp);
     }
 }
 
@@ -1329,11 +1294,11 @@ __global__ __launch_bounds__(NT) void decrypt_ring(const u64 *ct_in, const u64 *
 // enter the sums multiplied by P.  Needs P < 2^60 and P < 2q.
 struct SpecialJob {
     RingTables TP;          // transform tables of P
-    ulonglong2 Pq, Pinv;    // P mod q and P^-1 mod q with companions
+    ulonglong2 Pq, minus_Pinv;    // P and -P^-1 mod q, MontPairs
 };
 
 // IN8: the inputs lie in blocks of eight coefficients (PermJob::in8_S), as the matrix-core product leaves them.
-template <bool HAS_W, bool IN8 = false>
+template <bool WIDE, bool HAS_W, bool IN8 = false>
 __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob job, RingTables T, SpecialJob S, MaskJob mj,
                                                                       int gadget_bits, int ndigits) {
     __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
@@ -1343,22 +1308,21 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
     __shared__ u64 Rl[15 * NT];
     const int tid = threadIdx.x;
     if ((int)blockIdx.x >= job.items * job.nchunks) {   // only launched when mj.enabled
-        mask_partial(job, T, mj, (int)blockIdx.x - job.items * job.nchunks, bufA, bufB);
+        mask_partial<WIDE>(job, T, mj, (int)blockIdx.x - job.items * job.nchunks, bufA, bufB);
         return;
     }
     int item, chunk;
     item_and_chunk(job, item, chunk);
     int g0, g1;
     chunk_range(chunk, job.nchunks, job.G, g0, g1);
-    const NegQ q = T.nq, qP = S.TP.nq;
-    const u64 q8 = 8 * T.mod.q, P8 = 8 * S.TP.mod.q;
+    const MontQ q = T.mont, qP = S.TP.mont;
     const u64 digit_mask = (1ull << gadget_bits) - 1;
     // key pairs of a digit and modulus requested before the transform's last pass: three of eight, what 256 registers hold
     // (the 16x16x128 convolution at batch 16 485.6 -> 479.7 us, he_fc 100x784 at batch 7 74.7 -> 74.2 us)
     constexpr int AHEAD = 3;
     const size_t key_pairs = (size_t)ndigits * 4 * N;
 
-    u64 sum0[PER], sum1[PER];   // evaluation domain modulo q, below 8q between products
+    u64 sum0[PER], sum1[PER];   // evaluation domain modulo q, at most 5 between rotations
     u64 Rlast = 0;              // the sixteenth word of the remainder sums
 #pragma unroll
     for (int k = 0; k < PER; ++k) sum0[k] = sum1[k] = 0;
@@ -1381,11 +1345,11 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
                 u64 x0 = at(c0, i), x1 = at(c1, i);
                 if (HAS_W) {
                     const ulonglong2 ww = w[i];
-                    x0 = mul_const<true>(x0, ww.x, ww.y, q);
-                    x1 = mul_const<true>(x1, ww.x, ww.y, q);
+                    x0 = mont<WIDE>(plain_words(x0), ww, q);
+                    x1 = mont<WIDE>(plain_words(x1), ww, q);
                 }
-                sum0[k] = csub_dev(sum0[k] + mul_const<true>(x0, S.Pq.x, S.Pq.y, q), q8);
-                sum1[k] = csub_dev(sum1[k] + mul_const<true>(x1, S.Pq.x, S.Pq.y, q), q8);
+                sum0[k] = shrink(mont<WIDE, true, true>(plain_words(x0), S.Pq, q, sum0[k]), q);
+                sum1[k] = shrink(mont<WIDE, true, true>(plain_words(x1), S.Pq, q, sum1[k]), q);
             }
             continue;
         }
@@ -1402,15 +1366,15 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
                 const ulonglong2 cv = c1v[k];
                 if (HAS_W) {
                     const ulonglong2 wa = w[8 * tid + 2 * k], wb = w[8 * tid + 2 * k + 1];
-                    a[2 * k] = mul_const<true>(cv.x, wa.x, wa.y, q);
-                    a[2 * k + 1] = mul_const<true>(cv.y, wb.x, wb.y, q);
+                    a[2 * k] = mont<WIDE>(plain_words(cv.x), wa, q);
+                    a[2 * k + 1] = mont<WIDE>(plain_words(cv.y), wb, q);
                 } else {
                     a[2 * k] = cv.x;
                     a[2 * k + 1] = cv.y;
                 }
             }
         }
-        inverse_in_regs<true>(a, bufA, bufB, T, tid);
+        inverse_in_regs<WIDE>(a, bufA, bufB, T, tid);
 #pragma unroll
         for (int k = 0; k < PER; ++k) stash[tid + k * NT] = a[k];
         // the c0 part, times P, and the last digit's products modulo q (folded keys: the rotated c1 (.) w itself)
@@ -1422,16 +1386,18 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
                 u64 x = at(c0, src[k]), d = at(c1, src[k]);
                 if (HAS_W) {
                     const ulonglong2 ww = w[src[k]];
-                    x = mul_const<true>(x, ww.x, ww.y, q);
-                    d = mul_const<true>(d, ww.x, ww.y, q);
+                    x = mont<WIDE>(plain_words(x), ww, q);
+                    d = mont<WIDE>(plain_words(d), ww, q);
                 }
                 const ulonglong2 b = kb[i], aa = ka[i];
-                sum0[k] += mul_const<true>(x, S.Pq.x, S.Pq.y, q) + mul_const<true>(d, b.x, b.y, q);
-                sum1[k] += mul_const<true>(d, aa.x, aa.y, q);
+                const Words y = plain_words(d);
+                sum0[k] = mont<WIDE, true, true>(plain_words(x), S.Pq, q, sum0[k]);
+                sum0[k] = mont<WIDE, true>(y, b, q, sum0[k]);
+                sum1[k] = mont<WIDE, true>(y, aa, q, sum1[k]);
             }
         }
         int pending = 2, pendingP = 0;
-        u64 tp0[PER], tp1[PER];   // this rotation's sums modulo P, below 8P between products
+        u64 tp0[PER], tp1[PER];   // this rotation's sums modulo P
 #pragma unroll
         for (int k = 0; k < PER; ++k) tp0[k] = tp1[k] = 0;
         for (int j = 0; j < ndigits; ++j) {
@@ -1447,22 +1413,22 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
                         kav[k] = ka[tid + k * NT];
                     }
                 };
-                forward_to_lds<true>(a, bufA, bufB, T, tid, false, ahead);
+                forward_to_lds<WIDE>(a, bufA, bufB, T, tid, gadget_bits <= 31, ahead);
                 if (pending == 4) {
 #pragma unroll
                     for (int k = 0; k < PER; ++k) {
-                        sum0[k] = csub_dev(sum0[k], q8);
-                        sum1[k] = csub_dev(sum1[k], q8);
+                        sum0[k] = shrink(sum0[k], q);
+                        sum1[k] = shrink(sum1[k], q);
                     }
                     pending = 0;
                 }
 #pragma unroll
                 for (int k = 0; k < PER; ++k) {
                     const int i = tid + k * NT;
-                    const u64 d = bufA[pad(src[k])];
+                    const Words d = biased_words(bufA[pad(src[k])]);
                     const ulonglong2 b = k < AHEAD ? kbv[k < AHEAD ? k : 0] : kb[i], aa = k < AHEAD ? kav[k < AHEAD ? k : 0] : ka[i];
-                    sum0[k] += mul_const<true>(d, b.x, b.y, q);
-                    sum1[k] += mul_const<true>(d, aa.x, aa.y, q);
+                    sum0[k] = mont<WIDE, true>(d, b, q, sum0[k]);
+                    sum1[k] = mont<WIDE, true>(d, aa, q, sum1[k]);
                 }
                 ++pending;
             }
@@ -1478,43 +1444,43 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
                     kav[k] = kaP[tid + k * NT];
                 }
             };
-            forward_to_lds<true>(a, bufA, bufB, S.TP, tid, false, ahead);
+            forward_to_lds<WIDE>(a, bufA, bufB, S.TP, tid, gadget_bits <= 31, ahead);
             if (pendingP == 4) {
 #pragma unroll
                 for (int k = 0; k < PER; ++k) {
-                    tp0[k] = csub_dev(tp0[k], P8);
-                    tp1[k] = csub_dev(tp1[k], P8);
+                    tp0[k] = shrink(tp0[k], qP);
+                    tp1[k] = shrink(tp1[k], qP);
                 }
                 pendingP = 0;
             }
 #pragma unroll
             for (int k = 0; k < PER; ++k) {
                 const int i = tid + k * NT;
-                const u64 d = bufA[pad(src[k])];
+                const Words d = biased_words(bufA[pad(src[k])]);
                 const ulonglong2 b = k < AHEAD ? kbv[k < AHEAD ? k : 0] : kbP[i], aa = k < AHEAD ? kav[k < AHEAD ? k : 0] : kaP[i];
-                tp0[k] += mul_const<true>(d, b.x, b.y, qP);
-                tp1[k] += mul_const<true>(d, aa.x, aa.y, qP);
+                tp0[k] = mont<WIDE, true>(d, b, qP, tp0[k]);
+                tp1[k] = mont<WIDE, true>(d, aa, qP, tp1[k]);
             }
             ++pendingP;
         }
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
-            sum0[k] = csub_dev(sum0[k], q8);
-            sum1[k] = csub_dev(sum1[k], q8);
+            sum0[k] = shrink(sum0[k], q);
+            sum1[k] = shrink(sum1[k], q);
         }
-        // remainders modulo P: canonical, to the ownership the inverse transform starts from (through bufB, which
+        // remainders modulo P: below P, to the ownership the inverse transform starts from (through bufB, which
         // nobody reads any more), back to coefficients in [0,P), reduced modulo q and added up
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
 #pragma unroll
-            for (int k = 0; k < PER; ++k) bufB[pad(tid + k * NT)] = reduce64(h ? tp1[k] : tp0[k], S.TP.mod);
+            for (int k = 0; k < PER; ++k) bufB[pad(tid + k * NT)] = mont<WIDE, false, true>(plain_words(h ? tp1[k] : tp0[k]), S.TP.one, qP);
             __syncthreads();
             {
                 const u64 *pi = bufB + pad(tid << 3);
 #pragma unroll
                 for (int k = 0; k < PER; ++k) a[k] = pi[k];
             }
-            inverse_in_regs<true>(a, bufA, bufB, S.TP, tid);
+            inverse_in_regs<WIDE>(a, bufA, bufB, S.TP, tid);
 #pragma unroll
             for (int k = 0; k < PER; ++k) {
                 const u64 r = csub_dev(a[k], T.mod.q);
@@ -1534,21 +1500,20 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
         u64 a[PER];
 #pragma unroll
         for (int k = 0; k < PER; ++k) a[k] = (h && k == PER - 1) ? Rlast : Rl[(h * PER + k) * NT + tid];
-        forward_to_lds<true>(a, bufA, bufB, T, tid);
+        forward_to_lds<WIDE>(a, bufA, bufB, T, tid);
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
             const int i = tid + k * NT;
-            const u64 x = reduce64(bufA[pad(i)], T.mod);
-            const u64 t = reduce64(h ? sum1[k] : sum0[k], T.mod);
-            const u64 dlt = t >= x ? t - x : t + T.mod.q - x;
-            out[h * N + i] = csub_dev(mul_const<true>(dlt, S.Pinv.x, S.Pinv.y, q), T.mod.q);
+            const u64 minus = shrink(bufA[pad(i)], q) - (h ? sum1[k] : sum0[k]);
+            out[h * N + i] = unsign(mont<WIDE, false, true>(biased_words(minus), S.minus_Pinv, q), T.mod.q);
         }
     }
 }
 
 // ---- hoisted input rotations with a special prime ----------------------------------------------------------
-// DecPerm: one workgroup per (ciphertext, digit, modulus); digits[ct][j][modulus][i], lazy values of that modulus.
+// DecPerm: one workgroup per (ciphertext, digit, modulus); digits[ct][j][modulus][i], biased values of that modulus.
 // The last digit modulo q is not needed (folded keys), its place stays empty.
+template <bool WIDE>
 __global__ __launch_bounds__(NT) void decperm_special_ring(const u64 *ct_in, u64 *digits, RingTables T, RingTables TP,
                                                            int gadget_bits, int ndigits) {
     __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
@@ -1564,12 +1529,12 @@ __global__ __launch_bounds__(NT) void decperm_special_ring(const u64 *ct_in, u64
         a[2 * k] = cv.x;
         a[2 * k + 1] = cv.y;
     }
-    inverse_in_regs(a, bufA, bufB, T, tid);
+    inverse_in_regs<WIDE>(a, bufA, bufB, T, tid);
     const u64 digit_mask = (1ull << gadget_bits) - 1;
 #pragma unroll
     for (int k = 0; k < PER; ++k) a[k] = (a[k] >> (j * gadget_bits)) & digit_mask;
-    if (m) forward_to_lds(a, bufA, bufB, TP, tid);
-    else forward_to_lds(a, bufA, bufB, T, tid);
+    if (m) forward_to_lds<WIDE>(a, bufA, bufB, TP, tid, gadget_bits <= 31);
+    else forward_to_lds<WIDE>(a, bufA, bufB, T, tid, gadget_bits <= 31);
     u64 *out = digits + (((size_t)ct * ndigits + j) * 2 + m) * N;
 #pragma unroll
     for (int k = 0; k < PER; ++k) out[tid + k * NT] = bufA[pad(tid + k * NT)];
@@ -1578,6 +1543,7 @@ __global__ __launch_bounds__(NT) void decperm_special_ring(const u64 *ct_in, u64
 // HstPerm: one workgroup per (ciphertext, tap): inner products in both moduli from the stored digits, the sums
 // modulo P back to coefficients, lifted, reduced modulo q and transformed forward again, then
 // out = (P c0(X^g) + t_b - NTT(r_b)) / P, (t_a - NTT(r_a)) / P.  Output: xrot[ct][tap][c0|c1][i], canonical.
+template <bool WIDE>
 __global__ __launch_bounds__(NT, 3) void hstperm_special_ring(const u64 *ct_in, const u64 *digits, TermList terms,
                                                            const u64 *keys2, u64 *xrot, RingTables T, SpecialJob S,
                                                            int ndigits) {
@@ -1597,7 +1563,7 @@ __global__ __launch_bounds__(NT, 3) void hstperm_special_ring(const u64 *ct_in, 
         }
         return;
     }
-    const NegQ q = T.nq, qP = S.TP.nq;
+    const MontQ q = T.mont, qP = S.TP.mont;
     const u64 *dsrc = digits + ct * ndigits * 2 * N;
     const ulonglong2 *key = reinterpret_cast<const ulonglong2 *>(keys2) + (size_t)terms.key[e] * ndigits * 4 * N;
     int src[PER];
@@ -1608,22 +1574,23 @@ __global__ __launch_bounds__(NT, 3) void hstperm_special_ring(const u64 *ct_in, 
     // operands are in flight - the kernel fits three workgroups per CU instead of one.
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        u64 sum[PER], tp[PER];      // modulo q and modulo P, below 8 moduli (at most three digits)
+        u64 sum[PER], tp[PER];      // modulo q and modulo P, at most 4 (at most three digits)
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
-            sum[k] = h ? 0 : mul_const(c0[src[k]], S.Pq.x, S.Pq.y, q);
+            sum[k] = h ? 0 : mont<WIDE, false, true>(plain_words(c0[src[k]]), S.Pq, q);
             tp[k] = 0;
         }
         for (int j = 0; j < ndigits; ++j) {
             const ulonglong2 *kq = key + (size_t)(4 * j + h) * N, *kP = key + (size_t)(4 * j + 2 + h) * N;
             const u64 *djq = j == ndigits - 1 ? c1 : dsrc + (size_t)(2 * j) * N;       // folded keys modulo q
+            const u64 bias = j == ndigits - 1 ? BIAS : 0;
 #pragma unroll
             for (int k = 0; k < PER; ++k) {
                 const int i = tid + k * NT;
                 const u64 dq = djq[src[k]], dP = dsrc[(size_t)(2 * j + 1) * N + src[k]];
                 const ulonglong2 wq = kq[i], wP = kP[i];
-                sum[k] += mul_const(dq, wq.x, wq.y, q);
-                tp[k] += mul_const(dP, wP.x, wP.y, qP);
+                sum[k] = mont<WIDE, true>(biased_words(dq + bias), wq, q, sum[k]);
+                tp[k] = mont<WIDE, true>(biased_words(dP), wP, qP, tp[k]);
                 if (k == 3) __builtin_amdgcn_sched_barrier(0);
             }
             __builtin_amdgcn_sched_barrier(0);
@@ -1631,24 +1598,22 @@ __global__ __launch_bounds__(NT, 3) void hstperm_special_ring(const u64 *ct_in, 
         u64 a[PER];
         // LDS phases: B (ownership change), A B A (inverse), B A B A (forward), then reads of A
 #pragma unroll
-        for (int k = 0; k < PER; ++k) bufB[pad(tid + k * NT)] = reduce_below<8>(tp[k], S.TP.mod.q);
+        for (int k = 0; k < PER; ++k) bufB[pad(tid + k * NT)] = mont<WIDE, false, true>(plain_words(tp[k]), S.TP.one, qP);
         __syncthreads();
         {
             const u64 *pi = bufB + pad(tid << 3);
 #pragma unroll
             for (int k = 0; k < PER; ++k) a[k] = pi[k];
         }
-        inverse_in_regs(a, bufA, bufB, S.TP, tid);
+        inverse_in_regs<WIDE>(a, bufA, bufB, S.TP, tid);
 #pragma unroll
         for (int k = 0; k < PER; ++k) a[k] = csub_dev(a[k], T.mod.q);
-        forward_to_lds(a, bufA, bufB, T, tid);
+        forward_to_lds<WIDE>(a, bufA, bufB, T, tid);
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
             const int i = tid + k * NT;
-            const u64 x = reduce_below<16>(bufA[pad(i)], T.mod.q);
-            const u64 t = reduce_below<8>(sum[k], T.mod.q);
-            const u64 dlt = t >= x ? t - x : t + T.mod.q - x;
-            out[h * N + i] = csub_dev(mul_const(dlt, S.Pinv.x, S.Pinv.y, q), T.mod.q);
+            const u64 minus = shrink(bufA[pad(i)], q) - sum[k];
+            out[h * N + i] = unsign(mont<WIDE, false, true>(biased_words(minus), S.minus_Pinv, q), T.mod.q);
         }
     }
 }
@@ -1690,17 +1655,45 @@ __global__ void sum_few_partials_kernel(const u64 *partial, int slots, int used,
 
 }  // namespace
 
-static RingTables make_tables(const u64 *pairs, const NttHost &h) {
+static ulonglong2 as_words(const MontPair &w) { return make_ulonglong2(w.a, w.b); }
+static RingTables make_tables(const MontPair *pairs, const NttHost &h) {
     RingTables T;
     T.tw = reinterpret_cast<const ulonglong2 *>(pairs);
     T.itw = T.tw + FWD_PAIRS;
-    for (int e = 0; e < 3; ++e) T.w8[e] = make_ulonglong2(h.w8[e], h.w8s[e]);
+    for (int e = 0; e < 3; ++e) T.w8[e] = as_words(h.w8m[e]);
+    T.one = as_words(h.one_m);
     T.mod = h.mod;
-    const u64 neg = 0 - h.mod.q;
-    T.nq.lo = (u32)neg;
-    T.nq.hi = (u32)(neg >> 32);
+    u32 inv = (u32)h.mod.q;                           // Newton's iteration for m^-1 mod 2^32 (m is odd)
+    for (int i = 0; i < 5; ++i) inv *= 2 - (u32)h.mod.q * inv;
+    T.mont.inv = inv;
+    T.mont.lo = (int)(u32)h.mod.q;
+    T.mont.nlo = -T.mont.lo;
+    T.mont.nhi = -(int)((h.mod.q + BIAS) >> 32);
     return T;
 }
+// Runs go(std::integral_constant<bool, WIDE>).  WIDE = false needs |y| <= 7 2^60, which the bounds of the passes keep up to n = 2048 for
+// moduli close to 2^60, and low words up to 2^28 (with a special prime both moduli).  Primes searched from 2^60 down are
+// close to it; the low word is a matter of luck unless 2n is all that the prime has to fit.
+template <class Go>
+static auto by_width(const gala_ctx *c, Go go) {
+#if GALA_LOGN < 12
+    auto narrow = [](u64 m) {
+        const int lo = (int)(u32)m;
+        return m >= (1ull << 60) - (1ull << 56) && lo <= 1 << 28 && lo >= -(1 << 28);
+    };
+    if (narrow(c->q) && (!c->special || narrow(c->special))) return go(std::false_type{});
+#endif
+    return go(std::true_type{});
+}
+#if GALA_LOGN < 13
+static SpecialJob make_special(const gala_ctx *c) {
+    SpecialJob S;
+    S.TP = make_tables(c->d_tw2P, c->ntt_P);
+    S.Pq = as_words(c->Pq_m);
+    S.minus_Pinv = as_words(c->minus_Pinv_m);
+    return S;
+}
+#endif
 
 static SmallTables make_small(const gala_ctx *c) {
     SmallTables S{};
@@ -1717,40 +1710,38 @@ static int launch_perm(const gala_ctx *c, void *stream, const PermJob &job, cons
     hipStream_t st = (hipStream_t)stream;
     const RingTables T = make_tables(c->d_tw2, c->ntt_q);
     const dim3 grid((unsigned)(job.items * job.nchunks + (mj.enabled ? job.items : 0)));
-#if GALA_LOGN < 13
-    if (c->special) {
-        if (job.in8_S && job.w) return (int)hipErrorInvalidValue;
-        SpecialJob S;
-        S.TP = make_tables(c->d_tw2P, c->ntt_P);
-        S.Pq = make_ulonglong2(c->Pq, c->Pq_s);
-        S.Pinv = make_ulonglong2(c->Pinv, c->Pinv_s);
-        if (job.w)
-            hipLaunchKernelGGL(perm_accumulate_special_ring<true>, grid, dim3(NT), 0, st, job, T, S, mj, c->gadget_bits, c->ndigits);
-        else if (job.in8_S)
-            hipLaunchKernelGGL((perm_accumulate_special_ring<false, true>), grid, dim3(NT), 0, st, job, T, S, mj, c->gadget_bits,
-                               c->ndigits);
-        else
-            hipLaunchKernelGGL(perm_accumulate_special_ring<false>, grid, dim3(NT), 0, st, job, T, S, mj, c->gadget_bits, c->ndigits);
-        return (int)hipGetLastError();
-    }
-#endif
     if (job.in8_S && job.w) return (int)hipErrorInvalidValue;
-    auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, grid, dim3(NT), 0, st, job, T, mj, c->gadget_bits, c->ndigits);
-    };
+    return by_width(c, [&](auto width) {
+        constexpr bool WIDE = decltype(width)::value;
 #if GALA_LOGN < 13
-    // at most two wavefronts per SIMD in all: two workgroups per CU at n = 2048
-    if ((size_t)grid.x * NT <= (size_t)256 * 4 * 2 * 64) {
-        if (job.w) go(perm_accumulate_ring<true, false, true>);
-        else if (job.in8_S) go(perm_accumulate_ring<false, true, true>);
-        else go(perm_accumulate_ring<false, false, true>);
-        return (int)hipGetLastError();
-    }
+        if (c->special) {
+            const SpecialJob S = make_special(c);
+            auto go = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, grid, dim3(NT), 0, st, job, T, S, mj, c->gadget_bits, c->ndigits);
+            };
+            if (job.w) go(perm_accumulate_special_ring<WIDE, true>);
+            else if (job.in8_S) go(perm_accumulate_special_ring<WIDE, false, true>);
+            else go(perm_accumulate_special_ring<WIDE, false>);
+            return (int)hipGetLastError();
+        }
 #endif
-    if (job.w) go(perm_accumulate_ring<true>);
-    else if (job.in8_S) go(perm_accumulate_ring<false, true>);
-    else go(perm_accumulate_ring<false>);
-    return (int)hipGetLastError();
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, grid, dim3(NT), 0, st, job, T, mj, c->gadget_bits, c->ndigits);
+        };
+#if GALA_LOGN < 13
+        // at most two wavefronts per SIMD in all: two workgroups per CU at n = 2048
+        if ((size_t)grid.x * NT <= (size_t)256 * 4 * 2 * 64) {
+            if (job.w) go(perm_accumulate_ring<WIDE, true, false, true>);
+            else if (job.in8_S) go(perm_accumulate_ring<WIDE, false, true, true>);
+            else go(perm_accumulate_ring<WIDE, false, false, true>);
+            return (int)hipGetLastError();
+        }
+#endif
+        if (job.w) go(perm_accumulate_ring<WIDE, true>);
+        else if (job.in8_S) go(perm_accumulate_ring<WIDE, false, true>);
+        else go(perm_accumulate_ring<WIDE, false>);
+        return (int)hipGetLastError();
+    });
 }
 
 static int perm(const gala_ctx *c, void *stream, const PermJob &job) {
@@ -1769,7 +1760,7 @@ static int perm_masked(const gala_ctx *c, void *stream, const PermJob &job, cons
     mj.layout = fin.mask;
     mj.slot_to_idx = c->d_slot_to_idx;
     mj.pbits = c->pbits;
-    mj.delta = make_ulonglong2(c->delta, c->delta_s);
+    mj.delta = as_words(c->delta_m);
     mj.Tp = make_tables(c->d_tw2p, c->ntt_p);
     mj.small = make_small(c);
     hipStream_t st = (hipStream_t)stream;
@@ -1784,9 +1775,11 @@ static int perm_masked(const gala_ctx *c, void *stream, const PermJob &job, cons
     const bool r_apart = fin.ct_out + span <= fin.r || r_end <= fin.ct_out;
     const bool alone = job.product_only && apart && r_apart;
     if (alone) {
-        hipLaunchKernelGGL(scmult_masked_ring, dim3((unsigned)job.items), dim3(NT), 0, st, job, make_tables(c->d_tw2, c->ntt_q), mj,
-                           fin.ct_out);
-        rc = (int)hipGetLastError();
+        rc = by_width(c, [&](auto width) {
+            hipLaunchKernelGGL(scmult_masked_ring<decltype(width)::value>, dim3((unsigned)job.items), dim3(NT), 0, st, job,
+                               make_tables(c->d_tw2, c->ntt_q), mj, fin.ct_out);
+            return (int)hipGetLastError();
+        });
     } else {
         rc = launch_perm(c, stream, job, mj);
     }
@@ -1813,30 +1806,31 @@ static int hoist_taps(const gala_ctx *c, void *stream, const u64 *ct_in, int bat
     const RingTables T = make_tables(c->d_tw2, c->ntt_q);
     hipStream_t st = (hipStream_t)stream;
     const dim3 per_term((unsigned)((size_t)batch * terms.nterm));
+    return by_width(c, [&](auto width) {
+        constexpr bool WIDE = decltype(width)::value;
 #if GALA_LOGN < 13
-    if (c->special) {     // digits[ct][j][modulus][N]: twice the digit storage of the one-prime form
-        SpecialJob S;
-        S.TP = make_tables(c->d_tw2P, c->ntt_P);
-        S.Pq = make_ulonglong2(c->Pq, c->Pq_s);
-        S.Pinv = make_ulonglong2(c->Pinv, c->Pinv_s);
-        if (any_rotation) {
-            hipLaunchKernelGGL(decperm_special_ring, dim3((unsigned)(count * (2 * c->ndigits - 1))), dim3(NT), 0, st, ct_in, digits,
-                               T, S.TP, c->gadget_bits, c->ndigits);
+        if (c->special) {     // digits[ct][j][modulus][N]: twice the digit storage of the one-prime form
+            const SpecialJob S = make_special(c);
+            if (any_rotation) {
+                hipLaunchKernelGGL(decperm_special_ring<WIDE>, dim3((unsigned)(count * (2 * c->ndigits - 1))), dim3(NT), 0, st, ct_in,
+                                   digits, T, S.TP, c->gadget_bits, c->ndigits);
+                const int rc = (int)hipGetLastError();
+                if (rc) return rc;
+            }
+            hipLaunchKernelGGL(hstperm_special_ring<WIDE>, per_term, dim3(NT), 0, st, ct_in, digits, terms, keys2, xrot, T, S,
+                               c->ndigits);
+            return (int)hipGetLastError();
+        }
+#endif
+        if (any_rotation && c->ndigits > 1) {
+            hipLaunchKernelGGL(decperm_ring<WIDE>, dim3((unsigned)(count * (c->ndigits - 1))), dim3(NT), 0, st, ct_in, digits, T,
+                               c->gadget_bits, c->ndigits - 1);
             const int rc = (int)hipGetLastError();
             if (rc) return rc;
         }
-        hipLaunchKernelGGL(hstperm_special_ring, per_term, dim3(NT), 0, st, ct_in, digits, terms, keys2, xrot, T, S, c->ndigits);
+        hipLaunchKernelGGL(hstperm_taps_ring<WIDE>, per_term, dim3(NT), 0, st, ct_in, digits, terms, keys2, xrot, T, c->ndigits);
         return (int)hipGetLastError();
-    }
-#endif
-    if (any_rotation && c->ndigits > 1) {
-        hipLaunchKernelGGL(decperm_ring, dim3((unsigned)(count * (c->ndigits - 1))), dim3(NT), 0, st, ct_in, digits, T,
-                           c->gadget_bits, c->ndigits - 1);
-        const int rc = (int)hipGetLastError();
-        if (rc) return rc;
-    }
-    hipLaunchKernelGGL(hstperm_taps_ring, per_term, dim3(NT), 0, st, ct_in, digits, terms, keys2, xrot, T, c->ndigits);
-    return (int)hipGetLastError();
+    });
 }
 
 // DecPerm (when any term rotates) followed by the HstPerm of every term, written as the column image
@@ -1845,33 +1839,40 @@ static int hstperm_pack(const gala_ctx *c, void *stream, const u64 *ct_in, u64 *
     if (batch <= 0 || terms.nterm <= 0) return 0;
     const RingTables T = make_tables(c->d_tw2, c->ntt_q);
     hipStream_t st = (hipStream_t)stream;
-    if (any_rotation && c->ndigits > 1) {
-        hipLaunchKernelGGL(decperm_ring, dim3((unsigned)((size_t)batch * terms.nin * (c->ndigits - 1))), dim3(NT), 0, st, ct_in,
-                           digits, T, c->gadget_bits, c->ndigits - 1);
-        const int rc = (int)hipGetLastError();
-        if (rc) return rc;
-    }
     const int eblocks = (terms.nterm + 15) / 16, kblocks = (terms.nterm + 63) / 64;
     const dim3 grid(N / 64, (unsigned)eblocks, (unsigned)((batch + 3) / 4));
     v4i_t *out = reinterpret_cast<v4i_t *>(xl);
-    if (!any_rotation)
-        hipLaunchKernelGGL((hstperm_pack_ring<0, false>), grid, dim3(PACK_THREADS), 0, st, ct_in, digits, terms, kblocks, keys2, out, T, c->ndigits, batch);
-    else if (!keys2)
-        return (int)hipErrorInvalidValue;
-    else if (c->ndigits == 3)
-        hipLaunchKernelGGL((hstperm_pack_ring<3, true>), grid, dim3(PACK_THREADS), 0, st, ct_in, digits, terms, kblocks, keys2, out, T, c->ndigits, batch);
-    else
-        hipLaunchKernelGGL((hstperm_pack_ring<0, true>), grid, dim3(PACK_THREADS), 0, st, ct_in, digits, terms, kblocks, keys2, out, T, c->ndigits, batch);
-    return (int)hipGetLastError();
+    if (any_rotation && !keys2) return (int)hipErrorInvalidValue;
+    return by_width(c, [&](auto width) {
+        constexpr bool WIDE = decltype(width)::value;
+        if (any_rotation && c->ndigits > 1) {
+            hipLaunchKernelGGL(decperm_ring<WIDE>, dim3((unsigned)((size_t)batch * terms.nin * (c->ndigits - 1))), dim3(NT), 0, st,
+                               ct_in, digits, T, c->gadget_bits, c->ndigits - 1);
+            const int rc = (int)hipGetLastError();
+            if (rc) return rc;
+        }
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, grid, dim3(PACK_THREADS), 0, st, ct_in, digits, terms, kblocks, keys2, out, T, c->ndigits, batch);
+        };
+        if (!any_rotation) go(hstperm_pack_ring<WIDE, 0, false>);
+        else if (c->ndigits == 3) go(hstperm_pack_ring<WIDE, 3, true>);
+        else go(hstperm_pack_ring<WIDE, 0, true>);
+        return (int)hipGetLastError();
+    });
 }
 
 static int ntt(const gala_ctx *c, void *stream, const u64 *src, u64 *dst, size_t count, int inverse, bool special) {
     if (!count) return 0;
     const RingTables T = special ? make_tables(c->d_tw2P, c->ntt_P) : make_tables(c->d_tw2, c->ntt_q);
-    hipStream_t st = (hipStream_t)stream;
-    if (inverse) hipLaunchKernelGGL(ntt_ring<true>, dim3((unsigned)count), dim3(NT), 0, st, src, dst, T);
-    else hipLaunchKernelGGL(ntt_ring<false>, dim3((unsigned)count), dim3(NT), 0, st, src, dst, T);
-    return (int)hipGetLastError();
+    return by_width(c, [&](auto width) {
+        constexpr bool WIDE = decltype(width)::value;
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)count), dim3(NT), 0, (hipStream_t)stream, src, dst, T);
+        };
+        if (inverse) go(ntt_ring<WIDE, true>);
+        else go(ntt_ring<WIDE, false>);
+        return (int)hipGetLastError();
+    });
 }
 
 static int encrypt(const gala_ctx *c, void *stream, const u64 *s_hat, const u64 *slots, const u64 *seeds, int count,
@@ -1879,18 +1880,23 @@ static int encrypt(const gala_ctx *c, void *stream, const u64 *s_hat, const u64 
     if (!count) return 0;
     GaussCdf cdf;
     for (int i = 0; i < 2 * kGaussBound; ++i) cdf.t[i] = gauss_cdf_table()[i];
-    hipLaunchKernelGGL(encrypt_ring, dim3((unsigned)count), dim3(NT), 0, (hipStream_t)stream, slots, seeds, s_hat, ct_out,
-                       make_tables(c->d_tw2, c->ntt_q), make_tables(c->d_tw2p, c->ntt_p), make_small(c), c->d_slot_to_idx, cdf, c->qbits,
-                       make_ulonglong2(c->delta, c->delta_s));
-    return (int)hipGetLastError();
+    return by_width(c, [&](auto width) {
+        hipLaunchKernelGGL(encrypt_ring<decltype(width)::value>, dim3((unsigned)count), dim3(NT), 0, (hipStream_t)stream, slots, seeds,
+                           s_hat, ct_out, make_tables(c->d_tw2, c->ntt_q), make_tables(c->d_tw2p, c->ntt_p), make_small(c),
+                           c->d_slot_to_idx, cdf, c->qbits, as_words(c->delta_m));
+        return (int)hipGetLastError();
+    });
 }
 static int decrypt(const gala_ctx *c, void *stream, const u64 *s_hat, const u64 *ct_in, int count, u64 *slots) {
     if (!count) return 0;
     u64 inv = c->q;                                   // Newton's iteration for q^-1 mod 2^64 (q is odd)
     for (int i = 0; i < 6; ++i) inv *= 2 - c->q * inv;
-    hipLaunchKernelGGL(decrypt_ring, dim3((unsigned)count), dim3(NT), 0, (hipStream_t)stream, ct_in, s_hat, slots,
-                       make_tables(c->d_tw2, c->ntt_q), make_tables(c->d_tw2p, c->ntt_p), make_small(c), c->d_slot_to_idx, inv);
-    return (int)hipGetLastError();
+    return by_width(c, [&](auto width) {
+        hipLaunchKernelGGL(decrypt_ring<decltype(width)::value>, dim3((unsigned)count), dim3(NT), 0, (hipStream_t)stream, ct_in, s_hat,
+                           slots, make_tables(c->d_tw2, c->ntt_q), make_tables(c->d_tw2p, c->ntt_p), make_small(c), c->d_slot_to_idx,
+                           inv);
+        return (int)hipGetLastError();
+    });
 }
 
 #define GALA_RING_OPS_(logn) ring_ops_##logn

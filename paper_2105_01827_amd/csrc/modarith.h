@@ -50,6 +50,25 @@ GALA_HD u64 companion(u64 w, u64 q, const Reciprocal &r) {
     return quot;
 }
 
+// A constant of the ring kernels' products (gala_ring_impl.h): w 2^32 and w 2^64 mod m, centred, each written as
+// hi 2^32 + lo with both halves signed words.
+struct MontPair {
+    u64 a, b;
+};
+// a centred residue's two signed words: the high one absorbs the sign of the low one
+GALA_HD u64 signed_words(u64 v, u64 m) {
+    const u64 x = v > m / 2 ? v - m : v;
+    return x + ((x & 0x80000000ull) << 1);
+}
+// makes the pairs of one modulus m < 2^61, m odd
+struct MontMaker {
+    u64 m, r, rs;     // 2^32 mod m and its companion
+};
+GALA_HD MontPair mont_pair(u64 w, const MontMaker &k) {
+    const u64 a = mul_shoup(w, k.r, k.rs, k.m);
+    return {signed_words(a, k.m), signed_words(mul_shoup(a, k.r, k.rs, k.m), k.m)};
+}
+
 // What a kernel needs to know about a modulus (passed by value).
 struct Modulus {
     u64 q;       // the modulus
