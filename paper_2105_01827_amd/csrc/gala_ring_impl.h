@@ -37,9 +37,22 @@ namespace {
 constexpr int LOGN = GALA_LOGN, N = 1 << LOGN, PER = 8, NT = N / PER;
 // a wavefront's 64 threads own the same 512 consecutive indices in every pass on bits at or below this one
 constexpr int LOCAL_BITS = 6;
-constexpr int LDS_WORDS = N + N / 32;
 
-__device__ __forceinline__ int pad(int i) { return i + (i >> 5); }
+// Images of a polynomial in LDS.  A wavefront's range of 512 words has a stride of its own, 512 + 512 / 2^S words, and
+// inside it an exchange pads by one word every 2^SHIFT, SHIFT >= S: ranges do not move with the padding, so wavefronts
+// that are one exchange apart stay out of each other's way.  Measured clocks of a wavefront's eight-byte instruction on
+// the gfx950 LDS (a free read takes 2.2, a write 6): SHIFT 5 write 6 and read 2.2 between passes on bits 5 and up, but 7.8
+// and 15.6 write, 7.8 read in the patterns of bits 0, 2 and 3, where SHIFT 4 takes 6 to 7.9 and 4, SHIFT 3 6 and 2.2.  S is the
+// best that a kernel's LDS has room for.
+constexpr int stride_of(int S) { return 512 + (512 >> S); }
+constexpr int lds_words(int S) { return N / 512 * stride_of(S); }
+template <int S, int SHIFT = 5>
+__device__ __forceinline__ constexpr int pad(int i) {
+    // (i >> 9) stride + (i & 511) + ((i & 511) >> SHIFT)
+    return i + (i >> SHIFT) + (SHIFT == S ? 0 : (i >> 9) * ((512 >> S) - (512 >> SHIFT)));
+}
+// images of 32-bit words
+__device__ __forceinline__ int pad32(int i) { return i + (i >> 5); }
 __device__ __forceinline__ int bitrev(int v) { return (int)(__brev((unsigned)v) >> (32 - LOGN)); }
 __device__ __forceinline__ int galois_index(int i, int gal) {
     const int e = ((2 * bitrev(i) + 1) * gal) & (2 * N - 1);
@@ -105,8 +118,9 @@ __device__ __forceinline__ u64 mont_reduce(u64 L, u64 H, const MontQ &q) {
     }
     return H;
 }
-// w y, or x + w y.  UNIFORM: the constant is the same for all lanes and sits in scalar registers.
-template <bool WIDE, bool ADD = false, bool UNIFORM = false>
+// w y, or x + w y.  UNIFORM: the constant is the same for all lanes and sits in scalar registers.  IN_PLACE: nobody needs x
+// afterwards (a running sum), the result takes its registers.
+template <bool WIDE, bool ADD = false, bool UNIFORM = false, bool IN_PLACE = false>
 __device__ __forceinline__ u64 mont(Words y, const ulonglong2 w, const MontQ &q, u64 x = 0) {
     const u32 a0 = (u32)w.x, a1 = (u32)(w.x >> 32), b0 = (u32)w.y, b1 = (u32)(w.y >> 32);
     u64 L, H;
@@ -118,7 +132,16 @@ __device__ __forceinline__ u64 mont(Words y, const ulonglong2 w, const MontQ &q,
         : "=&v"(L), "=&v"(H)                                                                                          \
         : "v"(y.lo), "v"(y.hi), WHERE(a0), WHERE(a1), WHERE(b0), WHERE(b1) __VA_ARGS__                                \
         : "vcc")
-    if (UNIFORM) {
+    if (!UNIFORM && ADD && IN_PLACE) {
+        H = x;
+        asm("v_mad_i64_i32 %0, vcc, %2, %4, 0\n\t"
+            "v_mad_i64_i32 %1, vcc, %2, %5, %1\n\t"
+            "v_mad_i64_i32 %0, vcc, %3, %6, %0\n\t"
+            "v_mad_i64_i32 %1, vcc, %3, %7, %1"
+            : "=&v"(L), "+v"(H)
+            : "v"(y.lo), "v"(y.hi), "v"(a0), "v"(a1), "v"(b0), "v"(b1)
+            : "vcc");
+    } else if (UNIFORM) {
         if (ADD) GALA_MONT("%8", "s", , "v"(x));
         else GALA_MONT("0", "s");
     } else {
@@ -128,14 +151,76 @@ __device__ __forceinline__ u64 mont(Words y, const ulonglong2 w, const MontQ &q,
 #undef GALA_MONT
     return mont_reduce<WIDE>(L, H, q);
 }
-// x + w y for 0 <= y < 2^31 (a gadget digit, not biased): half of the products have nothing to do
+template <bool WIDE>
+__device__ __forceinline__ void add_product(u64 &sum, Words y, const ulonglong2 w, const MontQ &q) {
+    sum = mont<WIDE, true, false, true>(y, w, q, sum);
+}
+// Two products at once, xa + wa ya and xb + wb yb, their instructions in turn: a wavefront alone on its SIMD issues a
+// multiply-add every other slot only and waits for each result, so what it finds to do in between counts.  Butterflies of
+// one wavefront per SIMD 1.15 times as fast as one by one, of two 1.03 times, of three the same.
+template <bool WIDE, bool UNIFORM = false>
+__device__ __forceinline__ void mont2(u64 &ra, u64 &rb, Words ya, const ulonglong2 wa, Words yb, const ulonglong2 wb, const MontQ &q,
+                                      u64 xa, u64 xb) {
+    u64 L, H, M, I;
+#define GALA_MONT2(WHERE)                                                                                             \
+    asm("v_mad_i64_i32 %0, vcc, %4, %8, 0\n\t"                                                                       \
+        "v_mad_i64_i32 %2, vcc, %6, %12, 0\n\t"                                                                      \
+        "v_mad_i64_i32 %1, vcc, %4, %9, %16\n\t"                                                                     \
+        "v_mad_i64_i32 %3, vcc, %6, %13, %17\n\t"                                                                    \
+        "v_mad_i64_i32 %0, vcc, %5, %10, %0\n\t"                                                                     \
+        "v_mad_i64_i32 %2, vcc, %7, %14, %2\n\t"                                                                     \
+        "v_mad_i64_i32 %1, vcc, %5, %11, %1\n\t"                                                                     \
+        "v_mad_i64_i32 %3, vcc, %7, %15, %3"                                                                          \
+        : "=&v"(L), "=&v"(H), "=&v"(M), "=&v"(I)                                                                      \
+        : "v"(ya.lo), "v"(ya.hi), "v"(yb.lo), "v"(yb.hi), WHERE((u32)wa.x), WHERE((u32)(wa.x >> 32)), WHERE((u32)wa.y), \
+          WHERE((u32)(wa.y >> 32)), WHERE((u32)wb.x), WHERE((u32)(wb.x >> 32)), WHERE((u32)wb.y), WHERE((u32)(wb.y >> 32)), \
+          "v"(xa), "v"(xb)                                                                                            \
+        : "vcc")
+    if (UNIFORM) GALA_MONT2("s");
+    else GALA_MONT2("v");
+#undef GALA_MONT2
+    int k, l;
+    if (WIDE) {
+        asm("v_mul_lo_u32 %2, %4, %8\n\t"
+            "v_mul_lo_u32 %3, %5, %8\n\t"
+            "v_mad_i64_i32 %0, vcc, %2, %9, %0\n\t"
+            "v_mad_i64_i32 %1, vcc, %3, %9, %1\n\t"
+            "v_mul_hi_i32 %2, %2, %10\n\t"
+            "v_mul_hi_i32 %3, %3, %10\n\t"
+            "v_mad_i64_i32 %0, vcc, %6, 1, %0\n\t"
+            "v_mad_i64_i32 %1, vcc, %7, 1, %1\n\t"
+            "v_mad_i64_i32 %0, vcc, %2, -1, %0\n\t"
+            "v_mad_i64_i32 %1, vcc, %3, -1, %1"
+            : "+v"(H), "+v"(I), "=&v"(k), "=&v"(l)
+            : "v"((u32)L), "v"((u32)M), "v"((u32)(L >> 32)), "v"((u32)(M >> 32)), "s"(q.inv), "s"(q.nhi), "s"(q.lo)
+            : "vcc");
+    } else {
+        asm("v_mul_lo_u32 %4, %6, %8\n\t"
+            "v_mul_lo_u32 %5, %7, %8\n\t"
+            "v_mad_i64_i32 %0, vcc, %4, %9, %0\n\t"
+            "v_mad_i64_i32 %2, vcc, %5, %9, %2\n\t"
+            "v_mad_i64_i32 %1, vcc, %4, %10, %1\n\t"
+            "v_mad_i64_i32 %3, vcc, %5, %10, %3"
+            : "+v"(L), "+v"(H), "+v"(M), "+v"(I), "=&v"(k), "=&v"(l)
+            : "v"((u32)L), "v"((u32)M), "s"(q.inv), "s"(q.nlo), "s"(q.nhi)
+            : "vcc");
+        asm("v_mad_i64_i32 %0, vcc, %2, 1, %0\n\t"
+            "v_mad_i64_i32 %1, vcc, %3, 1, %1"
+            : "+v"(H), "+v"(I)
+            : "v"((u32)(L >> 32)), "v"((u32)(M >> 32))
+            : "vcc");
+    }
+    ra = H;
+    rb = I;
+}
+// x + w y for 0 <= y < 2^31 (a gadget digit, not biased), w in scalar registers: half of the products have nothing to do
 template <bool WIDE>
 __device__ __forceinline__ u64 mont_small(u32 y, const ulonglong2 w, const MontQ &q, u64 x) {
     u64 L, H;
     asm("v_mad_i64_i32 %0, vcc, %2, %3, 0\n\t"
         "v_mad_i64_i32 %1, vcc, %2, %4, %5"
         : "=&v"(L), "=&v"(H)
-        : "v"(y), "v"((u32)w.x), "v"((u32)(w.x >> 32)), "v"(x)
+        : "v"(y), "s"((u32)w.x), "s"((u32)(w.x >> 32)), "v"(x)
         : "vcc");
     return mont_reduce<WIDE>(L, H, q);
 }
@@ -162,11 +247,14 @@ __device__ __forceinline__ u64 csub_dev(u64 x, u64 c) {
 }
 
 // x, y -> x + w y, x - w y without any correction; the bound grows by 0.75 + c/32, c the bound of y.  Both biased.
-template <bool WIDE>
-__device__ __forceinline__ void bf(u64 &x, u64 &y, const ulonglong2 w, const MontQ &q) {
-    const u64 s = mont<WIDE, true>(biased_words(y), w, q, x);
-    y = (x << 1) - s;
-    x = s;
+template <bool WIDE, bool UNIFORM = false>
+__device__ __forceinline__ void bf2(u64 &xa, u64 &ya, const ulonglong2 wa, u64 &xb, u64 &yb, const ulonglong2 wb, const MontQ &q) {
+    u64 sa, sb;
+    mont2<WIDE, UNIFORM>(sa, sb, biased_words(ya), wa, biased_words(yb), wb, q, xa, xb);
+    ya = (xa << 1) - sa;
+    xa = sa;
+    yb = (xb << 1) - sb;
+    xb = sb;
 }
 // y not biased, the constant in scalar registers
 template <bool WIDE>
@@ -211,6 +299,21 @@ __host__ __device__ constexpr int level_offset(int c) {
     return at;
 }
 constexpr int FWD_PAIRS = level_offset(N / 8) + 7 * (N / 8);
+// The first pass has one block: its constants are the same for all lanes and come through the scalar cache.  The vector
+// cache hands a CU 64 bytes a clock, 16 clocks for a wavefront's load of a constant whether its lanes differ or not, and that
+// is what the Perm kernel runs into next to the vector ALU; scalar loads and LDS reads (4 clocks) do not count there.
+__device__ __forceinline__ Tw7 tw_first(const ulonglong2 *table) {
+    typedef __attribute__((address_space(4))) const u64 scalar_u64;
+    asm volatile("" : "+s"(table));        // loaded where it is used, not once for the whole kernel
+    scalar_u64 *p = (scalar_u64 *)reinterpret_cast<uintptr_t>(table);
+    Tw7 w;
+#pragma unroll
+    for (int e = 0; e < 7; ++e) w.t[e] = make_ulonglong2(p[2 * e], p[2 * e + 1]);
+    return w;
+}
+// Loads above this line stay above it: constants are requested a whole pass before their use, from the L2 as a rule, and
+// the compiler would sink the requests to where they are needed.
+__device__ __forceinline__ void pin_loads() { __builtin_amdgcn_sched_barrier(0x387); }
 // constants of block COUNT + j: the level's start is uniform, j*16 a 32-bit offset
 template <int COUNT>
 __device__ __forceinline__ Tw7 tw_level(const ulonglong2 *__restrict__ table, unsigned j) {
@@ -224,31 +327,27 @@ __device__ __forceinline__ Tw7 tw_level(const ulonglong2 *__restrict__ table, un
 // STAGE: the first of the three stages to run.  CORRECT: the values that the first stage does not multiply are shrunk.
 // digits (the same for every thread): a[4..7], the values that the first stage multiplies, are below 2^31 and not biased,
 // as gadget digits are.
-template <bool WIDE, int STAGE, bool CORRECT = false>
+template <bool WIDE, int STAGE, bool CORRECT = false, bool UNIFORM = false>
 __device__ __forceinline__ void fwd_pass(u64 (&a)[8], const Tw7 &w, const MontQ &q, bool digits = false) {
     if (CORRECT) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) a[k] = shrink(a[k], q);
     }
     if (STAGE == 0) {
-        if (digits) {
+        if (UNIFORM && digits) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) bf_digit<WIDE>(a[k], a[k + 4], w.t[0], q);
         } else {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) bf<WIDE>(a[k], a[k + 4], w.t[0], q);
+            bf2<WIDE, UNIFORM>(a[0], a[4], w.t[0], a[1], a[5], w.t[0], q);
+            bf2<WIDE, UNIFORM>(a[2], a[6], w.t[0], a[3], a[7], w.t[0], q);
         }
     }
     if (STAGE <= 1) {
-        bf<WIDE>(a[0], a[2], w.t[1], q);
-        bf<WIDE>(a[1], a[3], w.t[1], q);
-        bf<WIDE>(a[4], a[6], w.t[2], q);
-        bf<WIDE>(a[5], a[7], w.t[2], q);
+        bf2<WIDE, UNIFORM>(a[0], a[2], w.t[1], a[1], a[3], w.t[1], q);
+        bf2<WIDE, UNIFORM>(a[4], a[6], w.t[2], a[5], a[7], w.t[2], q);
     }
-    bf<WIDE>(a[0], a[1], w.t[3], q);
-    bf<WIDE>(a[2], a[3], w.t[4], q);
-    bf<WIDE>(a[4], a[5], w.t[5], q);
-    bf<WIDE>(a[6], a[7], w.t[6], q);
+    bf2<WIDE, UNIFORM>(a[0], a[1], w.t[3], a[2], a[3], w.t[4], q);
+    bf2<WIDE, UNIFORM>(a[4], a[5], w.t[5], a[6], a[7], w.t[6], q);
 }
 // Inverse transform.  The values sit in bit-reversed order, which is what a decimation-in-time transform starts from:
 // it evaluates the plain cyclic sum over the powers of psi^-2, and a multiplication of coefficient j by psi^-j / n at
@@ -288,18 +387,12 @@ __device__ __forceinline__ void inv_pass(u64 (&a)[8], const Tw7 &w, const MontQ 
 #pragma unroll
         for (int k = 0; k < 8; k += 2) a[k] = shrink(a[k], q);
     }
-    bf<WIDE>(a[0], a[1], w.t[0], q);
-    bf<WIDE>(a[2], a[3], w.t[0], q);
-    bf<WIDE>(a[4], a[5], w.t[0], q);
-    bf<WIDE>(a[6], a[7], w.t[0], q);
-    bf<WIDE>(a[0], a[2], w.t[1], q);
-    bf<WIDE>(a[1], a[3], w.t[2], q);
-    bf<WIDE>(a[4], a[6], w.t[1], q);
-    bf<WIDE>(a[5], a[7], w.t[2], q);
-    bf<WIDE>(a[0], a[4], w.t[3], q);
-    bf<WIDE>(a[1], a[5], w.t[4], q);
-    bf<WIDE>(a[2], a[6], w.t[5], q);
-    bf<WIDE>(a[3], a[7], w.t[6], q);
+    bf2<WIDE>(a[0], a[1], w.t[0], a[2], a[3], w.t[0], q);
+    bf2<WIDE>(a[4], a[5], w.t[0], a[6], a[7], w.t[0], q);
+    bf2<WIDE>(a[0], a[2], w.t[1], a[1], a[3], w.t[2], q);
+    bf2<WIDE>(a[4], a[6], w.t[1], a[5], a[7], w.t[2], q);
+    bf2<WIDE>(a[0], a[4], w.t[3], a[1], a[5], w.t[4], q);
+    bf2<WIDE>(a[2], a[6], w.t[5], a[3], a[7], w.t[6], q);
 }
 // The inverse table: bits 3-5 as [7][8], bits 6-8 as [7][64], from n = 4096 on bits 9-11 as [7][512], the last pass's one
 // or two stages as [4] or [6][n/8] (constant, low bits of the index), then psi^-j / n for j = 0 .. n-1.
@@ -317,28 +410,29 @@ __device__ __forceinline__ void inv_level(ulonglong2 (&t)[CONSTANTS], const ulon
 // Exchange between the pass on bits B_OUT .. B_OUT+2 and the one on B_IN .. B_IN+2: store, barrier, load.  The owned
 // indices have zeros in the three bits the register number fills, so the padded address of
 // register k is pad(owner) plus a compile-time offset.
-template <int SH>
-__device__ __forceinline__ constexpr int reg_offset(int k) { return (k << SH) + ((k << SH) >> 5); }
+template <int S, int SHIFT, int B>
+__device__ __forceinline__ constexpr int reg_offset(int k) { return pad<S, SHIFT>(k << B); }
 // Where every word a thread loads was stored by a thread of its own wavefront (both index sets lie in the
 // wavefront's 512-word range of the buffer), a wavefront's LDS instructions execute in order, so its loads see
 // its stores without a workgroup barrier; the fences only keep the compiler from moving the loads up.  At n = 2048
 // four of the seven exchanges of an inverse + forward transform pair are of this kind; <8,5>, <6,8> and the final
-// store of the forward transform cross wavefronts and keep the barrier.
-template <int B_OUT, int B_IN>
+// store of the forward transform cross wavefronts and keep the barrier.  BARRIER: one for the sake of what came before.
+template <int S, int B_OUT, int B_IN, bool BARRIER = false>
 __device__ __forceinline__ void exchange(u64 (&a)[8], u64 *buf, int tid) {
-    u64 *po = buf + pad(owner<B_OUT>(tid));
+    constexpr int SHIFT = B_OUT < 5 || B_IN < 5 ? S : 5;
+    u64 *po = buf + pad<S, SHIFT>(owner<B_OUT>(tid));
 #pragma unroll
-    for (int k = 0; k < 8; ++k) po[reg_offset<B_OUT>(k)] = a[k];
-    if (B_OUT <= LOCAL_BITS && B_IN <= LOCAL_BITS) {
+    for (int k = 0; k < 8; ++k) po[reg_offset<S, SHIFT, B_OUT>(k)] = a[k];
+    if (B_OUT <= LOCAL_BITS && B_IN <= LOCAL_BITS && !BARRIER) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     } else {
         __syncthreads();
     }
-    const u64 *pi = buf + pad(owner<B_IN>(tid));
+    const u64 *pi = buf + pad<S, SHIFT>(owner<B_IN>(tid));
 #pragma unroll
-    for (int k = 0; k < 8; ++k) a[k] = pi[reg_offset<B_IN>(k)];
+    for (int k = 0; k < 8; ++k) a[k] = pi[reg_offset<S, SHIFT, B_IN>(k)];
 }
 
 struct RingTables {
@@ -361,6 +455,40 @@ __device__ __forceinline__ int fresh(int tid) {
     return tid;
 }
 
+// The twiddle levels that few lanes tell apart, copied to LDS by kernels that run many transforms: the forward transform's
+// level of 8 blocks and the inverse's bits 3-5 (896 bytes each), LEVELS = 2 also the level of 64 and bits 6-8 (7 KiB each).
+struct NoCopy {
+    static constexpr int LEVELS = 0;
+    const ulonglong2 *f8 = nullptr, *i8 = nullptr, *f64 = nullptr, *i64 = nullptr;
+    template <int COUNT>
+    __device__ __forceinline__ Tw7 get(const ulonglong2 *, unsigned) const { return Tw7{}; }
+};
+template <int L>
+struct TableCopy {
+    static constexpr int LEVELS = L, PAIRS = L == 2 ? 14 * 72 : 14 * 8;
+    ulonglong2 *f8, *i8, *f64, *i64;
+    __device__ __forceinline__ TableCopy(ulonglong2 *at) : f8(at), i8(at + 56), f64(at + 112), i64(at + 112 + 7 * 64) {}
+    // a barrier has to follow
+    __device__ __forceinline__ void fill(const RingTables &T, int tid) {
+        for (int k = tid; k < 56; k += NT) {
+            f8[k] = T.tw[level_offset(8) + k];
+            i8[k] = T.itw[k];
+        }
+        if (L < 2) return;
+        for (int k = tid; k < 7 * 64; k += NT) {
+            f64[k] = T.tw[level_offset(64) + k];
+            i64[k] = T.itw[INV_MID + k];
+        }
+    }
+    template <int COUNT>
+    __device__ __forceinline__ Tw7 get(const ulonglong2 *level, unsigned j) const {
+        Tw7 w;
+#pragma unroll
+        for (int e = 0; e < 7; ++e) w.t[e] = level[e * COUNT + j];
+        return w;
+    }
+};
+
 // Forward transform of the 8 registers (ownership t + (n/8) k); the result is left in LDS buffer `res` (natural index,
 // padded), biased, below 7.3 (5.4 at n = 2048).  LDS phases: other, res, other, res; at n = 8192, where a
 // fifth phase would start and end on the same buffer, res, other, res, other, res behind a barrier.
@@ -371,9 +499,10 @@ struct NothingAhead {
     __device__ __forceinline__ void operator()() const {}
 };
 enum Entry { PLAIN, BIASED };
-template <bool WIDE, Entry IN = PLAIN, class Ahead = NothingAhead>
+// S: the padding of the images.  tab: the kernel's copy of the small levels in LDS (TableCopy), or nothing.
+template <bool WIDE, int S, Entry IN = PLAIN, class Copy = NoCopy, class Ahead = NothingAhead>
 __device__ __forceinline__ void forward_to_lds(u64 (&a)[8], u64 *res, u64 *other, const RingTables &T, int tid_,
-                                               bool digits = false, Ahead ahead = Ahead{}) {
+                                               bool digits = false, Copy copy = Copy{}, Ahead ahead = Ahead{}) {
     const int tid = fresh(tid_);
     const MontQ q = T.mont;
     constexpr int B1 = LOGN - 3, B2 = LOGN - 6, B3 = LOGN - 9, B4 = LOGN >= 12 ? LOGN - 12 : 0;
@@ -386,32 +515,44 @@ __device__ __forceinline__ void forward_to_lds(u64 (&a)[8], u64 *res, u64 *other
 #pragma unroll
             for (int k = 4; k < 8; ++k) a[k] += BIAS;
     }
-    Tw7 w = tw_level<1>(T.tw, 0);
-    fwd_pass<WIDE, 0>(a, w, q, digits);                                                  // stages 1-3
-    w = tw_level<8>(T.tw, (unsigned)tid >> B2);
-    exchange<B1, B2>(a, first, tid);
+    Tw7 w, next;
+    fwd_pass<WIDE, 0, false, true>(a, tw_first(T.tw), q, digits);                        // stages 1-3
+    if (Copy::LEVELS >= 1) w = copy.template get<8>(copy.f8, (unsigned)tid >> B2);
+    else w = tw_level<8>(T.tw, (unsigned)tid >> B2);
+    exchange<S, B1, B2>(a, first, tid);
+    if (Copy::LEVELS < 2) {
+        next = tw_level<64>(T.tw, (unsigned)tid >> B3);
+        pin_loads();
+    }
     fwd_pass<WIDE, 0>(a, w, q);                                                          // stages 4-6
-    w = tw_level<64>(T.tw, (unsigned)tid >> B3);
-    exchange<B2, B3>(a, second, tid);
-    fwd_pass<WIDE, 0, true>(a, w, q);                                                    // stages 7-9
+    if (Copy::LEVELS >= 2) next = copy.template get<64>(copy.f64, (unsigned)tid >> B3);
+    exchange<S, B2, B3>(a, second, tid);
     if (LOGN < 12) {
         w = tw_level<NT>(T.tw, (unsigned)tid);
-        exchange<B3, 0>(a, first, tid);
+        pin_loads();
+        fwd_pass<WIDE, 0, true>(a, next, q);                                             // stages 7-9
+        exchange<S, B3, 0>(a, first, tid);
         ahead();
         fwd_pass<WIDE, 3 - LOGN % 3>(a, w, q);                                           // stages 10, 11
     } else {
         w = tw_level<512>(T.tw, (unsigned)tid >> B4);
-        exchange<B3, B4>(a, first, tid);
-        if (LOGN == 12) ahead();
+        pin_loads();
+        fwd_pass<WIDE, 0, true>(a, next, q);                                             // stages 7-9
+        exchange<S, B3, B4>(a, first, tid);
+        if (LOGN == 12) {
+            ahead();
+        } else {
+            next = tw_level<NT>(T.tw, (unsigned)tid);
+            pin_loads();
+        }
         fwd_pass<WIDE, 0>(a, w, q);                                                      // stages 10-12
         if (LOGN == 13) {
-            w = tw_level<NT>(T.tw, (unsigned)tid);
-            exchange<B4, 0>(a, second, tid);
+            exchange<S, B4, 0>(a, second, tid);
             ahead();
-            fwd_pass<WIDE, 2>(a, w, q);                                                  // stage 13
+            fwd_pass<WIDE, 2>(a, next, q);                                               // stage 13
         }
     }
-    u64 *po = res + pad(tid << 3);
+    u64 *po = res + pad<S>(tid << 3);
 #pragma unroll
     for (int k = 0; k < 8; ++k) po[k] = a[k];
     __syncthreads();
@@ -419,43 +560,55 @@ __device__ __forceinline__ void forward_to_lds(u64 (&a)[8], u64 *res, u64 *other
 
 // Inverse transform: registers hold index 8t + k (not biased, |a| < m) on entry and index t + (n/8) k, canonical, on
 // return.  LDS phases A B A, one more on B at n = 8192.
-template <bool WIDE>
-__device__ __forceinline__ void inverse_in_regs(u64 (&a)[8], u64 *bufA, u64 *bufB, const RingTables &T, int tid_) {
+// FENCE: a barrier in the first exchange, for the sake of reads of bufB before the call.
+template <bool WIDE, int S, bool FENCE = false, class Copy = NoCopy>
+__device__ __forceinline__ void inverse_in_regs(u64 (&a)[8], u64 *bufA, u64 *bufB, const RingTables &T, int tid_, Copy copy = Copy{}) {
     const int tid = fresh(tid_);
     const MontQ q = T.mont;
     constexpr int TOP = LOGN - 3;
-    Tw7 w;
-    inv_level<7, 8>(w.t, T.itw, (unsigned)tid & 7);
+    Tw7 w, next;
+    ulonglong2 t[TOP_CONSTS], c[8];
+    auto top = [&] { inv_level<TOP_CONSTS, NT>(t, T.itw + INV_TOP, (unsigned)tid); };
+    auto twist = [&] { inv_level<8, NT>(c, T.itw + INV_TWIST, (unsigned)tid); };
+    if (Copy::LEVELS < 2) {
+        next = Tw7{};
+        inv_level<7, 64>(next.t, T.itw + INV_MID, (unsigned)tid & 63);
+    }
+    if (Copy::LEVELS >= 1) w = copy.template get<8>(copy.i8, (unsigned)tid & 7);
+    else inv_level<7, 8>(w.t, T.itw, (unsigned)tid & 7);
+    pin_loads();
     inv_first_pass<WIDE>(a, T.w8, q);                                                    // bits 0-2: 3.7
-    exchange<0, 3>(a, bufA, tid);
+    exchange<S, 0, 3, FENCE>(a, bufA, tid);
     inv_pass<WIDE, false>(a, w, q);                                                      // bits 3-5: 6.4
-    inv_level<7, 64>(w.t, T.itw + INV_MID, (unsigned)tid & 63);
-    exchange<3, 6>(a, bufB, tid);
-    inv_pass<WIDE, true>(a, w, q);                                                       // bits 6-8: 3.6
-    // requested right behind the last barrier and used after the last stages: asked for when they are needed, their
-    // latency cost he_fc 128x1024 at batch 64 10 us of 158
-    ulonglong2 c[8];
+    if (Copy::LEVELS >= 2) next = copy.template get<64>(copy.i64, (unsigned)tid & 63);
+    exchange<S, 3, 6>(a, bufB, tid);
     if (LOGN >= 12) {
         inv_level<7, 512>(w.t, T.itw + INV_HIGH, (unsigned)tid & 511);
-        exchange<6, 9>(a, bufA, tid);
-        if (!TOP_STAGES) inv_level<8, NT>(c, T.itw + INV_TWIST, (unsigned)tid);
+        pin_loads();
+        inv_pass<WIDE, true>(a, next, q);                                                // bits 6-8: 3.6
+        exchange<S, 6, 9>(a, bufA, tid);
+        if (TOP_STAGES) top();
+        else twist();
+        pin_loads();
         inv_pass<WIDE, false>(a, w, q);                                                  // bits 9-11: 6.3
+    } else {
+        top();
+        pin_loads();
+        inv_pass<WIDE, true>(a, next, q);                                                // bits 6-8: 3.6
     }
     if (TOP_STAGES) {
         // the last pass (register bit 2 is the top bit): 5.4, 7.2 at n = 8192
-        ulonglong2 t[TOP_CONSTS];
-        inv_level<TOP_CONSTS, NT>(t, T.itw + INV_TOP, (unsigned)tid);
-        if (LOGN >= 12) exchange<9, TOP>(a, bufB, tid);
-        else exchange<6, TOP>(a, bufA, tid);
-        inv_level<8, NT>(c, T.itw + INV_TWIST, (unsigned)tid);
+        if (LOGN >= 12) exchange<S, 9, TOP>(a, bufB, tid);
+        else exchange<S, 6, TOP>(a, bufA, tid);
+        twist();
+        pin_loads();
         if (TOP_STAGES == 2) {
-            bf<WIDE>(a[0], a[2], t[0], q);
-            bf<WIDE>(a[1], a[3], t[1], q);
-            bf<WIDE>(a[4], a[6], t[0], q);
-            bf<WIDE>(a[5], a[7], t[1], q);
+            bf2<WIDE>(a[0], a[2], t[0], a[1], a[3], t[1], q);
+            bf2<WIDE>(a[4], a[6], t[0], a[5], a[7], t[1], q);
         }
 #pragma unroll
-        for (int k = 0; k < 4; ++k) bf<WIDE>(a[k], a[k + 4], t[TOP_CONSTS - 4 + k], q);
+        for (int k = 0; k < 4; k += 2)
+            bf2<WIDE>(a[k], a[k + 4], t[TOP_CONSTS - 4 + k], a[k + 1], a[k + 5], t[TOP_CONSTS - 3 + k], q);
     }
 #pragma unroll
     for (int k = 0; k < PER; ++k) a[k] = unsign(mont<WIDE>(biased_words(a[k]), c[k], q), T.mod.q);
@@ -491,9 +644,9 @@ __device__ __forceinline__ void small_level(uint2 (&t)[CONSTANTS], const uint2 *
 }
 template <int B_OUT, int B_IN>
 __device__ __forceinline__ void exchange_small(u32 (&a)[8], u32 *buf, int tid) {
-    u32 *po = buf + pad(owner<B_OUT>(tid));
+    u32 *po = buf + pad32(owner<B_OUT>(tid));
 #pragma unroll
-    for (int k = 0; k < 8; ++k) po[reg_offset<B_OUT>(k)] = a[k];
+    for (int k = 0; k < 8; ++k) po[pad32(k << B_OUT)] = a[k];
     if (B_OUT <= LOCAL_BITS && B_IN <= LOCAL_BITS) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
@@ -501,9 +654,9 @@ __device__ __forceinline__ void exchange_small(u32 (&a)[8], u32 *buf, int tid) {
     } else {
         __syncthreads();
     }
-    const u32 *pi = buf + pad(owner<B_IN>(tid));
+    const u32 *pi = buf + pad32(owner<B_IN>(tid));
 #pragma unroll
-    for (int k = 0; k < 8; ++k) a[k] = pi[reg_offset<B_IN>(k)];
+    for (int k = 0; k < 8; ++k) a[k] = pi[pad32(k << B_IN)];
 }
 template <int STAGE>
 __device__ __forceinline__ void fwd_pass_small(u32 (&a)[8], const uint2 (&w)[7], u32 p) {
@@ -562,7 +715,7 @@ __device__ __forceinline__ void forward_small_to_lds(u32 (&a)[8], u32 *res, u32 
             fwd_pass_small<2>(a, w, T.p);
         }
     }
-    u32 *po = res + pad(tid << 3);
+    u32 *po = res + pad32(tid << 3);
 #pragma unroll
     for (int k = 0; k < 8; ++k) po[k] = a[k];
     __syncthreads();
@@ -618,33 +771,38 @@ __device__ __forceinline__ void inverse_small_in_regs(u32 (&a)[8], u32 *bufA, u3
     }
 }
 
-// The plaintext polynomial of a slot image: slot values sit at pad(position) of bufB, as 32-bit words when the plaintext
+// The plaintext polynomial of a slot image: slot values sit at the padded position of bufB, as 32-bit words when the plaintext
 // modulus is small (put_slot); coefficients t + (n/8) k come back in registers.  The image is padded like an exchange's,
 // because a wavefront reads the words it then writes in the second exchange, and no barrier separates those writes from
 // the other wavefronts' reads.
+template <int S>
 __device__ __forceinline__ void put_slot(u64 *bufB, int position, u64 v, bool small) {
-    if (small) reinterpret_cast<u32 *>(bufB)[pad(position)] = (u32)v;
-    else bufB[pad(position)] = v;
+    if (small) reinterpret_cast<u32 *>(bufB)[pad32(position)] = (u32)v;
+    else bufB[pad<S>(position)] = v;
 }
+template <int S>
 __device__ __forceinline__ u64 get_slot(const u64 *bufB, int position, bool small) {
-    return small ? reinterpret_cast<const u32 *>(bufB)[pad(position)] : bufB[pad(position)];
+    return small ? reinterpret_cast<const u32 *>(bufB)[pad32(position)] : bufB[pad<S>(position)];
 }
-template <bool WIDE>
+template <bool WIDE, int S>
 __device__ __forceinline__ void slots_to_coefficients(u64 (&a)[8], u64 *bufA, u64 *bufB, const RingTables &Tp,
                                                       const SmallTables &small, int tid) {
     if (small.tw) {
         u32 *A = reinterpret_cast<u32 *>(bufA), *B = reinterpret_cast<u32 *>(bufB), v[8];
 #pragma unroll
-        for (int k = 0; k < PER; ++k) v[k] = B[pad(8 * tid) + k];
+        for (int k = 0; k < PER; ++k) v[k] = B[pad32(8 * tid) + k];
         inverse_small_in_regs(v, A, B, small, tid);
 #pragma unroll
         for (int k = 0; k < PER; ++k) a[k] = v[k];
     } else {
 #pragma unroll
-        for (int k = 0; k < PER; ++k) a[k] = bufB[pad(8 * tid) + k];
-        inverse_in_regs<WIDE>(a, bufA, bufB, Tp, tid);
+        for (int k = 0; k < PER; ++k) a[k] = bufB[pad<S>(8 * tid) + k];
+        inverse_in_regs<WIDE, S>(a, bufA, bufB, Tp, tid);
     }
 }
+
+// the padding of kernels that have nothing but two images in LDS: four workgroups of them per CU at n = 2048
+constexpr int ALONE_S = 3;
 
 // Share generation inside the same launch: the workgroups after the last (item, chunk) pair build the
 // negated mask of one output ciphertext each and store it as one more partial ciphertext.
@@ -663,7 +821,7 @@ struct MaskJob {
 };
 
 // store(k, i, m): mask word i = tid + k NT of the evaluation domain, canonical.
-template <bool WIDE, class Store>
+template <bool WIDE, int S, class Store>
 __device__ __forceinline__ void mask_role(const RingTables &T, const MaskJob &mj, int item, u64 *bufA, u64 *bufB, Store store) {
     const int tid = threadIdx.x;
     const int b = item / mj.nout, O = item % mj.nout;
@@ -690,7 +848,7 @@ __device__ __forceinline__ void mask_role(const RingTables &T, const MaskJob &mj
     for (int s = tid; s < N; s += NT) {
         u64 v = 0;
         if (!is_first[s]) v = draw_uniform(p, mj.pbits, mj.mask_seed, kStreamMask, ((u64)b << 32) + ((u64)O << 16) + (u64)s);
-        put_slot(bufB, mj.slot_to_idx[s], v, small);
+        put_slot<S>(bufB, mj.slot_to_idx[s], v, small);
     }
     __syncthreads();
     // the first slot of every real row absorbs r minus the row's other slots.  The row sums are formed by all
@@ -713,7 +871,7 @@ __device__ __forceinline__ void mask_role(const RingTables &T, const MaskJob &mj
                 cur = t;
                 acc = 0;
             }
-            acc += get_slot(bufB, entry_idx[k], small);
+            acc += get_slot<S>(bufB, entry_idx[k], small);
         }
         if (cur >= 0) atomicAdd(&rowsum[cur], acc);
         __syncthreads();
@@ -723,28 +881,28 @@ __device__ __forceinline__ void mask_role(const RingTables &T, const MaskJob &mj
         if (first ? !has_row : row_ptr[t + 1] <= row_ptr[t]) continue;
         u64 rv = first ? row_r : mj.r[(size_t)b * mj.r_stride + row_rindex[t]];
         if (rv >= p) rv %= p;
-        put_slot(bufB, first ? row_place : first_idx[t], sub_mod(rv, sums ? rowsum[t] % p : 0, p), small);
+        put_slot<S>(bufB, first ? row_place : first_idx[t], sub_mod(rv, sums ? rowsum[t] % p : 0, p), small);
     }
     __syncthreads();
     // slots -> plaintext polynomial (inverse transform mod p) -> delta * m mod q -> evaluation domain mod q
     u64 a[PER];
-    slots_to_coefficients<WIDE>(a, bufA, bufB, mj.Tp, mj.small, tid);        // LDS phases A B A
+    slots_to_coefficients<WIDE, S>(a, bufA, bufB, mj.Tp, mj.small, tid);        // LDS phases A B A
 #pragma unroll
     for (int k = 0; k < PER; ++k) a[k] = mont<WIDE, true, true>(plain_words(a[k]), mj.delta, T.mont, BIAS);
-    forward_to_lds<WIDE, BIASED>(a, bufA, bufB, T, tid);             // LDS phases B A B A, result in bufA
+    forward_to_lds<WIDE, S, BIASED>(a, bufA, bufB, T, tid);             // LDS phases B A B A, result in bufA
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         const int i = tid + k * NT;
-        store(k, i, canonical<WIDE>(biased_words(bufA[pad(i)]), T));
+        store(k, i, canonical<WIDE>(biased_words(bufA[pad<S>(i)]), T));
     }
 }
 // ... as one more partial ciphertext of the item: minus the mask on c0
-template <bool WIDE>
+template <bool WIDE, int S>
 __device__ __forceinline__ void mask_partial(const PermJob &job, const RingTables &T, const MaskJob &mj, int item, u64 *bufA,
                                              u64 *bufB) {
     u64 *out = job.partial + ((size_t)item * job.slots + job.nchunks) * 2 * N;
     const u64 q = T.mod.q;
-    mask_role<WIDE>(T, mj, item, bufA, bufB, [&](int, int i, u64 m) {
+    mask_role<WIDE, S>(T, mj, item, bufA, bufB, [&](int, int i, u64 m) {
         out[i] = m ? q - m : 0;
         out[N + i] = 0;
     });
@@ -756,7 +914,7 @@ __device__ __forceinline__ void mask_partial(const PermJob &job, const RingTable
 // and he_fc 1000x512 on one input, where a mask is the longest workgroup, 40.9 -> 39.6 us.
 template <bool WIDE>
 __global__ __launch_bounds__(NT) void scmult_masked_ring(PermJob job, RingTables T, MaskJob mj, u64 *ct_out) {
-    __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
+    __shared__ u64 bufA[lds_words(ALONE_S)], bufB[lds_words(ALONE_S)];
     const int item = blockIdx.x;
     const u64 *c0 = job.ct_in + (size_t)item * job.in_item_stride, *c1 = c0 + N;
     const ulonglong2 *w = reinterpret_cast<const ulonglong2 *>(job.w2);
@@ -769,7 +927,7 @@ __global__ __launch_bounds__(NT) void scmult_masked_ring(PermJob job, RingTables
         x1[k] = unsign(mont<WIDE>(plain_words(c1[i]), ww, T.mont), T.mod.q);
     }
     u64 *out = ct_out + (size_t)item * 2 * N;
-    mask_role<WIDE>(T, mj, item, bufA, bufB, [&](int k, int i, u64 m) {
+    mask_role<WIDE, ALONE_S>(T, mj, item, bufA, bufB, [&](int k, int i, u64 m) {
         out[i] = sub_mod(x0[k], m, T.mod.q);
         out[N + i] = x1[k];
     });
@@ -797,15 +955,44 @@ __device__ __forceinline__ void item_and_chunk(const PermJob &job, int &item, in
 // takes L-1 forward transforms instead of L, for one more product (c1 (.) w at the rotated index).
 // From wire to wire, three digits: he_fc 128x1024 at batch 64 209 -> 162 us, 1000x2048 2669 -> 2195 us (the share of the
 // import and export transforms in that is 12 us); two digits and a special prime, 100x784 at batch 7: 92 -> 80 us.
+
+// a pair of a polynomial of which the start is uniform: a scalar base and 32 bits of offset, no address arithmetic
+__device__ __forceinline__ ulonglong2 pair_at(const ulonglong2 *base, int tid) {
+    typedef __attribute__((address_space(1))) const char global_char;
+    typedef __attribute__((address_space(1))) const u64 global_u64;
+    global_char *p = (global_char *)reinterpret_cast<uintptr_t>(base);
+    asm("" : "+s"(p));
+    global_u64 *at = (global_u64 *)(p + (unsigned)tid * 16u);
+    return make_ulonglong2(at[0], at[1]);
+}
+// What bounds the Perm kernel, in clocks of a CU per wavefront and rotation at n = 2048 with weights: the vector ALU, some 2730
+// instructions at one a clock, and behind it the vector cache, 113 loads at 16 clocks (178 before the first pass's
+// constants came through the scalar cache, the small levels through LDS, and c0 and c1 were read once, by the threads that own
+// them, instead of being gathered from memory), and the LDS, about 1250.  Most of what it waited for was the L2, where constants of 94 KiB a workgroup
+// come from (the vector cache has 32): requested a pass earlier than needed and pinned there, a wavefront's time in waits
+// fell from two fifths to one fifth.  From wire to wire, all of that: he_fc 1000x2048 at batch 64 2073 -> 1722 us, 128x1024 150 -> 135
+// us, 500x1024 at n = 4096, batch 8, 114 -> 103 us.
 //
-// Wavefronts per SIMD of the Perm kernel: what its LDS (two images and the parked coefficients) leaves room for, which
-// bounds the registers: three at n = 1024 and 2048 (168 registers; with weights at n = 2048 the compiler spills two of them,
-// 12 bytes a lane), two at 4096 (one workgroup), the workgroup's own four at 8192.
+// Wavefronts per SIMD: what its LDS (two images and the stash) leaves room for, which
+// bounds the registers: three at n = 1024 and 2048 (168 registers), two at 4096 (one workgroup), the workgroup's own four at 8192.
 constexpr int PERM_WAVES = LOGN <= 11 ? 3 : LOGN == 12 ? 2 : 4;
-//
+// What else fits: the padding of the images and the twiddle levels copied to LDS (TableCopy).  Three workgroups of n = 2048
+// take 53 504 bytes each of a CU's 160 KiB.
+constexpr int PERM_S = LOGN == 10 ? 5 : LOGN == 12 ? 3 : 4, PERM_LEVELS = LOGN == 10 ? 0 : LOGN == 11 ? 1 : 2;
+template <int L = PERM_LEVELS>
+__device__ __forceinline__ auto make_copy(ulonglong2 *at, const RingTables &T, int tid) {
+    if constexpr (L == 0) {
+        return NoCopy{};
+    } else {
+        TableCopy<L> copy(at);
+        copy.fill(T, tid);
+        return copy;
+    }
+}
+
 // Every product on this path is a multiplication by a constant (twiddles, encoded weights, key polynomials), so sums of
-// products stay in 64-bit registers: each product is below 0.99, a running sum is shrunk to 5 at most (1.1 when m is close to 2^60) and may take four
-// more products before it is shrunk again.
+// products stay in 64-bit registers: each product is below 0.99, a running sum is shrunk to 5 at most (1.1 when m is close to
+// 2^60) and may take four more products before it is shrunk again.
 // IN8: the inputs lie in blocks of eight coefficients (PermJob::in8_S), as the matrix-core product leaves them.
 // FEW: the launch leaves a CU at most two workgroups, so what counts is one workgroup's chain of dependent steps, not the
 // chip's issue rate: it takes up to 256 registers and requests all key pairs of a digit before its transform's last
@@ -815,27 +1002,31 @@ constexpr int PERM_WAVES = LOGN <= 11 ? 3 : LOGN == 12 ? 2 : 4;
 template <bool WIDE, bool HAS_W, bool IN8 = false, bool FEW = false>
 __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring(PermJob job, RingTables T, MaskJob mj,
                                                                                  int gadget_bits, int ndigits) {
-    __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
+    __shared__ u64 bufA[lds_words(PERM_S)], bufB[lds_words(PERM_S)];
+    __shared__ ulonglong2 tables[PERM_LEVELS ? TableCopy<PERM_LEVELS>::PAIRS : 1];
     // each thread parks its 8 coefficients here between digits (private slots, no barrier); at n = 8192 there is no LDS
     // left for them and they are variables: the workgroup's four wavefronts per SIMD leave 128 registers, and the
-    // compiler spills 97 with weights, 60 on blocks of eight and 46 on whole ciphertexts (304, 244 and 180 bytes of
+    // compiler spills 63 with weights, 72 on blocks of eight and 68 on whole ciphertexts (248, 292 and 276 bytes of
     // scratch a lane).  Against the any-n kernel he_fc 200x8192 at batch 40 takes 2904 us instead of 5562 all the same.
+    // Before that a rotation's c0 (.) w waits here, and c1 (.) w in bufB, for the threads that gather them.
     constexpr bool PARK = LOGN < 13;
-    __shared__ u64 stash[PARK ? N : 1];
+    __shared__ u64 stash[PARK ? lds_words(5) : 1];
     u64 coef[PARK ? 1 : PER];
-    // Key pairs of a digit requested before its transform's last pass, as many as the registers hold.  At n = 4096, two
-    // wavefronts per SIMD, three of eight: he_fc 500x1024 at batch 8 139.6 -> 135.7 us.  At three wavefronts per SIMD
-    // they gain nothing without weights and spill with them (he_fc 1000x2048 2185 -> 2270 us).
-    constexpr int AHEAD = FEW ? PER : LOGN == 12 ? 3 : 0;
+    // Key pairs of a digit requested before its transform's last pass, and of the last digit's products before their
+    // barrier: as many as the registers hold.  At three wavefronts per SIMD four and all eight instead of none: he_fc 1000x2048 at
+    // batch 64 1734 -> 1722 us, the 16x16x128 convolution at batch 16 279 -> 271 us; eight and eight spill, 2085 and 279 us.  At n = 4096,
+    // two wavefronts per SIMD, six: 103.2 us instead of 104.5 with three or eight.
+    constexpr int AHEAD = FEW ? PER : LOGN == 12 ? 6 : LOGN == 13 ? 0 : 4, EARLY = LOGN == 13 ? 0 : PER;
     const int tid = threadIdx.x;
     if ((int)blockIdx.x >= job.items * job.nchunks) {   // only launched when mj.enabled
-        mask_partial<WIDE>(job, T, mj, (int)blockIdx.x - job.items * job.nchunks, bufA, bufB);
+        mask_partial<WIDE, PERM_S>(job, T, mj, (int)blockIdx.x - job.items * job.nchunks, bufA, bufB);
         return;
     }
     int item, chunk;
     item_and_chunk(job, item, chunk);
     int g0, g1;
     chunk_range(chunk, job.nchunks, job.G, g0, g1);
+    const auto copy = make_copy(tables, T, tid);
     const MontQ q = T.mont;
     const u64 digit_mask = (1ull << gadget_bits) - 1;
     const size_t key_pairs = (size_t)ndigits * 2 * N;
@@ -871,73 +1062,104 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
             }
             continue;
         }
-        // LDS phases of one rotation: A B A (inverse), then B A B A per digit.  Consecutive phases use
-        // different buffers, which is what lets each exchange do with one barrier; a rotation ends on
-        // A and the next one starts on A, so that one boundary needs a barrier of its own.
-        __syncthreads();
+        // LDS phases of one rotation: the stash and B (gathers), A B A (inverse), then B A B A per digit.  Consecutive phases
+        // use different buffers, which is what lets each exchange do with one barrier.
         const ulonglong2 *key = reinterpret_cast<const ulonglong2 *>(job.keys2) + (size_t)job.key_idx[g] * key_pairs;
-        int src[PER];   // where the automorphism takes output index tid + (n/8) k from
-#pragma unroll
-        for (int k = 0; k < PER; ++k) src[k] = galois_index(tid + k * NT, gal);
-
-        // ScMult of c1 (8 consecutive coefficients per thread), then the inverse transform
+        // where the automorphism takes output index tid + (n/8) k from: with i = bitrev(tid) + bitrev3(k) the index is
+        // bitrev(((2i + 1) gal - 1) / 2)
+        const unsigned turn = (unsigned)((2 * bitrev(tid) + 1) * gal) >> 1;
+        auto source = [&](unsigned from, int k) {
+            const int k3 = ((k & 1) << 2) | (k & 2) | (k >> 2);
+            return (int)(__brev(from + (unsigned)(k3 * gal)) >> (32 - LOGN));
+        };
+        // ScMult of the thread's own eight coefficients.  c1 (.) w stays in registers for the inverse transform.
         u64 a[PER];
+        u32 from[4];     // where the automorphism takes the eight outputs from: word indices into an image, two to a register
         {
-            const ulonglong2 *c1v = reinterpret_cast<const ulonglong2 *>(IN8 ? c1 + (size_t)tid * S : c1 + 8 * tid);
+            const ulonglong2 *c0v = reinterpret_cast<const ulonglong2 *>(IN8 ? c0 + (size_t)tid * S : c0 + 8 * tid),
+                             *c1v = reinterpret_cast<const ulonglong2 *>(IN8 ? c1 + (size_t)tid * S : c1 + 8 * tid);
+            u64 *x0 = stash + pad<5>(8 * fresh(tid)), *x1 = bufB + pad<PERM_S>(8 * fresh(tid));
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const ulonglong2 cv = c1v[k];
+                a[2 * k] = cv.x;
+                a[2 * k + 1] = cv.y;
+                ulonglong2 c = make_ulonglong2(0, 0);
+                if (PARK) c = c0v[k];
                 if (HAS_W) {     // the copy in ownership order: 64 lanes read 1 KiB of whole lines
                     const ulonglong2 wa = *reinterpret_cast<const ulonglong2 *>(wo + (wmid + (unsigned)((2 * k - 4) * 1024))),
                                      wb = *reinterpret_cast<const ulonglong2 *>(wo + (wmid + (unsigned)((2 * k - 3) * 1024)));
                     a[2 * k] = mont<WIDE>(plain_words(cv.x), wa, q);
                     a[2 * k + 1] = mont<WIDE>(plain_words(cv.y), wb, q);
-                } else {
-                    a[2 * k] = cv.x;
-                    a[2 * k + 1] = cv.y;
+                    if (PARK) {
+                        c.x = mont<WIDE>(plain_words(c.x), wa, q);
+                        c.y = mont<WIDE>(plain_words(c.y), wb, q);
+                    }
+                }
+                if (PARK) {
+                    x0[2 * k] = c.x;
+                    x0[2 * k + 1] = c.y;
+                    x1[2 * k] = a[2 * k];
+                    x1[2 * k + 1] = a[2 * k + 1];
                 }
             }
         }
-        inverse_in_regs<WIDE>(a, bufA, bufB, T, tid);
+        const ulonglong2 *kb_last = key + (size_t)(2 * (ndigits - 1)) * N, *ka_last = kb_last + N;
+        ulonglong2 kbl[EARLY ? EARLY : 1], kal[EARLY ? EARLY : 1];
 #pragma unroll
-        for (int k = 0; k < PER; ++k) (PARK ? stash[tid + k * NT] : coef[PARK ? 0 : k]) = a[k];
-
+        for (int k = 0; k < EARLY; ++k) {
+            kbl[k] = pair_at(kb_last + k * NT, tid);
+            kal[k] = pair_at(ka_last + k * NT, tid);
+        }
+        if (EARLY) pin_loads();
+        __syncthreads();
         // the c0 part, permuted c0 (.) w, and the last digit's products: with the folded keys
         // (key_pack_kernel) they are products of the rotated c1 (.) w itself
         {
-            const ulonglong2 *kb = key + (size_t)(2 * (ndigits - 1)) * N, *ka = kb + N;
 #pragma unroll
             for (int k = 0; k < PER; ++k) {
-                const int i = tid + k * NT;
+                const int src = source(turn, k);
                 u64 d;
-                if (HAS_W) {
-                    const ulonglong2 ww = w[src[k]];
-                    sum0[k] = mont<WIDE, true>(plain_words(c0[src[k]]), ww, q, sum0[k]);
-                    d = mont<WIDE>(plain_words(c1[src[k]]), ww, q);
+                if (PARK) {
+                    const int at = pad<PERM_S>(src);
+                    from[k & 3] = k < 4 ? (u32)at : from[k & 3] | (u32)at << 16;
+                    sum0[k] += stash[pad<5>(src)];
+                    d = bufB[at];
+                } else if (from[k & 3] = k < 4 ? (u32)pad<PERM_S>(src) : from[k & 3] | (u32)pad<PERM_S>(src) << 16; HAS_W) {
+                    const ulonglong2 ww = w[src];
+                    sum0[k] = mont<WIDE, true>(plain_words(c0[src]), ww, q, sum0[k]);
+                    d = mont<WIDE>(plain_words(c1[src]), ww, q);
                 } else {
-                    sum0[k] += at(c0, src[k]);
-                    d = at(c1, src[k]);
+                    sum0[k] += at(c0, src);
+                    d = at(c1, src);
                 }
-                const ulonglong2 b = kb[i], aa = ka[i];
+                const ulonglong2 b = k < EARLY ? kbl[k < EARLY ? k : 0] : pair_at(kb_last + k * NT, tid),
+                                 aa = k < EARLY ? kal[k < EARLY ? k : 0] : pair_at(ka_last + k * NT, tid);
                 const Words y = plain_words(d);
-                sum0[k] = mont<WIDE, true>(y, b, q, sum0[k]);
-                sum1[k] = mont<WIDE, true>(y, aa, q, sum1[k]);
+                add_product<WIDE>(sum0[k], y, b, q);
+                add_product<WIDE>(sum1[k], y, aa, q);
             }
         }
+        inverse_in_regs<WIDE, PERM_S, PARK>(a, bufA, bufB, T, tid, copy);
+#pragma unroll
+        for (int k = 0; k < PER; ++k) (PARK ? stash[tid + k * NT] : coef[PARK ? 0 : k]) = a[k];
+
         int pending = 2;   // products added to sum0 since it was last shrunk
         for (int j = 0; j < ndigits - 1; ++j) {
 #pragma unroll
             for (int k = 0; k < PER; ++k) a[k] = ((PARK ? stash[tid + k * NT] : coef[PARK ? 0 : k]) >> (j * gadget_bits)) & digit_mask;
             const ulonglong2 *kb = key + (size_t)(2 * j) * N, *ka = kb + N;
             ulonglong2 kbv[AHEAD ? AHEAD : 1], kav[AHEAD ? AHEAD : 1];
-            forward_to_lds<WIDE>(a, bufA, bufB, T, tid, gadget_bits <= 31, [&] {
+            forward_to_lds<WIDE, PERM_S, PLAIN>(a, bufA, bufB, T, tid, gadget_bits <= 31, copy, [&] {
 #pragma unroll
                 for (int k = 0; k < AHEAD; ++k) {
-                    kbv[k] = kb[tid + k * NT];
-                    kav[k] = ka[tid + k * NT];
+                    kbv[k] = pair_at(kb + k * NT, tid);
+                    kav[k] = pair_at(ka + k * NT, tid);
                 }
+                if (AHEAD) pin_loads();
             });
-            if (pending == 4) {
+            if (pending == 4) {       // from four digits on
+                asm volatile("");     // not worth doing in advance
 #pragma unroll
                 for (int k = 0; k < PER; ++k) {
                     sum0[k] = shrink(sum0[k], q);
@@ -947,11 +1169,12 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
             }
 #pragma unroll
             for (int k = 0; k < PER; ++k) {
-                const int i = tid + k * NT;
-                const Words d = biased_words(bufA[pad(src[k])]);
-                const ulonglong2 b = k < AHEAD ? kbv[k < AHEAD ? k : 0] : kb[i], aa = k < AHEAD ? kav[k < AHEAD ? k : 0] : ka[i];
-                sum0[k] = mont<WIDE, true>(d, b, q, sum0[k]);       // the sum rides on the product
-                sum1[k] = mont<WIDE, true>(d, aa, q, sum1[k]);
+                const u32 at = k < 4 ? from[k] & 0xffff : from[k & 3] >> 16;
+                const Words d = biased_words(bufA[at]);
+                const ulonglong2 b = k < AHEAD ? kbv[k < AHEAD ? k : 0] : pair_at(kb + k * NT, tid),
+                                 aa = k < AHEAD ? kav[k < AHEAD ? k : 0] : pair_at(ka + k * NT, tid);
+                add_product<WIDE>(sum0[k], d, b, q);       // the sum rides on the product
+                add_product<WIDE>(sum1[k], d, aa, q);
             }
             ++pending;
         }
@@ -980,7 +1203,7 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
 template <bool WIDE>
 __global__ __launch_bounds__(NT) void decperm_ring(const u64 *ct_in, u64 *digits, RingTables T, int gadget_bits,
                                                    int stored) {
-    __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
+    __shared__ u64 bufA[lds_words(ALONE_S)], bufB[lds_words(ALONE_S)];
     const int tid = threadIdx.x;
     const int ct = blockIdx.x / stored, j = blockIdx.x % stored;
     const u64 *c1 = ct_in + (size_t)ct * 2 * N + N;
@@ -992,14 +1215,14 @@ __global__ __launch_bounds__(NT) void decperm_ring(const u64 *ct_in, u64 *digits
         a[2 * k] = cv.x;
         a[2 * k + 1] = cv.y;
     }
-    inverse_in_regs<WIDE>(a, bufA, bufB, T, tid);      // LDS phases A B A
+    inverse_in_regs<WIDE, ALONE_S>(a, bufA, bufB, T, tid);      // LDS phases A B A
     const u64 digit_mask = (1ull << gadget_bits) - 1;
 #pragma unroll
     for (int k = 0; k < PER; ++k) a[k] = (a[k] >> (j * gadget_bits)) & digit_mask;
-    forward_to_lds<WIDE>(a, bufA, bufB, T, tid, gadget_bits <= 31);       // LDS phases B A B A, ends on a barrier
+    forward_to_lds<WIDE, ALONE_S>(a, bufA, bufB, T, tid, gadget_bits <= 31);       // LDS phases B A B A, ends on a barrier
     u64 *out = digits + ((size_t)ct * stored + j) * N;
 #pragma unroll
-    for (int k = 0; k < PER; ++k) out[tid + k * NT] = bufA[pad(tid + k * NT)];
+    for (int k = 0; k < PER; ++k) out[tid + k * NT] = bufA[pad<ALONE_S>(tid + k * NT)];
 }
 
 // HstPerm: one workgroup per (ciphertext, tap).  c0 and the digits are read through the automorphism's index
@@ -1184,7 +1407,7 @@ __global__ __launch_bounds__(PACK_THREADS) void hstperm_pack_ring(const u64 *ct_
 // Inputs as the any-n kernel takes them: below 4q forward, below 2q inverse.
 template <bool WIDE, bool INVERSE>
 __global__ __launch_bounds__(NT) void ntt_ring(const u64 *src, u64 *dst, RingTables T) {
-    __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
+    __shared__ u64 bufA[lds_words(ALONE_S)], bufB[lds_words(ALONE_S)];
     const int tid = threadIdx.x;
     src += (size_t)blockIdx.x * N;
     dst += (size_t)blockIdx.x * N;
@@ -1192,20 +1415,20 @@ __global__ __launch_bounds__(NT) void ntt_ring(const u64 *src, u64 *dst, RingTab
     if (INVERSE) {
         // coalesced reads, then through LDS to the eight consecutive coefficients a thread starts from
 #pragma unroll
-        for (int k = 0; k < PER; ++k) bufB[pad(tid + k * NT)] = csub_dev(src[tid + k * NT], T.mod.q);
+        for (int k = 0; k < PER; ++k) bufB[pad<ALONE_S>(tid + k * NT)] = csub_dev(src[tid + k * NT], T.mod.q);
         __syncthreads();
-        const u64 *pi = bufB + pad(tid << 3);
+        const u64 *pi = bufB + pad<ALONE_S>(tid << 3);
 #pragma unroll
         for (int k = 0; k < PER; ++k) a[k] = pi[k];
-        inverse_in_regs<WIDE>(a, bufA, bufB, T, tid);       // LDS phases A B A; the reads of bufB above precede its barriers
+        inverse_in_regs<WIDE, ALONE_S>(a, bufA, bufB, T, tid);       // LDS phases A B A; the reads of bufB above precede its barriers
 #pragma unroll
         for (int k = 0; k < PER; ++k) dst[tid + k * NT] = a[k];
     } else {
 #pragma unroll
         for (int k = 0; k < PER; ++k) a[k] = shrink(src[tid + k * NT], T.mont);
-        forward_to_lds<WIDE>(a, bufA, bufB, T, tid);
+        forward_to_lds<WIDE, ALONE_S>(a, bufA, bufB, T, tid);
 #pragma unroll
-        for (int k = 0; k < PER; ++k) dst[tid + k * NT] = canonical<WIDE>(biased_words(bufA[pad(tid + k * NT)]), T);
+        for (int k = 0; k < PER; ++k) dst[tid + k * NT] = canonical<WIDE>(biased_words(bufA[pad<ALONE_S>(tid + k * NT)]), T);
     }
 }
 
@@ -1216,34 +1439,34 @@ template <bool WIDE>
 __global__ __launch_bounds__(NT, 4) void encrypt_ring(const u64 *slots, const u64 *seeds, const u64 *s_hat, u64 *ct_out,
                                                    RingTables T, RingTables Tp, SmallTables small, const int *slot_to_idx, GaussCdf cdf,
                                                    int qbits, ulonglong2 delta) {
-    __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
+    __shared__ u64 bufA[lds_words(ALONE_S)], bufB[lds_words(ALONE_S)];
     const int tid = threadIdx.x;
     const u64 q = T.mod.q, p = Tp.mod.q, seed = seeds[blockIdx.x];
     const u64 *sl = slots + (size_t)blockIdx.x * N;
     u64 *c0 = ct_out + (size_t)blockIdx.x * 2 * N, *c1 = c0 + N;
     for (int s = tid; s < N; s += NT) {
         const u64 v = sl[s];
-        put_slot(bufB, slot_to_idx[s], v >= p ? v % p : v, small.tw != nullptr);
+        put_slot<ALONE_S>(bufB, slot_to_idx[s], v >= p ? v % p : v, small.tw != nullptr);
     }
     __syncthreads();
     u64 a[PER];
-    slots_to_coefficients<WIDE>(a, bufA, bufB, Tp, small, tid);      // m, coefficient tid + (n/8) k, canonical mod p
+    slots_to_coefficients<WIDE, ALONE_S>(a, bufA, bufB, Tp, small, tid);      // m, coefficient tid + (n/8) k, canonical mod p
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         const int e = draw_gauss_cdf(cdf, seed, kStreamCtE, (u64)(tid + k * NT));
         a[k] = mont<WIDE, true, true>(plain_words(a[k]), delta, T.mont, BIAS + (u64)(i64)e);
     }
-    forward_to_lds<WIDE, BIASED>(a, bufA, bufB, T, tid);            // (e + delta m) in the evaluation domain, in bufA
+    forward_to_lds<WIDE, ALONE_S, BIASED>(a, bufA, bufB, T, tid);            // (e + delta m) in the evaluation domain, in bufA
     u64 t0[PER];
 #pragma unroll
-    for (int k = 0; k < PER; ++k) t0[k] = canonical<WIDE>(biased_words(bufA[pad(tid + k * NT)]), T);
+    for (int k = 0; k < PER; ++k) t0[k] = canonical<WIDE>(biased_words(bufA[pad<ALONE_S>(tid + k * NT)]), T);
 #pragma unroll
     for (int k = 0; k < PER; ++k) a[k] = draw_uniform(q, qbits, seed, kStreamCtA, (u64)(tid + k * NT));
-    forward_to_lds<WIDE>(a, bufA, bufB, T, tid);            // its first barrier comes after every read of bufA above
+    forward_to_lds<WIDE, ALONE_S>(a, bufA, bufB, T, tid);            // its first barrier comes after every read of bufA above
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         const int i = tid + k * NT;
-        const u64 ah = canonical<WIDE>(biased_words(bufA[pad(i)]), T);
+        const u64 ah = canonical<WIDE>(biased_words(bufA[pad<ALONE_S>(i)]), T);
         c1[i] = ah;
         c0[i] = sub_mod(t0[k], mul_mod(ah, s_hat[i], T.mod), q);
     }
@@ -1252,7 +1475,7 @@ __global__ __launch_bounds__(NT, 4) void encrypt_ring(const u64 *slots, const u6
 template <bool WIDE>
 __global__ __launch_bounds__(NT) void decrypt_ring(const u64 *ct_in, const u64 *s_hat, u64 *slots, RingTables T,
                                                    RingTables Tp, SmallTables small, const int *slot_to_idx, u64 q_inv64) {
-    __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
+    __shared__ u64 bufA[lds_words(ALONE_S)], bufB[lds_words(ALONE_S)];
     const int tid = threadIdx.x;
     const u64 q = T.mod.q, p = Tp.mod.q;
     const u64 *c0 = ct_in + (size_t)blockIdx.x * 2 * N, *c1 = c0 + N;
@@ -1262,7 +1485,7 @@ __global__ __launch_bounds__(NT) void decrypt_ring(const u64 *ct_in, const u64 *
         const int i = 8 * tid + k;
         a[k] = add_mod(c0[i], mul_mod(c1[i], s_hat[i], T.mod), q);
     }
-    inverse_in_regs<WIDE>(a, bufA, bufB, T, tid);           // c0 + c1 s, coefficient tid + (n/8) k, canonical
+    inverse_in_regs<WIDE, ALONE_S>(a, bufA, bufB, T, tid);           // c0 + c1 s, coefficient tid + (n/8) k, canonical
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         const u128 t = (u128)p * a[k] + (q >> 1);
@@ -1277,10 +1500,10 @@ __global__ __launch_bounds__(NT) void decrypt_ring(const u64 *ct_in, const u64 *
 #pragma unroll
         for (int k = 0; k < PER; ++k) v[k] = (u32)a[k];
         forward_small_to_lds(v, A, reinterpret_cast<u32 *>(bufB), small, tid);
-        for (int s = tid; s < N; s += NT) out[s] = reduce_small(A[pad(slot_to_idx[s])], small);
+        for (int s = tid; s < N; s += NT) out[s] = reduce_small(A[pad32(slot_to_idx[s])], small);
     } else {
-        forward_to_lds<WIDE>(a, bufA, bufB, Tp, tid);
-        for (int s = tid; s < N; s += NT) out[s] = canonical<WIDE>(biased_words(bufA[pad(slot_to_idx[s])]), Tp);
+        forward_to_lds<WIDE, ALONE_S>(a, bufA, bufB, Tp, tid);
+        for (int s = tid; s < N; s += NT) out[s] = canonical<WIDE>(biased_words(bufA[pad<ALONE_S>(slot_to_idx[s])]), Tp);
     }
 }
 
@@ -1301,14 +1524,15 @@ struct SpecialJob {
 template <bool WIDE, bool HAS_W, bool IN8 = false>
 __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob job, RingTables T, SpecialJob S, MaskJob mj,
                                                                       int gadget_bits, int ndigits) {
-    __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
+    constexpr int PS = 5;
+    __shared__ u64 bufA[lds_words(PS)], bufB[lds_words(PS)];
     __shared__ u64 stash[N];
     // Sums of the lifted remainders (coefficient domain modulo q, canonical, index tid + (n/8) k): 15 of a thread's 16
     // words live in LDS slots of its own (no barrier), which is what two workgroups per CU leave room for.
     __shared__ u64 Rl[15 * NT];
     const int tid = threadIdx.x;
     if ((int)blockIdx.x >= job.items * job.nchunks) {   // only launched when mj.enabled
-        mask_partial<WIDE>(job, T, mj, (int)blockIdx.x - job.items * job.nchunks, bufA, bufB);
+        mask_partial<WIDE, PS>(job, T, mj, (int)blockIdx.x - job.items * job.nchunks, bufA, bufB);
         return;
     }
     int item, chunk;
@@ -1374,7 +1598,7 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
                 }
             }
         }
-        inverse_in_regs<WIDE>(a, bufA, bufB, T, tid);
+        inverse_in_regs<WIDE, PS>(a, bufA, bufB, T, tid);
 #pragma unroll
         for (int k = 0; k < PER; ++k) stash[tid + k * NT] = a[k];
         // the c0 part, times P, and the last digit's products modulo q (folded keys: the rotated c1 (.) w itself)
@@ -1413,7 +1637,7 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
                         kav[k] = ka[tid + k * NT];
                     }
                 };
-                forward_to_lds<WIDE>(a, bufA, bufB, T, tid, gadget_bits <= 31, ahead);
+                forward_to_lds<WIDE, PS>(a, bufA, bufB, T, tid, gadget_bits <= 31, NoCopy{}, ahead);
                 if (pending == 4) {
 #pragma unroll
                     for (int k = 0; k < PER; ++k) {
@@ -1425,7 +1649,7 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
 #pragma unroll
                 for (int k = 0; k < PER; ++k) {
                     const int i = tid + k * NT;
-                    const Words d = biased_words(bufA[pad(src[k])]);
+                    const Words d = biased_words(bufA[pad<PS>(src[k])]);
                     const ulonglong2 b = k < AHEAD ? kbv[k < AHEAD ? k : 0] : kb[i], aa = k < AHEAD ? kav[k < AHEAD ? k : 0] : ka[i];
                     sum0[k] = mont<WIDE, true>(d, b, q, sum0[k]);
                     sum1[k] = mont<WIDE, true>(d, aa, q, sum1[k]);
@@ -1444,7 +1668,7 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
                     kav[k] = kaP[tid + k * NT];
                 }
             };
-            forward_to_lds<WIDE>(a, bufA, bufB, S.TP, tid, gadget_bits <= 31, ahead);
+            forward_to_lds<WIDE, PS>(a, bufA, bufB, S.TP, tid, gadget_bits <= 31, NoCopy{}, ahead);
             if (pendingP == 4) {
 #pragma unroll
                 for (int k = 0; k < PER; ++k) {
@@ -1456,7 +1680,7 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
 #pragma unroll
             for (int k = 0; k < PER; ++k) {
                 const int i = tid + k * NT;
-                const Words d = biased_words(bufA[pad(src[k])]);
+                const Words d = biased_words(bufA[pad<PS>(src[k])]);
                 const ulonglong2 b = k < AHEAD ? kbv[k < AHEAD ? k : 0] : kbP[i], aa = k < AHEAD ? kav[k < AHEAD ? k : 0] : kaP[i];
                 tp0[k] = mont<WIDE, true>(d, b, qP, tp0[k]);
                 tp1[k] = mont<WIDE, true>(d, aa, qP, tp1[k]);
@@ -1473,14 +1697,14 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
 #pragma unroll
-            for (int k = 0; k < PER; ++k) bufB[pad(tid + k * NT)] = mont<WIDE, false, true>(plain_words(h ? tp1[k] : tp0[k]), S.TP.one, qP);
+            for (int k = 0; k < PER; ++k) bufB[pad<PS>(tid + k * NT)] = mont<WIDE, false, true>(plain_words(h ? tp1[k] : tp0[k]), S.TP.one, qP);
             __syncthreads();
             {
-                const u64 *pi = bufB + pad(tid << 3);
+                const u64 *pi = bufB + pad<PS>(tid << 3);
 #pragma unroll
                 for (int k = 0; k < PER; ++k) a[k] = pi[k];
             }
-            inverse_in_regs<WIDE>(a, bufA, bufB, S.TP, tid);
+            inverse_in_regs<WIDE, PS>(a, bufA, bufB, S.TP, tid);
 #pragma unroll
             for (int k = 0; k < PER; ++k) {
                 const u64 r = csub_dev(a[k], T.mod.q);
@@ -1500,11 +1724,11 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
         u64 a[PER];
 #pragma unroll
         for (int k = 0; k < PER; ++k) a[k] = (h && k == PER - 1) ? Rlast : Rl[(h * PER + k) * NT + tid];
-        forward_to_lds<WIDE>(a, bufA, bufB, T, tid);
+        forward_to_lds<WIDE, PS>(a, bufA, bufB, T, tid);
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
             const int i = tid + k * NT;
-            const u64 minus = shrink(bufA[pad(i)], q) - (h ? sum1[k] : sum0[k]);
+            const u64 minus = shrink(bufA[pad<PS>(i)], q) - (h ? sum1[k] : sum0[k]);
             out[h * N + i] = unsign(mont<WIDE, false, true>(biased_words(minus), S.minus_Pinv, q), T.mod.q);
         }
     }
@@ -1516,7 +1740,7 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
 template <bool WIDE>
 __global__ __launch_bounds__(NT) void decperm_special_ring(const u64 *ct_in, u64 *digits, RingTables T, RingTables TP,
                                                            int gadget_bits, int ndigits) {
-    __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
+    __shared__ u64 bufA[lds_words(ALONE_S)], bufB[lds_words(ALONE_S)];
     const int tid = threadIdx.x;
     const int per_ct = 2 * ndigits - 1, ct = blockIdx.x / per_ct, v = blockIdx.x % per_ct;
     const int m = v == per_ct - 1 ? 1 : v & 1, j = v >> 1;
@@ -1529,15 +1753,15 @@ __global__ __launch_bounds__(NT) void decperm_special_ring(const u64 *ct_in, u64
         a[2 * k] = cv.x;
         a[2 * k + 1] = cv.y;
     }
-    inverse_in_regs<WIDE>(a, bufA, bufB, T, tid);
+    inverse_in_regs<WIDE, ALONE_S>(a, bufA, bufB, T, tid);
     const u64 digit_mask = (1ull << gadget_bits) - 1;
 #pragma unroll
     for (int k = 0; k < PER; ++k) a[k] = (a[k] >> (j * gadget_bits)) & digit_mask;
-    if (m) forward_to_lds<WIDE>(a, bufA, bufB, TP, tid, gadget_bits <= 31);
-    else forward_to_lds<WIDE>(a, bufA, bufB, T, tid, gadget_bits <= 31);
+    if (m) forward_to_lds<WIDE, ALONE_S>(a, bufA, bufB, TP, tid, gadget_bits <= 31);
+    else forward_to_lds<WIDE, ALONE_S>(a, bufA, bufB, T, tid, gadget_bits <= 31);
     u64 *out = digits + (((size_t)ct * ndigits + j) * 2 + m) * N;
 #pragma unroll
-    for (int k = 0; k < PER; ++k) out[tid + k * NT] = bufA[pad(tid + k * NT)];
+    for (int k = 0; k < PER; ++k) out[tid + k * NT] = bufA[pad<ALONE_S>(tid + k * NT)];
 }
 
 // HstPerm: one workgroup per (ciphertext, tap): inner products in both moduli from the stored digits, the sums
@@ -1547,7 +1771,7 @@ template <bool WIDE>
 __global__ __launch_bounds__(NT, 3) void hstperm_special_ring(const u64 *ct_in, const u64 *digits, TermList terms,
                                                            const u64 *keys2, u64 *xrot, RingTables T, SpecialJob S,
                                                            int ndigits) {
-    __shared__ u64 bufA[LDS_WORDS], bufB[LDS_WORDS];
+    __shared__ u64 bufA[lds_words(ALONE_S)], bufB[lds_words(ALONE_S)];
     const int tid = threadIdx.x;
     const int b = blockIdx.x / terms.nterm, e = blockIdx.x % terms.nterm;
     const size_t ct = (size_t)b * terms.nin + terms.ct[e];
@@ -1598,21 +1822,21 @@ __global__ __launch_bounds__(NT, 3) void hstperm_special_ring(const u64 *ct_in, 
         u64 a[PER];
         // LDS phases: B (ownership change), A B A (inverse), B A B A (forward), then reads of A
 #pragma unroll
-        for (int k = 0; k < PER; ++k) bufB[pad(tid + k * NT)] = mont<WIDE, false, true>(plain_words(tp[k]), S.TP.one, qP);
+        for (int k = 0; k < PER; ++k) bufB[pad<ALONE_S>(tid + k * NT)] = mont<WIDE, false, true>(plain_words(tp[k]), S.TP.one, qP);
         __syncthreads();
         {
-            const u64 *pi = bufB + pad(tid << 3);
+            const u64 *pi = bufB + pad<ALONE_S>(tid << 3);
 #pragma unroll
             for (int k = 0; k < PER; ++k) a[k] = pi[k];
         }
-        inverse_in_regs<WIDE>(a, bufA, bufB, S.TP, tid);
+        inverse_in_regs<WIDE, ALONE_S>(a, bufA, bufB, S.TP, tid);
 #pragma unroll
         for (int k = 0; k < PER; ++k) a[k] = csub_dev(a[k], T.mod.q);
-        forward_to_lds<WIDE>(a, bufA, bufB, T, tid);
+        forward_to_lds<WIDE, ALONE_S>(a, bufA, bufB, T, tid);
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
             const int i = tid + k * NT;
-            const u64 minus = shrink(bufA[pad(i)], q) - sum[k];
+            const u64 minus = shrink(bufA[pad<ALONE_S>(i)], q) - sum[k];
             out[h * N + i] = unsign(mont<WIDE, false, true>(biased_words(minus), S.minus_Pinv, q), T.mod.q);
         }
     }
