@@ -118,9 +118,8 @@ __device__ __forceinline__ u64 mont_reduce(u64 L, u64 H, const MontQ &q) {
     }
     return H;
 }
-// w y, or x + w y.  UNIFORM: the constant is the same for all lanes and sits in scalar registers.  IN_PLACE: nobody needs x
-// afterwards (a running sum), the result takes its registers.
-template <bool WIDE, bool ADD = false, bool UNIFORM = false, bool IN_PLACE = false>
+// w y, or x + w y.  UNIFORM: the constant is the same for all lanes and sits in scalar registers.
+template <bool WIDE, bool ADD = false, bool UNIFORM = false>
 __device__ __forceinline__ u64 mont(Words y, const ulonglong2 w, const MontQ &q, u64 x = 0) {
     const u32 a0 = (u32)w.x, a1 = (u32)(w.x >> 32), b0 = (u32)w.y, b1 = (u32)(w.y >> 32);
     u64 L, H;
@@ -132,16 +131,7 @@ __device__ __forceinline__ u64 mont(Words y, const ulonglong2 w, const MontQ &q,
         : "=&v"(L), "=&v"(H)                                                                                          \
         : "v"(y.lo), "v"(y.hi), WHERE(a0), WHERE(a1), WHERE(b0), WHERE(b1) __VA_ARGS__                                \
         : "vcc")
-    if (!UNIFORM && ADD && IN_PLACE) {
-        H = x;
-        asm("v_mad_i64_i32 %0, vcc, %2, %4, 0\n\t"
-            "v_mad_i64_i32 %1, vcc, %2, %5, %1\n\t"
-            "v_mad_i64_i32 %0, vcc, %3, %6, %0\n\t"
-            "v_mad_i64_i32 %1, vcc, %3, %7, %1"
-            : "=&v"(L), "+v"(H)
-            : "v"(y.lo), "v"(y.hi), "v"(a0), "v"(a1), "v"(b0), "v"(b1)
-            : "vcc");
-    } else if (UNIFORM) {
+    if (UNIFORM) {
         if (ADD) GALA_MONT("%8", "s", , "v"(x));
         else GALA_MONT("0", "s");
     } else {
@@ -151,33 +141,40 @@ __device__ __forceinline__ u64 mont(Words y, const ulonglong2 w, const MontQ &q,
 #undef GALA_MONT
     return mont_reduce<WIDE>(L, H, q);
 }
-template <bool WIDE>
-__device__ __forceinline__ void add_product(u64 &sum, Words y, const ulonglong2 w, const MontQ &q) {
-    sum = mont<WIDE, true, false, true>(y, w, q, sum);
-}
 // Two products at once, xa + wa ya and xb + wb yb, their instructions in turn: a wavefront alone on its SIMD issues a
 // multiply-add every other slot only and waits for each result, so what it finds to do in between counts.  Butterflies of
 // one wavefront per SIMD 1.15 times as fast as one by one, of two 1.03 times, of three the same.
-template <bool WIDE, bool UNIFORM = false>
+// KIND: products alone, added to xa and xb, or added to what ra and rb hold (running sums, nobody needs them afterwards).
+enum Addend { NONE, ADD, IN_PLACE };
+template <bool WIDE, bool UNIFORM = false, Addend KIND = ADD>
 __device__ __forceinline__ void mont2(u64 &ra, u64 &rb, Words ya, const ulonglong2 wa, Words yb, const ulonglong2 wb, const MontQ &q,
-                                      u64 xa, u64 xb) {
+                                      u64 xa = 0, u64 xb = 0) {
     u64 L, H, M, I;
-#define GALA_MONT2(WHERE)                                                                                             \
+#define GALA_MONT2(WHERE, OUT, XA, XB, ...)                                                                           \
     asm("v_mad_i64_i32 %0, vcc, %4, %8, 0\n\t"                                                                       \
         "v_mad_i64_i32 %2, vcc, %6, %12, 0\n\t"                                                                      \
-        "v_mad_i64_i32 %1, vcc, %4, %9, %16\n\t"                                                                     \
-        "v_mad_i64_i32 %3, vcc, %6, %13, %17\n\t"                                                                    \
+        "v_mad_i64_i32 %1, vcc, %4, %9, " XA "\n\t"                                                                  \
+        "v_mad_i64_i32 %3, vcc, %6, %13, " XB "\n\t"                                                                 \
         "v_mad_i64_i32 %0, vcc, %5, %10, %0\n\t"                                                                     \
         "v_mad_i64_i32 %2, vcc, %7, %14, %2\n\t"                                                                     \
         "v_mad_i64_i32 %1, vcc, %5, %11, %1\n\t"                                                                     \
         "v_mad_i64_i32 %3, vcc, %7, %15, %3"                                                                          \
-        : "=&v"(L), "=&v"(H), "=&v"(M), "=&v"(I)                                                                      \
+        : "=&v"(L), OUT(H), "=&v"(M), OUT(I)                                                                          \
         : "v"(ya.lo), "v"(ya.hi), "v"(yb.lo), "v"(yb.hi), WHERE((u32)wa.x), WHERE((u32)(wa.x >> 32)), WHERE((u32)wa.y), \
-          WHERE((u32)(wa.y >> 32)), WHERE((u32)wb.x), WHERE((u32)(wb.x >> 32)), WHERE((u32)wb.y), WHERE((u32)(wb.y >> 32)), \
-          "v"(xa), "v"(xb)                                                                                            \
+          WHERE((u32)(wa.y >> 32)), WHERE((u32)wb.x), WHERE((u32)(wb.x >> 32)), WHERE((u32)wb.y),                     \
+          WHERE((u32)(wb.y >> 32)) __VA_ARGS__                                                                        \
         : "vcc")
-    if (UNIFORM) GALA_MONT2("s");
-    else GALA_MONT2("v");
+    if (KIND == IN_PLACE) {        // the first operands are tied to their outputs: %4 to %15 are still the inputs
+        H = ra;
+        I = rb;
+        GALA_MONT2("v", "+&v", "%1", "%3");
+    } else if (UNIFORM) {
+        if (KIND == ADD) GALA_MONT2("s", "=&v", "%16", "%17", , "v"(xa), "v"(xb));
+        else GALA_MONT2("s", "=&v", "0", "0");
+    } else {
+        if (KIND == ADD) GALA_MONT2("v", "=&v", "%16", "%17", , "v"(xa), "v"(xb));
+        else GALA_MONT2("v", "=&v", "0", "0");
+    }
 #undef GALA_MONT2
     int k, l;
     if (WIDE) {
@@ -447,6 +444,12 @@ template <bool WIDE>
 __device__ __forceinline__ u64 canonical(Words y, const RingTables &T) {
     return unsign(mont<WIDE, false, true>(y, T.one, T.mont), T.mod.q);
 }
+template <bool WIDE>
+__device__ __forceinline__ void canonical2(u64 &ra, u64 &rb, Words ya, Words yb, const RingTables &T) {
+    mont2<WIDE, true, NONE>(ra, rb, ya, T.one, yb, T.one, T.mont);
+    ra = unsign(ra, T.mod.q);
+    rb = unsign(rb, T.mod.q);
+}
 
 // The thread id goes through an empty asm so that the address arithmetic of a transform is redone
 // where it is used instead of being hoisted out of the rotation loop into long-lived registers.
@@ -499,8 +502,10 @@ struct NothingAhead {
     __device__ __forceinline__ void operator()() const {}
 };
 enum Entry { PLAIN, BIASED };
-// S: the padding of the images.  tab: the kernel's copy of the small levels in LDS (TableCopy), or nothing.
-template <bool WIDE, int S, Entry IN = PLAIN, class Copy = NoCopy, class Ahead = NothingAhead>
+// S: the padding of the images.  copy: the kernel's copy of the small levels in LDS (TableCopy), or nothing.
+// ALONE: the launch leaves registers idle and a workgroup's chain of steps is what it takes: all constants are requested at
+// the start, one trip to the L2 for a transform instead of one a pass.
+template <bool WIDE, int S, Entry IN = PLAIN, bool ALONE = false, class Copy = NoCopy, class Ahead = NothingAhead>
 __device__ __forceinline__ void forward_to_lds(u64 (&a)[8], u64 *res, u64 *other, const RingTables &T, int tid_,
                                                bool digits = false, Copy copy = Copy{}, Ahead ahead = Ahead{}) {
     const int tid = fresh(tid_);
@@ -515,41 +520,57 @@ __device__ __forceinline__ void forward_to_lds(u64 (&a)[8], u64 *res, u64 *other
 #pragma unroll
             for (int k = 4; k < 8; ++k) a[k] += BIAS;
     }
-    Tw7 w, next;
-    fwd_pass<WIDE, 0, false, true>(a, tw_first(T.tw), q, digits);                        // stages 1-3
-    if (Copy::LEVELS >= 1) w = copy.template get<8>(copy.f8, (unsigned)tid >> B2);
-    else w = tw_level<8>(T.tw, (unsigned)tid >> B2);
-    exchange<S, B1, B2>(a, first, tid);
-    if (Copy::LEVELS < 2) {
-        next = tw_level<64>(T.tw, (unsigned)tid >> B3);
+    Tw7 w8, w64, w512, last;        // levels 8, 64, 512 (from n = 4096 on) and n/8 (but at n = 4096, where it is level 512)
+    auto get8 = [&] {
+        if (Copy::LEVELS >= 1) w8 = copy.template get<8>(copy.f8, (unsigned)tid >> B2);
+        else w8 = tw_level<8>(T.tw, (unsigned)tid >> B2);
+    };
+    auto get64 = [&] {
+        if (Copy::LEVELS >= 2) w64 = copy.template get<64>(copy.f64, (unsigned)tid >> B3);
+        else w64 = tw_level<64>(T.tw, (unsigned)tid >> B3);
+    };
+    auto get512 = [&] { w512 = tw_level<LOGN >= 12 ? 512 : NT>(T.tw, (unsigned)tid >> B4); };
+    auto get_last = [&] { last = tw_level<NT>(T.tw, (unsigned)tid); };
+    if (ALONE) {
+        get8();
+        get64();
+        if (LOGN >= 12) get512();
+        if (LOGN != 12) get_last();
         pin_loads();
     }
-    fwd_pass<WIDE, 0>(a, w, q);                                                          // stages 4-6
-    if (Copy::LEVELS >= 2) next = copy.template get<64>(copy.f64, (unsigned)tid >> B3);
-    exchange<S, B2, B3>(a, second, tid);
-    if (LOGN < 12) {
-        w = tw_level<NT>(T.tw, (unsigned)tid);
+    fwd_pass<WIDE, 0, false, true>(a, tw_first(T.tw), q, digits);                        // stages 1-3
+    if (!ALONE) get8();
+    exchange<S, B1, B2>(a, first, tid);
+    if (!ALONE && Copy::LEVELS < 2) {
+        get64();
         pin_loads();
-        fwd_pass<WIDE, 0, true>(a, next, q);                                             // stages 7-9
+    }
+    fwd_pass<WIDE, 0>(a, w8, q);                                                         // stages 4-6
+    if (!ALONE && Copy::LEVELS >= 2) get64();
+    exchange<S, B2, B3>(a, second, tid);
+    if (!ALONE) {
+        if (LOGN < 12) get_last();
+        else get512();
+        pin_loads();
+    }
+    fwd_pass<WIDE, 0, true>(a, w64, q);                                                  // stages 7-9
+    if (LOGN < 12) {
         exchange<S, B3, 0>(a, first, tid);
         ahead();
-        fwd_pass<WIDE, 3 - LOGN % 3>(a, w, q);                                           // stages 10, 11
+        fwd_pass<WIDE, 3 - LOGN % 3>(a, last, q);                                        // stages 10, 11
     } else {
-        w = tw_level<512>(T.tw, (unsigned)tid >> B4);
-        pin_loads();
-        fwd_pass<WIDE, 0, true>(a, next, q);                                             // stages 7-9
         exchange<S, B3, B4>(a, first, tid);
         if (LOGN == 12) {
             ahead();
-        } else {
-            next = tw_level<NT>(T.tw, (unsigned)tid);
+        } else if (!ALONE) {
+            get_last();
             pin_loads();
         }
-        fwd_pass<WIDE, 0>(a, w, q);                                                      // stages 10-12
+        fwd_pass<WIDE, 0>(a, w512, q);                                                   // stages 10-12
         if (LOGN == 13) {
             exchange<S, B4, 0>(a, second, tid);
             ahead();
-            fwd_pass<WIDE, 2>(a, next, q);                                               // stage 13
+            fwd_pass<WIDE, 2>(a, last, q);                                               // stage 13
         }
     }
     u64 *po = res + pad<S>(tid << 3);
@@ -560,48 +581,58 @@ __device__ __forceinline__ void forward_to_lds(u64 (&a)[8], u64 *res, u64 *other
 
 // Inverse transform: registers hold index 8t + k (not biased, |a| < m) on entry and index t + (n/8) k, canonical, on
 // return.  LDS phases A B A, one more on B at n = 8192.
-// FENCE: a barrier in the first exchange, for the sake of reads of bufB before the call.
-template <bool WIDE, int S, bool FENCE = false, class Copy = NoCopy>
+// FENCE: a barrier in the first exchange, for the sake of reads of bufB before the call.  ALONE: as above.
+template <bool WIDE, int S, bool FENCE = false, bool ALONE = false, class Copy = NoCopy>
 __device__ __forceinline__ void inverse_in_regs(u64 (&a)[8], u64 *bufA, u64 *bufB, const RingTables &T, int tid_, Copy copy = Copy{}) {
     const int tid = fresh(tid_);
     const MontQ q = T.mont;
     constexpr int TOP = LOGN - 3;
-    Tw7 w, next;
+    Tw7 w8, w64, w512;        // of bits 3-5, 6-8 and, from n = 4096 on, 9-11
     ulonglong2 t[TOP_CONSTS], c[8];
+    auto get64 = [&] {
+        if (Copy::LEVELS >= 2) w64 = copy.template get<64>(copy.i64, (unsigned)tid & 63);
+        else inv_level<7, 64>(w64.t, T.itw + INV_MID, (unsigned)tid & 63);
+    };
+    auto get512 = [&] { inv_level<7, 512>(w512.t, T.itw + INV_HIGH, (unsigned)tid & 511); };
     auto top = [&] { inv_level<TOP_CONSTS, NT>(t, T.itw + INV_TOP, (unsigned)tid); };
     auto twist = [&] { inv_level<8, NT>(c, T.itw + INV_TWIST, (unsigned)tid); };
-    if (Copy::LEVELS < 2) {
-        next = Tw7{};
-        inv_level<7, 64>(next.t, T.itw + INV_MID, (unsigned)tid & 63);
+    if (Copy::LEVELS >= 1) w8 = copy.template get<8>(copy.i8, (unsigned)tid & 7);
+    else inv_level<7, 8>(w8.t, T.itw, (unsigned)tid & 7);
+    if (ALONE || Copy::LEVELS < 2) get64();
+    if (ALONE) {
+        if (LOGN >= 12) get512();
+        if (TOP_STAGES) top();
+        twist();
     }
-    if (Copy::LEVELS >= 1) w = copy.template get<8>(copy.i8, (unsigned)tid & 7);
-    else inv_level<7, 8>(w.t, T.itw, (unsigned)tid & 7);
     pin_loads();
     inv_first_pass<WIDE>(a, T.w8, q);                                                    // bits 0-2: 3.7
     exchange<S, 0, 3, FENCE>(a, bufA, tid);
-    inv_pass<WIDE, false>(a, w, q);                                                      // bits 3-5: 6.4
-    if (Copy::LEVELS >= 2) next = copy.template get<64>(copy.i64, (unsigned)tid & 63);
+    inv_pass<WIDE, false>(a, w8, q);                                                     // bits 3-5: 6.4
+    if (!ALONE && Copy::LEVELS >= 2) get64();
     exchange<S, 3, 6>(a, bufB, tid);
+    if (!ALONE) {
+        if (LOGN >= 12) get512();
+        else top();
+        pin_loads();
+    }
+    inv_pass<WIDE, true>(a, w64, q);                                                     // bits 6-8: 3.6
     if (LOGN >= 12) {
-        inv_level<7, 512>(w.t, T.itw + INV_HIGH, (unsigned)tid & 511);
-        pin_loads();
-        inv_pass<WIDE, true>(a, next, q);                                                // bits 6-8: 3.6
         exchange<S, 6, 9>(a, bufA, tid);
-        if (TOP_STAGES) top();
-        else twist();
-        pin_loads();
-        inv_pass<WIDE, false>(a, w, q);                                                  // bits 9-11: 6.3
-    } else {
-        top();
-        pin_loads();
-        inv_pass<WIDE, true>(a, next, q);                                                // bits 6-8: 3.6
+        if (!ALONE) {
+            if (TOP_STAGES) top();
+            else twist();
+            pin_loads();
+        }
+        inv_pass<WIDE, false>(a, w512, q);                                               // bits 9-11: 6.3
     }
     if (TOP_STAGES) {
         // the last pass (register bit 2 is the top bit): 5.4, 7.2 at n = 8192
         if (LOGN >= 12) exchange<S, 9, TOP>(a, bufB, tid);
         else exchange<S, 6, TOP>(a, bufA, tid);
-        twist();
-        pin_loads();
+        if (!ALONE) {
+            twist();
+            pin_loads();
+        }
         if (TOP_STAGES == 2) {
             bf2<WIDE>(a[0], a[2], t[0], a[1], a[3], t[1], q);
             bf2<WIDE>(a[4], a[6], t[0], a[5], a[7], t[1], q);
@@ -611,7 +642,9 @@ __device__ __forceinline__ void inverse_in_regs(u64 (&a)[8], u64 *bufA, u64 *buf
             bf2<WIDE>(a[k], a[k + 4], t[TOP_CONSTS - 4 + k], a[k + 1], a[k + 5], t[TOP_CONSTS - 3 + k], q);
     }
 #pragma unroll
-    for (int k = 0; k < PER; ++k) a[k] = unsign(mont<WIDE>(biased_words(a[k]), c[k], q), T.mod.q);
+    for (int k = 0; k < PER; k += 2) mont2<WIDE, false, NONE>(a[k], a[k + 1], biased_words(a[k]), c[k], biased_words(a[k + 1]), c[k + 1], q);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) a[k] = unsign(a[k], T.mod.q);
 }
 
 // ---- transforms modulo a small plaintext prime -------------------------------------------------------------------
@@ -720,12 +753,23 @@ __device__ __forceinline__ void forward_small_to_lds(u32 (&a)[8], u32 *res, u32 
     for (int k = 0; k < 8; ++k) po[k] = a[k];
     __syncthreads();
 }
+// The constants of the inverse transform, 28 to 36 pairs of eight bytes: requested all at once, before what precedes the
+// transform is done (a mask of a lone workgroup's launch: he_fc 1000x512 on one input 34.3 -> 32.5 us).
+struct SmallInverse {
+    uint2 w8[7], w64[7], w512[7], t[TOP_CONSTS], c[8];
+    __device__ __forceinline__ void request(const SmallTables &T, int tid) {
+        small_level<7, 8>(w8, T.itw, (unsigned)tid & 7);
+        small_level<7, 64>(w64, T.itw + INV_MID, (unsigned)tid & 63);
+        if (LOGN >= 12) small_level<7, 512>(w512, T.itw + INV_HIGH, (unsigned)tid & 511);
+        if (TOP_STAGES) small_level<TOP_CONSTS, NT>(t, T.itw + INV_TOP, (unsigned)tid);
+        small_level<8, NT>(c, T.itw + INV_TWIST, (unsigned)tid);
+    }
+};
 // as inverse_in_regs: canonical in, canonical out
-__device__ __forceinline__ void inverse_small_in_regs(u32 (&a)[8], u32 *bufA, u32 *bufB, const SmallTables &T, int tid) {
+__device__ __forceinline__ void inverse_small_in_regs(u32 (&a)[8], u32 *bufA, u32 *bufB, const SmallTables &T, const SmallInverse &I,
+                                                      int tid) {
     constexpr int TOP = LOGN - 3;
     const u32 p = T.p;
-    uint2 w[7];
-    small_level<7, 8>(w, T.itw, (unsigned)tid & 7);
 #pragma unroll
     for (int k = 0; k < 4; ++k) bf_small_one(a[2 * k], a[2 * k + 1], p);                 // below 2p
     bf_small_one(a[0], a[2], 2 * p);
@@ -737,36 +781,28 @@ __device__ __forceinline__ void inverse_small_in_regs(u32 (&a)[8], u32 *bufA, u3
     bf_small(a[2], a[6], T.w8[1], p);
     bf_small(a[3], a[7], T.w8[2], p);
     exchange_small<0, 3>(a, bufA, tid);
-    inv_pass_small(a, w, p);
-    small_level<7, 64>(w, T.itw + INV_MID, (unsigned)tid & 63);
+    inv_pass_small(a, I.w8, p);
     exchange_small<3, 6>(a, bufB, tid);
-    inv_pass_small(a, w, p);
+    inv_pass_small(a, I.w64, p);
     if (LOGN >= 12) {
-        small_level<7, 512>(w, T.itw + INV_HIGH, (unsigned)tid & 511);
         exchange_small<6, 9>(a, bufA, tid);
-        inv_pass_small(a, w, p);
+        inv_pass_small(a, I.w512, p);
     }
-    uint2 c[8];
     if (TOP_STAGES) {
-        uint2 t[TOP_CONSTS];
-        small_level<TOP_CONSTS, NT>(t, T.itw + INV_TOP, (unsigned)tid);
         if (LOGN >= 12) exchange_small<9, TOP>(a, bufB, tid);
         else exchange_small<6, TOP>(a, bufA, tid);
-        small_level<8, NT>(c, T.itw + INV_TWIST, (unsigned)tid);
         if (TOP_STAGES == 2) {
-            bf_small(a[0], a[2], t[0], p);
-            bf_small(a[1], a[3], t[1], p);
-            bf_small(a[4], a[6], t[0], p);
-            bf_small(a[5], a[7], t[1], p);
+            bf_small(a[0], a[2], I.t[0], p);
+            bf_small(a[1], a[3], I.t[1], p);
+            bf_small(a[4], a[6], I.t[0], p);
+            bf_small(a[5], a[7], I.t[1], p);
         }
 #pragma unroll
-        for (int k = 0; k < 4; ++k) bf_small(a[k], a[k + 4], t[TOP_CONSTS - 4 + k], p);
-    } else {
-        small_level<8, NT>(c, T.itw + INV_TWIST, (unsigned)tid);
+        for (int k = 0; k < 4; ++k) bf_small(a[k], a[k + 4], I.t[TOP_CONSTS - 4 + k], p);
     }
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
-        const u32 r = mul_small(a[k], c[k], p);
+        const u32 r = mul_small(a[k], I.c[k], p);
         a[k] = r >= p ? r - p : r;
     }
 }
@@ -786,12 +822,12 @@ __device__ __forceinline__ u64 get_slot(const u64 *bufB, int position, bool smal
 }
 template <bool WIDE, int S>
 __device__ __forceinline__ void slots_to_coefficients(u64 (&a)[8], u64 *bufA, u64 *bufB, const RingTables &Tp,
-                                                      const SmallTables &small, int tid) {
+                                                      const SmallTables &small, const SmallInverse &consts, int tid) {
     if (small.tw) {
         u32 *A = reinterpret_cast<u32 *>(bufA), *B = reinterpret_cast<u32 *>(bufB), v[8];
 #pragma unroll
         for (int k = 0; k < PER; ++k) v[k] = B[pad32(8 * tid) + k];
-        inverse_small_in_regs(v, A, B, small, tid);
+        inverse_small_in_regs(v, A, B, small, consts, tid);
 #pragma unroll
         for (int k = 0; k < PER; ++k) a[k] = v[k];
     } else {
@@ -844,12 +880,22 @@ __device__ __forceinline__ void mask_role(const RingTables &T, const MaskJob &mj
     const u64 row_r = has_row ? mj.r[(size_t)b * mj.r_stride + row_rindex[tid]] : 0;
     const int row_place = has_row ? first_idx[tid] : 0;
     // every slot but the first of each real output is a draw from the mask stream; values go to the
-    // position the mod-p transform expects them at
+    // position the mod-p transform expects them at.  What the next draw reads is requested before this one is made.
+    bool drawn = !is_first[tid];
+    int position = mj.slot_to_idx[tid];
+#pragma unroll 1
     for (int s = tid; s < N; s += NT) {
+        const int next = min(s + NT, N - 1);
+        const bool next_drawn = !is_first[next];
+        const int next_position = mj.slot_to_idx[next];
         u64 v = 0;
-        if (!is_first[s]) v = draw_uniform(p, mj.pbits, mj.mask_seed, kStreamMask, ((u64)b << 32) + ((u64)O << 16) + (u64)s);
-        put_slot<S>(bufB, mj.slot_to_idx[s], v, small);
+        if (drawn) v = draw_uniform(p, mj.pbits, mj.mask_seed, kStreamMask, ((u64)b << 32) + ((u64)O << 16) + (u64)s);
+        put_slot<S>(bufB, position, v, small);
+        drawn = next_drawn;
+        position = next_position;
     }
+    SmallInverse consts;
+    if (small) consts.request(mj.small, tid);
     __syncthreads();
     // the first slot of every real row absorbs r minus the row's other slots.  The row sums are formed by all
     // threads: a thread adds up its strip of consecutive entries and flushes to the row's cell in LDS whenever the
@@ -886,7 +932,7 @@ __device__ __forceinline__ void mask_role(const RingTables &T, const MaskJob &mj
     __syncthreads();
     // slots -> plaintext polynomial (inverse transform mod p) -> delta * m mod q -> evaluation domain mod q
     u64 a[PER];
-    slots_to_coefficients<WIDE, S>(a, bufA, bufB, mj.Tp, mj.small, tid);        // LDS phases A B A
+    slots_to_coefficients<WIDE, S>(a, bufA, bufB, mj.Tp, mj.small, consts, tid);        // LDS phases A B A
 #pragma unroll
     for (int k = 0; k < PER; ++k) a[k] = mont<WIDE, true, true>(plain_words(a[k]), mj.delta, T.mont, BIAS);
     forward_to_lds<WIDE, S, BIASED>(a, bufA, bufB, T, tid);             // LDS phases B A B A, result in bufA
@@ -995,9 +1041,9 @@ __device__ __forceinline__ auto make_copy(ulonglong2 *at, const RingTables &T, i
 // 2^60) and may take four more products before it is shrunk again.
 // IN8: the inputs lie in blocks of eight coefficients (PermJob::in8_S), as the matrix-core product leaves them.
 // FEW: the launch leaves a CU at most two workgroups, so what counts is one workgroup's chain of dependent steps, not the
-// chip's issue rate: it takes up to 256 registers and requests all key pairs of a digit before its transform's last
-// pass.  A convolution of 13x11x24 to 40 channels at batch 5 (175 workgroups) 86.7 -> 82.8 us, he_fc 1000x512 on one
-// input (257) 40.7 -> 40.2 us.  Sharing a rotation's two digits out to two workgroups as well lost: 45.8 us, the inverse
+// chip's issue rate: it takes up to 256 registers, requests all key pairs of a digit before its transform's last
+// pass and a transform's constants at its start.  A convolution of 13x11x24 to 40 channels at batch 5 (175 workgroups) 86.7 -> 82.8 us, he_fc 1000x512 on one
+// input (257) 40.7 -> 40.2 us; the constants at the start and products two at a time 78.2 -> 72.9 and 33.8 -> 32.5 us.  Sharing a rotation's two digits out to two workgroups as well lost: 45.8 us, the inverse
 // transforms and the partial ciphertexts double.
 template <bool WIDE, bool HAS_W, bool IN8 = false, bool FEW = false>
 __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring(PermJob job, RingTables T, MaskJob mj,
@@ -1089,11 +1135,11 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
                 if (HAS_W) {     // the copy in ownership order: 64 lanes read 1 KiB of whole lines
                     const ulonglong2 wa = *reinterpret_cast<const ulonglong2 *>(wo + (wmid + (unsigned)((2 * k - 4) * 1024))),
                                      wb = *reinterpret_cast<const ulonglong2 *>(wo + (wmid + (unsigned)((2 * k - 3) * 1024)));
-                    a[2 * k] = mont<WIDE>(plain_words(cv.x), wa, q);
-                    a[2 * k + 1] = mont<WIDE>(plain_words(cv.y), wb, q);
+                    u64 va, vb;
+                    mont2<WIDE, false, NONE>(a[2 * k], a[2 * k + 1], plain_words(cv.x), wa, plain_words(cv.y), wb, q);
                     if (PARK) {
-                        c.x = mont<WIDE>(plain_words(c.x), wa, q);
-                        c.y = mont<WIDE>(plain_words(c.y), wb, q);
+                        mont2<WIDE, false, NONE>(va, vb, plain_words(c.x), wa, plain_words(c.y), wb, q);
+                        c = make_ulonglong2(va, vb);
                     }
                 }
                 if (PARK) {
@@ -1136,11 +1182,10 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
                 const ulonglong2 b = k < EARLY ? kbl[k < EARLY ? k : 0] : pair_at(kb_last + k * NT, tid),
                                  aa = k < EARLY ? kal[k < EARLY ? k : 0] : pair_at(ka_last + k * NT, tid);
                 const Words y = plain_words(d);
-                add_product<WIDE>(sum0[k], y, b, q);
-                add_product<WIDE>(sum1[k], y, aa, q);
+                mont2<WIDE, false, IN_PLACE>(sum0[k], sum1[k], y, b, y, aa, q);
             }
         }
-        inverse_in_regs<WIDE, PERM_S, PARK>(a, bufA, bufB, T, tid, copy);
+        inverse_in_regs<WIDE, PERM_S, PARK, FEW>(a, bufA, bufB, T, tid, copy);
 #pragma unroll
         for (int k = 0; k < PER; ++k) (PARK ? stash[tid + k * NT] : coef[PARK ? 0 : k]) = a[k];
 
@@ -1150,7 +1195,7 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
             for (int k = 0; k < PER; ++k) a[k] = ((PARK ? stash[tid + k * NT] : coef[PARK ? 0 : k]) >> (j * gadget_bits)) & digit_mask;
             const ulonglong2 *kb = key + (size_t)(2 * j) * N, *ka = kb + N;
             ulonglong2 kbv[AHEAD ? AHEAD : 1], kav[AHEAD ? AHEAD : 1];
-            forward_to_lds<WIDE, PERM_S, PLAIN>(a, bufA, bufB, T, tid, gadget_bits <= 31, copy, [&] {
+            forward_to_lds<WIDE, PERM_S, PLAIN, FEW>(a, bufA, bufB, T, tid, gadget_bits <= 31, copy, [&] {
 #pragma unroll
                 for (int k = 0; k < AHEAD; ++k) {
                     kbv[k] = pair_at(kb + k * NT, tid);
@@ -1173,8 +1218,7 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
                 const Words d = biased_words(bufA[at]);
                 const ulonglong2 b = k < AHEAD ? kbv[k < AHEAD ? k : 0] : pair_at(kb + k * NT, tid),
                                  aa = k < AHEAD ? kav[k < AHEAD ? k : 0] : pair_at(ka + k * NT, tid);
-                add_product<WIDE>(sum0[k], d, b, q);       // the sum rides on the product
-                add_product<WIDE>(sum1[k], d, aa, q);
+                mont2<WIDE, false, IN_PLACE>(sum0[k], sum1[k], d, b, d, aa, q);       // the sums ride on the products
             }
             ++pending;
         }
@@ -1200,7 +1244,7 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
 // forward transform of its digit.  digits[ct][j][i] holds the transform's biased values, which is
 // what the products of the inner product take.  In the place of the last digit the inner products
 // take c1 itself (folded keys).  stored: L-1 digits.
-template <bool WIDE>
+template <bool WIDE, bool FEW>
 __global__ __launch_bounds__(NT) void decperm_ring(const u64 *ct_in, u64 *digits, RingTables T, int gadget_bits,
                                                    int stored) {
     __shared__ u64 bufA[lds_words(ALONE_S)], bufB[lds_words(ALONE_S)];
@@ -1215,11 +1259,11 @@ __global__ __launch_bounds__(NT) void decperm_ring(const u64 *ct_in, u64 *digits
         a[2 * k] = cv.x;
         a[2 * k + 1] = cv.y;
     }
-    inverse_in_regs<WIDE, ALONE_S>(a, bufA, bufB, T, tid);      // LDS phases A B A
+    inverse_in_regs<WIDE, ALONE_S, false, FEW>(a, bufA, bufB, T, tid);      // LDS phases A B A
     const u64 digit_mask = (1ull << gadget_bits) - 1;
 #pragma unroll
     for (int k = 0; k < PER; ++k) a[k] = (a[k] >> (j * gadget_bits)) & digit_mask;
-    forward_to_lds<WIDE, ALONE_S>(a, bufA, bufB, T, tid, gadget_bits <= 31);       // LDS phases B A B A, ends on a barrier
+    forward_to_lds<WIDE, ALONE_S, PLAIN, FEW>(a, bufA, bufB, T, tid, gadget_bits <= 31);       // LDS phases B A B A, ends on a barrier
     u64 *out = digits + ((size_t)ct * stored + j) * N;
 #pragma unroll
     for (int k = 0; k < PER; ++k) out[tid + k * NT] = bufA[pad<ALONE_S>(tid + k * NT)];
@@ -1277,8 +1321,7 @@ __global__ __launch_bounds__(NT) void hstperm_taps_ring(const u64 *ct_in, const 
 #pragma unroll
             for (int k = 0; k < H; ++k) {
                 const Words y = biased_words(d[k] + bias);
-                s0[k] += mont<WIDE>(y, b[k], q);    // each product is below 1: at most 4 in all
-                s1[k] += mont<WIDE>(y, aa[k], q);
+                mont2<WIDE, false, IN_PLACE>(s0[k], s1[k], y, b[k], y, aa[k], q);    // each product is below 1: at most 4 in all
             }
         }
 #pragma unroll
@@ -1355,19 +1398,16 @@ __global__ __launch_bounds__(PACK_THREADS) void hstperm_pack_ring(const u64 *ct_
 #pragma unroll
                 for (int j = 0; j < KD; ++j) {
                     const Words d = j == KD - 1 ? plain_words(last) : biased_words(dsrc[(size_t)j * N + src]);
-                    s0 = mont<WIDE, true>(d, kwb[j], q, s0);        // each product is below 1: at most 4 in all
-                    s1 = mont<WIDE, true>(d, kwa[j], q, s1);
+                    mont2<WIDE, false, IN_PLACE>(s0, s1, d, kwb[j], d, kwa[j], q);       // each product is below 1: at most 4 in all
                 }
             } else {
                 for (int j = 0; j < ndigits; ++j) {
                     const Words d = biased_words(j == ndigits - 1 ? last + BIAS : dsrc[(size_t)j * N + src]);
                     const ulonglong2 wb = key[(size_t)(2 * j) * N + i], wa = key[(size_t)(2 * j + 1) * N + i];
-                    s0 = mont<WIDE, true>(d, wb, q, s0);
-                    s1 = mont<WIDE, true>(d, wa, q, s1);
+                    mont2<WIDE, false, IN_PLACE>(s0, s1, d, wb, d, wa, q);
                 }
             }
-            v0 = canonical<WIDE>(plain_words(s0), T);
-            v1 = canonical<WIDE>(plain_words(s1), T);
+            canonical2<WIDE>(v0, v1, plain_words(s0), plain_words(s1), T);
         }
         if (!live) v0 = v1 = 0;
         const u64 k80 = 0x8080808080808080ull;   // bytes of x + 0x80..80 are the balanced digits plus 128
@@ -1448,9 +1488,11 @@ __global__ __launch_bounds__(NT, 4) void encrypt_ring(const u64 *slots, const u6
         const u64 v = sl[s];
         put_slot<ALONE_S>(bufB, slot_to_idx[s], v >= p ? v % p : v, small.tw != nullptr);
     }
+    SmallInverse consts;
+    if (small.tw) consts.request(small, tid);
     __syncthreads();
     u64 a[PER];
-    slots_to_coefficients<WIDE, ALONE_S>(a, bufA, bufB, Tp, small, tid);      // m, coefficient tid + (n/8) k, canonical mod p
+    slots_to_coefficients<WIDE, ALONE_S>(a, bufA, bufB, Tp, small, consts, tid);      // m, coefficient tid + (n/8) k, canonical mod p
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
         const int e = draw_gauss_cdf(cdf, seed, kStreamCtE, (u64)(tid + k * NT));
@@ -1526,7 +1568,7 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
                                                                       int gadget_bits, int ndigits) {
     constexpr int PS = 5;
     __shared__ u64 bufA[lds_words(PS)], bufB[lds_words(PS)];
-    __shared__ u64 stash[N];
+    __shared__ u64 stash[lds_words(PS)];      // a rotation's c0 (.) w for the threads that gather it, then the parked coefficients
     // Sums of the lifted remainders (coefficient domain modulo q, canonical, index tid + (n/8) k): 15 of a thread's 16
     // words live in LDS slots of its own (no barrier), which is what two workgroups per CU leave room for.
     __shared__ u64 Rl[15 * NT];
@@ -1541,8 +1583,9 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
     chunk_range(chunk, job.nchunks, job.G, g0, g1);
     const MontQ q = T.mont, qP = S.TP.mont;
     const u64 digit_mask = (1ull << gadget_bits) - 1;
-    // key pairs of a digit and modulus requested before the transform's last pass: three of eight, what 256 registers hold
-    // (the 16x16x128 convolution at batch 16 485.6 -> 479.7 us, he_fc 100x784 at batch 7 74.7 -> 74.2 us)
+    // key pairs of a digit and modulus requested before the transform's last pass: three of eight, what 256 registers hold.
+    // With them pinned there, c0 and c1 gathered in LDS and the weights read in the threads' order: he_fc 100x784 at batch 7 66.9 -> 64.8
+    // us.
     constexpr int AHEAD = 3;
     const size_t key_pairs = (size_t)ndigits * 4 * N;
 
@@ -1577,49 +1620,54 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
             }
             continue;
         }
-        __syncthreads();   // the previous rotation ended reading bufA, this one starts by writing it
+        // as in the one-prime kernel: what the automorphism moves goes through LDS
         const ulonglong2 *key = reinterpret_cast<const ulonglong2 *>(job.keys2) + (size_t)job.key_idx[g] * key_pairs;
-        int src[PER];
-#pragma unroll
-        for (int k = 0; k < PER; ++k) src[k] = galois_index(tid + k * NT, gal);
+        const unsigned turn = (unsigned)((2 * bitrev(tid) + 1) * gal) >> 1;
         u64 a[PER];
+        u32 from[4];
         {
-            const ulonglong2 *c1v = reinterpret_cast<const ulonglong2 *>(IN8 ? c1 + (size_t)tid * S8 : c1 + 8 * tid);
+            const ulonglong2 *c0v = reinterpret_cast<const ulonglong2 *>(IN8 ? c0 + (size_t)tid * S8 : c0 + 8 * tid),
+                             *c1v = reinterpret_cast<const ulonglong2 *>(IN8 ? c1 + (size_t)tid * S8 : c1 + 8 * tid);
+            const int own = pad<PS>(8 * fresh(tid));
+            const char *wo = HAS_W ? reinterpret_cast<const char *>(w + (size_t)job.G * N) : nullptr;
+            const unsigned wmid = ((unsigned)(fresh(tid) >> 6) * 512u + 256u + (unsigned)(tid & 63)) * 16u;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
-                const ulonglong2 cv = c1v[k];
+                const ulonglong2 cv = c1v[k], c = c0v[k];
+                a[2 * k] = cv.x;
+                a[2 * k + 1] = cv.y;
+                u64 xa = c.x, xb = c.y;
                 if (HAS_W) {
-                    const ulonglong2 wa = w[8 * tid + 2 * k], wb = w[8 * tid + 2 * k + 1];
-                    a[2 * k] = mont<WIDE>(plain_words(cv.x), wa, q);
-                    a[2 * k + 1] = mont<WIDE>(plain_words(cv.y), wb, q);
-                } else {
-                    a[2 * k] = cv.x;
-                    a[2 * k + 1] = cv.y;
+                    const ulonglong2 wa = *reinterpret_cast<const ulonglong2 *>(wo + (wmid + (unsigned)((2 * k - 4) * 1024))),
+                                     wb = *reinterpret_cast<const ulonglong2 *>(wo + (wmid + (unsigned)((2 * k - 3) * 1024)));
+                    mont2<WIDE, false, NONE>(a[2 * k], a[2 * k + 1], plain_words(cv.x), wa, plain_words(cv.y), wb, q);
+                    mont2<WIDE, false, NONE>(xa, xb, plain_words(c.x), wa, plain_words(c.y), wb, q);
                 }
+                stash[own + 2 * k] = xa;
+                stash[own + 2 * k + 1] = xb;
+                bufB[own + 2 * k] = a[2 * k];
+                bufB[own + 2 * k + 1] = a[2 * k + 1];
             }
         }
-        inverse_in_regs<WIDE, PS>(a, bufA, bufB, T, tid);
-#pragma unroll
-        for (int k = 0; k < PER; ++k) stash[tid + k * NT] = a[k];
+        __syncthreads();
         // the c0 part, times P, and the last digit's products modulo q (folded keys: the rotated c1 (.) w itself)
         {
             const ulonglong2 *kb = key + (size_t)(4 * (ndigits - 1)) * N, *ka = kb + N;
 #pragma unroll
             for (int k = 0; k < PER; ++k) {
-                const int i = tid + k * NT;
-                u64 x = at(c0, src[k]), d = at(c1, src[k]);
-                if (HAS_W) {
-                    const ulonglong2 ww = w[src[k]];
-                    x = mont<WIDE>(plain_words(x), ww, q);
-                    d = mont<WIDE>(plain_words(d), ww, q);
-                }
-                const ulonglong2 b = kb[i], aa = ka[i];
-                const Words y = plain_words(d);
+                const int k3 = ((k & 1) << 2) | (k & 2) | (k >> 2);
+                const int at = pad<PS>((int)(__brev(turn + (unsigned)(k3 * gal)) >> (32 - LOGN)));
+                from[k & 3] = k < 4 ? (u32)at : from[k & 3] | (u32)at << 16;
+                const u64 x = stash[at];
+                const Words y = plain_words(bufB[at]);
+                const ulonglong2 b = pair_at(kb + k * NT, tid), aa = pair_at(ka + k * NT, tid);
                 sum0[k] = mont<WIDE, true, true>(plain_words(x), S.Pq, q, sum0[k]);
-                sum0[k] = mont<WIDE, true>(y, b, q, sum0[k]);
-                sum1[k] = mont<WIDE, true>(y, aa, q, sum1[k]);
+                mont2<WIDE, false, IN_PLACE>(sum0[k], sum1[k], y, b, y, aa, q);
             }
         }
+        inverse_in_regs<WIDE, PS, true>(a, bufA, bufB, T, tid);
+#pragma unroll
+        for (int k = 0; k < PER; ++k) stash[tid + k * NT] = a[k];
         int pending = 2, pendingP = 0;
         u64 tp0[PER], tp1[PER];   // this rotation's sums modulo P
 #pragma unroll
@@ -1633,12 +1681,14 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
                 auto ahead = [&] {
 #pragma unroll
                     for (int k = 0; k < AHEAD; ++k) {
-                        kbv[k] = kb[tid + k * NT];
-                        kav[k] = ka[tid + k * NT];
+                        kbv[k] = pair_at(kb + k * NT, tid);
+                        kav[k] = pair_at(ka + k * NT, tid);
                     }
+                    pin_loads();
                 };
                 forward_to_lds<WIDE, PS>(a, bufA, bufB, T, tid, gadget_bits <= 31, NoCopy{}, ahead);
                 if (pending == 4) {
+                    asm volatile("");
 #pragma unroll
                     for (int k = 0; k < PER; ++k) {
                         sum0[k] = shrink(sum0[k], q);
@@ -1648,11 +1698,10 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
                 }
 #pragma unroll
                 for (int k = 0; k < PER; ++k) {
-                    const int i = tid + k * NT;
-                    const Words d = biased_words(bufA[pad<PS>(src[k])]);
-                    const ulonglong2 b = k < AHEAD ? kbv[k < AHEAD ? k : 0] : kb[i], aa = k < AHEAD ? kav[k < AHEAD ? k : 0] : ka[i];
-                    sum0[k] = mont<WIDE, true>(d, b, q, sum0[k]);
-                    sum1[k] = mont<WIDE, true>(d, aa, q, sum1[k]);
+                    const Words d = biased_words(bufA[k < 4 ? from[k] & 0xffff : from[k & 3] >> 16]);
+                    const ulonglong2 b = k < AHEAD ? kbv[k < AHEAD ? k : 0] : pair_at(kb + k * NT, tid),
+                                     aa = k < AHEAD ? kav[k < AHEAD ? k : 0] : pair_at(ka + k * NT, tid);
+                    mont2<WIDE, false, IN_PLACE>(sum0[k], sum1[k], d, b, d, aa, q);
                 }
                 ++pending;
             }
@@ -1664,12 +1713,14 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
             auto ahead = [&] {
 #pragma unroll
                 for (int k = 0; k < AHEAD; ++k) {
-                    kbv[k] = kbP[tid + k * NT];
-                    kav[k] = kaP[tid + k * NT];
+                    kbv[k] = pair_at(kbP + k * NT, tid);
+                    kav[k] = pair_at(kaP + k * NT, tid);
                 }
+                pin_loads();
             };
             forward_to_lds<WIDE, PS>(a, bufA, bufB, S.TP, tid, gadget_bits <= 31, NoCopy{}, ahead);
             if (pendingP == 4) {
+                asm volatile("");
 #pragma unroll
                 for (int k = 0; k < PER; ++k) {
                     tp0[k] = shrink(tp0[k], qP);
@@ -1679,11 +1730,10 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
             }
 #pragma unroll
             for (int k = 0; k < PER; ++k) {
-                const int i = tid + k * NT;
-                const Words d = biased_words(bufA[pad<PS>(src[k])]);
-                const ulonglong2 b = k < AHEAD ? kbv[k < AHEAD ? k : 0] : kbP[i], aa = k < AHEAD ? kav[k < AHEAD ? k : 0] : kaP[i];
-                tp0[k] = mont<WIDE, true>(d, b, qP, tp0[k]);
-                tp1[k] = mont<WIDE, true>(d, aa, qP, tp1[k]);
+                const Words d = biased_words(bufA[k < 4 ? from[k] & 0xffff : from[k & 3] >> 16]);
+                const ulonglong2 b = k < AHEAD ? kbv[k < AHEAD ? k : 0] : pair_at(kbP + k * NT, tid),
+                                 aa = k < AHEAD ? kav[k < AHEAD ? k : 0] : pair_at(kaP + k * NT, tid);
+                mont2<WIDE, false, IN_PLACE>(tp0[k], tp1[k], d, b, d, aa, qP);
             }
             ++pendingP;
         }
@@ -1697,7 +1747,12 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
 #pragma unroll
-            for (int k = 0; k < PER; ++k) bufB[pad<PS>(tid + k * NT)] = mont<WIDE, false, true>(plain_words(h ? tp1[k] : tp0[k]), S.TP.one, qP);
+            for (int k = 0; k < PER; k += 2) {
+                u64 ra, rb;
+                mont2<WIDE, true, NONE>(ra, rb, plain_words(h ? tp1[k] : tp0[k]), S.TP.one, plain_words(h ? tp1[k + 1] : tp0[k + 1]), S.TP.one, qP);
+                bufB[pad<PS>(tid + k * NT)] = ra;
+                bufB[pad<PS>(tid + (k + 1) * NT)] = rb;
+            }
             __syncthreads();
             {
                 const u64 *pi = bufB + pad<PS>(tid << 3);
@@ -1809,13 +1864,14 @@ __global__ __launch_bounds__(NT, 3) void hstperm_special_ring(const u64 *ct_in, 
             const u64 *djq = j == ndigits - 1 ? c1 : dsrc + (size_t)(2 * j) * N;       // folded keys modulo q
             const u64 bias = j == ndigits - 1 ? BIAS : 0;
 #pragma unroll
-            for (int k = 0; k < PER; ++k) {
-                const int i = tid + k * NT;
-                const u64 dq = djq[src[k]], dP = dsrc[(size_t)(2 * j + 1) * N + src[k]];
-                const ulonglong2 wq = kq[i], wP = kP[i];
-                sum[k] = mont<WIDE, true>(biased_words(dq + bias), wq, q, sum[k]);
-                tp[k] = mont<WIDE, true>(biased_words(dP), wP, qP, tp[k]);
-                if (k == 3) __builtin_amdgcn_sched_barrier(0);
+            for (int k = 0; k < PER; k += 2) {
+                const u64 *djP = dsrc + (size_t)(2 * j + 1) * N;
+                const u64 qa = djq[src[k]], qb = djq[src[k + 1]], Pa = djP[src[k]], Pb = djP[src[k + 1]];
+                const ulonglong2 wqa = pair_at(kq + k * NT, tid), wqb = pair_at(kq + (k + 1) * NT, tid),
+                                 wPa = pair_at(kP + k * NT, tid), wPb = pair_at(kP + (k + 1) * NT, tid);
+                mont2<WIDE, false, IN_PLACE>(sum[k], sum[k + 1], biased_words(qa + bias), wqa, biased_words(qb + bias), wqb, q);
+                mont2<WIDE, false, IN_PLACE>(tp[k], tp[k + 1], biased_words(Pa), wPa, biased_words(Pb), wPb, qP);
+                if (k == 2) __builtin_amdgcn_sched_barrier(0);
             }
             __builtin_amdgcn_sched_barrier(0);
         }
@@ -1930,6 +1986,8 @@ static SmallTables make_small(const gala_ctx *c) {
     return S;
 }
 
+// whether a launch of so many workgroups leaves a CU at most two wavefronts per SIMD: two workgroups at n = 2048
+static bool few(size_t workgroups) { return workgroups * NT <= (size_t)256 * 4 * 2 * 64; }
 static int launch_perm(const gala_ctx *c, void *stream, const PermJob &job, const MaskJob &mj) {
     hipStream_t st = (hipStream_t)stream;
     const RingTables T = make_tables(c->d_tw2, c->ntt_q);
@@ -1953,8 +2011,7 @@ static int launch_perm(const gala_ctx *c, void *stream, const PermJob &job, cons
             hipLaunchKernelGGL(kernel, grid, dim3(NT), 0, st, job, T, mj, c->gadget_bits, c->ndigits);
         };
 #if GALA_LOGN < 13
-        // at most two wavefronts per SIMD in all: two workgroups per CU at n = 2048
-        if ((size_t)grid.x * NT <= (size_t)256 * 4 * 2 * 64) {
+        if (few(grid.x)) {
             if (job.w) go(perm_accumulate_ring<WIDE, true, false, true>);
             else if (job.in8_S) go(perm_accumulate_ring<WIDE, false, true, true>);
             else go(perm_accumulate_ring<WIDE, false, false, true>);
@@ -2023,6 +2080,15 @@ static int perm_masked(const gala_ctx *c, void *stream, const PermJob &job, cons
     return (int)hipGetLastError();
 }
 
+template <bool WIDE>
+static int decperm(const gala_ctx *c, hipStream_t st, const u64 *ct_in, size_t count, const RingTables &T, u64 *digits) {
+    const size_t workgroups = count * (c->ndigits - 1);
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)workgroups), dim3(NT), 0, st, ct_in, digits, T, c->gadget_bits, c->ndigits - 1);
+    };
+    few(workgroups) ? go(decperm_ring<WIDE, true>) : go(decperm_ring<WIDE, false>);
+    return (int)hipGetLastError();
+}
 static int hoist_taps(const gala_ctx *c, void *stream, const u64 *ct_in, int batch, const TermList &terms,
                            bool any_rotation, const u64 *keys2, u64 *digits, u64 *xrot) {
     if (batch <= 0 || terms.nterm <= 0) return 0;
@@ -2047,9 +2113,7 @@ static int hoist_taps(const gala_ctx *c, void *stream, const u64 *ct_in, int bat
         }
 #endif
         if (any_rotation && c->ndigits > 1) {
-            hipLaunchKernelGGL(decperm_ring<WIDE>, dim3((unsigned)(count * (c->ndigits - 1))), dim3(NT), 0, st, ct_in, digits, T,
-                               c->gadget_bits, c->ndigits - 1);
-            const int rc = (int)hipGetLastError();
+            const int rc = decperm<WIDE>(c, st, ct_in, count, T, digits);
             if (rc) return rc;
         }
         hipLaunchKernelGGL(hstperm_taps_ring<WIDE>, per_term, dim3(NT), 0, st, ct_in, digits, terms, keys2, xrot, T, c->ndigits);
@@ -2070,9 +2134,7 @@ static int hstperm_pack(const gala_ctx *c, void *stream, const u64 *ct_in, u64 *
     return by_width(c, [&](auto width) {
         constexpr bool WIDE = decltype(width)::value;
         if (any_rotation && c->ndigits > 1) {
-            hipLaunchKernelGGL(decperm_ring<WIDE>, dim3((unsigned)((size_t)batch * terms.nin * (c->ndigits - 1))), dim3(NT), 0, st,
-                               ct_in, digits, T, c->gadget_bits, c->ndigits - 1);
-            const int rc = (int)hipGetLastError();
+            const int rc = decperm<WIDE>(c, st, ct_in, (size_t)batch * terms.nin, T, digits);
             if (rc) return rc;
         }
         auto go = [&](auto kernel) {
