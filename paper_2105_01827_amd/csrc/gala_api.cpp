@@ -20,9 +20,8 @@ namespace {
 // what the chip holds at once (256 CUs, three workgroups each at this kernel's register count): every further
 // chunk costs a partial ciphertext and a mask round.  Long sums (an FC layer's G rotations) are cut finer, into
 // 1280 to 2560 workgroups: chunks of equal length matter more there than a single round (63 rotations in 12 chunks
-// leave a third of the workgroups with 6 instead of 5), and a chunk count that is a multiple of eight lets the
-// XCD-aware mapping keep every chunk's keys in one L2.  Measured on he_fc 128x1024 and 1000x2048 at batch 64:
-// 32 chunks are 4 % and 6 % faster than 12.
+// leave a third of the workgroups with 6 instead of 5).  Measured on he_fc 128x1024 and 1000x2048 at batch 64:
+// 32 chunks 134 and 1679 us, 24 133 and 1685, 16 132 and 1737, 12 138 and 1742, 11 141 and 1849.
 // The G rotations of one item are split into this many chunks, each summed by one workgroup.
 int choose_chunks(const gala_ctx *ctx, int items, int G) {
     items = std::max(items, 1);
@@ -37,7 +36,7 @@ int choose_chunks(const gala_ctx *ctx, int items, int G) {
     // batch 50, 128 chunks and 403 MiB of workspace in 5568 us against 5 chunks and 19 MiB in 5089 us; batch 86, 128 chunks
     // and 693 MiB in 9563 us against 32 and 177 MiB in 8986 us.  At n = 4096 they are 60 ns each beside 5 us for a fifth
     // of a rotation: 80 of them count as one.  At n = 8192 (105 ns, 14 us) they only decide near-ties, 512 count as one: by
-    // their time 250x8192 at batch 86 would go from 32 chunks to 17, which lose the XCD mapping, 6475 us against 6290.
+    // their time 250x8192 at batch 86 would go from 32 chunks to 17, 6475 us against 6290.
     // No cut has more than 32 workgroups a CU (four chunks an input for larger batches): 1000x8192 at n = 8192, batch 130,
     // takes 57 chunks, 29 a CU, 39.7 ms, and would take 41.8 ms with 31.  From 64 chunks on the counts are tried in steps of
     // an eighth.
@@ -57,12 +56,17 @@ int choose_chunks(const gala_ctx *ctx, int items, int G) {
         const int c = ((ctx->special ? 512 : 768) + items - 1) / items;
         return std::max(1, std::min(c, G - 1));     // G-1 entries cost a key switch (chunk_range)
     }
-    // a power of two (it divides the padded G, and from 8 on it keeps the XCD mapping): 1280 to 2560 workgroups,
+    // a power of two (it divides the padded G): 1280 to 2560 workgroups,
     // halved while a workgroup would be left with a single term and a round of the chip is still filled
     int c = 1;
     while (2 * c * items <= 2560) c *= 2;
     c = std::min(c, G);
     while (c > 1 && G / c < 2 && items * (c / 2) >= 768) c /= 2;
+    // where every rotation has a chunk to itself, none for the rotation by zero alone; not in launches of two
+    // workgroups a CU or fewer, where the longest chain counts, nor at n = 1024, where it gains nothing (100x500 at batch 20
+    // 42.8 us either way).  With the order of item_and_chunk: 1000x512 at batch 5 70 -> 58.8 us, 128x1024 at batch 20 61.0 -> 57.5,
+    // 100x784 at batch 12 47.3 -> 42.9
+    if (ctx->n == 2048 && items * G > 512) c = std::min(c, G - 1);
     return std::max(1, c);
 }
 size_t align_up(size_t v) { return (v + 255) & ~(size_t)255; }

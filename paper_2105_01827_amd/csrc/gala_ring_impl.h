@@ -979,15 +979,29 @@ __global__ __launch_bounds__(NT) void scmult_masked_ring(PermJob job, RingTables
     });
 }
 
-// Workgroup -> (item, chunk).  Consecutive workgroup ids go to the eight XCDs in turn, each with an L2 of its own.
-// When the chunk count is a multiple of eight, chunk c is always given to XCD c % 8, so that an XCD only ever
-// reads the keys and weights of its own chunks and they stay in its L2.
+// Workgroup -> (item, chunk).  Consecutive workgroup ids go to the eight XCDs in turn, each with an L2 of its own.  Long sums
+// are handed out so that an XCD has consecutive chunks for all items, and starts the workgroups that read the same keys and
+// weights one after the other: a chunk count that is a multiple of eight gives every XCD its eighth of the chunks, eight chunks
+// at a time, item by item; other counts are split anywhere, chunk by chunk.  Eighths in order rather than every eighth
+// chunk, because the longer chunks recur: 63 rotations in 24 chunks left three XCDs with two thirds of the others' work (145 us
+// instead of 133).  Eight at a time, because item by item through all of an XCD's chunks the keys of many chunks do not
+// stay in its L2, and one at a time its workgroups ask for the same keys in step (he_fc 128x1024 at batch 64 134 us, 132 with
+// eight; 100x784 at batch 7 38.2 us with four, 37.6 with eight).  From wire to wire, against item by item and every eighth
+// chunk: he_fc 1000x1024 at batch 5 109 -> 92 us, at batch 16 242 -> 232, 1000x1024 at n = 4096, batch 13, 264 -> 243; against
+// item by item where the count is no multiple of eight: 100x784 at batch 7 with the special prime 64.7 -> 60.6 us, 1000x512 at batch 5
+// 174 -> 163, 100x2048 at n = 4096, batch 9, 142 -> 137.
+// Short sums (a convolution's kernel orders) of other counts have keys that fit an L2 and chunks of unequal length: the chunks of
+// an item in turn, so that every CU gets some of each.
 __device__ __forceinline__ void item_and_chunk(const PermJob &job, int &item, int &chunk) {
-    const int w = blockIdx.x;
+    const int w = blockIdx.x, xcd = w & 7, s = w >> 3;
     if ((job.nchunks & 7) == 0) {
-        const int per = job.nchunks >> 3, s = w >> 3;
-        chunk = (w & 7) + 8 * (s % per);
-        item = s / per;
+        const int per = job.nchunks >> 3, first = s / (8 * job.items) * 8, width = min(8, per - first), r = s - first * job.items;
+        chunk = xcd * per + first + r % width;
+        item = r / width;
+    } else if (job.G >= 32) {
+        const int total = job.items * job.nchunks, at = xcd * (total >> 3) + min(xcd, total & 7) + s;
+        chunk = at / job.items;
+        item = at % job.items;
     } else {
         item = w / job.nchunks;
         chunk = w % job.nchunks;
