@@ -38,14 +38,15 @@ HBM_PEAK_GBS = 8000.0   # MI355X HBM3E, published
 # Two operation counts per unit of work.
 # (1) every 32-bit integer operation of the leanest formulation known here of each 64-bit modular primitive
 #     (multiply-adds, adds with carry, selects; no address arithmetic, no register moves):
-OPS_CONST_MUL = 13      # y*w mod q, w with precomputed quotient: 6 for the high product, 6 + 1 for y*w - h*q
-OPS_CSUB = 4            # conditional subtraction: sub, subb, two selects on the borrow
+OPS_CONST_MUL = 8       # y*w mod q, a signed Montgomery product: 4 + 2 multiply-adds, a low product, a carry word
+OPS_QUOTIENT_MUL = 13   # the same with a precomputed quotient: 6 for the high product, 6 + 1 for y*w - h*q
+OPS_CSUB = 4            # a value brought near or below the modulus
 OPS_BF = OPS_CONST_MUL + 3                     # lazy butterfly: x + v rides on the product, 2x + 2q - (x + v)
 OPS_MAC128 = 10         # 64x64 product added into a 128-bit sum: 4 multiply-adds and 6 carry additions
-OPS_REDUCE128 = 2 * OPS_CONST_MUL + 2 * OPS_CSUB + 1
-# (2) 32x32-bit multiplies only, 10 per modular multiplication (a 64x64 high product and two 64x64 low products
-#     from 32-bit halves), against the measured multiply issue rate.
-MUL32_PER_MODMUL = 10
+OPS_REDUCE128 = 2 * OPS_QUOTIENT_MUL + 2 * OPS_CSUB + 1
+# (2) 32x32-bit multiplies only, 7 per modular multiplication (four of the operand's words, one for the quotient
+#     modulo 2^32, two by the modulus), against the measured multiply issue rate.
+MUL32_PER_MODMUL = 7
 
 
 def transform_ops(n, logn):
@@ -82,9 +83,9 @@ def ops_per_fused_perm_special(n, logn, ndigits):
     summed remainders happen once per workgroup and are not counted."""
     inverse, forward = transform_ops(n, logn)
     scmult_c1 = n * OPS_CONST_MUL
-    c0_term = n * (3 * OPS_CONST_MUL + 1)                       # permuted c0 (.) w, times P, and c1 (.) w
+    c0_term = n * 3 * OPS_CONST_MUL                             # permuted c0 (.) w, times P, and c1 (.) w
     digits = (2 * ndigits - 1) * n * 2
-    key_mac = 4 * ndigits * n * (OPS_CONST_MUL + 1)             # (b_j, a_j) modulo q and modulo P
+    key_mac = 4 * ndigits * n * OPS_CONST_MUL                   # (b_j, a_j) modulo q and modulo P
     accumulate = 2 * n * OPS_CSUB
     remainders = 2 * n * (OPS_CONST_MUL + OPS_CSUB + 2 * OPS_CSUB + 1)   # canonical mod P, lift, reduce mod q, add
     return 3 * inverse + (2 * ndigits - 1) * forward + scmult_c1 + c0_term + digits + key_mac + accumulate + remainders
