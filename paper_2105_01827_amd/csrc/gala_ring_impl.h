@@ -1200,8 +1200,13 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
             }
         }
         inverse_in_regs<WIDE, PERM_S, PARK, FEW>(a, bufA, bufB, T, tid, copy);
+        // Parked only where a digit reads it back.  With one digit no transform follows, so no barrier would lie between these
+        // stores and those of the next rotation's c0 (.) w by other wavefronts; the gathers of the stash end at the barrier of
+        // the inverse transform's first exchange.  Variables need no such care.
+        if (!PARK || ndigits > 1) {
 #pragma unroll
-        for (int k = 0; k < PER; ++k) (PARK ? stash[tid + k * NT] : coef[PARK ? 0 : k]) = a[k];
+            for (int k = 0; k < PER; ++k) (PARK ? stash[tid + k * NT] : coef[PARK ? 0 : k]) = a[k];
+        }
 
         int pending = 2;   // products added to sum0 since it was last shrunk
         for (int j = 0; j < ndigits - 1; ++j) {
