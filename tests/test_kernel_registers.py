@@ -1,0 +1,53 @@
+"""What the compiler gave the ring kernels, read from the metadata of the built library: kernels that are only worth having
+where they stay in registers do."""
+import struct
+
+import msgpack
+import pytest
+
+from paper_2105_01827_amd.build import LIB
+
+MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
+
+
+def _kernels():
+    """(n, mangled name) -> metadata of every kernel that runs n / 8 threads a workgroup"""
+    data, found, at = open(LIB, "rb").read(), {}, 0
+    while (at := data.find(MAGIC, at)) >= 0:
+        count, = struct.unpack_from("<Q", data, at + 24)
+        entry = at + 32
+        for _ in range(count):
+            offset, size, length = struct.unpack_from("<QQQ", data, entry)
+            triple = data[entry + 24:entry + 24 + length]
+            entry += 24 + length
+            if b"gfx950" in triple:
+                for k in _metadata(data[at + offset:at + offset + size])["amdhsa.kernels"]:
+                    found[8 * k[".max_flat_workgroup_size"], k[".name"]] = k
+        at += len(MAGIC)
+    return found
+
+
+def _metadata(elf):
+    phoff, = struct.unpack_from("<Q", elf, 32)
+    phsize, phnum = struct.unpack_from("<HH", elf, 54)
+    for i in range(phnum):
+        kind, _, offset, _, _, size = struct.unpack_from("<IIQQQQ", elf, phoff + i * phsize)
+        if kind == 4:                      # PT_NOTE
+            namesz, descsz, note = struct.unpack_from("<III", elf, offset)
+            assert note == 32              # NT_AMDGPU_METADATA
+            start = offset + 12 + (namesz + 3 & ~3)
+            return msgpack.unpackb(elf[start:start + descsz])
+    raise AssertionError("no metadata")
+
+
+@pytest.fixture(scope="module")
+def kernels():
+    found = _kernels()
+    assert {n for n, name in found if "perm_accumulate_ring" in name} == {1024, 2048, 4096, 8192}
+    return found
+
+
+def test_hoisted_decomposition_spills_nothing(kernels):
+    for (n, name), k in kernels.items():
+        if "decperm" in name and "ring" in name:
+            assert k[".private_segment_fixed_size"] == 0, (n, name)
