@@ -1066,8 +1066,8 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
     __shared__ ulonglong2 tables[PERM_LEVELS ? TableCopy<PERM_LEVELS>::PAIRS : 1];
     // each thread parks its 8 coefficients here between digits (private slots, no barrier); at n = 8192 there is no LDS
     // left for them and they are variables: the workgroup's four wavefronts per SIMD leave 128 registers, and the
-    // compiler spills 63 with weights, 72 on blocks of eight and 68 on whole ciphertexts (248, 292 and 276 bytes of
-    // scratch a lane).  Against the any-n kernel he_fc 200x8192 at batch 40 takes 2904 us instead of 5562 all the same.
+    // compiler spills 62 with weights, 75 on blocks of eight and 55 on whole ciphertexts (188, 264 and 216 bytes of
+    // scratch a lane).  Against the any-n kernel he_fc 200x8192 at batch 40 takes 2345 us instead of 5562 all the same.
     // Before that a rotation's c0 (.) w waits here, and c1 (.) w in bufB, for the threads that gather them.
     constexpr bool PARK = LOGN < 13;
     __shared__ u64 stash[PARK ? lds_words(5) : 1];
@@ -1127,14 +1127,18 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
         const ulonglong2 *key = reinterpret_cast<const ulonglong2 *>(job.keys2) + (size_t)job.key_idx[g] * key_pairs;
         // where the automorphism takes output index tid + (n/8) k from: with i = bitrev(tid) + bitrev3(k) the index is
         // bitrev(((2i + 1) gal - 1) / 2)
-        const unsigned turn = (unsigned)((2 * bitrev(tid) + 1) * gal) >> 1;
-        auto source = [&](unsigned from, int k) {
+        auto turn_of = [&](int t) { return (unsigned)((2 * bitrev(t) + 1) * gal) >> 1; };
+        auto source = [&](unsigned turn, int k) {
             const int k3 = ((k & 1) << 2) | (k & 2) | (k >> 2);
-            return (int)(__brev(from + (unsigned)(k3 * gal)) >> (32 - LOGN));
+            return (int)(__brev(turn + (unsigned)(k3 * gal)) >> (32 - LOGN));
         };
+        const unsigned turn = turn_of(tid);
         // ScMult of the thread's own eight coefficients.  c1 (.) w stays in registers for the inverse transform.
         u64 a[PER];
-        u32 from[4];     // where the automorphism takes the eight outputs from: word indices into an image, two to a register
+        // Where the automorphism takes the eight outputs from: word indices into an image, two to a register.  At n = 8192 they
+        // are worked out again for each digit: kept, they were spilled with what they displaced (700 rotations 173 us, 151 now;
+        // he_fc 100x784 at batch 64 250 us, 217 now).
+        u32 from[PARK ? 4 : 1];
         {
             const ulonglong2 *c0v = reinterpret_cast<const ulonglong2 *>(IN8 ? c0 + (size_t)tid * S : c0 + 8 * tid),
                              *c1v = reinterpret_cast<const ulonglong2 *>(IN8 ? c1 + (size_t)tid * S : c1 + 8 * tid);
@@ -1182,10 +1186,10 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
                 u64 d;
                 if (PARK) {
                     const int at = pad<PERM_S>(src);
-                    from[k & 3] = k < 4 ? (u32)at : from[k & 3] | (u32)at << 16;
+                    from[PARK ? k & 3 : 0] = k < 4 ? (u32)at : from[PARK ? k & 3 : 0] | (u32)at << 16;
                     sum0[k] += stash[pad<5>(src)];
                     d = bufB[at];
-                } else if (from[k & 3] = k < 4 ? (u32)pad<PERM_S>(src) : from[k & 3] | (u32)pad<PERM_S>(src) << 16; HAS_W) {
+                } else if (HAS_W) {
                     const ulonglong2 ww = w[src];
                     sum0[k] = mont<WIDE, true>(plain_words(c0[src]), ww, q, sum0[k]);
                     d = mont<WIDE>(plain_words(c1[src]), ww, q);
@@ -1231,9 +1235,10 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
                 }
                 pending = 0;
             }
+            const unsigned turn_j = PARK ? 0 : turn_of(fresh(tid));
 #pragma unroll
             for (int k = 0; k < PER; ++k) {
-                const u32 at = k < 4 ? from[k] & 0xffff : from[k & 3] >> 16;
+                const u32 at = !PARK ? (u32)pad<PERM_S>(source(turn_j, k)) : from[PARK ? k & 3 : 0] >> (k < 4 ? 0 : 16) & 0xffff;
                 const Words d = biased_words(bufA[at]);
                 const ulonglong2 b = k < AHEAD ? kbv[k < AHEAD ? k : 0] : pair_at(kb + k * NT, tid),
                                  aa = k < AHEAD ? kav[k < AHEAD ? k : 0] : pair_at(ka + k * NT, tid);

@@ -51,3 +51,11 @@ def test_hoisted_decomposition_spills_nothing(kernels):
     for (n, name), k in kernels.items():
         if "decperm" in name and "ring" in name:
             assert k[".private_segment_fixed_size"] == 0, (n, name)
+
+
+@pytest.mark.parametrize("weights,blocks,scratch", [(1, 0, 224), (0, 1, 280), (0, 0, 240)])
+def test_perm_spills_at_n8192(kernels, weights, blocks, scratch):
+    """There 128 registers do not hold everything; the bounds are bytes a lane."""
+    found = [k for (n, name), k in kernels.items()
+             if n == 8192 and f"perm_accumulate_ringILb1ELb{weights}ELb{blocks}E" in name]
+    assert len(found) == 1 and found[0][".private_segment_fixed_size"] <= scratch
