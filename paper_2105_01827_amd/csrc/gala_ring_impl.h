@@ -754,22 +754,36 @@ __device__ __forceinline__ void forward_small_to_lds(u32 (&a)[8], u32 *res, u32 
     __syncthreads();
 }
 // The constants of the inverse transform, 28 to 36 pairs of eight bytes: requested all at once, before what precedes the
-// transform is done (a mask of a lone workgroup's launch: he_fc 1000x512 on one input 34.3 -> 32.5 us).
+// transform is done (a mask of a lone workgroup's launch: he_fc 1000x512 on one input 34.3 -> 32.5 us).  At n = 8192, where a lane
+// has 128 registers whatever the launch, each pass requests its own behind the pass before it: an encryption 50.5 us, 53.2 with
+// all at once, 16x512 on one input 46.1 and 47.4.
 struct SmallInverse {
+    static constexpr bool AT_ONCE = LOGN < 13;
     uint2 w8[7], w64[7], w512[7], t[TOP_CONSTS], c[8];
-    __device__ __forceinline__ void request(const SmallTables &T, int tid) {
-        small_level<7, 8>(w8, T.itw, (unsigned)tid & 7);
-        small_level<7, 64>(w64, T.itw + INV_MID, (unsigned)tid & 63);
+    __device__ __forceinline__ void low(const SmallTables &T, int tid) { small_level<7, 8>(w8, T.itw, (unsigned)tid & 7); }
+    __device__ __forceinline__ void mid(const SmallTables &T, int tid) { small_level<7, 64>(w64, T.itw + INV_MID, (unsigned)tid & 63); }
+    __device__ __forceinline__ void high(const SmallTables &T, int tid) {
         if (LOGN >= 12) small_level<7, 512>(w512, T.itw + INV_HIGH, (unsigned)tid & 511);
+    }
+    __device__ __forceinline__ void top(const SmallTables &T, int tid) {
         if (TOP_STAGES) small_level<TOP_CONSTS, NT>(t, T.itw + INV_TOP, (unsigned)tid);
-        small_level<8, NT>(c, T.itw + INV_TWIST, (unsigned)tid);
+    }
+    __device__ __forceinline__ void twist(const SmallTables &T, int tid) { small_level<8, NT>(c, T.itw + INV_TWIST, (unsigned)tid); }
+    __device__ __forceinline__ void request(const SmallTables &T, int tid) {
+        if (!AT_ONCE) return;
+        low(T, tid);
+        mid(T, tid);
+        high(T, tid);
+        top(T, tid);
+        twist(T, tid);
     }
 };
 // as inverse_in_regs: canonical in, canonical out
-__device__ __forceinline__ void inverse_small_in_regs(u32 (&a)[8], u32 *bufA, u32 *bufB, const SmallTables &T, const SmallInverse &I,
-                                                      int tid) {
+__device__ __forceinline__ void inverse_small_in_regs(u32 (&a)[8], u32 *bufA, u32 *bufB, const SmallTables &T, SmallInverse &I, int tid) {
     constexpr int TOP = LOGN - 3;
+    constexpr bool LATE = !SmallInverse::AT_ONCE;
     const u32 p = T.p;
+    if (LATE) I.low(T, tid);
 #pragma unroll
     for (int k = 0; k < 4; ++k) bf_small_one(a[2 * k], a[2 * k + 1], p);                 // below 2p
     bf_small_one(a[0], a[2], 2 * p);
@@ -782,15 +796,19 @@ __device__ __forceinline__ void inverse_small_in_regs(u32 (&a)[8], u32 *bufA, u3
     bf_small(a[3], a[7], T.w8[2], p);
     exchange_small<0, 3>(a, bufA, tid);
     inv_pass_small(a, I.w8, p);
+    if (LATE) I.mid(T, tid);
     exchange_small<3, 6>(a, bufB, tid);
     inv_pass_small(a, I.w64, p);
     if (LOGN >= 12) {
+        if (LATE) I.high(T, tid);
         exchange_small<6, 9>(a, bufA, tid);
         inv_pass_small(a, I.w512, p);
     }
     if (TOP_STAGES) {
+        if (LATE) I.top(T, tid);
         if (LOGN >= 12) exchange_small<9, TOP>(a, bufB, tid);
         else exchange_small<6, TOP>(a, bufA, tid);
+        if (LATE) I.twist(T, tid);
         if (TOP_STAGES == 2) {
             bf_small(a[0], a[2], I.t[0], p);
             bf_small(a[1], a[3], I.t[1], p);
@@ -822,7 +840,7 @@ __device__ __forceinline__ u64 get_slot(const u64 *bufB, int position, bool smal
 }
 template <bool WIDE, int S>
 __device__ __forceinline__ void slots_to_coefficients(u64 (&a)[8], u64 *bufA, u64 *bufB, const RingTables &Tp,
-                                                      const SmallTables &small, const SmallInverse &consts, int tid) {
+                                                      const SmallTables &small, SmallInverse &consts, int tid) {
     if (small.tw) {
         u32 *A = reinterpret_cast<u32 *>(bufA), *B = reinterpret_cast<u32 *>(bufB), v[8];
 #pragma unroll

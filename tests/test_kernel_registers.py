@@ -59,3 +59,9 @@ def test_perm_spills_at_n8192(kernels, weights, blocks, scratch):
     found = [k for (n, name), k in kernels.items()
              if n == 8192 and f"perm_accumulate_ringILb1ELb{weights}ELb{blocks}E" in name]
     assert len(found) == 1 and found[0][".private_segment_fixed_size"] <= scratch
+
+
+def test_masks_at_n8192_do_not_hold_a_whole_transform(kernels):
+    """The constants of the small plaintext transform held all at once took 72 bytes a lane of a layer without rotations."""
+    found = [k for (n, name), k in kernels.items() if n == 8192 and "scmult_masked_ring" in name]
+    assert len(found) == 1 and found[0][".private_segment_fixed_size"] <= 64
