@@ -1996,6 +1996,9 @@ static RingTables make_tables(const MontPair *pairs, const NttHost &h) {
 // Runs go(std::integral_constant<bool, WIDE>).  WIDE = false needs |y| <= 7 2^60, which the bounds of the passes keep up to n = 2048 for
 // moduli close to 2^60, and low words up to 2^28 (with a special prime both moduli).  Primes searched from 2^60 down are
 // close to it; the low word is a matter of luck unless 2n is all that the prime has to fit.
+// The same variant also transforms modulo the plaintext prime, 2^26 <= p < 2^31, whose low word is p itself: |m0| <= 2^31, but
+// the constants are at most p / 2 < 2^30 and a value stays below 20 p < 2^36 (shrink finds nothing to take off), so |y0 A0| + |k m0| +
+// |y1 B0| <= 2^61 + 2^62 + 2^35.  A plaintext prime of 2^31 or more is refused by gala_ctx_create.
 template <class Go>
 static auto by_width(const gala_ctx *c, Go go) {
 #if GALA_LOGN < 12

@@ -1,5 +1,7 @@
 """Moduli that the ring kernels' signed products tell apart: close to 2^60 with a small low word (one multiply-add fewer) or
 another one, far below 2^60, and small; on ciphertexts whose residues are the largest and the least, against the oracle."""
+import concurrent.futures
+
 import numpy as np
 import pytest
 
@@ -54,3 +56,45 @@ def test_rotations_of_extreme_residues(n, kind, special):
         ksk = o.galois_key(osk, g, 42)
         for i in range(len(cts)):
             assert np.array_equal(got[i], o.perm(cts[i], g, ksk)), (rot, i)
+
+
+def _extreme_cts(n, q, count, seed):
+    """Random ciphertexts, the first five with the largest and least residues in either form."""
+    cts = np.random.default_rng(seed).integers(0, q, (count, 2 * n), dtype=np.uint64)
+    cts[1] = q - 1
+    cts[2] = 0
+    cts[3, ::2], cts[3, 1::2] = q - 1, 0
+    cts[4] = 0
+    cts[4, 0] = cts[4, n] = q - 1
+    return cts
+
+
+@pytest.mark.parametrize("n,kind,gadget_bits,special", [
+    (n, kind, bits, special) for n in (1024, 2048, 4096, 8192) for kind in ("middle", "half")
+    for bits, special in ((12, False), (7, False), (12, True)) if not special or n < 8192
+])
+def test_long_sums_far_below_2_60(n, kind, gadget_bits, special):
+    """Running sums over several rotations of five and nine digits a workgroup: how far they may grow before they are brought
+    near the modulus again depends on its distance from 2^60."""
+    q, p = _modulus(kind, n), wl.find_prime_below(1 << 20, 2 * n)
+    P = wl.find_prime_below(1 << 60, 2 * n) if special else 0
+    ctx, o = binding.Context(n, q, p, gadget_bits, P), Oracle(n, q, p, gadget_bits, P)
+    sk, osk = ctx.keygen(3), o.keygen(3)
+    n_o, n_i, batch = 128, n // 2, 300 if n <= 2048 else 64
+    W, _, r = wl.fc_inputs(wl.FcShape("t", n_o, n_i, batch), p=p, seed=n)
+    plan = ctx.fc_plan(W)
+    assert plan.G == 64
+    plan.bind(ctx.galois_keygen(sk, plan.rotations(), seed=1))
+    chunks = plan.workspace_bytes(batch) // (batch * 2 * n * 8) - 1
+    assert chunks <= 16                                        # four rotations a workgroup at least
+    cts = _extreme_cts(n, q, batch, seed=gadget_bits)
+    got, _ = H.gpu_he_fc(ctx, plan, cts, r, mask_seed=17)
+    wpoly, ksk = o.fc_encode_rowwise(W), o.fc_keys(osk, n_o, n_i, seed=1)
+
+    def item(b):
+        return o.he_fc(wpoly, cts[b], ksk, o.fc_mask_slots(n_o, n_i, r[b], 17, b))[0]
+
+    items = [0, 1, 2, 3, 4, batch - 1]
+    with concurrent.futures.ThreadPoolExecutor(len(items)) as pool:      # the C call releases the interpreter lock
+        for b, want in zip(items, pool.map(item, items)):
+            assert np.array_equal(got[b], want), b

@@ -47,3 +47,28 @@ def test_layer_without_rotations(n, n_o, n_i, batch, p_limit):
         d_in.copy_(H.import_cts(ctx, cts))
         plan.he_fc(d_in, batch, H.to_dev(r), 17, d_out, ws, wsb)
         assert np.array_equal(H.export_cts(ctx, d_out.clone(), batch), got)
+
+
+@pytest.mark.parametrize("p_limit", [1 << 27, 1 << 31])
+@pytest.mark.parametrize("n,n_o,n_i", [(1024, 64, 16), (1024, 20, 300), (2048, 16, 128), (2048, 30, 500)])
+def test_modulus_with_a_small_low_word(n, n_o, n_i, p_limit):
+    """Under such a modulus the transforms modulo p are the narrow products too, whatever p's low word: the client's steps, and
+    masks of layers without and with rotations."""
+    p, q = wl.find_prime_below(p_limit, 2 * n), wl.find_prime_below(1 << 60, 2 * n)
+    low = q & 0xFFFFFFFF
+    assert min(low, (1 << 32) - low) <= 1 << 28 and q >= (1 << 60) - (1 << 56)
+    par = wl.Params(n=n, q=q, p=p, gadget_bits=20)
+    H = harness()
+    ctx, o, plan, sk, W, x, r, got = fc_case(par, n_o, n_i, 3, [0, 1, 2], seed=n_o)
+    osk = o.keygen(0)
+    slots = np.random.default_rng(n).integers(0, p, (3, n), dtype=np.uint64)
+    slots[1] = p - 1
+    slots[2, ::2], slots[2, 1::2] = p - 1, 0
+    d_ct, d_slots = H.dev_empty(3 * 2 * n), H.dev_empty(3 * n)
+    ctx.encrypt_batch(sk, H.to_dev(slots), H.to_dev(np.arange(3, dtype=np.uint64) + 5), 3, d_ct)
+    cts = H.export_cts(ctx, d_ct, 3)
+    for b in range(3):
+        assert np.array_equal(cts[b], o.encrypt(osk, slots[b], 5 + b)), b
+    ctx.decrypt_batch(sk, d_ct, 3, d_slots)
+    torch.cuda.synchronize()
+    assert np.array_equal(H.to_host(d_slots).reshape(3, n), np.stack([o.decrypt(osk, c) for c in cts]))
