@@ -41,7 +41,7 @@ HBM_PEAK_GBS = 8000.0   # MI355X HBM3E, published
 OPS_CONST_MUL = 8       # y*w mod q, a signed Montgomery product: 4 + 2 multiply-adds, a low product, a carry word
 OPS_QUOTIENT_MUL = 13   # the same with a precomputed quotient: 6 for the high product, 6 + 1 for y*w - h*q
 OPS_CSUB = 4            # a value brought near or below the modulus
-OPS_BF = OPS_CONST_MUL + 3                     # lazy butterfly: x + v rides on the product, 2x + 2q - (x + v)
+OPS_BF = OPS_CONST_MUL + 3                     # lazy butterfly: x + w y rides on the product, x - w y = 2x - (x + w y)
 OPS_MAC128 = 10         # 64x64 product added into a 128-bit sum: 4 multiply-adds and 6 carry additions
 OPS_REDUCE128 = 2 * OPS_QUOTIENT_MUL + 2 * OPS_CSUB + 1
 # (2) 32x32-bit multiplies only, 7 per modular multiplication (four of the operand's words, one for the quotient
@@ -67,7 +67,7 @@ def ops_per_fused_perm(n, logn, ndigits):
     c0_term = n * 2 * OPS_CONST_MUL                             # permuted c0 (.) w, on the sum, and c1 (.) w
     digits = (ndigits - 1) * n * 2                              # shift and mask
     key_mac = 2 * ndigits * n * OPS_CONST_MUL                   # inner product with (b_j, a_j), on the sums
-    accumulate = 2 * n * OPS_CSUB                               # keep the running sums below 8q
+    accumulate = 2 * n * OPS_CSUB                               # bring the running sums near q
     return inverse + (ndigits - 1) * forward + scmult_c1 + c0_term + digits + key_mac + accumulate
 
 

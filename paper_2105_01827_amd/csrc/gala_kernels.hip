@@ -989,7 +989,7 @@ const RingOps *ring_ops_11();
 const RingOps *ring_ops_12();
 const RingOps *ring_ops_13();
 const RingOps *ring_ops(const gala_ctx *c) {
-    // lazy residues reach 16q, and P's are lifted modulo q by one subtraction
+    // lazy residues are signed words of up to eight times 2^60, and P's are lifted modulo q by one subtraction
     if (c->q >= (1ull << 60) || (c->special && (c->special >= (1ull << 60) || c->special >= 2 * c->q))) return nullptr;
     switch (c->logn) {
         case 10: return ring_ops_10();
@@ -1000,7 +1000,8 @@ const RingOps *ring_ops(const gala_ctx *c) {
     }
 }
 bool uses_fast_perm(const gala_ctx *c) { return ring_ops(c) != nullptr; }
-// the hoisted inner products add a rotation's terms without corrections: at most 2q for each digit and q for c0
+// the hoisted inner products add a rotation's terms without corrections, less than a modulus for each digit and for c0, and with the
+// special prime subtract the sum from a value of up to 3 2^60: together below the eight that a signed word holds
 constexpr int kHoistDigits = 3;
 bool uses_fast_hoist(const gala_ctx *c) { return ring_ops(c) && c->ndigits <= kHoistDigits; }
 int launch_perm_accumulate(const gala_ctx *c, void *stream, const PermJob &job) {

@@ -5,8 +5,7 @@
 // One workgroup of n / 8 threads (four wavefronts at n = 2048) owns one polynomial; every thread
 // keeps 8 coefficients in registers and runs radix-8 passes (three butterfly
 // stages each) on them, so a 2048-point transform is 3 + 3 + 3 + 2 stages with
-// only three exchanges through LDS.  The LDS image is padded by one word every
-// 32 so that the exchange patterns are bank-conflict free at n = 2048, and two buffers
+// only three exchanges through LDS.  The LDS image is padded against bank conflicts (pad below), and two buffers
 // alternate so that each exchange needs a single barrier.
 //
 // Index ownership of register k of thread t in a pass on bits B .. B+2 of the coefficient index: those three bits are
@@ -649,7 +648,7 @@ __device__ __forceinline__ void inverse_in_regs(u64 (&a)[8], u64 *bufA, u64 *buf
 
 // ---- transforms modulo a small plaintext prime -------------------------------------------------------------------
 // Below 2^26 the plaintext modulus leaves 32-bit words room for every stage without corrections (at most 36p after 13
-// stages), and a product by a constant is three 32-bit multiplies instead of nine: the slots of masks and messages are
+// stages), and a product by a constant is three 32-bit multiplies instead of eight: the slots of masks and messages are
 // transformed this way, half the LDS words included.  Same passes, ownership and tables as above, with (constant,
 // floor(constant 2^32 / p)) pairs of eight bytes; larger plaintext primes keep the 64-bit transforms.
 // From wire to wire: 16x128 on one input 24.1 -> 22.4 us, 1000x512 39.6 -> 37.2 us; 1024 encryptions 67.5 -> 62.4 us, 256
@@ -1006,8 +1005,8 @@ __global__ __launch_bounds__(NT) void scmult_masked_ring(PermJob job, RingTables
 // stay in its L2, and one at a time its workgroups ask for the same keys in step (he_fc 128x1024 at batch 64 134 us, 132 with
 // eight; 100x784 at batch 7 38.2 us with four, 37.6 with eight).  From wire to wire, against item by item and every eighth
 // chunk: he_fc 1000x1024 at batch 5 109 -> 92 us, at batch 16 242 -> 232, 1000x1024 at n = 4096, batch 13, 264 -> 243; against
-// item by item where the count is no multiple of eight: 100x784 at batch 7 with the special prime 64.7 -> 60.6 us, 1000x512 at batch 5
-// 174 -> 163, 100x2048 at n = 4096, batch 9, 142 -> 137.
+// item by item where the count is no multiple of eight: 100x784 at batch 7 with the special prime 64.7 -> 60.6 us, 1000x512 at batch 5 with
+// it 174 -> 163, 100x2048 at n = 4096, batch 9, 142 -> 137.
 // Short sums (a convolution's kernel orders) of other counts have keys that fit an L2 and chunks of unequal length: the chunks of
 // an item in turn, so that every CU gets some of each.
 __device__ __forceinline__ void item_and_chunk(const PermJob &job, int &item, int &chunk) {
@@ -1997,7 +1996,7 @@ static RingTables make_tables(const MontPair *pairs, const NttHost &h) {
 // moduli close to 2^60, and low words up to 2^28 (with a special prime both moduli).  Primes searched from 2^60 down are
 // close to it; the low word is a matter of luck unless 2n is all that the prime has to fit.
 // The same variant also transforms modulo the plaintext prime, 2^26 <= p < 2^31, whose low word is p itself: |m0| <= 2^31, but
-// the constants are at most p / 2 < 2^30 and a value stays below 20 p < 2^36 (shrink finds nothing to take off), so |y0 A0| + |k m0| +
+// the constants are at most p / 2 < 2^30 and a value stays below 20 p < 2^36 (shrink adds p to a negative one), so |y0 A0| + |k m0| +
 // |y1 B0| <= 2^61 + 2^62 + 2^35.  A plaintext prime of 2^31 or more is refused by gala_ctx_create.
 template <class Go>
 static auto by_width(const gala_ctx *c, Go go) {
