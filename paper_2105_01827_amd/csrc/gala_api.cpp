@@ -53,7 +53,13 @@ int choose_chunks(const gala_ctx *ctx, int items, int G) {
         return best;
     }
     if (G < 32 || ctx->special) {
-        const int c = ((ctx->special ? 512 : 768) + items - 1) / items;
+        int c = ((ctx->special ? 512 : 768) + items - 1) / items;
+        // Long sums at n = 2048: no workgroup above the round.  A few above it doubled the launch's tail, and with chunks of
+        // unequal length handed out chunk by chunk they queued behind XCDs that have only long ones: a modulus near 2^59,
+        // five digits, 17x1251 at batch 30 in 18 chunks (540 workgroups) 238 us, item by item 204, in 17 chunks 155; 64x2048,
+        // two digits: batch 30 219 -> 152 us, batch 57 (9 and 8 chunks) 395 -> 271.  Above 256 inputs the rest of half a
+        // round costs more: batch 257 in two chunks 1671 us, in one 2016.
+        if (ctx->special && ctx->n == 2048 && uses_fast_perm(ctx) && G >= 32 && items <= 256) c = 512 / items;
         return std::max(1, std::min(c, G - 1));     // G-1 entries cost a key switch (chunk_range)
     }
     // a power of two (it divides the padded G): 1280 to 2560 workgroups,
