@@ -26,7 +26,7 @@ namespace {
 int choose_chunks(const gala_ctx *ctx, int items, int G) {
     items = std::max(items, 1);
     // With a special prime the kernel holds two workgroups per CU, not three, and a rotation is twice the work:
-    // one round of 512 workgroups was the fastest cut for short and long sums alike (he_fc 128x1024: 0.43 ms
+    // about one round of 512 workgroups was the fastest cut for short and long sums alike (he_fc 128x1024: 0.43 ms
     // against 0.48 ms with 2048 workgroups and 0.58 ms with 768).
     // Smaller rings keep n = 2048's targets (a static call's fixed scratch is sized by them).  From n = 4096 on a CU holds
     // one workgroup, and what counts is rounds of the 256 CUs times the rotations of the longest chunk,

@@ -1006,7 +1006,7 @@ __global__ __launch_bounds__(NT) void scmult_masked_ring(PermJob job, RingTables
 // eight; 100x784 at batch 7 38.2 us with four, 37.6 with eight).  From wire to wire, against item by item and every eighth
 // chunk: he_fc 1000x1024 at batch 5 109 -> 92 us, at batch 16 242 -> 232, 1000x1024 at n = 4096, batch 13, 264 -> 243; against
 // item by item where the count is no multiple of eight: 100x784 at batch 7 with the special prime 64.7 -> 60.6 us, 1000x512 at batch 5 with
-// it 174 -> 163, 100x2048 at n = 4096, batch 9, 142 -> 137.
+// it 131 -> 123, 100x2048 at n = 4096, batch 9, 142 -> 137.
 // Short sums (a convolution's kernel orders) of other counts have keys that fit an L2 and chunks of unequal length: the chunks of
 // an item in turn, so that every CU gets some of each.
 __device__ __forceinline__ void item_and_chunk(const PermJob &job, int &item, int &chunk) {
