@@ -98,3 +98,17 @@ def test_long_sums_far_below_2_60(n, kind, gadget_bits, special):
     with concurrent.futures.ThreadPoolExecutor(len(items)) as pool:      # the C call releases the interpreter lock
         for b, want in zip(items, pool.map(item, items)):
             assert np.array_equal(got[b], want), b
+
+
+@pytest.mark.parametrize("kind", ["low_word_small", "low_word_large", "middle", "half", "small"])
+@pytest.mark.parametrize("n", [1024, 2048, 4096, 8192])
+def test_import_of_words_below_four_moduli(n, kind):
+    """Import takes words up to 4q - 1 as their residues, whatever the modulus."""
+    q = _modulus(kind, n)
+    ctx = binding.Context(n, q, wl.find_prime_below(1 << 20, 2 * n), 20)
+    cts = _extreme_cts(n, q, 6, seed=n)
+    more = np.random.default_rng(n + 1).integers(0, 4, cts.shape, dtype=np.uint64)
+    more[:5] = 3
+    want, got = H.import_cts(ctx, cts), H.import_cts(ctx, cts + more * np.uint64(q))
+    assert np.array_equal(H.to_host(got), H.to_host(want))
+    assert np.array_equal(H.export_cts(ctx, got, len(cts)), cts)
