@@ -308,8 +308,8 @@ extern "C" int gala_ctx_create(const gala_params *par, gala_ctx **out) {
     if (P) {
         c->special = P;
         c->ntt_P.init(n, P, primitive_2n_root(P, n));
-        c->Pq = P % q; c->Pq_s = shoup_companion(c->Pq, q);
-        c->Pinv = inv_mod(c->Pq, q); c->Pinv_s = shoup_companion(c->Pinv, q);
+        c->Pq = P % q;
+        c->Pinv = inv_mod(c->Pq, q);
         c->Pq_m = mont_pair(c->Pq, make_mont(q));
         c->minus_Pinv_m = mont_pair(q - c->Pinv, make_mont(q));
     }

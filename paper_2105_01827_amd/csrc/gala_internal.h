@@ -85,7 +85,7 @@ struct gala_ctx {
     gala::u64 q = 0, p = 0, delta = 0, delta_s = 0, zeta = 0;
     gala::NttHost ntt_q, ntt_p;
     // special prime of key switching (0: keys modulo q only)
-    gala::u64 special = 0, Pq = 0, Pq_s = 0, Pinv = 0, Pinv_s = 0;   // P mod q and P^-1 mod q with companions
+    gala::u64 special = 0, Pq = 0, Pinv = 0;   // P mod q and P^-1 mod q
     gala::NttHost ntt_P;
     gala::MontPair delta_m{}, Pq_m{}, minus_Pinv_m{};   // delta, P and -P^-1 mod q for the ring kernels
     std::vector<int> slot_to_idx;      // slot s -> index of its value in the mod-p transform
