@@ -247,30 +247,31 @@ static int upload_mask_layout(const gala_ctx *c, const MaskLayoutHost &h, MaskLa
     if ((rc = upload(&d->row_rindex, h.row_rindex))) return rc;
     if ((rc = upload(&d->nrows, h.nrows))) return rc;
     if ((rc = upload(&d->is_first, h.is_first))) return rc;
-    // the same CSR seen from its entries, with the slot -> transform-position map applied
+    // the same CSR seen from its slots
     const int n = c->n;
-    std::vector<int> entry_row((size_t)h.nout * n, -1), entry_idx((size_t)h.nout * n, 0), first_idx((size_t)h.nout * n, 0);
-    std::vector<int> slot_rowid((size_t)h.nout * n, -1);
+    std::vector<int> slot_rowid((size_t)h.nout * n, -1), slot_mask(2 * (size_t)h.nout * n, 0);
+    d->sums = false;
     for (int O = 0; O < h.nout; ++O) {
         const int *rp = h.row_ptr.data() + (size_t)O * (n + 1), *rs = h.row_slots.data() + (size_t)O * n;
+        int *of_slot = slot_mask.data() + 2 * (size_t)O * n;
+        for (int s = 0; s < n; ++s) of_slot[2 * s] = c->slot_to_idx[s];
         for (int t = 0; t < h.nrows[O]; ++t) {
             if (rp[t + 1] <= rp[t]) continue;
-            first_idx[(size_t)O * n + t] = c->slot_to_idx[rs[rp[t]]];
-            for (int e = rp[t]; e < rp[t + 1]; ++e) slot_rowid[(size_t)O * n + rs[e]] = t;
-            for (int e = rp[t] + 1; e < rp[t + 1]; ++e) {
-                entry_row[(size_t)O * n + e] = t;
-                entry_idx[(size_t)O * n + e] = c->slot_to_idx[rs[e]];
+            if (rp[t + 1] > rp[t] + 1) d->sums = true;
+            for (int e = rp[t]; e < rp[t + 1]; ++e) {
+                slot_rowid[(size_t)O * n + rs[e]] = t;
+                of_slot[2 * rs[e]] |= t << MaskSlot::kBits | MaskSlot::kInRow;
             }
+            of_slot[2 * rs[rp[t]]] |= MaskSlot::kFirst;
+            of_slot[2 * rs[rp[t]] + 1] = h.row_rindex[(size_t)O * n + t];
         }
     }
-    if ((rc = upload(&d->entry_row, entry_row))) return rc;
-    if ((rc = upload(&d->entry_idx, entry_idx))) return rc;
     if ((rc = upload(&d->slot_rowid, slot_rowid))) return rc;
-    return upload(&d->first_idx, first_idx);
+    return upload(&d->slot_mask, slot_mask);
 }
 static void free_mask_layout(MaskLayoutDev *d) {
     hipFree(d->row_ptr); hipFree(d->row_slots); hipFree(d->row_rindex); hipFree(d->nrows); hipFree(d->is_first);
-    hipFree(d->entry_row); hipFree(d->entry_idx); hipFree(d->first_idx); hipFree(d->slot_rowid);
+    hipFree(d->slot_rowid); hipFree(d->slot_mask);
 }
 
 }  // namespace gala

@@ -30,8 +30,9 @@ GALA_HD int draw_gauss_cdf(const GaussCdf &cdf, u64 seed, u64 stream, u64 idx) {
 // rotation by zero in he_fc and he_conv (a ScMult and no key switch): it rides with chunk 0, and the G-1 entries
 // after it are spread evenly, so that no workgroup is launched for the cheap entry alone.
 GALA_HD void chunk_range(int chunk, int nchunks, int G, int &g0, int &g1) {
-    g0 = chunk ? 1 + (int)((long)chunk * (G - 1) / nchunks) : 0;
-    g1 = 1 + (int)((long)(chunk + 1) * (G - 1) / nchunks);
+    // 32 bits hold the products: chunk < G <= kMaxN; a workgroup starts with these divisions
+    g0 = chunk ? 1 + (int)((u32)chunk * (u32)(G - 1) / (u32)nchunks) : 0;
+    g1 = 1 + (int)((u32)(chunk + 1) * (u32)(G - 1) / (u32)nchunks);
 }
 
 // ---------------------------------------------------------------------------
@@ -126,6 +127,12 @@ struct gala_gk {
     size_t key_words() const { return (size_t)ndigits * polys * n; }
 };
 
+// A slot in one word: its position in the mod-p transform's input, its row, whether it is in a row at all and whether it
+// is the row's first.
+struct MaskSlot {
+    static constexpr int kBits = 13, kFirst = 1 << 26, kInRow = 1 << 27;      // positions and rows are below n <= 8192
+};
+
 // Device description of how the server's mask is laid out in one output
 // ciphertext: which slots are drawn from the generator and which absorb r.
 struct MaskLayoutHost {
@@ -139,10 +146,11 @@ struct MaskLayoutHost {
 struct MaskLayoutDev {
     int *row_ptr = nullptr, *row_slots = nullptr, *row_rindex = nullptr, *nrows = nullptr;
     unsigned char *is_first = nullptr;
-    // per entry e of the CSR (nout x n): its row, or -1 for the first entry of a row, and the position of its slot
-    // in the mod-p transform's input; per row (nout x n): that position for the row's first slot
-    int *entry_row = nullptr, *entry_idx = nullptr, *first_idx = nullptr;
     int *slot_rowid = nullptr;         // nout x n: the row a slot belongs to, -1 for slots outside every row
+    // nout x n pairs, by slot: what the ring kernels' masks need to know of it (MaskSlot), and the index into r of the row
+    // whose first slot it is
+    int *slot_mask = nullptr;
+    bool sums = false;                 // some row has more than one slot
 };
 
 struct gala_fc_plan {

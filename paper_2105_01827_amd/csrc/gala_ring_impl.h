@@ -873,99 +873,111 @@ struct MaskJob {
     SmallTables small;
 };
 
-// store(k, i, m): mask word i = tid + k NT of the evaluation domain, canonical.
-template <bool WIDE, int S, class Store>
+// The state of the generator behind rand64(seed, stream, idx, attempt) that all draws of a stream share.
+__device__ __forceinline__ u64 stream_state(u64 seed, u64 stream) { return mix64(mix64(seed + 0x9E3779B97F4A7C15ull) + stream); }
+// draw_uniform of the indices first + k STEP.  The first attempts are made together: one by one, each with its own chance of
+// another attempt, the draws of a lone wavefront are one chain of multiplications.
+template <int STEP, int COUNT>
+__device__ __forceinline__ void draw_uniforms(u64 (&v)[COUNT], u64 m, int bits, u64 state, u64 first) {
+    u64 h[COUNT];
+#pragma unroll
+    for (int k = 0; k < COUNT; ++k) {
+        h[k] = mix64(state + (first + (u64)(k * STEP)));
+        v[k] = mix64(h[k]) >> (64 - bits);
+    }
+#pragma unroll
+    for (int k = 0; k < COUNT; ++k) {
+        u64 attempt = 0;
+        while (v[k] >= m) v[k] = mix64(h[k] + ++attempt) >> (64 - bits);
+    }
+}
+
+// store(k, i, m): mask word i = threadIdx.x + k NT GROUPS of the evaluation domain, canonical.
+// ALONE: as in the transforms.  GROUPS: the workgroup's threads in units of NT; the first group runs the transforms.
+// Bound by its own chain of steps: at n = 2048 with 1000 rows, in a launch of one workgroup a CU, 34 400 clocks when each thread
+// drew its slots one after the other (10 100) and then walked the rows, each with its row pointers, indices and share behind
+// each other and two divisions (12 900); 29 200 by slots, with 7 600 and 3 800.  Rotations hide it where there are any.
+template <bool WIDE, int S, bool ALONE = false, int GROUPS = 1, class Store>
 __device__ __forceinline__ void mask_role(const RingTables &T, const MaskJob &mj, int item, u64 *bufA, u64 *bufB, Store store) {
+    constexpr int ALL = NT * GROUPS, OWN = PER / GROUPS;
     const int tid = threadIdx.x;
+    const bool transforms = GROUPS == 1 || __builtin_amdgcn_readfirstlane(tid) < NT;
     const int b = item / mj.nout, O = item % mj.nout;
     const u64 p = mj.Tp.mod.q;
-    const bool small = mj.small.tw != nullptr;
-    const int *row_ptr = mj.layout.row_ptr + (size_t)O * (N + 1);
-    const int *row_rindex = mj.layout.row_rindex + (size_t)O * N;
-    const unsigned char *is_first = mj.layout.is_first + (size_t)O * N;
-    // Everything read from the layout is requested before the draws: the chain of dependent steps is what a mask takes
-    const int nrows = mj.layout.nrows[O];
-    const int *first_idx = mj.layout.first_idx + (size_t)O * N;
-    const int4 *entries = reinterpret_cast<const int4 *>(mj.layout.entry_row + (size_t)O * N + PER * tid),
-               *places = reinterpret_cast<const int4 *>(mj.layout.entry_idx + (size_t)O * N + PER * tid);
-    const int4 e_lo = entries[0], e_hi = entries[1], p_lo = places[0], p_hi = places[1];
-    const int entry_row[PER] = {e_lo.x, e_lo.y, e_lo.z, e_lo.w, e_hi.x, e_hi.y, e_hi.z, e_hi.w};
-    const int entry_idx[PER] = {p_lo.x, p_lo.y, p_lo.z, p_lo.w, p_hi.x, p_hi.y, p_hi.z, p_hi.w};
-    const int nent = row_ptr[nrows];
-    // the first of this thread's rows
-    const bool has_row = tid < nrows && row_ptr[tid + 1] > row_ptr[tid];
-    const u64 row_r = has_row ? mj.r[(size_t)b * mj.r_stride + row_rindex[tid]] : 0;
-    const int row_place = has_row ? first_idx[tid] : 0;
-    // every slot but the first of each real output is a draw from the mask stream; values go to the
-    // position the mod-p transform expects them at.  What the next draw reads is requested before this one is made.
-    bool drawn = !is_first[tid];
-    int position = mj.slot_to_idx[tid];
-#pragma unroll 1
-    for (int s = tid; s < N; s += NT) {
-        const int next = min(s + NT, N - 1);
-        const bool next_drawn = !is_first[next];
-        const int next_position = mj.slot_to_idx[next];
-        u64 v = 0;
-        if (drawn) v = draw_uniform(p, mj.pbits, mj.mask_seed, kStreamMask, ((u64)b << 32) + ((u64)O << 16) + (u64)s);
-        put_slot<S>(bufB, position, v, small);
-        drawn = next_drawn;
-        position = next_position;
-    }
-    SmallInverse consts;
-    if (small) consts.request(mj.small, tid);
-    __syncthreads();
-    // the first slot of every real row absorbs r minus the row's other slots.  The row sums are formed by all
-    // threads: a thread adds up its strip of consecutive entries and flushes to the row's cell in LDS whenever the
-    // row changes (plain integer sums of values below p: at most n of them, far from 64 bits).
-    unsigned long long *rowsum = reinterpret_cast<unsigned long long *>(bufA);
-    const bool sums = nent > nrows;      // rows of a single slot (convolutions) have nothing to add up
-    if (sums) {
-        for (int t = tid; t < nrows; t += NT) rowsum[t] = 0;
-        __syncthreads();
-        int cur = -1;
-        u64 acc = 0;
+    const bool small = mj.small.tw != nullptr, sums = mj.layout.sums;
+    // everything read from memory is requested before the draws
+    const int2 *meta = reinterpret_cast<const int2 *>(mj.layout.slot_mask) + (size_t)O * N;
+    const u64 *r = mj.r + (size_t)b * mj.r_stride;
+    int slot[OWN], rindex[OWN];
+    u64 share[OWN];
 #pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int e = PER * tid + k;
-            const int t = e < nent ? entry_row[k] : -1;
-            if (t < 0) continue;
-            if (t != cur) {
-                if (cur >= 0) atomicAdd(&rowsum[cur], acc);
-                cur = t;
-                acc = 0;
-            }
-            acc += get_slot<S>(bufB, entry_idx[k], small);
-        }
-        if (cur >= 0) atomicAdd(&rowsum[cur], acc);
-        __syncthreads();
+    for (int k = 0; k < OWN; ++k) {
+        const int2 m = meta[tid + k * ALL];
+        slot[k] = m.x;
+        rindex[k] = m.y;
     }
-    for (int t = tid; t < nrows; t += NT) {
-        const bool first = t == tid;
-        if (first ? !has_row : row_ptr[t + 1] <= row_ptr[t]) continue;
-        u64 rv = first ? row_r : mj.r[(size_t)b * mj.r_stride + row_rindex[t]];
-        if (rv >= p) rv %= p;
-        put_slot<S>(bufB, first ? row_place : first_idx[t], sub_mod(rv, sums ? rowsum[t] % p : 0, p), small);
+#pragma unroll
+    for (int k = 0; k < OWN; ++k) share[k] = slot[k] & MaskSlot::kFirst ? r[rindex[k]] : 0;
+    SmallInverse consts;
+    if (small && transforms) consts.request(mj.small, tid);
+    unsigned long long *rowsum = reinterpret_cast<unsigned long long *>(bufA);
+    if (sums) {
+#pragma unroll
+        for (int k = 0; k < OWN; ++k) rowsum[tid + k * ALL] = 0;
+    }
+    // every slot but the first of each real output is a draw from the mask stream; values go to the position the mod-p
+    // transform expects them at
+    u64 v[OWN];
+    draw_uniforms<ALL>(v, p, mj.pbits, stream_state(mj.mask_seed, kStreamMask), ((u64)b << 32) + ((u64)O << 16) + (u64)tid);
+    if (sums) __syncthreads();
+    // plain integer sums of a row's values below p: at most n of them, far from 64 bits
+#pragma unroll
+    for (int k = 0; k < OWN; ++k) {
+        if (slot[k] & MaskSlot::kFirst) continue;
+        put_slot<S>(bufB, slot[k] & (N - 1), v[k], small);
+        if (sums && (slot[k] & MaskSlot::kInRow)) atomicAdd(&rowsum[slot[k] >> MaskSlot::kBits & (N - 1)], (unsigned long long)v[k]);
+    }
+    if (sums) __syncthreads();
+    // the first slot of every real row absorbs r minus the row's other slots
+#pragma unroll
+    for (int k = 0; k < OWN; ++k) {
+        if (!(slot[k] & MaskSlot::kFirst)) continue;
+        u64 x = share[k];
+        if (x >= p) x %= p;
+        if (sums) {
+            const u64 sum = rowsum[slot[k] >> MaskSlot::kBits & (N - 1)];
+            x = sub_mod(x, csub(sum - mulhi64(sum, mj.Tp.mod.one_s) * p, p), p);
+        }
+        put_slot<S>(bufB, slot[k] & (N - 1), x, small);
     }
     __syncthreads();
     // slots -> plaintext polynomial (inverse transform mod p) -> delta * m mod q -> evaluation domain mod q
-    u64 a[PER];
-    slots_to_coefficients<WIDE, S>(a, bufA, bufB, mj.Tp, mj.small, consts, tid);        // LDS phases A B A
+    if (transforms) {
+        u64 a[PER];
+        slots_to_coefficients<WIDE, S>(a, bufA, bufB, mj.Tp, mj.small, consts, tid);        // LDS phases A B A
 #pragma unroll
-    for (int k = 0; k < PER; ++k) a[k] = mont<WIDE, true, true>(plain_words(a[k]), mj.delta, T.mont, BIAS);
-    forward_to_lds<WIDE, S, BIASED>(a, bufA, bufB, T, tid);             // LDS phases B A B A, result in bufA
+        for (int k = 0; k < PER; ++k) a[k] = mont<WIDE, true, true>(plain_words(a[k]), mj.delta, T.mont, BIAS);
+        forward_to_lds<WIDE, S, BIASED, ALONE>(a, bufA, bufB, T, tid);      // LDS phases B A B A, result in bufA
+    } else {
+        // as many barriers as the transforms of n = 1024 and 2048 have: one, then two
+        static_assert(GROUPS == 1 || LOGN <= 11, "");
+        __syncthreads();
+        __syncthreads();
+        __syncthreads();
+    }
 #pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const int i = tid + k * NT;
+    for (int k = 0; k < OWN; ++k) {
+        const int i = tid + k * ALL;
         store(k, i, canonical<WIDE>(biased_words(bufA[pad<S>(i)]), T));
     }
 }
 // ... as one more partial ciphertext of the item: minus the mask on c0
-template <bool WIDE, int S>
+template <bool WIDE, int S, bool ALONE = false, int GROUPS = 1>
 __device__ __forceinline__ void mask_partial(const PermJob &job, const RingTables &T, const MaskJob &mj, int item, u64 *bufA,
                                              u64 *bufB) {
     u64 *out = job.partial + ((size_t)item * job.slots + job.nchunks) * 2 * N;
     const u64 q = T.mod.q;
-    mask_role<WIDE, S>(T, mj, item, bufA, bufB, [&](int, int i, u64 m) {
+    mask_role<WIDE, S, ALONE, GROUPS>(T, mj, item, bufA, bufB, [&](int, int i, u64 m) {
         out[i] = m ? q - m : 0;
         out[N + i] = 0;
     });
@@ -975,24 +987,37 @@ __device__ __forceinline__ void mask_partial(const PermJob &job, const RingTable
 // launch and without partial ciphertexts.
 // From wire to wire (with the layout's loads requested ahead of the draws): 16x128 on one input 27.5 -> 24.1 us; that
 // and he_fc 1000x512 on one input, where a mask is the longest workgroup, 40.9 -> 39.6 us.
-template <bool WIDE>
-__global__ __launch_bounds__(NT) void scmult_masked_ring(PermJob job, RingTables T, MaskJob mj, u64 *ct_out) {
+// GROUPS = 2: as in mask_role, for launches that leave a CU two wavefronts per SIMD at most; larger ones are bound by the
+// vector ALU.  16x128 on one input 20.9 us, 19.6 with the slots' draws together and 18.2 with two groups; on 512 inputs, one
+// group, 41.5 -> 39.7 us.
+template <bool WIDE, int GROUPS>
+__global__ __launch_bounds__(NT * GROUPS) void scmult_masked_ring(PermJob job, RingTables T, MaskJob mj, u64 *ct_out) {
     __shared__ u64 bufA[lds_words(ALONE_S)], bufB[lds_words(ALONE_S)];
     const int item = blockIdx.x;
     const u64 *c0 = job.ct_in + (size_t)item * job.in_item_stride, *c1 = c0 + N;
     const ulonglong2 *w = reinterpret_cast<const ulonglong2 *>(job.w2);
-    u64 x0[PER], x1[PER];
+    // requested ahead of the mask and multiplied behind it; at n = 8192 there are no registers to hold them meanwhile
+    constexpr bool EARLY = LOGN < 13;
+    constexpr int OWN = PER / GROUPS, HELD = EARLY ? OWN : 1;
+    u64 x0[HELD], x1[HELD];
+    ulonglong2 ww[HELD];
+    if (EARLY) {
 #pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const int i = threadIdx.x + k * NT;
-        const ulonglong2 ww = w[i];
-        x0[k] = unsign(mont<WIDE>(plain_words(c0[i]), ww, T.mont), T.mod.q);
-        x1[k] = unsign(mont<WIDE>(plain_words(c1[i]), ww, T.mont), T.mod.q);
+        for (int k = 0; k < HELD; ++k) {
+            const int i = threadIdx.x + k * NT * GROUPS;
+            ww[k] = w[i];
+            x0[k] = c0[i];
+            x1[k] = c1[i];
+        }
     }
     u64 *out = ct_out + (size_t)item * 2 * N;
-    mask_role<WIDE, ALONE_S>(T, mj, item, bufA, bufB, [&](int k, int i, u64 m) {
-        out[i] = sub_mod(x0[k], m, T.mod.q);
-        out[N + i] = x1[k];
+    mask_role<WIDE, ALONE_S, EARLY, GROUPS>(T, mj, item, bufA, bufB, [&](int k, int i, u64 m) {
+        const int h = EARLY ? k : 0;
+        const ulonglong2 wk = EARLY ? ww[h] : w[i];
+        u64 a, b;
+        mont2<WIDE, false, NONE>(a, b, plain_words(EARLY ? x0[h] : c0[i]), wk, plain_words(EARLY ? x1[h] : c1[i]), wk, T.mont);
+        out[i] = sub_mod(unsign(a, T.mod.q), m, T.mod.q);
+        out[N + i] = unsign(b, T.mod.q);
     });
 }
 
@@ -1010,18 +1035,18 @@ __global__ __launch_bounds__(NT) void scmult_masked_ring(PermJob job, RingTables
 // Short sums (a convolution's kernel orders) of other counts have keys that fit an L2 and chunks of unequal length: the chunks of
 // an item in turn, so that every CU gets some of each.
 __device__ __forceinline__ void item_and_chunk(const PermJob &job, int &item, int &chunk) {
-    const int w = blockIdx.x, xcd = w & 7, s = w >> 3;
-    if ((job.nchunks & 7) == 0) {
-        const int per = job.nchunks >> 3, first = s / (8 * job.items) * 8, width = min(8, per - first), r = s - first * job.items;
-        chunk = xcd * per + first + r % width;
-        item = r / width;
+    const u32 w = blockIdx.x, xcd = w & 7, s = w >> 3, items = (u32)job.items, nchunks = (u32)job.nchunks;
+    if ((nchunks & 7) == 0) {
+        const u32 per = nchunks >> 3, first = s / (8 * items) * 8, width = min(8u, per - first), r = s - first * items;
+        item = (int)(r / width);
+        chunk = (int)(xcd * per + first + r - (u32)item * width);
     } else if (job.G >= 32) {
-        const int total = job.items * job.nchunks, at = xcd * (total >> 3) + min(xcd, total & 7) + s;
-        chunk = at / job.items;
-        item = at % job.items;
+        const u32 total = items * nchunks, at = xcd * (total >> 3) + min(xcd, total & 7) + s;
+        chunk = (int)(at / items);
+        item = (int)(at - (u32)chunk * items);
     } else {
-        item = w / job.nchunks;
-        chunk = w % job.nchunks;
+        item = (int)(w / nchunks);
+        chunk = (int)(w - (u32)item * nchunks);
     }
 }
 
@@ -1096,7 +1121,7 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
     constexpr int AHEAD = FEW ? PER : LOGN == 12 ? 6 : LOGN == 13 ? 0 : 4, EARLY = LOGN == 13 ? 0 : PER;
     const int tid = threadIdx.x;
     if ((int)blockIdx.x >= job.items * job.nchunks) {   // only launched when mj.enabled
-        mask_partial<WIDE, PERM_S>(job, T, mj, (int)blockIdx.x - job.items * job.nchunks, bufA, bufB);
+        mask_partial<WIDE, PERM_S, FEW>(job, T, mj, (int)blockIdx.x - job.items * job.nchunks, bufA, bufB);
         return;
     }
     int item, chunk;
@@ -2102,9 +2127,16 @@ static int perm_masked(const gala_ctx *c, void *stream, const PermJob &job, cons
     const bool alone = job.product_only && apart && r_apart;
     if (alone) {
         rc = by_width(c, [&](auto width) {
-            hipLaunchKernelGGL(scmult_masked_ring<decltype(width)::value>, dim3((unsigned)job.items), dim3(NT), 0, st, job,
-                               make_tables(c->d_tw2, c->ntt_q), mj, fin.ct_out);
-            return (int)hipGetLastError();
+            constexpr bool WIDE = decltype(width)::value;
+            auto go = [&](auto kernel, int groups) {
+                hipLaunchKernelGGL(kernel, dim3((unsigned)job.items), dim3(NT * groups), 0, st, job, make_tables(c->d_tw2, c->ntt_q),
+                                   mj, fin.ct_out);
+                return (int)hipGetLastError();
+            };
+#if GALA_LOGN <= 11
+            if (few(2 * (size_t)job.items)) return go(scmult_masked_ring<WIDE, 2>, 2);
+#endif
+            return go(scmult_masked_ring<WIDE, 1>, 1);
         });
     } else {
         rc = launch_perm(c, stream, job, mj);

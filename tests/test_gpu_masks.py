@@ -1,0 +1,31 @@
+"""Share masks of the ring kernels against the oracle: plaintext primes under which every second or third draw is made again,
+rows of one, several and all slots, and layers without rotations on both sides of the launch that gives a mask two groups
+of threads (512 inputs at n = 1024, 256 at 2048)."""
+import pytest
+
+from paper_2105_01827_amd import workloads as wl
+from tests.helpers import small_params
+from tests.test_gpu_parity import conv_case, fc_case
+
+pytestmark = pytest.mark.gpu
+
+
+def _often_redrawn(n):
+    return small_params(n, p=wl.find_prime_below((1 << 19) + (1 << 17), 2 * n))
+
+
+@pytest.mark.parametrize("n", [1024, 2048, 4096, 8192])
+@pytest.mark.parametrize("n_o,n_i", [(1, 100), (16, 64), (5, 3), (40, 300)])
+def test_he_fc_masks(n, n_o, n_i):
+    fc_case(_often_redrawn(n), n_o, n_i, 2, [0, 1], seed=n_o)
+
+
+@pytest.mark.parametrize("n", [1024, 2048, 4096, 8192])
+def test_he_conv_masks(n):
+    conv_case(_often_redrawn(n), (n // 64 + 1, 3, 1, 1, 7, 6), 2, [(0, 0), (1, 1)], seed=n)
+
+
+@pytest.mark.parametrize("n,batch", [(1024, 512), (1024, 513), (2048, 256), (2048, 257)])
+def test_layers_without_rotations_around_the_two_group_launch(n, batch):
+    plan = fc_case(_often_redrawn(n), 16, 50, batch, [0, 1, batch - 1], seed=batch)[2]
+    assert plan.G == 1
