@@ -115,117 +115,186 @@ __device__ __forceinline__ u128 recombine(const int (&c)[15]) {
     return ((u128)(w2 | (w3 << 32)) << 64) | (w0 | (w1 << 32));
 }
 
-// One workgroup = one coefficient, WAVES row tiles (one per wavefront) and 2 column tiles.  The column
-// operand (rotated inputs) of a term block is staged once in LDS and read by all wavefronts; every wavefront
-// streams its own row operand (encoded kernels) from memory, so each operand byte is fetched once per
-// workgroup.  Loads of the next term block are issued before the MFMAs of the current one.
+// Moves 16 bytes a lane from base + offset (a byte offset of each lane) to LDS, 1 KiB in the order of the lanes from `to` on.
+// Nothing comes back to a register: what is in flight costs LDS only.  The caller waits with vmcnt.
+template <bool ONCE>
+__device__ __forceinline__ void load_to_lds(const v4i *base, u32 offset, u32 to) {
+    if (ONCE)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" : : "s"(to), "v"(offset), "s"(base) : "memory");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(to), "v"(offset), "s"(base) : "memory");
+}
+
+// A task of the product: one coefficient, four row tiles and CT column tiles.
+struct MfmaTasks {
+    int row_groups, groups, count;         // groups = row groups x column groups, count = groups n
+    u32 per_groups, per_rows;              // ceil(2^32 / groups), ceil(2^32 / row_groups), or 0: divide
+};
+
+// A workgroup of RT x CT wavefronts, one 16x16 tile each, takes every gridDim.x-th task.  Its work is one sequence of stages, a
+// stage being one term block of one coefficient: 8 KiB of digit planes for each row and column tile, moved straight into
+// LDS STAGES - 1 stages ahead, through the ends of coefficients.
+// Bound by the row operand's stream from HBM.  One workgroup for each coefficient, its loads in registers one block ahead and
+// two workgroups a CU, spent half of its time on the first trip to memory and the last block's recombination: 16x16x128 to
+// 128 channels at batch 16 254 us from wire to wire, now 238 (212 without the products, 236 without the recombination; 246
+// with one stage ahead instead of two); at batch 3 162 -> 131, 13x11x24 to 40 channels at batch 5 73.5 -> 67.4, 22x29x154 to 21 at
+// batch 6 276 -> 220.  Eight consecutive coefficients a workgroup lost the gain: the eight-byte pieces of an output
+// line (BLK8) left the L2 one by one (285 us).
 // Output: tmp[i][row][column] (rows and columns padded to tiles), transposed afterwards; or, BLK8, in blocks of
 // eight coefficients tmp[i/8][row][column][i%8], which the Perm kernels read as they are (a thread's eight
 // consecutive coefficients of c0 and of c1 are the two halves of one 128-byte line).
 // ONCE: the row operand is past what the last-level cache holds and is loaded without being kept, which leaves the caches
 // to the column operand and the sums: 16x16x128 to 128 channels at batch 16 291.5 -> 275.4 us, with a special prime 523.7 -> 515.6 us.
-template <int WAVES, bool BLK8, bool FOLD, bool ONCE>
-__global__ __launch_bounds__(64 * WAVES, 8 / WAVES) void conv_mfma_kernel(const v4i *wl, const v4i *xl, u64 *tmp, int mtiles,
-                                                               int ntiles, int kblocks, int nblk16, int n, Modulus mod) {
-    constexpr int NT = 64 * WAVES, BLOADS = 1024 / NT;
-    __shared__ v4i bsm[2][2][8][64];     // [buffer][column tile][digit][lane], 32 KiB
+template <int RT, int CT, bool BLK8, bool FOLD, bool ONCE>
+__global__ __launch_bounds__(64 * RT * CT, 2) void conv_mfma_kernel(const v4i *wl, const v4i *xl, u64 *tmp, int mtiles, int ntiles,
+                                                                int kblocks, int nblk16, int n, MfmaTasks tasks, Modulus mod) {
+    constexpr int STAGES = RT * CT == 8 ? 3 : 2, TILE = 8192, STAGE = (RT + CT) * TILE;
+    constexpr int A_LOADS = 8 / CT, B_LOADS = 8 / RT, LOADS = A_LOADS + B_LOADS;       // of a wavefront and stage
+    __shared__ __attribute__((aligned(16))) unsigned char lds[STAGES * STAGE];
+    const u32 lds_at = (u32)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds;
     // the wavefront's number is the same in all its lanes: kept in a scalar register, with everything derived from it
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // BLK8: eight consecutive coefficients are handled by workgroups 8 apart, which run on the same XCD
-    const size_t i = BLK8 ? (size_t)(blockIdx.x & 7) * (n >> 3) + (blockIdx.x >> 3) : (size_t)blockIdx.x;
-    const int mt = blockIdx.y * WAVES + wave, nt0 = blockIdx.z * 2;
-    const bool live = mt < mtiles;
-    const int mtc = live ? mt : mtiles - 1;
+    const int row_tile = wave / CT, col_tile = wave % CT;
+    const int rem = nblk16 - 4 * (kblocks - 1);       // groups of 16 terms in the last term block
+
+    // Consecutive workgroups go to the eight XCDs in turn.  An XCD takes every eighth block of eight coefficients, one after the
+    // other with all of their groups: those read the same operands at the same time, and the coefficients of a
+    // block fill the same lines of the output (BLK8) while its L2 holds them.
+    const int spread = ((n >> 3) & 7) == 0 ? 8 : 1;
+    struct Task {
+        const v4i *a, *b;       // this wavefront's first chunks
+        int i, mt, nt;
+    };
+    // what a wavefront loads: digits of its row tile, and eighths of a column tile
+    const int load_row = wave / CT, load_digit = wave % CT * A_LOADS, load_col = wave / RT, load_eighth = wave % RT * B_LOADS;
+    auto task = [&](int t) {
+        const u32 xcd = spread == 8 ? (u32)t & 7 : 0, at = spread == 8 ? (u32)t >> 3 : (u32)t;
+        const u32 c = tasks.per_groups ? __umulhi(at, tasks.per_groups) : at / (u32)tasks.groups, g = at - c * (u32)tasks.groups;
+        const u32 ng = tasks.per_rows ? __umulhi(g, tasks.per_rows) : g / (u32)tasks.row_groups, mg = g - ng * (u32)tasks.row_groups;
+        Task k;
+        k.i = (int)(((c >> 3) * (u32)spread + xcd) * 8 + (c & 7));
+        k.mt = (int)mg * RT;
+        k.nt = (int)ng * CT;
+        k.a = wl + ((((size_t)k.i * mtiles + min(k.mt + load_row, mtiles - 1)) * kblocks) * 8 + load_digit) * 64;
+        k.b = xl + (((size_t)min(k.nt + load_col, ntiles - 1) * kblocks * 64) * n + k.i) * 8;
+        return k;
+    };
+    // Lanes beyond the last term read the last group's chunks again: every stage is the same number of loads, and nothing
+    // beyond the last term is read.
+    const u32 a_lane = (u32)lane * 16u, a_last = (u32)((min(lane >> 4, rem - 1) << 4) + (lane & 15)) * 16u;
+    // A column tile's chunks lie [lane][digit] in LDS, the digit xored with the lane's low bits: the eight digits of a
+    // coefficient are one line of memory, and 8 lanes that read the same digit find it in all of the banks.
+    const u32 b_lane = ((u32)(lane >> 3) * (u32)n * 8u + (u32)((lane & 7) ^ (lane >> 3))) * 16u;
+    auto load = [&](const Task &t, int kb, u32 to) {
+        const bool last = kb == kblocks - 1;
+        const v4i *a = t.a + (size_t)kb * 512, *b = t.b + (size_t)kb * 512 * n;
+        const u32 a_off = last ? a_last : a_lane;
+#pragma unroll
+        for (int r = 0; r < A_LOADS; ++r)
+            load_to_lds<ONCE>(a + r * 64, a_off, to + (u32)(load_row * TILE + (load_digit + r) * 1024));
+#pragma unroll
+        for (int r = 0; r < B_LOADS; ++r) {
+            const int eighth = load_eighth + r, from = last ? min(eighth >> 1, rem - 1) * 2 + (eighth & 1) : eighth;
+            load_to_lds<false>(b + (size_t)from * 64 * n, b_lane, to + (u32)((RT + load_col) * TILE + eighth * 1024));
+        }
+    };
     const v4i zero = v4i{0, 0, 0, 0};
-    // cooperative load of the column operand: 2 tiles x 64 lanes x 8 digits chunks, BLOADS per thread, with the
-    // digit fastest (128 contiguous bytes per lane); chunks beyond the last term block are zero without a load
-    auto b_load = [&](int kb, int r) -> v4i {
-        const int c = threadIdx.x + NT * r, nl = c >> 9, ln = (c >> 3) & 63, dg = c & 7;
-        const int nt = min(nt0 + nl, ntiles - 1);
-        if (kb * 4 + (ln >> 4) >= nblk16) return zero;
-        return xl[((((size_t)nt * kblocks + kb) * 64 + ln) * n + i) * 8 + dg];
-    };
-    auto b_slot = [&](int r) { const int c = threadIdx.x + NT * r; return (c >> 9) * 512 + (c & 7) * 64 + ((c >> 3) & 63); };
-    auto a_load = [&](int kb, v4i (&dst)[8]) {
-        const v4i *a = wl + (((i * mtiles + mtc) * kblocks + kb) * 8) * 64 + lane;
-        const bool on = kb * 4 + (lane >> 4) < nblk16;
+    v4i s[15];
+    // D_(u+v) += W_u X_v for all digit pairs.  A last block of at most 32 terms puts two digit pairs of the same sum into the
+    // 64 terms of an instruction, one of at most 16 terms four: 36 and 22 instructions instead of 64.
+    auto multiply = [&](const unsigned char *A, const unsigned char *B, auto groups, bool partial) {
+        constexpr int G = decltype(groups)::value;
+        const int g = G == 1 ? 0 : G == 2 ? lane >> 5 : lane >> 4, ln = G == 1 ? lane : lane & (64 / G - 1);
+        v4i av[8 / G];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            if (ONCE) dst[u] = on ? __builtin_nontemporal_load(a + (size_t)u * 64) : zero;
-            else dst[u] = on ? a[(size_t)u * 64] : zero;
-        }
-    };
-    v4i s[2][15];
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int k = 0; k < 15; ++k) s[t][k] = v4i{0, 0, 0, 0};
-    v4i av[8], an[8], bstage[BLOADS];
-#pragma unroll
-    for (int r = 0; r < BLOADS; ++r) bstage[r] = b_load(0, r);
-    a_load(0, av);
-    for (int kb = 0; kb < kblocks; ++kb) {
-        v4i *flat = &bsm[kb & 1][0][0][0];
-#pragma unroll
-        for (int r = 0; r < BLOADS; ++r) flat[b_slot(r)] = bstage[r];
-        __syncthreads();     // the other buffer was last read two barriers ago
-        const int nxt = min(kb + 1, kblocks - 1);
-#pragma unroll
-        for (int r = 0; r < BLOADS; ++r) bstage[r] = b_load(nxt, r);
-        a_load(nxt, an);
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            v4i bv[8];
-#pragma unroll
-            for (int v = 0; v < 8; ++v) bv[v] = bsm[kb & 1][t][v][lane];
-            // column-major over the digit pairs: the same accumulator comes back only every seventh instruction
-#pragma unroll
-            for (int v = 0; v < 8; ++v)
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    s[t][u + v] = __builtin_amdgcn_mfma_i32_16x16x64_i8(av[u], bv[v], s[t][u + v], 0, 0, 0);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
+        for (int u = 0; u < 8 / G; ++u) {
+            av[u] = *reinterpret_cast<const v4i *>(A + (u * G + g) * 1024 + ln * 16);
+            if (G == 1 && partial && lane >= 48) av[u] = zero;
         }
 #pragma unroll
-        for (int u = 0; u < 8; ++u) av[u] = an[u];
+        for (int v = 0; v < 7 + G; ++v) {
+            const int digit = v - g;
+            v4i bv = *reinterpret_cast<const v4i *>(B + ln * 128 + ((digit ^ ln) & 7) * 16);
+            if (G > 1 && (v < G - 1 || v > 7) && (digit < 0 || digit > 7)) bv = zero;
+#pragma unroll
+            for (int u = 0; u < 8 / G; ++u) s[u * G + v] = __builtin_amdgcn_mfma_i32_16x16x64_i8(av[u], bv, s[u * G + v], 0, 0, 0);
+        }
+    };
+
+    const int mine = (tasks.count - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x, total = mine * kblocks;
+    // the stage to load next and the stage at hand
+    int ahead_task = blockIdx.x, ahead_kb = 0, loaded = 0, now_task = blockIdx.x, kb = 0, i = 0, mt = 0, nt = 0;
+    u32 to = 0, from = 0;
+    Task ahead = task(ahead_task);
+    auto load_next = [&] {
+        if (loaded >= total) return;
+        load(ahead, ahead_kb, lds_at + to);
+        ++loaded;
+        to = to + STAGE == STAGES * STAGE ? 0 : to + STAGE;
+        if (++ahead_kb < kblocks) return;
+        ahead_kb = 0;
+        ahead_task += gridDim.x;
+        ahead = task(ahead_task);
+    };
+#pragma unroll
+    for (int k = 0; k < STAGES - 1; ++k) load_next();
+    for (int stage = 0; stage < total; ++stage) {
+        // this stage's loads are done, and everybody's products of the stage before: its buffer is the next one's
+        if (STAGES == 3 && stage + 1 < total) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(LOADS) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" : : : "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" : : : "memory");
+        load_next();
+        if (kb == 0) {
+            const Task t = task(now_task);
+            i = t.i;
+            mt = t.mt + row_tile;
+            nt = t.nt + col_tile;
+            now_task += gridDim.x;
+#pragma unroll
+            for (int k = 0; k < 15; ++k) s[k] = zero;
+        }
+        const bool live = mt < mtiles && nt < ntiles;
+        if (live) {
+            const unsigned char *A = lds + from + row_tile * TILE, *B = lds + from + (RT + col_tile) * TILE;
+            if (kb < kblocks - 1 || rem == 4) multiply(A, B, std::integral_constant<int, 1>{}, false);
+            else if (rem == 3) multiply(A, B, std::integral_constant<int, 1>{}, true);
+            else if (rem == 2) multiply(A, B, std::integral_constant<int, 2>{}, false);
+            else multiply(A, B, std::integral_constant<int, 4>{}, false);
+        }
+        from = from + STAGE == STAGES * STAGE ? 0 : from + STAGE;
         // The exact sum of K products of residues below 2^60 needs K * 2^120 < 2^128, and an int32 diagonal
         // 8 * K * 2^14 < 2^31: after every kFoldBlocks term blocks (192 terms) the sums so far are reduced mod q
         // and put back as three small non-negative diagonals (24 + 24 + 12 bits at 256^0, 256^3, 256^6), so sums
-        // of any length stay exact.  Layers of at most 192 terms run the instantiation without this branch (FOLD =
-        // false: the branch costs three spilled registers that the main loop reloads).
-        if (FOLD && kb % kFoldBlocks == kFoldBlocks - 1 && kb + 1 < kblocks) {
+        // of any length stay exact.  Layers of at most 192 terms run the instantiation without this branch.
+        if (FOLD && live && kb % kFoldBlocks == kFoldBlocks - 1 && kb + 1 < kblocks) {
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
+            for (int r = 0; r < 4; ++r) {
+                int c[15];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    int c[15];
+                for (int k = 0; k < 15; ++k) c[k] = s[k][r];
+                const u64 val = reduce128(recombine(c), mod);
 #pragma unroll
-                    for (int k = 0; k < 15; ++k) c[k] = s[t][k][r];
-                    const u64 val = reduce128(recombine(c), mod);
-#pragma unroll
-                    for (int k = 0; k < 15; ++k) s[t][k][r] = 0;
-                    s[t][0][r] = (int)(val & 0xffffff);
-                    s[t][3][r] = (int)((val >> 24) & 0xffffff);
-                    s[t][6][r] = (int)(val >> 48);
-                }
+                for (int k = 0; k < 15; ++k) s[k][r] = 0;
+                s[0][r] = (int)(val & 0xffffff);
+                s[3][r] = (int)((val >> 24) & 0xffffff);
+                s[6][r] = (int)(val >> 48);
+            }
         }
-    }
-    if (!live) return;
-    // lane holds rows 4*(lane/16) + r, column lane%16 of each 16x16 output tile
-    const size_t rowsP = (size_t)mtiles * 16, colsP = (size_t)ntiles * 16;
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-        if (nt0 + t >= ntiles) break;
+        if (++kb < kblocks) continue;
+        kb = 0;
+        if (!live) continue;
+        // lane holds rows 4*(lane/16) + r, column lane%16 of the 16x16 output tile
+        const size_t rowsP = (size_t)mtiles * 16, colsP = (size_t)ntiles * 16;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             int c[15];
 #pragma unroll
-            for (int k = 0; k < 15; ++k) c[k] = s[t][k][r];
+            for (int k = 0; k < 15; ++k) c[k] = s[k][r];
             const u64 val = reduce128(recombine(c), mod);
-            const int m = mt * 16 + 4 * (lane >> 4) + r, col = (nt0 + t) * 16 + (lane & 15);
-            if (BLK8) tmp[(((i >> 3) * rowsP + m) * colsP + col) * 8 + (i & 7)] = val;
-            else tmp[(i * rowsP + m) * colsP + col] = val;
+            const int m = mt * 16 + 4 * (lane >> 4) + r, col = nt * 16 + (lane & 15);
+            if (BLK8) tmp[(((size_t)(i >> 3) * rowsP + m) * colsP + col) * 8 + (i & 7)] = val;
+            else tmp[((size_t)i * rowsP + m) * colsP + col] = val;
         }
     }
 }
@@ -273,23 +342,37 @@ int launch_conv_mfma(const gala_ctx *c, void *stream, const u64 *wl, const u64 *
                      u64 *tmp, bool blocks_of_eight) {
     int mtiles, ntiles, kblocks;
     conv_mfma_geometry(groups, 2 * batch, nterm, &mtiles, &ntiles, &kblocks);
-    constexpr int WAVES = 4;
-    const dim3 grid((unsigned)c->n, (unsigned)((mtiles + WAVES - 1) / WAVES), (unsigned)((ntiles + 1) / 2));
     const bool fold = kblocks > kFoldBlocks;
-    auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, grid, dim3(64 * WAVES), 0, (hipStream_t)stream, reinterpret_cast<const v4i *>(wl),
-                           reinterpret_cast<const v4i *>(xl), tmp, mtiles, ntiles, kblocks, (nterm + 15) / 16, c->n,
-                           c->dev_q.mod);
+    auto go = [&](auto kernel, int row_tiles, int col_tiles, int slots) {
+        const int row_groups = (mtiles + row_tiles - 1) / row_tiles, groups = row_groups * ((ntiles + col_tiles - 1) / col_tiles);
+        // Rounded up, a reciprocal divides x exactly while x d < 2^32, and x < groups n / 8, or groups n where n < 64.  2^32 itself does not fit.
+        auto reciprocal = [&](int d) { return d == 1 || groups >= 2048 ? 0 : (u32)((((u64)1 << 32) + d - 1) / d); };
+        const MfmaTasks tasks{row_groups, groups, groups * c->n, reciprocal(groups), reciprocal(row_groups)};
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(tasks.count < slots ? tasks.count : slots)), dim3(64 * row_tiles * col_tiles), 0,
+                           (hipStream_t)stream, reinterpret_cast<const v4i *>(wl), reinterpret_cast<const v4i *>(xl), tmp, mtiles, ntiles,
+                           kblocks, (nterm + 15) / 16, c->n, tasks, c->dev_q.mod);
     };
-    auto pick = [&](auto once) {
+    auto pick = [&](auto once, auto rows, auto cols) {
         constexpr bool ONCE = decltype(once)::value;
-        if (blocks_of_eight) fold ? go(conv_mfma_kernel<WAVES, true, true, ONCE>) : go(conv_mfma_kernel<WAVES, true, false, ONCE>);
-        else fold ? go(conv_mfma_kernel<WAVES, false, true, ONCE>) : go(conv_mfma_kernel<WAVES, false, false, ONCE>);
+        constexpr int RT = decltype(rows)::value, CT = decltype(cols)::value;
+        // as many workgroups as a CU's LDS holds: 144 KiB each, 64 to 80, or 48
+        auto run = [&](auto kernel) { go(kernel, RT, CT, RT * CT == 8 ? 256 : RT * CT == 2 ? 768 : 512); };
+        if (blocks_of_eight) fold ? run(conv_mfma_kernel<RT, CT, true, true, ONCE>) : run(conv_mfma_kernel<RT, CT, true, false, ONCE>);
+        else fold ? run(conv_mfma_kernel<RT, CT, false, true, ONCE>) : run(conv_mfma_kernel<RT, CT, false, false, ONCE>);
     };
     // the chunks of the row operand that are read: none beyond the last term
     const size_t row_bytes = (size_t)c->n * mtiles * 16 * ((nterm + 15) / 16) * 16 * sizeof(u64);
-    if (streams_past_cache(row_bytes)) pick(std::true_type{});
-    else pick(std::false_type{});
+    const bool once = streams_past_cache(row_bytes);
+    std::integral_constant<int, 1> one;
+    std::integral_constant<int, 2> two;
+    std::integral_constant<int, 4> four;
+    // Two row tiles a workgroup where there are no more of them: 40 channels 3x3 at 22x7 to 5, batch 16, 77.7 -> 71.5 us from wire to
+    // wire, 16x16x128 to 32 at batch 16 119.1 -> 112.3, to 16 at batch 8 78.8 -> 75.9.  With four and eight row tiles four are
+    // faster: 64 to 64 channels 1x1 at batch 16 94.7 us against 96.2, 128 to 128 3x3 237.7 against 254.8.
+    if (mtiles <= 2 && ntiles == 1) once ? pick(std::true_type{}, two, one) : pick(std::false_type{}, two, one);
+    else if (mtiles <= 2) once ? pick(std::true_type{}, two, two) : pick(std::false_type{}, two, two);
+    else if (ntiles == 1) once ? pick(std::true_type{}, four, one) : pick(std::false_type{}, four, one);
+    else once ? pick(std::true_type{}, four, two) : pick(std::false_type{}, four, two);
     return (int)hipGetLastError();
 }
 int launch_conv_untranspose(const gala_ctx *c, void *stream, const u64 *tmp, int batch, int groups, u64 *acc) {
