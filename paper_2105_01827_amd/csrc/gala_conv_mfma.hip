@@ -115,20 +115,29 @@ __device__ __forceinline__ u128 recombine(const int (&c)[15]) {
     return ((u128)(w2 | (w3 << 32)) << 64) | (w0 | (w1 << 32));
 }
 
-// Moves 16 bytes a lane from base + offset (a byte offset of each lane) to LDS, 1 KiB in the order of the lanes from `to` on.
-// Nothing comes back to a register: what is in flight costs LDS only.  The caller waits with vmcnt.
-template <bool ONCE>
+// f(integral_constant k) for k = FROM .. TO - 1
+template <int FROM, int TO, class F>
+__device__ __forceinline__ void for_each(F f) {
+    if constexpr (FROM < TO) {
+        f(std::integral_constant<int, FROM>{});
+        for_each<FROM + 1, TO>(f);
+    }
+}
+// Moves 16 bytes a lane from base + offset (a byte offset of each lane) + AT to LDS, 1 KiB in the order of the lanes from
+// to + AT on.  Nothing comes back to a register: what is in flight costs LDS only.  The caller waits with vmcnt, and reads
+// what it waited for behind a barrier that also orders memory; the load itself may move among reads of other parts of LDS.
+template <bool ONCE, int AT>
 __device__ __forceinline__ void load_to_lds(const v4i *base, u32 offset, u32 to) {
     if (ONCE)
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt" : : "s"(to), "v"(offset), "s"(base) : "memory");
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3 nt" : : "s"(to), "v"(offset), "s"(base), "n"(AT));
     else
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" : : "s"(to), "v"(offset), "s"(base) : "memory");
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 offset:%3" : : "s"(to), "v"(offset), "s"(base), "n"(AT));
 }
 
-// A task of the product: one coefficient, four row tiles and CT column tiles.
+// A task of the product: one coefficient, RT row tiles and CT column tiles.  groups = row groups x column groups.
+// A workgroup's next task is `step` = coefficients groups + part further on its XCD.
 struct MfmaTasks {
-    int row_groups, groups, count;         // groups = row groups x column groups, count = groups n
-    u32 per_groups, per_rows;              // ceil(2^32 / groups), ceil(2^32 / row_groups), or 0: divide
+    u32 row_groups, groups, count, step_coefs, step_part;         // count = groups n
 };
 
 // A workgroup of RT x CT wavefronts, one 16x16 tile each, takes every gridDim.x-th task.  Its work is one sequence of stages, a
@@ -136,9 +145,10 @@ struct MfmaTasks {
 // LDS STAGES - 1 stages ahead, through the ends of coefficients.
 // Bound by the row operand's stream from HBM.  One workgroup for each coefficient, its loads in registers one block ahead and
 // two workgroups a CU, spent half of its time on the first trip to memory and the last block's recombination: 16x16x128 to
-// 128 channels at batch 16 254 us from wire to wire, now 238 (212 without the products, 236 without the recombination; 246
-// with one stage ahead instead of two); at batch 3 162 -> 131, 13x11x24 to 40 channels at batch 5 73.5 -> 67.4, 22x29x154 to 21 at
-// batch 6 276 -> 220.  Eight consecutive coefficients a workgroup lost the gain: the eight-byte pieces of an output
+// 128 channels at batch 16 254 us from wire to wire, 238 in stages (212 without the products, 236 without the recombination;
+// 246 with one stage ahead instead of two; 257 with five stages of half a block ahead), 230 with the loads among the products and
+// the next task found by two additions; at batch 3 162 -> 131, 13x11x24 to 40 channels at batch 5 73.5 -> 66.3, 22x29x154 to
+// 21 at batch 6 276 -> 219.  Eight consecutive coefficients a workgroup lost the gain: the eight-byte pieces of an output
 // line (BLK8) left the L2 one by one (285 us).
 // Output: tmp[i][row][column] (rows and columns padded to tiles), transposed afterwards; or, BLK8, in blocks of
 // eight coefficients tmp[i/8][row][column][i%8], which the Perm kernels read as they are (a thread's eight
@@ -160,108 +170,138 @@ __global__ __launch_bounds__(64 * RT * CT, 2) void conv_mfma_kernel(const v4i *w
     // Consecutive workgroups go to the eight XCDs in turn.  An XCD takes every eighth block of eight coefficients, one after the
     // other with all of their groups: those read the same operands at the same time, and the coefficients of a
     // block fill the same lines of the output (BLK8) while its L2 holds them.
-    const int spread = ((n >> 3) & 7) == 0 ? 8 : 1;
+    const u32 spread = ((n >> 3) & 7) == 0 ? 8 : 1, xcd = blockIdx.x & (spread - 1);
     struct Task {
-        const v4i *a, *b;       // this wavefront's first chunks
-        int i, mt, nt;
+        u32 coef, group;        // number of the coefficient on the XCD, and group
+    };
+    auto coefficient = [&](const Task &t) { return (int)(((t.coef >> 3) * spread + xcd) * 8 + (t.coef & 7)); };
+    auto step = [&](Task &t) {
+        t.coef += tasks.step_coefs;
+        t.group += tasks.step_part;
+        if (t.group >= tasks.groups) {
+            t.group -= tasks.groups;
+            ++t.coef;
+        }
     };
     // what a wavefront loads: digits of its row tile, and eighths of a column tile
     const int load_row = wave / CT, load_digit = wave % CT * A_LOADS, load_col = wave / RT, load_eighth = wave % RT * B_LOADS;
-    auto task = [&](int t) {
-        const u32 xcd = spread == 8 ? (u32)t & 7 : 0, at = spread == 8 ? (u32)t >> 3 : (u32)t;
-        const u32 c = tasks.per_groups ? __umulhi(at, tasks.per_groups) : at / (u32)tasks.groups, g = at - c * (u32)tasks.groups;
-        const u32 ng = tasks.per_rows ? __umulhi(g, tasks.per_rows) : g / (u32)tasks.row_groups, mg = g - ng * (u32)tasks.row_groups;
-        Task k;
-        k.i = (int)(((c >> 3) * (u32)spread + xcd) * 8 + (c & 7));
-        k.mt = (int)mg * RT;
-        k.nt = (int)ng * CT;
-        k.a = wl + ((((size_t)k.i * mtiles + min(k.mt + load_row, mtiles - 1)) * kblocks) * 8 + load_digit) * 64;
-        k.b = xl + (((size_t)min(k.nt + load_col, ntiles - 1) * kblocks * 64) * n + k.i) * 8;
-        return k;
-    };
     // Lanes beyond the last term read the last group's chunks again: every stage is the same number of loads, and nothing
     // beyond the last term is read.
     const u32 a_lane = (u32)lane * 16u, a_last = (u32)((min(lane >> 4, rem - 1) << 4) + (lane & 15)) * 16u;
     // A column tile's chunks lie [lane][digit] in LDS, the digit xored with the lane's low bits: the eight digits of a
     // coefficient are one line of memory, and 8 lanes that read the same digit find it in all of the banks.
-    const u32 b_lane = ((u32)(lane >> 3) * (u32)n * 8u + (u32)((lane & 7) ^ (lane >> 3))) * 16u;
-    auto load = [&](const Task &t, int kb, u32 to) {
-        const bool last = kb == kblocks - 1;
-        const v4i *a = t.a + (size_t)kb * 512, *b = t.b + (size_t)kb * 512 * n;
-        const u32 a_off = last ? a_last : a_lane;
+    u32 b_lane[B_LOADS], b_last[B_LOADS];
 #pragma unroll
-        for (int r = 0; r < A_LOADS; ++r)
-            load_to_lds<ONCE>(a + r * 64, a_off, to + (u32)(load_row * TILE + (load_digit + r) * 1024));
-#pragma unroll
-        for (int r = 0; r < B_LOADS; ++r) {
-            const int eighth = load_eighth + r, from = last ? min(eighth >> 1, rem - 1) * 2 + (eighth & 1) : eighth;
-            load_to_lds<false>(b + (size_t)from * 64 * n, b_lane, to + (u32)((RT + load_col) * TILE + eighth * 1024));
-        }
-    };
+    for (int r = 0; r < B_LOADS; ++r) {
+        const int eighth = load_eighth + r, from = min(eighth >> 1, rem - 1) * 2 + (eighth & 1);
+        const u32 chunk = (u32)(lane >> 3) * (u32)n * 8u + (u32)((lane & 7) ^ (lane >> 3));
+        b_lane[r] = (chunk + (u32)(eighth * 64 * n)) * 16u;
+        b_last[r] = (chunk + (u32)(from * 64 * n)) * 16u;
+    }
     const v4i zero = v4i{0, 0, 0, 0};
     v4i s[15];
     // D_(u+v) += W_u X_v for all digit pairs.  A last block of at most 32 terms puts two digit pairs of the same sum into the
     // 64 terms of an instruction, one of at most 16 terms four: 36 and 22 instructions instead of 64.
-    auto multiply = [&](const unsigned char *A, const unsigned char *B, auto groups, bool partial) {
-        constexpr int G = decltype(groups)::value;
-        const int g = G == 1 ? 0 : G == 2 ? lane >> 5 : lane >> 4, ln = G == 1 ? lane : lane & (64 / G - 1);
-        v4i av[8 / G];
+    // load(r), r < LOADS: the next stage's loads.  With eight wavefronts they are asked for between the products (SPREAD): all at the
+    // start of a stage they held every wavefront up for 1070 clocks, 51 000 of a launch's 238 000.
+    constexpr bool SPREAD = RT * CT == 8;
+    auto multiply = [&](const unsigned char *A, const unsigned char *B, auto groups, bool partial, auto load) {
+        constexpr int G = decltype(groups)::value, STEPS = 7 + G;
+        const int g = lane / (64 / G), ln = lane % (64 / G);
+        auto column = [&](int v) {
+            const int digit = v - g;
+            v4i bv = *reinterpret_cast<const v4i *>(B + ln * 128 + ((digit ^ ln) & 7) * 16);
+            if (G > 1 && (v < G - 1 || v > 7) && (digit < 0 || digit > 7)) bv = zero;
+            return bv;
+        };
+        if constexpr (!SPREAD) for_each<0, LOADS>(load);
+        v4i av[8 / G], bv = column(0);
 #pragma unroll
         for (int u = 0; u < 8 / G; ++u) {
             av[u] = *reinterpret_cast<const v4i *>(A + (u * G + g) * 1024 + ln * 16);
             if (G == 1 && partial && lane >= 48) av[u] = zero;
         }
-#pragma unroll
-        for (int v = 0; v < 7 + G; ++v) {
-            const int digit = v - g;
-            v4i bv = *reinterpret_cast<const v4i *>(B + ln * 128 + ((digit ^ ln) & 7) * 16);
-            if (G > 1 && (v < G - 1 || v > 7) && (digit < 0 || digit > 7)) bv = zero;
+        for_each<0, STEPS>([&](auto number) {
+            constexpr int v = decltype(number)::value;
+            const v4i next = column(v + 1 < STEPS ? v + 1 : v);
+            if constexpr (SPREAD) for_each<v * LOADS / STEPS, (v + 1) * LOADS / STEPS>(load);
 #pragma unroll
             for (int u = 0; u < 8 / G; ++u) s[u * G + v] = __builtin_amdgcn_mfma_i32_16x16x64_i8(av[u], bv, s[u * G + v], 0, 0, 0);
-        }
+            __builtin_amdgcn_sched_barrier(0);
+            bv = next;
+        });
     };
 
-    const int mine = (tasks.count - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x, total = mine * kblocks;
+    const int mine = ((int)tasks.count - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x, total = mine * kblocks;
+    const u32 place = blockIdx.x / spread;
     // the stage to load next and the stage at hand
-    int ahead_task = blockIdx.x, ahead_kb = 0, loaded = 0, now_task = blockIdx.x, kb = 0, i = 0, mt = 0, nt = 0;
-    u32 to = 0, from = 0;
-    Task ahead = task(ahead_task);
-    auto load_next = [&] {
+    Task ahead{place / tasks.groups, place % tasks.groups}, now = ahead;
+    int ahead_kb = 0, loaded = 0, kb = 0, i = 0, mt = 0, nt = 0;
+    u32 to = lds_at, from = 0;
+    const v4i *a_next, *b_next;        // this wavefront's chunks of the stage to load next
+    auto start = [&] {
+        const u32 ng = tasks.groups == tasks.row_groups ? 0 : ahead.group / tasks.row_groups, mg = ahead.group - ng * tasks.row_groups;
+        const size_t row = (size_t)coefficient(ahead) * mtiles + min((int)mg * RT + load_row, mtiles - 1);
+        a_next = wl + (row * kblocks * 8 + load_digit) * 64;
+        b_next = xl + ((size_t)min((int)ng * CT + load_col, ntiles - 1) * kblocks * 64 * n + coefficient(ahead)) * 8;
+    };
+    start();
+    // load r of this wavefront's of the next stage
+    auto load_one = [&](auto number) {
+        constexpr int r = decltype(number)::value;
         if (loaded >= total) return;
-        load(ahead, ahead_kb, lds_at + to);
+        const bool last = ahead_kb == kblocks - 1;
+        if constexpr (r < A_LOADS)
+            load_to_lds<ONCE, r % 4 * 1024>(a_next + r / 4 * 256, last ? a_last : a_lane,
+                                            to + (u32)(load_row * TILE + (load_digit + r / 4 * 4) * 1024));
+        else
+            load_to_lds<false, 0>(b_next, last ? b_last[r - A_LOADS] : b_lane[r - A_LOADS],
+                                  to + (u32)((RT + load_col) * TILE + (load_eighth + r - A_LOADS) * 1024));
+    };
+    auto loaded_all = [&] {
+        if (loaded >= total) return;
         ++loaded;
-        to = to + STAGE == STAGES * STAGE ? 0 : to + STAGE;
-        if (++ahead_kb < kblocks) return;
-        ahead_kb = 0;
-        ahead_task += gridDim.x;
-        ahead = task(ahead_task);
+        to = to + STAGE == lds_at + STAGES * STAGE ? lds_at : to + STAGE;
+        if (++ahead_kb < kblocks) {
+            a_next += 512;
+            b_next += 512 * (size_t)n;
+        } else {
+            ahead_kb = 0;
+            step(ahead);
+            start();
+        }
     };
 #pragma unroll
-    for (int k = 0; k < STAGES - 1; ++k) load_next();
+    for (int k = 0; k < STAGES - 1; ++k) {
+        for_each<0, LOADS>(load_one);
+        loaded_all();
+    }
     for (int stage = 0; stage < total; ++stage) {
         // this stage's loads are done, and everybody's products of the stage before: its buffer is the next one's
         if (STAGES == 3 && stage + 1 < total) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"(LOADS) : "memory");
         else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" : : : "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" : : : "memory");
-        load_next();
         if (kb == 0) {
-            const Task t = task(now_task);
-            i = t.i;
-            mt = t.mt + row_tile;
-            nt = t.nt + col_tile;
-            now_task += gridDim.x;
+            const u32 ng = tasks.groups == tasks.row_groups ? 0 : now.group / tasks.row_groups;
+            i = coefficient(now);
+            mt = (int)(now.group - ng * tasks.row_groups) * RT + row_tile;
+            nt = (int)ng * CT + col_tile;
+            step(now);
 #pragma unroll
             for (int k = 0; k < 15; ++k) s[k] = zero;
         }
         const bool live = mt < mtiles && nt < ntiles;
         if (live) {
             const unsigned char *A = lds + from + row_tile * TILE, *B = lds + from + (RT + col_tile) * TILE;
-            if (kb < kblocks - 1 || rem == 4) multiply(A, B, std::integral_constant<int, 1>{}, false);
-            else if (rem == 3) multiply(A, B, std::integral_constant<int, 1>{}, true);
-            else if (rem == 2) multiply(A, B, std::integral_constant<int, 2>{}, false);
-            else multiply(A, B, std::integral_constant<int, 4>{}, false);
+            if (kb < kblocks - 1 || rem == 4) multiply(A, B, std::integral_constant<int, 1>{}, false, load_one);
+            else if (rem == 3) multiply(A, B, std::integral_constant<int, 1>{}, true, load_one);
+            else if (rem == 2) multiply(A, B, std::integral_constant<int, 2>{}, false, load_one);
+            else multiply(A, B, std::integral_constant<int, 4>{}, false, load_one);
+        } else {
+            for_each<0, LOADS>(load_one);
         }
+        loaded_all();
         from = from + STAGE == STAGES * STAGE ? 0 : from + STAGE;
         // The exact sum of K products of residues below 2^60 needs K * 2^120 < 2^128, and an int32 diagonal
         // 8 * K * 2^14 < 2^31: after every kFoldBlocks term blocks (192 terms) the sums so far are reduced mod q
@@ -345,10 +385,10 @@ int launch_conv_mfma(const gala_ctx *c, void *stream, const u64 *wl, const u64 *
     const bool fold = kblocks > kFoldBlocks;
     auto go = [&](auto kernel, int row_tiles, int col_tiles, int slots) {
         const int row_groups = (mtiles + row_tiles - 1) / row_tiles, groups = row_groups * ((ntiles + col_tiles - 1) / col_tiles);
-        // Rounded up, a reciprocal divides x exactly while x d < 2^32, and x < groups n / 8, or groups n where n < 64.  2^32 itself does not fit.
-        auto reciprocal = [&](int d) { return d == 1 || groups >= 2048 ? 0 : (u32)((((u64)1 << 32) + d - 1) / d); };
-        const MfmaTasks tasks{row_groups, groups, groups * c->n, reciprocal(groups), reciprocal(row_groups)};
-        hipLaunchKernelGGL(kernel, dim3((unsigned)(tasks.count < slots ? tasks.count : slots)), dim3(64 * row_tiles * col_tiles), 0,
+        const long count = (long)groups * c->n, grid = count < slots ? count : slots;
+        const int step = (int)grid / (((c->n >> 3) & 7) == 0 ? 8 : 1);
+        const MfmaTasks tasks{(u32)row_groups, (u32)groups, (u32)count, (u32)(step / groups), (u32)(step % groups)};
+        hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(64 * row_tiles * col_tiles), 0,
                            (hipStream_t)stream, reinterpret_cast<const v4i *>(wl), reinterpret_cast<const v4i *>(xl), tmp, mtiles, ntiles,
                            kblocks, (nterm + 15) / 16, c->n, tasks, c->dev_q.mod);
     };
