@@ -127,13 +127,13 @@ extern "C" int gala_encrypt_batch(const gala_ctx *c, void *stream, const gala_sk
                                   const uint64_t *seeds, int count, uint64_t *ct) {
     if (!c || !sk || !slots || !seeds || !ct || count < 0) return GALA_EARG;
     if (!c->has_device || !sk->d_s_hat) return GALA_EHIP;
-    return launch_encrypt(c, stream, sk->d_s_hat, slots, seeds, count, ct) ? GALA_EHIP : GALA_OK;
+    return launch_encrypt(c, stream, sk, slots, seeds, count, ct) ? GALA_EHIP : GALA_OK;
 }
 extern "C" int gala_decrypt_batch(const gala_ctx *c, void *stream, const gala_sk *sk, const uint64_t *ct, int count,
                                   uint64_t *slots) {
     if (!c || !sk || !slots || !ct || count < 0) return GALA_EARG;
     if (!c->has_device || !sk->d_s_hat) return GALA_EHIP;
-    return launch_decrypt(c, stream, sk->d_s_hat, ct, count, slots) ? GALA_EHIP : GALA_OK;
+    return launch_decrypt(c, stream, sk, ct, count, slots) ? GALA_EHIP : GALA_OK;
 }
 
 extern "C" int gala_fc_unpack_share_batch(const gala_fc_plan *pl, void *stream, const uint64_t *slots, int count,

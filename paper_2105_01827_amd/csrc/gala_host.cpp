@@ -163,6 +163,22 @@ static const u64 kGaussCdf[38] = {
     0xffff40fa0088d11dull, 0xffffd2e835e1c57dull, 0xfffff6524386ff1eull, 0xfffffe1db4769da5ull,
     0xffffffac0a1dcb08ull, 0xfffffff428673853ull};
 const u64 *gauss_cdf_table() { return kGaussCdf; }
+const GaussBuckets &gauss_buckets() {
+    static const GaussBuckets table = [] {
+        GaussBuckets b;
+        for (int i = 0; i < 2 * kGaussBound; ++i) b.t[i] = kGaussCdf[i];
+        for (int byte = 0; byte < 256; ++byte) {
+            int passed = 0, inside = 0;
+            for (const u64 t : kGaussCdf) {
+                if (t <= (u64)byte << 56) ++passed;
+                else if (t >> 56 == (u64)byte) ++inside;
+            }
+            b.passed[byte] = (unsigned char)(passed | (inside > 1 ? GaussBuckets::kSeveral : 0));
+        }
+        return b;
+    }();
+    return table;
+}
 }  // namespace gala
 extern "C" uint64_t gala_mix64(uint64_t z) { return gala::mix64(z); }
 extern "C" uint64_t gala_rand64(uint64_t seed, uint64_t stream, uint64_t idx, uint64_t attempt) {
@@ -474,9 +490,14 @@ extern "C" int gala_keygen(const gala_ctx *c, uint64_t seed, gala_sk **out) {
     for (int i = 0; i < c->n; ++i) sk->s[i] = lift_signed(draw_ternary(seed, kStreamSk, (u64)i), c->q);
     sk->s_hat = sk->s;
     c->ntt_q.forward(sk->s_hat.data());
-    if (c->has_device && upload(&sk->d_s_hat, sk->s_hat)) {
-        gala_sk_destroy(sk);
-        return GALA_EHIP;
+    if (c->has_device) {
+        const MontMaker mont = make_mont(c->q);
+        std::vector<MontPair> pairs(c->n);
+        for (int i = 0; i < c->n; ++i) pairs[i] = mont_pair(sk->s_hat[i], mont);
+        if (upload(&sk->d_s_hat, sk->s_hat) || upload(&sk->d_s_pairs, pairs)) {
+            gala_sk_destroy(sk);
+            return GALA_EHIP;
+        }
     }
     *out = sk;
     return GALA_OK;
@@ -484,6 +505,7 @@ extern "C" int gala_keygen(const gala_ctx *c, uint64_t seed, gala_sk **out) {
 extern "C" void gala_sk_destroy(gala_sk *sk) {
     if (!sk) return;
     if (sk->d_s_hat) hipFree(sk->d_s_hat);
+    if (sk->d_s_pairs) hipFree(sk->d_s_pairs);
     delete sk;
 }
 extern "C" int gala_sk_export(const gala_ctx *c, const gala_sk *sk, uint64_t *s_host) {

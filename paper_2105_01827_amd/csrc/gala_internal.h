@@ -19,6 +19,13 @@ constexpr int kGaussBound = 19;
 struct GaussCdf {
     u64 t[2 * kGaussBound];   // floor(2^64 * P[X <= -bound + i])
 };
+// The same by the draw's top byte, for kernels that make many draws: how many thresholds the byte's whole range has passed, and
+// kSeveral where more than one lies inside of it (the tails; elsewhere thresholds are further apart than a range is wide).
+struct GaussBuckets {
+    static constexpr unsigned char kSeveral = 64;
+    u64 t[2 * kGaussBound];
+    unsigned char passed[256];
+};
 GALA_HD int draw_gauss_cdf(const GaussCdf &cdf, u64 seed, u64 stream, u64 idx) {
     const u64 u = rand64(seed, stream, idx, 0);
     int x = -kGaussBound;
@@ -111,6 +118,7 @@ struct gala_sk {
     std::vector<gala::u64> s;          // coefficients mod q (0, 1, q-1)
     std::vector<gala::u64> s_hat;      // forward transform of s
     gala::u64 *d_s_hat = nullptr;      // device copy of s_hat (null on a host without a device)
+    gala::MontPair *d_s_pairs = nullptr;   // the same as MontPairs, for the ring kernels
 };
 
 struct gala_gk {
@@ -222,10 +230,11 @@ int launch_ntt(const gala_ctx *ctx, void *stream, const u64 *src, u64 *dst, size
 // the same with the tables of another modulus of the context (dev_q, dev_p or dev_P)
 int launch_ntt_mod(const gala_ctx *ctx, void *stream, const u64 *src, u64 *dst, size_t count, int inverse, const NttDev &T);
 // Batched client steps on internal-form ciphertexts (one workgroup per ciphertext).
-int launch_encrypt(const gala_ctx *ctx, void *stream, const u64 *s_hat, const u64 *slots, const u64 *seeds, int count,
+int launch_encrypt(const gala_ctx *ctx, void *stream, const gala_sk *sk, const u64 *slots, const u64 *seeds, int count,
                    u64 *ct_out);
-int launch_decrypt(const gala_ctx *ctx, void *stream, const u64 *s_hat, const u64 *ct_in, int count, u64 *slots);
+int launch_decrypt(const gala_ctx *ctx, void *stream, const gala_sk *sk, const u64 *ct_in, int count, u64 *slots);
 const u64 *gauss_cdf_table();
+const GaussBuckets &gauss_buckets();
 // Stand-alone Add / ScMult / plaintext operations on internal-form buffers (op: 0 add ct, 1 scmult, 2 sub plain, 3 add plain).
 int launch_encode_plain(const gala_ctx *ctx, void *stream, const u64 *slots, int count, int mode, u64 *plain);
 int launch_ct_op(const gala_ctx *ctx, void *stream, int op, const u64 *a, const u64 *b, size_t b_stride, int count, u64 *out);
@@ -381,8 +390,8 @@ struct RingOps {
                       const u64 *keys2, u64 *digits, u64 *xrot);
     int (*hstperm_pack)(const gala_ctx *, void *stream, const u64 *ct_in, u64 *digits, int batch, const TermList &,
                         bool any_rotation, const u64 *keys2, u64 *xl);
-    int (*encrypt)(const gala_ctx *, void *stream, const u64 *s_hat, const u64 *slots, const u64 *seeds, int count, u64 *ct_out);
-    int (*decrypt)(const gala_ctx *, void *stream, const u64 *s_hat, const u64 *ct_in, int count, u64 *slots);
+    int (*encrypt)(const gala_ctx *, void *stream, const MontPair *s_hat, const u64 *slots, const u64 *seeds, int count, u64 *ct_out);
+    int (*decrypt)(const gala_ctx *, void *stream, const MontPair *s_hat, const u64 *ct_in, int count, u64 *slots);
 };
 // the context's, or nullptr: its ring size or moduli have none and the any-n kernels serve it
 const RingOps *ring_ops(const gala_ctx *ctx);

@@ -920,31 +920,31 @@ int launch_unpack_share(const gala_ctx *c, void *stream, const u64 *slots, int c
                        out);
     return last_error();
 }
-int launch_encrypt(const gala_ctx *c, void *stream, const u64 *s_hat, const u64 *slots, const u64 *seeds, int count,
+int launch_encrypt(const gala_ctx *c, void *stream, const gala_sk *sk, const u64 *slots, const u64 *seeds, int count,
                    u64 *ct_out) {
     if (!count) return 0;
-    if (const RingOps *ops = ring_ops(c)) return ops->encrypt(c, stream, s_hat, slots, seeds, count, ct_out);
+    if (const RingOps *ops = ring_ops(c)) return ops->encrypt(c, stream, sk->d_s_pairs, slots, seeds, count, ct_out);
     GaussCdf cdf;
     for (int i = 0; i < 2 * kGaussBound; ++i) cdf.t[i] = gauss_cdf_table()[i];
     const size_t lds = sizeof(u64) * c->n;
     hipStream_t st = (hipStream_t)stream;
     by_threads(c->n, [&](auto nt) {
         constexpr int NT = decltype(nt)::value;
-        hipLaunchKernelGGL(encrypt_kernel<NT>, dim3((unsigned)count), dim3(NT), lds, st, slots, seeds, s_hat, ct_out, c->dev_q,
+        hipLaunchKernelGGL(encrypt_kernel<NT>, dim3((unsigned)count), dim3(NT), lds, st, slots, seeds, sk->d_s_hat, ct_out, c->dev_q,
                            c->dev_p, c->d_slot_to_idx, cdf, c->n, c->logn, c->qbits, c->delta, c->delta_s);
     });
     return last_error();
 }
-int launch_decrypt(const gala_ctx *c, void *stream, const u64 *s_hat, const u64 *ct_in, int count, u64 *slots) {
+int launch_decrypt(const gala_ctx *c, void *stream, const gala_sk *sk, const u64 *ct_in, int count, u64 *slots) {
     if (!count) return 0;
-    if (const RingOps *ops = ring_ops(c)) return ops->decrypt(c, stream, s_hat, ct_in, count, slots);
+    if (const RingOps *ops = ring_ops(c)) return ops->decrypt(c, stream, sk->d_s_pairs, ct_in, count, slots);
     u64 inv = c->q;                                   // Newton's iteration for q^-1 mod 2^64 (q is odd)
     for (int i = 0; i < 6; ++i) inv *= 2 - c->q * inv;
     const size_t lds = sizeof(u64) * c->n;
     hipStream_t st = (hipStream_t)stream;
     by_threads(c->n, [&](auto nt) {
         constexpr int NT = decltype(nt)::value;
-        hipLaunchKernelGGL(decrypt_kernel<NT>, dim3((unsigned)count), dim3(NT), lds, st, ct_in, s_hat, slots, c->dev_q, c->dev_p,
+        hipLaunchKernelGGL(decrypt_kernel<NT>, dim3((unsigned)count), dim3(NT), lds, st, ct_in, sk->d_s_hat, slots, c->dev_q, c->dev_p,
                            c->d_slot_to_idx, c->n, c->logn, inv);
     });
     return last_error();

@@ -1541,11 +1541,16 @@ __global__ __launch_bounds__(NT) void ntt_ring(const u64 *src, u64 *dst, RingTab
 // ---- the client's two steps with the radix-8 transforms (one workgroup per ciphertext) ------------------------
 // ct = (-a s + e + delta m, a) (Sec. II-C(1)), bit for bit the any-n kernel: m = the plaintext polynomial of the
 // slots, a uniform, e Gaussian, all drawn from the ciphertext's seed by coefficient index.
+//
+// The Gaussian draws by buckets: a draw compared with all 38 thresholds takes as long as three butterfly passes for each of a
+// thread's coefficients.  The products by the secret as those by any constant.
 template <bool WIDE>
-__global__ __launch_bounds__(NT, 4) void encrypt_ring(const u64 *slots, const u64 *seeds, const u64 *s_hat, u64 *ct_out,
-                                                   RingTables T, RingTables Tp, SmallTables small, const int *slot_to_idx, GaussCdf cdf,
+__global__ __launch_bounds__(NT, 4) void encrypt_ring(const u64 *slots, const u64 *seeds, const ulonglong2 *s_hat, u64 *ct_out,
+                                                   RingTables T, RingTables Tp, SmallTables small, const int *slot_to_idx, GaussBuckets gauss,
                                                    int qbits, ulonglong2 delta) {
     __shared__ u64 bufA[lds_words(ALONE_S)], bufB[lds_words(ALONE_S)];
+    __shared__ u64 thresholds[2 * kGaussBound];
+    __shared__ unsigned char passed[256];
     const int tid = threadIdx.x;
     const u64 q = T.mod.q, p = Tp.mod.q, seed = seeds[blockIdx.x];
     const u64 *sl = slots + (size_t)blockIdx.x * N;
@@ -1554,51 +1559,90 @@ __global__ __launch_bounds__(NT, 4) void encrypt_ring(const u64 *slots, const u6
         const u64 v = sl[s];
         put_slot<ALONE_S>(bufB, slot_to_idx[s], v >= p ? v % p : v, small.tw != nullptr);
     }
+    for (int b = tid; b < 256; b += NT) passed[b] = gauss.passed[b];
+    if (tid < 2 * kGaussBound) thresholds[tid] = gauss.t[tid];
     SmallInverse consts;
     if (small.tw) consts.request(small, tid);
     __syncthreads();
     u64 a[PER];
     slots_to_coefficients<WIDE, ALONE_S>(a, bufA, bufB, Tp, small, consts, tid);      // m, coefficient tid + (n/8) k, canonical mod p
+    {
+        const u64 state = stream_state(seed, kStreamCtE);
+        u64 u[PER];
+        int e[PER], several = 0;
 #pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const int e = draw_gauss_cdf(cdf, seed, kStreamCtE, (u64)(tid + k * NT));
-        a[k] = mont<WIDE, true, true>(plain_words(a[k]), delta, T.mont, BIAS + (u64)(i64)e);
+        for (int k = 0; k < PER; ++k) {
+            u[k] = mix64(mix64(state + (u64)(tid + k * NT)));
+            e[k] = passed[u[k] >> 56];
+            several |= e[k];
+            e[k] &= GaussBuckets::kSeveral - 1;
+        }
+#pragma unroll
+        for (int k = 0; k < PER; ++k) e[k] += e[k] < 2 * kGaussBound && u[k] >= thresholds[e[k]] ? 1 : 0;
+        if (several & GaussBuckets::kSeveral) {
+#pragma unroll
+            for (int k = 0; k < PER; ++k)
+                while (e[k] < 2 * kGaussBound && u[k] >= thresholds[e[k]]) ++e[k];
+        }
+#pragma unroll
+        for (int k = 0; k < PER; ++k)
+            a[k] = mont<WIDE, true, true>(plain_words(a[k]), delta, T.mont, BIAS + (u64)(i64)(e[k] - kGaussBound));
     }
     forward_to_lds<WIDE, ALONE_S, BIASED>(a, bufA, bufB, T, tid);            // (e + delta m) in the evaluation domain, in bufA
+    // biased; with the product by the secret on top it has to stay below 8, which the transform's 7.3 at n = 8192 would not
     u64 t0[PER];
 #pragma unroll
-    for (int k = 0; k < PER; ++k) t0[k] = canonical<WIDE>(biased_words(bufA[pad<ALONE_S>(tid + k * NT)]), T);
-#pragma unroll
-    for (int k = 0; k < PER; ++k) a[k] = draw_uniform(q, qbits, seed, kStreamCtA, (u64)(tid + k * NT));
+    for (int k = 0; k < PER; ++k) {
+        t0[k] = bufA[pad<ALONE_S>(tid + k * NT)];
+        if (LOGN == 13) t0[k] = shrink(t0[k], T.mont);
+    }
+    draw_uniforms<NT>(a, q, qbits, stream_state(seed, kStreamCtA), (u64)tid);
     forward_to_lds<WIDE, ALONE_S>(a, bufA, bufB, T, tid);            // its first barrier comes after every read of bufA above
 #pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const int i = tid + k * NT;
-        const u64 ah = canonical<WIDE>(biased_words(bufA[pad<ALONE_S>(i)]), T);
-        c1[i] = ah;
-        c0[i] = sub_mod(t0[k], mul_mod(ah, s_hat[i], T.mod), q);
+    for (int k = 0; k < PER; k += 2) {
+        u64 ah[2], as[2], c[2];
+        canonical2<WIDE>(ah[0], ah[1], biased_words(bufA[pad<ALONE_S>(tid + k * NT)]), biased_words(bufA[pad<ALONE_S>(tid + (k + 1) * NT)]), T);
+        mont2<WIDE, false, NONE>(as[0], as[1], plain_words(ah[0]), pair_at(s_hat + k * NT, tid), plain_words(ah[1]),
+                                 pair_at(s_hat + (k + 1) * NT, tid), T.mont);
+        canonical2<WIDE>(c[0], c[1], biased_words(t0[k] - as[0]), biased_words(t0[k + 1] - as[1]), T);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int i = tid + (k + h) * NT;
+            c1[i] = ah[h];
+            c0[i] = c[h];
+        }
     }
 }
-// slots = decode(round(p (c0 + c1 s) / q) mod p); the rounded quotient through the exact division by q (q^-1 mod 2^64).
+// slots = decode(round(p (c0 + c1 s) / q) mod p).  per_q = floor(p 2^64 / q): the high word of a per_q is the quotient of
+// p a by q or one less, and what is left of p a + floor(q/2) is below 3q.
 template <bool WIDE>
-__global__ __launch_bounds__(NT) void decrypt_ring(const u64 *ct_in, const u64 *s_hat, u64 *slots, RingTables T,
-                                                   RingTables Tp, SmallTables small, const int *slot_to_idx, u64 q_inv64) {
+__global__ __launch_bounds__(NT) void decrypt_ring(const u64 *ct_in, const ulonglong2 *s_hat, u64 *slots, RingTables T,
+                                                   RingTables Tp, SmallTables small, const int *slot_to_idx, u64 per_q) {
     __shared__ u64 bufA[lds_words(ALONE_S)], bufB[lds_words(ALONE_S)];
     const int tid = threadIdx.x;
     const u64 q = T.mod.q, p = Tp.mod.q;
     const u64 *c0 = ct_in + (size_t)blockIdx.x * 2 * N, *c1 = c0 + N;
     u64 a[PER];
+    // coalesced, then through LDS to the eight consecutive coefficients a thread starts from
 #pragma unroll
-    for (int k = 0; k < PER; ++k) {
-        const int i = 8 * tid + k;
-        a[k] = add_mod(c0[i], mul_mod(c1[i], s_hat[i], T.mod), q);
+    for (int k = 0; k < PER; k += 2) {
+        u64 x, y;
+        mont2<WIDE, false, NONE>(x, y, plain_words(c1[tid + k * NT]), pair_at(s_hat + k * NT, tid), plain_words(c1[tid + (k + 1) * NT]),
+                                 pair_at(s_hat + (k + 1) * NT, tid), T.mont);
+        bufB[pad<ALONE_S>(tid + k * NT)] = add_mod(c0[tid + k * NT], unsign(x, q), q);
+        bufB[pad<ALONE_S>(tid + (k + 1) * NT)] = add_mod(c0[tid + (k + 1) * NT], unsign(y, q), q);
     }
+    __syncthreads();
+    const u64 *own = bufB + pad<ALONE_S>(tid << 3);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) a[k] = own[k];
     inverse_in_regs<WIDE, ALONE_S>(a, bufA, bufB, T, tid);           // c0 + c1 s, coefficient tid + (n/8) k, canonical
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
-        const u128 t = (u128)p * a[k] + (q >> 1);
-        const u64 r = reduce128(t, T.mod);
-        const u64 quot = ((u64)t - r) * q_inv64;      // t - r is a multiple of q and the quotient is at most p
+        u64 quot = mulhi64(a[k], per_q);
+        const u64 left = p * a[k] + (q >> 1) - quot * q;
+        quot += left >= q ? 1 : 0;
+        quot += left >= 2 * q ? 1 : 0;
         a[k] = quot >= p ? quot - p : quot;
     }
     u64 *out = slots + (size_t)blockIdx.x * N;
@@ -2245,26 +2289,23 @@ static int ntt(const gala_ctx *c, void *stream, const u64 *src, u64 *dst, size_t
     });
 }
 
-static int encrypt(const gala_ctx *c, void *stream, const u64 *s_hat, const u64 *slots, const u64 *seeds, int count,
+static int encrypt(const gala_ctx *c, void *stream, const MontPair *s_hat, const u64 *slots, const u64 *seeds, int count,
                         u64 *ct_out) {
     if (!count) return 0;
-    GaussCdf cdf;
-    for (int i = 0; i < 2 * kGaussBound; ++i) cdf.t[i] = gauss_cdf_table()[i];
     return by_width(c, [&](auto width) {
         hipLaunchKernelGGL(encrypt_ring<decltype(width)::value>, dim3((unsigned)count), dim3(NT), 0, (hipStream_t)stream, slots, seeds,
-                           s_hat, ct_out, make_tables(c->d_tw2, c->ntt_q), make_tables(c->d_tw2p, c->ntt_p), make_small(c),
-                           c->d_slot_to_idx, cdf, c->qbits, as_words(c->delta_m));
+                           reinterpret_cast<const ulonglong2 *>(s_hat), ct_out, make_tables(c->d_tw2, c->ntt_q),
+                           make_tables(c->d_tw2p, c->ntt_p), make_small(c), c->d_slot_to_idx, gauss_buckets(), c->qbits,
+                           as_words(c->delta_m));
         return (int)hipGetLastError();
     });
 }
-static int decrypt(const gala_ctx *c, void *stream, const u64 *s_hat, const u64 *ct_in, int count, u64 *slots) {
+static int decrypt(const gala_ctx *c, void *stream, const MontPair *s_hat, const u64 *ct_in, int count, u64 *slots) {
     if (!count) return 0;
-    u64 inv = c->q;                                   // Newton's iteration for q^-1 mod 2^64 (q is odd)
-    for (int i = 0; i < 6; ++i) inv *= 2 - c->q * inv;
     return by_width(c, [&](auto width) {
-        hipLaunchKernelGGL(decrypt_ring<decltype(width)::value>, dim3((unsigned)count), dim3(NT), 0, (hipStream_t)stream, ct_in, s_hat,
-                           slots, make_tables(c->d_tw2, c->ntt_q), make_tables(c->d_tw2p, c->ntt_p), make_small(c), c->d_slot_to_idx,
-                           inv);
+        hipLaunchKernelGGL(decrypt_ring<decltype(width)::value>, dim3((unsigned)count), dim3(NT), 0, (hipStream_t)stream, ct_in,
+                           reinterpret_cast<const ulonglong2 *>(s_hat), slots, make_tables(c->d_tw2, c->ntt_q),
+                           make_tables(c->d_tw2p, c->ntt_p), make_small(c), c->d_slot_to_idx, (u64)(((u128)c->p << 64) / c->q));
         return (int)hipGetLastError();
     });
 }
