@@ -37,56 +37,59 @@ __device__ __forceinline__ u64 balanced_digits(u64 x) {
     return (x + k) ^ k;
 }
 
-// Builds the digit-plane image of 16 rows x 16 terms x 16 coefficients per workgroup.  Phase 1 reads the
-// source with the coefficient index fastest (128-byte segments); phase 2 writes with the index fastest that
-// is contiguous in the destination layout.  mode 0: source is the encoded
-// kernels [row][e][i]; mode 1: the tap-rotated inputs [input][e][polynomial][i] with row = 2*input + polynomial.
-__global__ __launch_bounds__(256) void limb_pack_kernel(const u64 *src, int mode, int rows, int nterm, int n, int tiles,
-                                                        int kblocks, v4i *dst) {
-    __shared__ u64 stage[16 * 16 * 17];   // [row][term][coefficient], coefficient dimension padded
+// Builds the digit-plane image of 16 rows x 16 terms x 16 coefficients per workgroup; one that holds no term has nothing to do.
+// COLUMNS: the source is the tap-rotated inputs [input][e][polynomial][i] with row = 2*input + polynomial, otherwise the encoded
+// kernels [row][e][i].  Both are read with the coefficient index fastest (128-byte segments).
+// Bound by memory: the columns of 16x16x128 to 128 channels at batch 16 are 75 MB in and 75 MB out, 30.9 us (4.9 TB/s).  It took 40.0 when
+// the columns' residues went through LDS too, though a thread got back what it had put there, their chunks were stored to an
+// eighth of the banks, and the quarter of the image beyond the last term was written; that layer with special-prime keys 433.9 -> 422.6 us.
+template <bool COLUMNS>
+__global__ __launch_bounds__(256) void limb_pack_kernel(const u64 *src, int rows, int nterm, int n, int tiles, int kblocks, v4i *dst) {
+    // rows: the residues [row][term][coefficient], coefficient dimension padded; columns: chunks [row][coefficient][digit]
+    __shared__ __attribute__((aligned(16))) u64 stage[COLUMNS ? 16 * 16 * 16 : 16 * 16 * 17];
     const int i0 = blockIdx.x * 16, tile = blockIdx.y, kb = blockIdx.z >> 2, g = blockIdx.z & 3;
-    {
-        const int il = threadIdx.x & 15, rl = threadIdx.x >> 4, row = tile * 16 + rl;
-        const size_t row_off = mode == 0 ? (size_t)row * nterm * n : ((size_t)(row >> 1) * nterm * 2 + (row & 1)) * n;
-        const size_t e_stride = mode == 0 ? (size_t)n : 2 * (size_t)n;
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const int e = kb * 64 + g * 16 + j;
-            const u64 x = (row < rows && e < nterm && i0 + il < n) ? src[row_off + (size_t)e * e_stride + i0 + il] : 0;
-            stage[(rl * 16 + j) * 17 + il] = balanced_digits(x);
-        }
-    }
-    __syncthreads();
-    // phase 2: mode 0 runs the row across the threads, mode 1 the coefficient
-    const int rl = mode == 0 ? threadIdx.x & 15 : threadIdx.x >> 4, il = mode == 0 ? threadIdx.x >> 4 : threadIdx.x & 15;
-    const bool live = i0 + il < n;
+    if (kb * 64 + g * 16 >= nterm) return;
+    const int il = threadIdx.x & 15, rl = threadIdx.x >> 4, row = tile * 16 + rl;
+    const size_t row_off = COLUMNS ? ((size_t)(row >> 1) * nterm * 2 + (row & 1)) * n : (size_t)row * nterm * n;
+    const size_t e_stride = COLUMNS ? 2 * (size_t)n : (size_t)n;
     u64 d[16];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) d[j] = stage[(rl * 16 + j) * 17 + il];
+    for (int j = 0; j < 16; ++j) {
+        const int e = kb * 64 + g * 16 + j;
+        d[j] = (row < rows && e < nterm && i0 + il < n) ? src[row_off + (size_t)e * e_stride + i0 + il] : 0;
+    }
+#pragma unroll
+    for (int j = 0; j < 16; ++j) d[j] = balanced_digits(d[j]);
     v4i chunk[8];
-    digit_chunks(d, chunk);
-    const size_t lane = (size_t)(g * 16 + rl);
-    if (mode == 0) {
-        if (!live) return;
-        // 16 threads (the rows of a tile) write 256 contiguous bytes per digit
-        const size_t base = ((((size_t)(i0 + il) * tiles + tile) * kblocks + kb) * 8) * 64 + lane;
+    if constexpr (!COLUMNS) {
+        // written with the row across the threads: 16 of them (the rows of a tile) write 256 contiguous bytes per digit
+#pragma unroll
+        for (int j = 0; j < 16; ++j) stage[(rl * 16 + j) * 17 + il] = d[j];
+        __syncthreads();
+        const int to_row = threadIdx.x & 15, to_i = threadIdx.x >> 4;
+        if (i0 + to_i >= n) return;
+#pragma unroll
+        for (int j = 0; j < 16; ++j) d[j] = stage[(to_row * 16 + j) * 17 + to_i];
+        digit_chunks(d, chunk);
+        const size_t base = ((((size_t)(i0 + to_i) * tiles + tile) * kblocks + kb) * 8) * 64 + (size_t)(g * 16 + to_row);
 #pragma unroll
         for (int limb = 0; limb < 8; ++limb) dst[base + (size_t)limb * 64] = chunk[limb];
-        return;
-    }
-    // mode 1: a row's 16 coefficients x 8 digits are 2 KiB contiguous in the image, but a thread owns the 128
-    // bytes of one coefficient: the chunks change owner in LDS so that the 16 threads of a row write 256
-    // contiguous bytes per instruction instead of 16 bytes in each of 16 lines
-    __syncthreads();                                   // everybody has read its digits out of `stage`
-    v4i *tr = reinterpret_cast<v4i *>(stage);          // [row][coefficient][digit], 32 KiB
+    } else {
+        // a row's 16 coefficients x 8 digits are 2 KiB contiguous in the image, but a thread owns the 128
+        // bytes of one coefficient: the chunks change owner in LDS so that the 16 threads of a row write 256
+        // contiguous bytes per instruction instead of 16 bytes in each of 16 lines.  Within a coefficient the digits are xored
+        // with its number halved: the 16 threads that store a digit then use all banks instead of an eighth of them.
+        digit_chunks(d, chunk);
+        v4i *tr = reinterpret_cast<v4i *>(stage);
 #pragma unroll
-    for (int limb = 0; limb < 8; ++limb) tr[(rl * 16 + il) * 8 + limb] = chunk[limb];
-    __syncthreads();
-    const size_t base = ((((size_t)tile * kblocks + kb) * 64 + lane) * n + i0) * 8;
+        for (int limb = 0; limb < 8; ++limb) tr[(rl * 16 + il) * 8 + (limb ^ (il >> 1))] = chunk[limb];
+        __syncthreads();
+        const size_t base = ((((size_t)tile * kblocks + kb) * 64 + (size_t)(g * 16 + rl)) * n + i0) * 8;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-        const int c = k * 16 + il;                     // chunk c of the row: coefficient c / 8, digit c % 8
-        if (i0 + (c >> 3) < n) dst[base + c] = tr[rl * 128 + c];
+        for (int k = 0; k < 8; ++k) {
+            const int c = k * 16 + il, from = c >> 3;      // chunk c of the row: digit c % 8 of coefficient c / 8
+            if (i0 + from < n) dst[base + c] = tr[rl * 128 + (c ^ (from >> 1))];
+        }
     }
 }
 
@@ -374,8 +377,12 @@ int launch_limb_pack(const gala_ctx *c, void *stream, const u64 *src, int mode, 
     int tiles, unused, kblocks;
     conv_mfma_geometry(rows, rows, nterm, &tiles, &unused, &kblocks);
     const dim3 grid((unsigned)((c->n + 15) / 16), (unsigned)tiles, (unsigned)(kblocks * 4));
-    hipLaunchKernelGGL(limb_pack_kernel, grid, dim3(256), 0, (hipStream_t)stream, src, mode, rows, nterm, c->n, tiles,
-                       kblocks, reinterpret_cast<v4i *>(dst));
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(256), 0, (hipStream_t)stream, src, rows, nterm, c->n, tiles, kblocks,
+                           reinterpret_cast<v4i *>(dst));
+    };
+    if (mode) go(limb_pack_kernel<true>);
+    else go(limb_pack_kernel<false>);
     return (int)hipGetLastError();
 }
 int launch_conv_mfma(const gala_ctx *c, void *stream, const u64 *wl, const u64 *xl, int batch, int groups, int nterm,
