@@ -833,10 +833,6 @@ __device__ __forceinline__ void put_slot(u64 *bufB, int position, u64 v, bool sm
     if (small) reinterpret_cast<u32 *>(bufB)[pad32(position)] = (u32)v;
     else bufB[pad<S>(position)] = v;
 }
-template <int S>
-__device__ __forceinline__ u64 get_slot(const u64 *bufB, int position, bool small) {
-    return small ? reinterpret_cast<const u32 *>(bufB)[pad32(position)] : bufB[pad<S>(position)];
-}
 template <bool WIDE, int S>
 __device__ __forceinline__ void slots_to_coefficients(u64 (&a)[8], u64 *bufA, u64 *bufB, const RingTables &Tp,
                                                       const SmallTables &small, SmallInverse &consts, int tid) {
