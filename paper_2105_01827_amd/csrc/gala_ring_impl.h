@@ -888,13 +888,14 @@ __device__ __forceinline__ void draw_uniforms(u64 (&v)[COUNT], u64 m, int bits, 
     }
 }
 
-// store(k, i, m): mask word i = threadIdx.x + k NT GROUPS of the evaluation domain, canonical.
+// store(k, i, m): mask word i = threadIdx.x + k NT GROUPS of the evaluation domain, canonical.  before() runs once ahead of them.
 // ALONE: as in the transforms.  GROUPS: the workgroup's threads in units of NT; the first group runs the transforms.
 // Bound by its own chain of steps: at n = 2048 with 1000 rows, in a launch of one workgroup a CU, 34 400 clocks when each thread
 // drew its slots one after the other (10 100) and then walked the rows, each with its row pointers, indices and share behind
 // each other and two divisions (12 900); 29 200 by slots, with 7 600 and 3 800.  Rotations hide it where there are any.
-template <bool WIDE, int S, bool ALONE = false, int GROUPS = 1, class Store>
-__device__ __forceinline__ void mask_role(const RingTables &T, const MaskJob &mj, int item, u64 *bufA, u64 *bufB, Store store) {
+template <bool WIDE, int S, bool ALONE = false, int GROUPS = 1, class Store, class Before = NothingAhead>
+__device__ __forceinline__ void mask_role(const RingTables &T, const MaskJob &mj, int item, u64 *bufA, u64 *bufB, Store store,
+                                          Before before = Before{}) {
     constexpr int ALL = NT * GROUPS, OWN = PER / GROUPS;
     const int tid = threadIdx.x;
     const bool transforms = GROUPS == 1 || __builtin_amdgcn_readfirstlane(tid) < NT;
@@ -961,6 +962,7 @@ __device__ __forceinline__ void mask_role(const RingTables &T, const MaskJob &mj
         __syncthreads();
         __syncthreads();
     }
+    before();
 #pragma unroll
     for (int k = 0; k < OWN; ++k) {
         const int i = tid + k * ALL;
@@ -984,37 +986,46 @@ __device__ __forceinline__ void mask_partial(const PermJob &job, const RingTable
 // From wire to wire (with the layout's loads requested ahead of the draws): 16x128 on one input 27.5 -> 24.1 us; that
 // and he_fc 1000x512 on one input, where a mask is the longest workgroup, 40.9 -> 39.6 us.
 // GROUPS = 2: as in mask_role, for launches that leave a CU two wavefronts per SIMD at most; larger ones are bound by the
-// vector ALU.  16x128 on one input 20.9 us, 19.6 with the slots' draws together and 18.2 with two groups; on 512 inputs, one
-// group, 41.5 -> 39.7 us.
-template <bool WIDE, int GROUPS>
-__global__ __launch_bounds__(NT * GROUPS) void scmult_masked_ring(PermJob job, RingTables T, MaskJob mj, u64 *ct_out) {
+// vector ALU.  16x128 on one input 20.9 us, 19.6 with the slots' draws together and 18.2 with two groups.
+// EARLY: launches that leave registers idle (few) request the operands ahead of the mask and all constants of the forward
+// transform at its start.  Elsewhere that takes 181 to 191 registers, so that two wavefronts are left on a SIMD; behind the mask and
+// within 128 there are four.  The layer alone, operands early and late: 16x128 on 513 inputs 21.0 and 16.8 us, 768 23.1 and 18.6, 3000 70.8
+// and 55.0; n = 1024, 16x64 on 1025 18.9 and 15.9, 4000 47.9 and 38.8; n = 4096, 16x128 on 257 28.7 and 22.4, 1000 65.9 and 43.2.
+// Late operands all at once where workgroups are small, one index after the other from n = 4096 on (with all at once n = 4096 on
+// 1000 inputs 45.7, n = 8192, 16x512 on 256, 30.7 and 28.4; one by one 16x128 on 3000 56.5, n = 1024 on 1025 17.6).
+template <bool WIDE, int GROUPS, bool EARLY>
+__global__ __launch_bounds__(NT * GROUPS, EARLY ? 2 : 4) void scmult_masked_ring(PermJob job, RingTables T, MaskJob mj, u64 *ct_out) {
     __shared__ u64 bufA[lds_words(ALONE_S)], bufB[lds_words(ALONE_S)];
     const int item = blockIdx.x;
     const u64 *c0 = job.ct_in + (size_t)item * job.in_item_stride, *c1 = c0 + N;
     const ulonglong2 *w = reinterpret_cast<const ulonglong2 *>(job.w2);
-    // requested ahead of the mask and multiplied behind it; at n = 8192 there are no registers to hold them meanwhile
-    constexpr bool EARLY = LOGN < 13;
-    constexpr int OWN = PER / GROUPS, HELD = EARLY ? OWN : 1;
-    u64 x0[HELD], x1[HELD];
-    ulonglong2 ww[HELD];
-    if (EARLY) {
+    constexpr int OWN = PER / GROUPS, AT_ONCE = EARLY || LOGN < 12 ? OWN : 1;
+    u64 x0[AT_ONCE], x1[AT_ONCE];
+    ulonglong2 ww[AT_ONCE];
+    auto request = [&](int first) {
 #pragma unroll
-        for (int k = 0; k < HELD; ++k) {
-            const int i = threadIdx.x + k * NT * GROUPS;
+        for (int k = 0; k < AT_ONCE; ++k) {
+            const int i = threadIdx.x + (first + k) * NT * GROUPS;
             ww[k] = w[i];
             x0[k] = c0[i];
             x1[k] = c1[i];
         }
-    }
+    };
+    if (EARLY) request(0);
     u64 *out = ct_out + (size_t)item * 2 * N;
-    mask_role<WIDE, ALONE_S, EARLY, GROUPS>(T, mj, item, bufA, bufB, [&](int k, int i, u64 m) {
-        const int h = EARLY ? k : 0;
-        const ulonglong2 wk = EARLY ? ww[h] : w[i];
-        u64 a, b;
-        mont2<WIDE, false, NONE>(a, b, plain_words(EARLY ? x0[h] : c0[i]), wk, plain_words(EARLY ? x1[h] : c1[i]), wk, T.mont);
-        out[i] = sub_mod(unsign(a, T.mod.q), m, T.mod.q);
-        out[N + i] = unsign(b, T.mod.q);
-    });
+    mask_role<WIDE, ALONE_S, EARLY, GROUPS>(
+        T, mj, item, bufA, bufB,
+        [&](int k, int i, u64 m) {
+            if (AT_ONCE == 1) request(k);
+            const int h = AT_ONCE == 1 ? 0 : k;
+            u64 a, b;
+            mont2<WIDE, false, NONE>(a, b, plain_words(x0[h]), ww[h], plain_words(x1[h]), ww[h], T.mont);
+            out[i] = sub_mod(unsign(a, T.mod.q), m, T.mod.q);
+            out[N + i] = unsign(b, T.mod.q);
+        },
+        [&] {
+            if (!EARLY && AT_ONCE > 1) request(0);
+        });
 }
 
 // Workgroup -> (item, chunk).  Consecutive workgroup ids go to the eight XCDs in turn, each with an L2 of its own.  Long sums
@@ -2176,9 +2187,12 @@ static int perm_masked(const gala_ctx *c, void *stream, const PermJob &job, cons
                 return (int)hipGetLastError();
             };
 #if GALA_LOGN <= 11
-            if (few(2 * (size_t)job.items)) return go(scmult_masked_ring<WIDE, 2>, 2);
+            if (few(2 * (size_t)job.items)) return go(scmult_masked_ring<WIDE, 2, true>, 2);
 #endif
-            return go(scmult_masked_ring<WIDE, 1>, 1);
+#if GALA_LOGN < 13       // a workgroup of n = 8192 leaves no registers idle
+            if (few((size_t)job.items)) return go(scmult_masked_ring<WIDE, 1, true>, 1);
+#endif
+            return go(scmult_masked_ring<WIDE, 1, false>, 1);
         });
     } else {
         rc = launch_perm(c, stream, job, mj);

@@ -1,6 +1,6 @@
 """Share masks of the ring kernels against the oracle: plaintext primes under which every second or third draw is made again,
 rows of one, several and all slots, and layers without rotations on both sides of the launch that gives a mask two groups
-of threads (512 inputs at n = 1024, 256 at 2048)."""
+of threads (512 inputs at n = 1024, 256 at 2048) and of the one that reads the operands ahead of the mask (1024, 512 and 256)."""
 import pytest
 
 from paper_2105_01827_amd import workloads as wl
@@ -28,4 +28,10 @@ def test_he_conv_masks(n):
 @pytest.mark.parametrize("n,batch", [(1024, 512), (1024, 513), (2048, 256), (2048, 257)])
 def test_layers_without_rotations_around_the_two_group_launch(n, batch):
     plan = fc_case(_often_redrawn(n), 16, 50, batch, [0, 1, batch - 1], seed=batch)[2]
+    assert plan.G == 1
+
+
+@pytest.mark.parametrize("n,batch", [(1024, 1024), (1024, 1025), (2048, 512), (2048, 513), (4096, 256), (4096, 257)])
+def test_layers_without_rotations_around_the_launch_with_early_operands(n, batch):
+    plan = fc_case(_often_redrawn(n), 16, 50, batch, [0, 1, batch // 2, batch - 1], seed=batch)[2]
     assert plan.G == 1

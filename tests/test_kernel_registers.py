@@ -65,3 +65,12 @@ def test_masks_at_n8192_do_not_hold_a_whole_transform(kernels):
     """The constants of the small plaintext transform held all at once took 72 bytes a lane of a layer without rotations."""
     found = [k for (n, name), k in kernels.items() if n == 8192 and "scmult_masked_ring" in name]
     assert len(found) == 1 and found[0][".private_segment_fixed_size"] <= 64
+
+
+@pytest.mark.parametrize("n", [1024, 2048, 4096, 8192])
+def test_large_layers_without_rotations_leave_room_for_four_wavefronts(kernels, n):
+    """One form of each ring, and of both widths below n = 4096, has at most 128 registers and spills none of them (to
+    60 bytes a lane at n = 8192)."""
+    fits = {"ILb1E" in name for (m, name), k in kernels.items() if m == n and "scmult_masked_ring" in name and
+            k[".vgpr_count"] <= 128 and k[".private_segment_fixed_size"] <= (60 if n == 8192 else 0)}
+    assert fits == ({True, False} if n < 4096 else {True})
