@@ -267,6 +267,7 @@ static int upload_mask_layout(const gala_ctx *c, const MaskLayoutHost &h, MaskLa
     const int n = c->n;
     std::vector<int> slot_rowid((size_t)h.nout * n, -1), slot_mask(2 * (size_t)h.nout * n, 0);
     d->sums = false;
+    size_t in_rows = 0, same_thread = 0;
     for (int O = 0; O < h.nout; ++O) {
         const int *rp = h.row_ptr.data() + (size_t)O * (n + 1), *rs = h.row_slots.data() + (size_t)O * n;
         int *of_slot = slot_mask.data() + 2 * (size_t)O * n;
@@ -281,7 +282,14 @@ static int upload_mask_layout(const gala_ctx *c, const MaskLayoutHost &h, MaskLa
             of_slot[2 * rs[rp[t]]] |= MaskSlot::kFirst;
             of_slot[2 * rs[rp[t]] + 1] = h.row_rindex[(size_t)O * n + t];
         }
+        const int *row = slot_rowid.data() + (size_t)O * n;
+        for (int s = 0; s < n; ++s) {
+            if (row[s] < 0) continue;
+            ++in_rows;
+            if (s + n / 8 < n && row[s] == row[s + n / 8]) ++same_thread;
+        }
     }
+    d->strided = 2 * same_thread > in_rows;
     if ((rc = upload(&d->slot_rowid, slot_rowid))) return rc;
     return upload(&d->slot_mask, slot_mask);
 }

@@ -159,6 +159,7 @@ struct MaskLayoutDev {
     // whose first slot it is
     int *slot_mask = nullptr;
     bool sums = false;                 // some row has more than one slot
+    bool strided = false;              // most slots of rows are n / 8 slots, a mask's threads, away from the next of their row
 };
 
 struct gala_fc_plan {

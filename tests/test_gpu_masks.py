@@ -2,10 +2,11 @@
 rows of one, several and all slots, and layers without rotations on both sides of the launch that gives a mask two groups
 of threads (512 inputs at n = 1024, 256 at 2048) and of the one that reads the operands ahead of the mask (1024, 512 and 256)."""
 import pytest
+import torch
 
 from paper_2105_01827_amd import workloads as wl
 from tests.helpers import small_params
-from tests.test_gpu_parity import conv_case, fc_case
+from tests.test_gpu_parity import conv_case, fc_case, harness
 
 pytestmark = pytest.mark.gpu
 
@@ -35,3 +36,33 @@ def test_layers_without_rotations_around_the_two_group_launch(n, batch):
 def test_layers_without_rotations_around_the_launch_with_early_operands(n, batch):
     plan = fc_case(_often_redrawn(n), 16, 50, batch, [0, 1, batch // 2, batch - 1], seed=batch)[2]
     assert plan.G == 1
+
+
+# rows whose slots are n / 8 apart, so that a thread draws several of a row: all, and all but some at the end of the ring
+@pytest.mark.parametrize("n", [1024, 2048, 4096, 8192])
+@pytest.mark.parametrize("n_o,part", [(1, 1), (1, 2), (2, 2), (3, 4)])
+def test_few_rows(n, n_o, part):
+    plan = fc_case(_often_redrawn(n), n_o, n // part, 2, [0, 1], seed=part)[2]
+    assert plan.G == 1
+
+
+def test_a_single_row_takes_no_longer_than_sixteen():
+    """All slots in one row are as many sums as in sixteen; one by one into the row's cell they took 1.27 times as long, now 1.03."""
+    H, n = harness(), 8192
+    par = small_params(n)
+    layers = []
+    for n_o in (1, 16):
+        ctx, _, plan, _, _, _, r, _ = fc_case(par, n_o, n // n_o, 1, [], seed=n_o)
+        need = plan.workspace_bytes(1)
+        layers.append((plan, H.dev_empty(2 * n).zero_(), H.to_dev(r), H.dev_empty(2 * n), torch.empty(need, dtype=torch.uint8, device="cuda"), need, ctx))
+    best = [float("inf")] * 2
+    for _ in range(20):
+        for which, (plan, ct, r, out, ws, need, _) in enumerate(layers):
+            begin, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            begin.record()
+            for _ in range(50):
+                plan.he_fc(ct, 1, r, 7, out, ws, need)
+            end.record()
+            end.synchronize()
+            best[which] = min(best[which], begin.elapsed_time(end))
+    assert best[0] < 1.13 * best[1], best
