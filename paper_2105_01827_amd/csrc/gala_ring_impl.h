@@ -36,6 +36,8 @@ namespace {
 constexpr int LOGN = GALA_LOGN, N = 1 << LOGN, PER = 8, NT = N / PER;
 // a wavefront's 64 threads own the same 512 consecutive indices in every pass on bits at or below this one
 constexpr int LOCAL_BITS = 6;
+// ... and an exchange between the passes on bits b_out and b_in up hands words from one wavefront to another
+constexpr bool crosses(int b_out, int b_in) { return b_out > LOCAL_BITS || b_in > LOCAL_BITS; }
 
 // Images of a polynomial in LDS.  A wavefront's range of 512 words has a stride of its own, 512 + 512 / 2^S words, and
 // inside it an exchange pads by one word every 2^SHIFT, SHIFT >= S: ranges do not move with the padding, so wavefronts
@@ -419,7 +421,7 @@ __device__ __forceinline__ void exchange(u64 (&a)[8], u64 *buf, int tid) {
     u64 *po = buf + pad<S, SHIFT>(owner<B_OUT>(tid));
 #pragma unroll
     for (int k = 0; k < 8; ++k) po[reg_offset<S, SHIFT, B_OUT>(k)] = a[k];
-    if (B_OUT <= LOCAL_BITS && B_IN <= LOCAL_BITS && !BARRIER) {
+    if (!crosses(B_OUT, B_IN) && !BARRIER) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -504,6 +506,10 @@ enum Entry { PLAIN, BIASED };
 // S: the padding of the images.  copy: the kernel's copy of the small levels in LDS (TableCopy), or nothing.
 // ALONE: the launch leaves registers idle and a workgroup's chain of steps is what it takes: all constants are requested at
 // the start, one trip to the L2 for a transform instead of one a pass.
+// FORWARD_BARRIERS: those of this transform and of forward_small_to_lds, for wavefronts of the workgroup that take no part: the one at
+// the start, the exchanges' in their order, the one at the end.
+constexpr int FORWARD_BARRIERS = (LOGN == 13) + crosses(LOGN - 3, LOGN - 6) + crosses(LOGN - 6, LOGN - 9) +
+                                 crosses(LOGN - 9, LOGN < 12 ? 0 : LOGN - 12) + (LOGN == 13 && crosses(LOGN - 12, 0)) + 1;
 template <bool WIDE, int S, Entry IN = PLAIN, bool ALONE = false, class Copy = NoCopy, class Ahead = NothingAhead>
 __device__ __forceinline__ void forward_to_lds(u64 (&a)[8], u64 *res, u64 *other, const RingTables &T, int tid_,
                                                bool digits = false, Copy copy = Copy{}, Ahead ahead = Ahead{}) {
@@ -581,6 +587,9 @@ __device__ __forceinline__ void forward_to_lds(u64 (&a)[8], u64 *res, u64 *other
 // Inverse transform: registers hold index 8t + k (not biased, |a| < m) on entry and index t + (n/8) k, canonical, on
 // return.  LDS phases A B A, one more on B at n = 8192.
 // FENCE: a barrier in the first exchange, for the sake of reads of bufB before the call.  ALONE: as above.
+// INVERSE_BARRIERS: without FENCE, those of this transform and of inverse_small_in_regs: the exchanges' in their order.
+constexpr int INVERSE_BARRIERS = crosses(0, 3) + crosses(3, 6) + (LOGN >= 12 && crosses(6, 9)) +
+                                 (TOP_STAGES && crosses(LOGN >= 12 ? 9 : 6, LOGN - 3));
 template <bool WIDE, int S, bool FENCE = false, bool ALONE = false, class Copy = NoCopy>
 __device__ __forceinline__ void inverse_in_regs(u64 (&a)[8], u64 *bufA, u64 *bufB, const RingTables &T, int tid_, Copy copy = Copy{}) {
     const int tid = fresh(tid_);
@@ -679,7 +688,7 @@ __device__ __forceinline__ void exchange_small(u32 (&a)[8], u32 *buf, int tid) {
     u32 *po = buf + pad32(owner<B_OUT>(tid));
 #pragma unroll
     for (int k = 0; k < 8; ++k) po[pad32(k << B_OUT)] = a[k];
-    if (B_OUT <= LOCAL_BITS && B_IN <= LOCAL_BITS) {
+    if (!crosses(B_OUT, B_IN)) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -979,11 +988,8 @@ __device__ __forceinline__ void mask_role(const RingTables &T, const MaskJob &mj
         for (int k = 0; k < PER; ++k) a[k] = mont<WIDE, true, true>(plain_words(a[k]), mj.delta, T.mont, BIAS);
         forward_to_lds<WIDE, S, BIASED, ALONE>(a, bufA, bufB, T, tid);      // LDS phases B A B A, result in bufA
     } else {
-        // as many barriers as the transforms of n = 1024 and 2048 have: one, then two
-        static_assert(GROUPS == 1 || LOGN <= 11, "");
-        __syncthreads();
-        __syncthreads();
-        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < INVERSE_BARRIERS + FORWARD_BARRIERS; ++k) __syncthreads();
     }
     before();
 #pragma unroll
