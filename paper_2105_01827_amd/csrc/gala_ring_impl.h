@@ -871,7 +871,6 @@ struct MaskJob {
     size_t r_stride;
     u64 mask_seed;
     MaskLayoutDev layout;
-    const int *slot_to_idx;
     int pbits;
     ulonglong2 delta;           // delta = floor(q/p), a MontPair mod q
     RingTables Tp;              // inverse-transform tables of the plaintext modulus
@@ -2191,7 +2190,6 @@ static int perm_masked(const gala_ctx *c, void *stream, const PermJob &job, cons
     mj.r_stride = fin.r_stride;
     mj.mask_seed = fin.mask_seed;
     mj.layout = fin.mask;
-    mj.slot_to_idx = c->d_slot_to_idx;
     mj.pbits = c->pbits;
     mj.delta = as_words(c->delta_m);
     mj.Tp = make_tables(c->d_tw2p, c->ntt_p);
