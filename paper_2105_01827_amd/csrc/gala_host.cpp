@@ -265,7 +265,7 @@ static int upload_mask_layout(const gala_ctx *c, const MaskLayoutHost &h, MaskLa
     if ((rc = upload(&d->is_first, h.is_first))) return rc;
     // the same CSR seen from its slots
     const int n = c->n;
-    std::vector<int> slot_rowid((size_t)h.nout * n, -1), slot_mask(2 * (size_t)h.nout * n, 0);
+    std::vector<int> slot_rowid((size_t)h.nout * n, -1), slot_mask(2 * (size_t)h.nout * n, 0), row_first(2 * (size_t)h.nout * n, -1);
     d->sums = false;
     size_t in_rows = 0, same_thread = 0;
     for (int O = 0; O < h.nout; ++O) {
@@ -281,6 +281,8 @@ static int upload_mask_layout(const gala_ctx *c, const MaskLayoutHost &h, MaskLa
             }
             of_slot[2 * rs[rp[t]]] |= MaskSlot::kFirst;
             of_slot[2 * rs[rp[t]] + 1] = h.row_rindex[(size_t)O * n + t];
+            row_first[2 * ((size_t)O * n + t)] = c->slot_to_idx[rs[rp[t]]];
+            row_first[2 * ((size_t)O * n + t) + 1] = h.row_rindex[(size_t)O * n + t];
         }
         const int *row = slot_rowid.data() + (size_t)O * n;
         for (int s = 0; s < n; ++s) {
@@ -291,11 +293,12 @@ static int upload_mask_layout(const gala_ctx *c, const MaskLayoutHost &h, MaskLa
     }
     d->strided = 2 * same_thread > in_rows;
     if ((rc = upload(&d->slot_rowid, slot_rowid))) return rc;
+    if ((rc = upload(&d->row_first, row_first))) return rc;
     return upload(&d->slot_mask, slot_mask);
 }
 static void free_mask_layout(MaskLayoutDev *d) {
     hipFree(d->row_ptr); hipFree(d->row_slots); hipFree(d->row_rindex); hipFree(d->nrows); hipFree(d->is_first);
-    hipFree(d->slot_rowid); hipFree(d->slot_mask);
+    hipFree(d->slot_rowid); hipFree(d->slot_mask); hipFree(d->row_first);
 }
 
 }  // namespace gala

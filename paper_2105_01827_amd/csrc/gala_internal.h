@@ -158,6 +158,7 @@ struct MaskLayoutDev {
     // nout x n pairs, by slot: what the ring kernels' masks need to know of it (MaskSlot), and the index into r of the row
     // whose first slot it is
     int *slot_mask = nullptr;
+    int *row_first = nullptr;          // nout x n pairs, by row: the position of its first slot (-1: a row without slots) and its index into r
     bool sums = false;                 // some row has more than one slot
     bool strided = false;              // most slots of rows are n / 8 slots, a mask's threads, away from the next of their row
 };

@@ -901,7 +901,11 @@ __device__ __forceinline__ void draw_uniforms(u64 (&v)[COUNT], u64 m, int bits, 
 // Bound by its own chain of steps: at n = 2048 with 1000 rows, in a launch of one workgroup a CU, 34 400 clocks when each thread
 // drew its slots one after the other (10 100) and then walked the rows, each with its row pointers, indices and share behind
 // each other and two divisions (12 900); 29 200 by slots, with 7 600 and 3 800.  Rotations hide it where there are any.
-// SOLE: the launch is its masks; others hide what a few rows take behind their rotations.
+// SOLE: the launch is its masks; others hide what the rows take behind their rotations.
+// BY_ROWS: thread t forms the first slots of rows t, t + NT, ...  Where a thread does that for its own slots and there are many rows, every
+// wavefront does it OWN times for a few lanes each, and the loads of their shares wait for one another.  The layer alone on one input,
+// n = 4096: 256x16 16.5 -> 14.3 us, 512x8 16.7 -> 14.5, 16x128 14.4 both; n = 8192: 512x16 25.5 -> 22.7.  Two groups of threads have half as
+// many slots each: 256x8 10.2 by slots, as fast as by rows.
 template <bool WIDE, int S, bool ALONE = false, int GROUPS = 1, bool SOLE = false, class Store, class Before = NothingAhead>
 __device__ __forceinline__ void mask_role(const RingTables &T, const MaskJob &mj, int item, u64 *bufA, u64 *bufB, Store store,
                                           Before before = Before{}) {
@@ -922,8 +926,16 @@ __device__ __forceinline__ void mask_role(const RingTables &T, const MaskJob &mj
         slot[k] = m.x;
         rindex[k] = m.y;
     }
+    constexpr bool BY_ROWS = SOLE && GROUPS == 1;
+    const int2 *row_first = reinterpret_cast<const int2 *>(mj.layout.row_first) + (size_t)O * N;
+    const int nrows = BY_ROWS ? mj.layout.nrows[O] : 0;
+    int2 first = make_int2(-1, 0);
+    if (BY_ROWS) {
+        if (tid < nrows) first = row_first[tid];
+    } else {
 #pragma unroll
-    for (int k = 0; k < OWN; ++k) share[k] = slot[k] & MaskSlot::kFirst ? r[rindex[k]] : 0;
+        for (int k = 0; k < OWN; ++k) share[k] = slot[k] & MaskSlot::kFirst ? r[rindex[k]] : 0;
+    }
     SmallInverse consts;
     if (small && transforms) consts.request(mj.small, tid);
     unsigned long long *rowsum = reinterpret_cast<unsigned long long *>(bufA);
@@ -935,6 +947,8 @@ __device__ __forceinline__ void mask_role(const RingTables &T, const MaskJob &mj
     // transform expects them at
     u64 v[OWN];
     draw_uniforms<ALL>(v, p, mj.pbits, stream_state(mj.mask_seed, kStreamMask), ((u64)b << 32) + ((u64)O << 16) + (u64)tid);
+    u64 row_share = 0;
+    if (BY_ROWS && first.x >= 0) row_share = r[first.y];
     if (sums) __syncthreads();
     // plain integer sums of a row's values below p: at most n of them, far from 64 bits
     auto add = [&](int row, u64 x) { atomicAdd(&rowsum[row], (unsigned long long)x); };
@@ -967,16 +981,24 @@ __device__ __forceinline__ void mask_role(const RingTables &T, const MaskJob &mj
     }
     if (sums) __syncthreads();
     // the first slot of every real row absorbs r minus the row's other slots
-#pragma unroll
-    for (int k = 0; k < OWN; ++k) {
-        if (!(slot[k] & MaskSlot::kFirst)) continue;
-        u64 x = share[k];
+    auto first_slot = [&](int position, u64 x, int row) {
         if (x >= p) x %= p;
         if (sums) {
-            const u64 sum = rowsum[slot[k] >> MaskSlot::kBits & (N - 1)];
+            const u64 sum = rowsum[row];
             x = sub_mod(x, csub(sum - mulhi64(sum, mj.Tp.mod.one_s) * p, p), p);
         }
-        put_slot<S>(bufB, slot[k] & (N - 1), x, small);
+        put_slot<S>(bufB, position, x, small);
+    };
+    if (BY_ROWS) {
+        if (first.x >= 0) first_slot(first.x, row_share, tid);
+        for (int t = tid + ALL; t < nrows; t += ALL) {
+            const int2 f = row_first[t];
+            if (f.x >= 0) first_slot(f.x, r[f.y], t);
+        }
+    } else {
+#pragma unroll
+        for (int k = 0; k < OWN; ++k)
+            if (slot[k] & MaskSlot::kFirst) first_slot(slot[k] & (N - 1), share[k], slot[k] >> MaskSlot::kBits & (N - 1));
     }
     __syncthreads();
     // slots -> plaintext polynomial (inverse transform mod p) -> delta * m mod q -> evaluation domain mod q

@@ -1,6 +1,7 @@
 """Share masks of the ring kernels against the oracle: plaintext primes under which every second or third draw is made again,
 rows of one, several and all slots, and layers without rotations on both sides of the launch that gives a mask two groups
 of threads (512 inputs at n = 1024, 256 at 2048) and of the one that reads the operands ahead of the mask (1024, 512 and 256)."""
+import numpy as np
 import pytest
 import torch
 
@@ -46,12 +47,35 @@ def test_few_rows(n, n_o, part):
     assert plan.G == 1
 
 
-def test_a_single_row_takes_no_longer_than_sixteen():
-    """All slots in one row are as many sums as in sixteen; one by one into the row's cell they took 1.27 times as long, now 1.03."""
-    H, n = harness(), 8192
+# more rows than a workgroup has threads, and not; layers without rotations in launches with one group of threads a mask, and two
+@pytest.mark.parametrize("n,batch", [(1024, 2), (1024, 513), (2048, 257), (4096, 2), (8192, 2)])
+@pytest.mark.parametrize("rows,n_i", [(8, 4), (2, 2)])
+def test_many_rows(n, batch, rows, n_i):
+    plan = fc_case(_often_redrawn(n), n // rows - 3, n_i, batch, [0, batch - 1], seed=rows)[2]
+    assert plan.G == 1
+
+
+@pytest.mark.parametrize("n,batch", [(1024, 2), (1024, 513), (4096, 2)])
+def test_shares_above_the_plaintext_modulus(n, batch):
+    """The same outputs for every share that is the same modulo p."""
+    H, par = harness(), small_params(n)
+    ctx, _, plan, _, _, x, r, got = fc_case(par, 33, 20, batch, [], seed=n)
+    sk = ctx.keygen(0)
+    cts = np.stack([ctx.encrypt(sk, plan.pack_input(v), seed=b) for b, v in enumerate(x)])
+    want = H.gpu_he_fc(ctx, plan, cts, r, 9)[0]
+    k = np.random.default_rng(n).integers(0, 2 ** 64 // par.p, size=r.shape, dtype=np.uint64)
+    k[0, :3] = 0
+    assert np.array_equal(H.gpu_he_fc(ctx, plan, cts, r + k * np.uint64(par.p), 9)[0], want)
+
+
+# Figures beside the limits: the ratio when a row's cell in LDS took every slot by itself (1.27), and when each thread formed the first
+# slots among its own (1.13); 1.03 and 0.98 now.
+@pytest.mark.parametrize("n,rows,others,limit", [(8192, 1, 16, 1.13), (4096, 256, 4, 1.06)])
+def test_rows_take_no_longer_than_fewer_or_more_of_them(n, rows, others, limit):
+    H = harness()
     par = small_params(n)
     layers = []
-    for n_o in (1, 16):
+    for n_o in (rows, others):
         ctx, _, plan, _, _, _, r, _ = fc_case(par, n_o, n // n_o, 1, [], seed=n_o)
         need = plan.workspace_bytes(1)
         layers.append((plan, H.dev_empty(2 * n).zero_(), H.to_dev(r), H.dev_empty(2 * n), torch.empty(need, dtype=torch.uint8, device="cuda"), need, ctx))
@@ -65,4 +89,4 @@ def test_a_single_row_takes_no_longer_than_sixteen():
             end.record()
             end.synchronize()
             best[which] = min(best[which], begin.elapsed_time(end))
-    assert best[0] < 1.13 * best[1], best
+    assert best[0] < limit * best[1], best
