@@ -147,11 +147,14 @@ struct MfmaTasks {
 // A workgroup of RT x CT wavefronts, one 16x16 tile each, takes every gridDim.x-th task.  Its work is one sequence of stages, a
 // stage being one term block of one coefficient: 8 KiB of digit planes for each row and column tile, moved straight into
 // LDS STAGES - 1 stages ahead, through the ends of coefficients.
-// Bound by the row operand's stream from HBM.  One workgroup for each coefficient, its loads in registers one block ahead and
-// two workgroups a CU, spent half of its time on the first trip to memory and the last block's recombination: 16x16x128 to
-// 128 channels at batch 16 254 us from wire to wire, 238 in stages (212 without the products, 236 without the recombination;
-// 246 with one stage ahead instead of two; 257 with five stages of half a block ahead), 230 with the loads among the products and
-// the next task found by two additions; at batch 3 162 -> 131, 13x11x24 to 40 channels at batch 5 73.5 -> 66.3, 22x29x154 to
+// No single part bounds it.  16x16x128 to 128 channels at batch 16, the launch alone 100 us: 91 without the loads, 90 without the
+// products, 91 without the stores, as long without the recombination, 70 without loads and products, 86 without loads and stores.  Its
+// 445 MB, at 4.4 TB/s of the 6.2 that a read reaches, mostly hide behind the rest; every stage ends with its slowest wavefront.  Sums of
+// one term block are bound by their eight-byte stores: 256 to 256 channels 1x1 at 7x7, batch 16, 97 us, 71 without them.
+// One workgroup for each coefficient, its loads in registers one block ahead and two workgroups a CU, spent half of its time on
+// the first trip to memory and the last block's recombination: 16x16x128 to 128 channels at batch 16 254 us from wire to wire, 238 in
+// stages (246 with one stage ahead instead of two; 257 with five stages of half a block ahead), 230 with the loads among the products
+// and the next task found by two additions; at batch 3 162 -> 131, 13x11x24 to 40 channels at batch 5 73.5 -> 66.3, 22x29x154 to
 // 21 at batch 6 276 -> 219.  Eight consecutive coefficients a workgroup lost the gain: the eight-byte pieces of an output
 // line (BLK8) left the L2 one by one (285 us).
 // Output: tmp[i][row][column] (rows and columns padded to tiles), transposed afterwards; or, BLK8, in blocks of

@@ -1089,8 +1089,9 @@ __global__ __launch_bounds__(NT * GROUPS, EARLY ? 2 : 4) void scmult_masked_ring
 // chunk: he_fc 1000x1024 at batch 5 109 -> 92 us, at batch 16 242 -> 232, 1000x1024 at n = 4096, batch 13, 264 -> 243; against
 // item by item where the count is no multiple of eight: 100x784 at batch 7 with the special prime 64.7 -> 60.6 us, 1000x512 at batch 5 with
 // it 131 -> 123, 100x2048 at n = 4096, batch 9, 142 -> 137.
-// Short sums (a convolution's kernel orders) of other counts have keys that fit an L2 and chunks of unequal length: the chunks of
-// an item in turn, so that every CU gets some of each.
+// Short sums (a convolution's kernel orders) of other counts have keys that fit an L2: the chunks of an item in turn.  With an odd count
+// every XCD gets chunks of each length.  With an even one it does not: of two chunks an item the even XCDs have all of the shorter
+// ones and the odd XCDs all of the longer.
 __device__ __forceinline__ void item_and_chunk(const PermJob &job, int &item, int &chunk) {
     const u32 w = blockIdx.x, xcd = w & 7, s = w >> 3, items = (u32)job.items, nchunks = (u32)job.nchunks;
     if ((nchunks & 7) == 0) {
@@ -1601,7 +1602,7 @@ __global__ __launch_bounds__(NT) void ntt_ring(const u64 *src, u64 *dst, RingTab
 //
 // The Gaussian draws by buckets: a draw compared with all 38 thresholds takes as long as three butterfly passes for each of a
 // thread's coefficients.  The products by the secret as those by any constant.  Bound by the vector ALU: the generator's draws and five
-// transforms at four wavefronts per SIMD.  1024 encryptions from wire to wire 62.9 -> 55.8 us, 50 at n = 8192 53.9 -> 47.4.
+// transforms at four wavefronts per SIMD.  1024 encryptions from wire to wire 59.4 -> 52.0 us; on another box 50 at n = 8192 53.9 -> 47.4.
 template <bool WIDE>
 __global__ __launch_bounds__(NT, 4) void encrypt_ring(const u64 *slots, const u64 *seeds, const ulonglong2 *s_hat, u64 *ct_out,
                                                    RingTables T, RingTables Tp, SmallTables small, const int *slot_to_idx, GaussBuckets gauss,
@@ -1673,7 +1674,8 @@ __global__ __launch_bounds__(NT, 4) void encrypt_ring(const u64 *slots, const u6
 }
 // slots = decode(round(p (c0 + c1 s) / q) mod p).  per_q = floor(p 2^64 / q): the high word of a per_q is the quotient of
 // p a by q or one less, and what is left of p a + floor(q/2) is below 3q.  One round of workgroups, a chain of two transforms: 256
-// decryptions from wire to wire 23.9 -> 22.9 us against a 128-bit remainder and eight consecutive words a thread, 1000 50.3 -> 48.0.
+// decryptions from wire to wire 25.8 -> 24.8 us against a 128-bit remainder and eight consecutive words a thread; on another box 1000
+// 50.3 -> 48.0.
 template <bool WIDE>
 __global__ __launch_bounds__(NT) void decrypt_ring(const u64 *ct_in, const ulonglong2 *s_hat, u64 *slots, RingTables T,
                                                    RingTables Tp, SmallTables small, const int *slot_to_idx, u64 per_q) {
