@@ -367,7 +367,7 @@ ConvWorkspace conv_workspace(const gala_conv_plan *pl, int batch) {
     const size_t n = c->n, w = sizeof(u64);
     ConvWorkspace ws{};
     ws.chunks = choose_chunks(c, batch * pl->nout, pl->cn);
-    ws.mfma = pl->d_wl && batch >= 2;    // from two inputs on (4 of a workgroup's 32 columns) the matrix cores win
+    ws.mfma = pl->d_wl && batch >= 2;    // from two inputs on (4 of a tile's 16 columns) the matrix cores win
     // with one-prime keys the ring kernels write the rotated inputs straight into the product's column image and the Perm
     // kernel reads the product in place: neither the rotated inputs nor the per-ciphertext sums are materialised
     const bool rotates = pl->nrot_terms > 0;
