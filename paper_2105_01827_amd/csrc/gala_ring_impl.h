@@ -1990,41 +1990,37 @@ __global__ __launch_bounds__(NT) void decperm_special_ring(const u64 *ct_in, u64
     for (int k = 0; k < PER; ++k) out[tid + k * NT] = bufA[pad<ALONE_S>(tid + k * NT)];
 }
 
-// HstPerm: one workgroup per (ciphertext, tap): inner products in both moduli from the stored digits, the sums
-// modulo P back to coefficients, lifted, reduced modulo q and transformed forward again, then
-// out = (P c0(X^g) + t_b - NTT(r_b)) / P, (t_a - NTT(r_a)) / P.  Output: xrot[ct][tap][c0|c1][i], canonical.
+// HstPerm: one workgroup per (ciphertext, tap, output polynomial h): inner products in both moduli from the stored digits, the
+// sum modulo P back to coefficients, lifted, reduced modulo q and transformed forward again, then
+// out = (P c0(X^g) + t_b - NTT(r_b)) / P or (t_a - NTT(r_a)) / P.  Output: xrot[ct][tap][c0|c1][i], canonical.
+// A polynomial a workgroup instead of both, one after the other: 118 registers instead of 146, so four wavefronts per SIMD instead
+// of three, and half the chain of steps: the 16x16x128 convolution at batch 16 (2048 rotations) 421 -> 413 us.  The vector ALU
+// (1700 instructions a wavefront) and the vector cache (some 100 loads at 16 clocks) are busy for about 50 of its 90 us each.
 template <bool WIDE>
-__global__ __launch_bounds__(NT, 3) void hstperm_special_ring(const u64 *ct_in, const u64 *digits, TermList terms,
+__global__ __launch_bounds__(NT, 4) void hstperm_special_ring(const u64 *ct_in, const u64 *digits, TermList terms,
                                                            const u64 *keys2, u64 *xrot, RingTables T, SpecialJob S,
                                                            int ndigits) {
     __shared__ u64 bufA[lds_words(ALONE_S)], bufB[lds_words(ALONE_S)];
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, h = blockIdx.y;
     const int b = blockIdx.x / terms.nterm, e = blockIdx.x % terms.nterm;
     const size_t ct = (size_t)b * terms.nin + terms.ct[e];
     const u64 *c0 = ct_in + ct * 2 * N, *c1 = c0 + N;
-    u64 *out = xrot + (size_t)blockIdx.x * 2 * N;
+    u64 *out = xrot + ((size_t)blockIdx.x * 2 + h) * N;
     const int gal = terms.gal[e];
     if (gal == 1) {
+        const u64 *c = h ? c1 : c0;
 #pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int i = tid + k * NT;
-            out[i] = c0[i];
-            out[N + i] = c1[i];
-        }
+        for (int k = 0; k < PER; ++k) out[tid + k * NT] = c[tid + k * NT];
         return;
     }
     const MontQ q = T.mont, qP = S.TP.mont;
     const u64 *dsrc = digits + ct * ndigits * 2 * N;
     const ulonglong2 *key = reinterpret_cast<const ulonglong2 *>(keys2) + (size_t)terms.key[e] * ndigits * 4 * N;
-    int src[PER];
+    u64 sum[PER], tp[PER];      // modulo q and modulo P, at most 4 (at most three digits)
+    {
+        int src[PER];
 #pragma unroll
-    for (int k = 0; k < PER; ++k) src[k] = galois_index(tid + k * NT, gal);
-    // The two output polynomials one after the other (the digits are read twice, out of the L2): half the sums
-    // are alive at a time, and the products are formed four coefficients at a time so that no more than their
-    // operands are in flight - the kernel fits three workgroups per CU instead of one.
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        u64 sum[PER], tp[PER];      // modulo q and modulo P, at most 4 (at most three digits)
+        for (int k = 0; k < PER; ++k) src[k] = galois_index(tid + k * NT, gal);
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
             sum[k] = h ? 0 : mont<WIDE, false, true>(plain_words(c0[src[k]]), S.Pq, q);
@@ -2034,9 +2030,9 @@ __global__ __launch_bounds__(NT, 3) void hstperm_special_ring(const u64 *ct_in, 
             const ulonglong2 *kq = key + (size_t)(4 * j + h) * N, *kP = key + (size_t)(4 * j + 2 + h) * N;
             const u64 *djq = j == ndigits - 1 ? c1 : dsrc + (size_t)(2 * j) * N;       // folded keys modulo q
             const u64 bias = j == ndigits - 1 ? BIAS : 0;
+            const u64 *djP = dsrc + (size_t)(2 * j + 1) * N;
 #pragma unroll
             for (int k = 0; k < PER; k += 2) {
-                const u64 *djP = dsrc + (size_t)(2 * j + 1) * N;
                 const u64 qa = djq[src[k]], qb = djq[src[k + 1]], Pa = djP[src[k]], Pb = djP[src[k + 1]];
                 const ulonglong2 wqa = pair_at(kq + k * NT, tid), wqb = pair_at(kq + (k + 1) * NT, tid),
                                  wPa = pair_at(kP + k * NT, tid), wPb = pair_at(kP + (k + 1) * NT, tid);
@@ -2046,26 +2042,26 @@ __global__ __launch_bounds__(NT, 3) void hstperm_special_ring(const u64 *ct_in, 
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-        u64 a[PER];
-        // LDS phases: B (ownership change), A B A (inverse), B A B A (forward), then reads of A
+    }
+    u64 a[PER];
+    // LDS phases: B (ownership change), A B A (inverse), B A B A (forward), then reads of A
 #pragma unroll
-        for (int k = 0; k < PER; ++k) bufB[pad<ALONE_S>(tid + k * NT)] = mont<WIDE, false, true>(plain_words(tp[k]), S.TP.one, qP);
-        __syncthreads();
-        {
-            const u64 *pi = bufB + pad<ALONE_S>(tid << 3);
+    for (int k = 0; k < PER; ++k) bufB[pad<ALONE_S>(tid + k * NT)] = mont<WIDE, false, true>(plain_words(tp[k]), S.TP.one, qP);
+    __syncthreads();
+    {
+        const u64 *pi = bufB + pad<ALONE_S>(tid << 3);
 #pragma unroll
-            for (int k = 0; k < PER; ++k) a[k] = pi[k];
-        }
-        inverse_in_regs<WIDE, ALONE_S>(a, bufA, bufB, S.TP, tid);
+        for (int k = 0; k < PER; ++k) a[k] = pi[k];
+    }
+    inverse_in_regs<WIDE, ALONE_S>(a, bufA, bufB, S.TP, tid);
 #pragma unroll
-        for (int k = 0; k < PER; ++k) a[k] = csub_dev(a[k], T.mod.q);
-        forward_to_lds<WIDE, ALONE_S>(a, bufA, bufB, T, tid);
+    for (int k = 0; k < PER; ++k) a[k] = csub_dev(a[k], T.mod.q);
+    forward_to_lds<WIDE, ALONE_S>(a, bufA, bufB, T, tid);
 #pragma unroll
-        for (int k = 0; k < PER; ++k) {
-            const int i = tid + k * NT;
-            const u64 minus = shrink(bufA[pad<ALONE_S>(i)], q) - sum[k];
-            out[h * N + i] = unsign(mont<WIDE, false, true>(biased_words(minus), S.minus_Pinv, q), T.mod.q);
-        }
+    for (int k = 0; k < PER; ++k) {
+        const int i = tid + k * NT;
+        const u64 minus = shrink(bufA[pad<ALONE_S>(i)], q) - sum[k];
+        out[i] = unsign(mont<WIDE, false, true>(biased_words(minus), S.minus_Pinv, q), T.mod.q);
     }
 }
 
@@ -2298,7 +2294,7 @@ static int hoist_taps(const gala_ctx *c, void *stream, const u64 *ct_in, int bat
                 const int rc = (int)hipGetLastError();
                 if (rc) return rc;
             }
-            hipLaunchKernelGGL(hstperm_special_ring<WIDE>, per_term, dim3(NT), 0, st, ct_in, digits, terms, keys2, xrot, T, S,
+            hipLaunchKernelGGL(hstperm_special_ring<WIDE>, dim3(per_term.x, 2), dim3(NT), 0, st, ct_in, digits, terms, keys2, xrot, T, S,
                                c->ndigits);
             return (int)hipGetLastError();
         }
