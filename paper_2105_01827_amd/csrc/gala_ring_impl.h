@@ -866,6 +866,7 @@ constexpr int ALONE_S = 3;
 // negated mask of one output ciphertext each and store it as one more partial ciphertext.
 struct MaskJob {
     int enabled;
+    int first_chunk;            // the first chunk's workgroup builds the mask of its item behind its rotations; no workgroups for masks alone
     int nout;                   // output ciphertexts per batch element
     const u64 *r;               // batch x r_stride server shares mod p
     size_t r_stride;
@@ -1030,6 +1031,25 @@ __device__ __forceinline__ void mask_partial(const PermJob &job, const RingTable
         out[N + i] = 0;
     });
 }
+// ... or taken off the c0 of a partial ciphertext that the same threads have written.
+template <bool WIDE, int S, bool ALONE>
+__device__ __forceinline__ void mask_behind(const RingTables &T, const MaskJob &mj, int item, u64 *bufA, u64 *bufB, u64 *out) {
+    const u64 q = T.mod.q;
+    __syncthreads();        // the images may still be read
+    mask_role<WIDE, S, ALONE>(T, mj, item, bufA, bufB, [&](int, int i, u64 m) { out[i] = sub_mod(out[i], m, q); });
+}
+// At n = 4096 a workgroup has a CU to itself and sums are cut into whole rounds of the 256 CUs.  In a launch of one round the masks
+// wait for the first workgroups to end, and then start from the beginning.  Where the G - 1 rotations do not divide by the number of
+// chunks the first chunk is one of the shorter ones, and a mask takes less than a rotation: there its workgroup builds the mask.
+// he_fc 500x1024 at batch 8 86.4 -> 80.4 us, 16x2048 at batch 64 55.2 -> 46.1, with the special prime 102.6 -> 91.5, 100x1000 at
+// batch 23 (253 chunks) 70.3 -> 63.8.  Not where CUs are left for a good part of the masks (9x600 at batch 100, 200 chunks: 43.6 us, 46.9
+// behind first chunks), nor in launches of several rounds, whose tail the masks fill (16x2048 at batch 300 209 us and 220).
+// Instantiations of their own (MASK_BEHIND): the rotations of a kernel that has a mask behind them are up to a tenth slower (60x4000 at
+// batch 20 109 -> 119 us).
+static bool mask_in_first_chunk(const PermJob &job) {
+    const long chunks = (long)job.items * job.nchunks, idle = 256 - chunks;
+    return LOGN == 12 && (job.G - 1) % job.nchunks != 0 && idle >= 0 && idle < job.items && 4 * idle <= job.items;
+}
 // A layer without rotations (he_fc with G = 1: a matrix that fits one ciphertext; a convolution always has two kernel
 // orders at least) is one product and the mask: the workgroup that builds an item's mask forms its output at once, in one
 // launch and without partial ciphertexts.
@@ -1159,7 +1179,7 @@ __device__ __forceinline__ auto make_copy(ulonglong2 *at, const RingTables &T, i
 // pass and a transform's constants at its start.  A convolution of 13x11x24 to 40 channels at batch 5 (175 workgroups) 86.7 -> 82.8 us, he_fc 1000x512 on one
 // input (257) 40.7 -> 40.2 us; the constants at the start and products two at a time 78.2 -> 72.9 and 33.8 -> 32.5 us.  Sharing a rotation's two digits out to two workgroups as well lost: 45.8 us, the inverse
 // transforms and the partial ciphertexts double.
-template <bool WIDE, bool HAS_W, bool IN8 = false, bool FEW = false>
+template <bool WIDE, bool HAS_W, bool IN8 = false, bool FEW = false, bool MASK_BEHIND = false>
 __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring(PermJob job, RingTables T, MaskJob mj,
                                                                                  int gadget_bits, int ndigits) {
     __shared__ u64 bufA[lds_words(PERM_S)], bufB[lds_words(PERM_S)];
@@ -1359,6 +1379,7 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
         out[i] = canonical<WIDE>(plain_words(sum0[k]), T);
         out[N + i] = canonical<WIDE>(plain_words(sum1[k]), T);
     }
+    if (MASK_BEHIND && chunk == 0) mask_behind<WIDE, PERM_S, FEW>(T, mj, item, bufA, bufB, out);
 }
 
 // Hoisted rotations of the input ciphertexts (Sec. III-B: one DecPerm shared by all the taps of a kernel,
@@ -1734,7 +1755,7 @@ struct SpecialJob {
 };
 
 // IN8: the inputs lie in blocks of eight coefficients (PermJob::in8_S), as the matrix-core product leaves them.
-template <bool WIDE, bool HAS_W, bool IN8 = false>
+template <bool WIDE, bool HAS_W, bool IN8 = false, bool MASK_BEHIND = false>
 __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob job, RingTables T, SpecialJob S, MaskJob mj,
                                                                       int gadget_bits, int ndigits) {
     constexpr int PS = 5;
@@ -1958,6 +1979,7 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
             out[h * N + i] = unsign(mont<WIDE, false, true>(biased_words(minus), S.minus_Pinv, q), T.mod.q);
         }
     }
+    if (MASK_BEHIND && chunk == 0) mask_behind<WIDE, PS, false>(T, mj, item, bufA, bufB, out);
 }
 
 // ---- hoisted input rotations with a special prime ----------------------------------------------------------
@@ -2162,7 +2184,7 @@ static bool few(size_t workgroups) { return workgroups * NT <= (size_t)256 * 4 *
 static int launch_perm(const gala_ctx *c, void *stream, const PermJob &job, const MaskJob &mj) {
     hipStream_t st = (hipStream_t)stream;
     const RingTables T = make_tables(c->d_tw2, c->ntt_q);
-    const dim3 grid((unsigned)(job.items * job.nchunks + (mj.enabled ? job.items : 0)));
+    const dim3 grid((unsigned)(job.items * job.nchunks + (mj.enabled && !mj.first_chunk ? job.items : 0)));
     if (job.in8_S && job.w) return (int)hipErrorInvalidValue;
     return by_width(c, [&](auto width) {
         constexpr bool WIDE = decltype(width)::value;
@@ -2172,6 +2194,14 @@ static int launch_perm(const gala_ctx *c, void *stream, const PermJob &job, cons
             auto go = [&](auto kernel) {
                 hipLaunchKernelGGL(kernel, grid, dim3(NT), 0, st, job, T, S, mj, c->gadget_bits, c->ndigits);
             };
+#if GALA_LOGN == 12
+            if (mj.first_chunk) {
+                if (job.w) go(perm_accumulate_special_ring<WIDE, true, false, true>);
+                else if (job.in8_S) go(perm_accumulate_special_ring<WIDE, false, true, true>);
+                else go(perm_accumulate_special_ring<WIDE, false, false, true>);
+                return (int)hipGetLastError();
+            }
+#endif
             if (job.w) go(perm_accumulate_special_ring<WIDE, true>);
             else if (job.in8_S) go(perm_accumulate_special_ring<WIDE, false, true>);
             else go(perm_accumulate_special_ring<WIDE, false>);
@@ -2181,6 +2211,14 @@ static int launch_perm(const gala_ctx *c, void *stream, const PermJob &job, cons
         auto go = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, grid, dim3(NT), 0, st, job, T, mj, c->gadget_bits, c->ndigits);
         };
+#if GALA_LOGN == 12
+        if (mj.first_chunk) {        // with all constants at the start 500x1024 at batch 8 takes 84.2 us, 80.4 without
+            if (job.w) go(perm_accumulate_ring<WIDE, true, false, false, true>);
+            else if (job.in8_S) go(perm_accumulate_ring<WIDE, false, true, false, true>);
+            else go(perm_accumulate_ring<WIDE, false, false, false, true>);
+            return (int)hipGetLastError();
+        }
+#endif
 #if GALA_LOGN < 13
         if (few(grid.x)) {
             if (job.w) go(perm_accumulate_ring<WIDE, true, false, true>);
@@ -2205,6 +2243,8 @@ static int perm(const gala_ctx *c, void *stream, const PermJob &job) {
 static int perm_masked(const gala_ctx *c, void *stream, const PermJob &job, const FinalizeJob &fin) {
     MaskJob mj{};
     mj.enabled = 1;
+    mj.first_chunk = !job.product_only && mask_in_first_chunk(job);
+    const int used = job.nchunks + !mj.first_chunk;      // partial ciphertexts
     mj.nout = fin.nout;
     mj.r = fin.r;
     mj.r_stride = fin.r_stride;
@@ -2248,15 +2288,15 @@ static int perm_masked(const gala_ctx *c, void *stream, const PermJob &job, cons
     if (rc || alone) return rc;
     const size_t words = span;
     // many partials of few items: more wavefronts per word
-    if (job.nchunks + 1 <= 8)
+    if (used <= 8)
         hipLaunchKernelGGL(sum_few_partials_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, st, job.partial, job.slots,
-                           job.nchunks + 1, fin.ct_out, words, c->q);
-    else if (job.nchunks + 1 > 64 && words / 64 < 2048)
+                           used, fin.ct_out, words, c->q);
+    else if (used > 64 && words / 64 < 2048)
         hipLaunchKernelGGL(sum_partials_kernel<16>, dim3((unsigned)(words / 64)), dim3(1024), 0, st, job.partial, job.slots,
-                           job.nchunks + 1, fin.ct_out, words, c->q);
+                           used, fin.ct_out, words, c->q);
     else
         hipLaunchKernelGGL(sum_partials_kernel<4>, dim3((unsigned)(words / 64)), dim3(256), 0, st, job.partial, job.slots,
-                           job.nchunks + 1, fin.ct_out, words, c->q);
+                           used, fin.ct_out, words, c->q);
     return (int)hipGetLastError();
 }
 
