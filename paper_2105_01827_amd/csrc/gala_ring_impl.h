@@ -119,6 +119,40 @@ __device__ __forceinline__ u64 mont_reduce(u64 L, u64 H, const MontQ &q) {
     }
     return H;
 }
+template <bool WIDE>
+__device__ __forceinline__ void mont_reduce2(u64 &L, u64 &H, u64 &M, u64 &I, const MontQ &q) {
+    int k, l;
+    if (WIDE) {
+        asm("v_mul_lo_u32 %2, %4, %8\n\t"
+            "v_mul_lo_u32 %3, %5, %8\n\t"
+            "v_mad_i64_i32 %0, vcc, %2, %9, %0\n\t"
+            "v_mad_i64_i32 %1, vcc, %3, %9, %1\n\t"
+            "v_mul_hi_i32 %2, %2, %10\n\t"
+            "v_mul_hi_i32 %3, %3, %10\n\t"
+            "v_mad_i64_i32 %0, vcc, %6, 1, %0\n\t"
+            "v_mad_i64_i32 %1, vcc, %7, 1, %1\n\t"
+            "v_mad_i64_i32 %0, vcc, %2, -1, %0\n\t"
+            "v_mad_i64_i32 %1, vcc, %3, -1, %1"
+            : "+v"(H), "+v"(I), "=&v"(k), "=&v"(l)
+            : "v"((u32)L), "v"((u32)M), "v"((u32)(L >> 32)), "v"((u32)(M >> 32)), "s"(q.inv), "s"(q.nhi), "s"(q.lo)
+            : "vcc");
+    } else {
+        asm("v_mul_lo_u32 %4, %6, %8\n\t"
+            "v_mul_lo_u32 %5, %7, %8\n\t"
+            "v_mad_i64_i32 %0, vcc, %4, %9, %0\n\t"
+            "v_mad_i64_i32 %2, vcc, %5, %9, %2\n\t"
+            "v_mad_i64_i32 %1, vcc, %4, %10, %1\n\t"
+            "v_mad_i64_i32 %3, vcc, %5, %10, %3"
+            : "+v"(L), "+v"(H), "+v"(M), "+v"(I), "=&v"(k), "=&v"(l)
+            : "v"((u32)L), "v"((u32)M), "s"(q.inv), "s"(q.nlo), "s"(q.nhi)
+            : "vcc");
+        asm("v_mad_i64_i32 %0, vcc, %2, 1, %0\n\t"
+            "v_mad_i64_i32 %1, vcc, %3, 1, %1"
+            : "+v"(H), "+v"(I)
+            : "v"((u32)(L >> 32)), "v"((u32)(M >> 32))
+            : "vcc");
+    }
+}
 // w y, or x + w y.  UNIFORM: the constant is the same for all lanes and sits in scalar registers.
 template <bool WIDE, bool ADD = false, bool UNIFORM = false>
 __device__ __forceinline__ u64 mont(Words y, const ulonglong2 w, const MontQ &q, u64 x = 0) {
@@ -177,37 +211,7 @@ __device__ __forceinline__ void mont2(u64 &ra, u64 &rb, Words ya, const ulonglon
         else GALA_MONT2("v", "=&v", "0", "0");
     }
 #undef GALA_MONT2
-    int k, l;
-    if (WIDE) {
-        asm("v_mul_lo_u32 %2, %4, %8\n\t"
-            "v_mul_lo_u32 %3, %5, %8\n\t"
-            "v_mad_i64_i32 %0, vcc, %2, %9, %0\n\t"
-            "v_mad_i64_i32 %1, vcc, %3, %9, %1\n\t"
-            "v_mul_hi_i32 %2, %2, %10\n\t"
-            "v_mul_hi_i32 %3, %3, %10\n\t"
-            "v_mad_i64_i32 %0, vcc, %6, 1, %0\n\t"
-            "v_mad_i64_i32 %1, vcc, %7, 1, %1\n\t"
-            "v_mad_i64_i32 %0, vcc, %2, -1, %0\n\t"
-            "v_mad_i64_i32 %1, vcc, %3, -1, %1"
-            : "+v"(H), "+v"(I), "=&v"(k), "=&v"(l)
-            : "v"((u32)L), "v"((u32)M), "v"((u32)(L >> 32)), "v"((u32)(M >> 32)), "s"(q.inv), "s"(q.nhi), "s"(q.lo)
-            : "vcc");
-    } else {
-        asm("v_mul_lo_u32 %4, %6, %8\n\t"
-            "v_mul_lo_u32 %5, %7, %8\n\t"
-            "v_mad_i64_i32 %0, vcc, %4, %9, %0\n\t"
-            "v_mad_i64_i32 %2, vcc, %5, %9, %2\n\t"
-            "v_mad_i64_i32 %1, vcc, %4, %10, %1\n\t"
-            "v_mad_i64_i32 %3, vcc, %5, %10, %3"
-            : "+v"(L), "+v"(H), "+v"(M), "+v"(I), "=&v"(k), "=&v"(l)
-            : "v"((u32)L), "v"((u32)M), "s"(q.inv), "s"(q.nlo), "s"(q.nhi)
-            : "vcc");
-        asm("v_mad_i64_i32 %0, vcc, %2, 1, %0\n\t"
-            "v_mad_i64_i32 %1, vcc, %3, 1, %1"
-            : "+v"(H), "+v"(I)
-            : "v"((u32)(L >> 32)), "v"((u32)(M >> 32))
-            : "vcc");
-    }
+    mont_reduce2<WIDE>(L, H, M, I, q);
     ra = H;
     rb = I;
 }
@@ -258,13 +262,6 @@ __device__ __forceinline__ void bf2(u64 &xa, u64 &ya, const ulonglong2 wa, u64 &
 template <bool WIDE>
 __device__ __forceinline__ void bf_plain(u64 &x, u64 &y, const ulonglong2 w, const MontQ &q) {
     const u64 s = mont<WIDE, true, true>(plain_words(y), w, q, x);
-    y = (x << 1) - s;
-    x = s;
-}
-// y below 2^31 and not biased
-template <bool WIDE>
-__device__ __forceinline__ void bf_digit(u64 &x, u64 &y, const ulonglong2 w, const MontQ &q) {
-    const u64 s = mont_small<WIDE>((u32)y, w, q, x);
     y = (x << 1) - s;
     x = s;
 }
@@ -323,22 +320,15 @@ __device__ __forceinline__ Tw7 tw_level(const ulonglong2 *__restrict__ table, un
     return w;
 }
 // STAGE: the first of the three stages to run.  CORRECT: the values that the first stage does not multiply are shrunk.
-// digits (the same for every thread): a[4..7], the values that the first stage multiplies, are below 2^31 and not biased,
-// as gadget digits are.
 template <bool WIDE, int STAGE, bool CORRECT = false, bool UNIFORM = false>
-__device__ __forceinline__ void fwd_pass(u64 (&a)[8], const Tw7 &w, const MontQ &q, bool digits = false) {
+__device__ __forceinline__ void fwd_pass(u64 (&a)[8], const Tw7 &w, const MontQ &q) {
     if (CORRECT) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) a[k] = shrink(a[k], q);
     }
     if (STAGE == 0) {
-        if (UNIFORM && digits) {
-#pragma unroll
-            for (int k = 0; k < 4; ++k) bf_digit<WIDE>(a[k], a[k + 4], w.t[0], q);
-        } else {
-            bf2<WIDE, UNIFORM>(a[0], a[4], w.t[0], a[1], a[5], w.t[0], q);
-            bf2<WIDE, UNIFORM>(a[2], a[6], w.t[0], a[3], a[7], w.t[0], q);
-        }
+        bf2<WIDE, UNIFORM>(a[0], a[4], w.t[0], a[1], a[5], w.t[0], q);
+        bf2<WIDE, UNIFORM>(a[2], a[6], w.t[0], a[3], a[7], w.t[0], q);
     }
     if (STAGE <= 1) {
         bf2<WIDE, UNIFORM>(a[0], a[2], w.t[1], a[1], a[3], w.t[1], q);
@@ -346,6 +336,66 @@ __device__ __forceinline__ void fwd_pass(u64 (&a)[8], const Tw7 &w, const MontQ 
     }
     bf2<WIDE, UNIFORM>(a[0], a[1], w.t[3], a[2], a[3], w.t[4], q);
     bf2<WIDE, UNIFORM>(a[4], a[5], w.t[5], a[6], a[7], w.t[6], q);
+}
+// The first pass on eight gadget digits x_0 .. x_7, not biased; a biased.  Digits are short, so products of several of them by
+// constants add up in the words of one product and are reduced together: three of stages 1 and 2 for x_0, x_2, x_4, x_6, and what stage 3
+// adds to and takes from those, sums of four products of x_1, x_3, x_5, x_7 each.  91 instructions instead of 144, or 132 with
+// a first stage of small factors.  Constants (see append_digit_sums): words w 2^32 mod m alone, the other half of a pair has nothing to
+// multiply.  Bounds with digits of 30 bits: 0.63 | 1.4 | 2.4.
+// With offsets of bytes for the gathers (Perm kernels), from wire to wire: he_fc 1000x2048 at batch 64 1711 -> 1676 us, 128x1024 135.2 -> 133.1,
+// the 16x16x128 convolution at batch 16 245.0 -> 241.9.
+template <bool WIDE>
+__device__ __forceinline__ void digit_pass(u64 (&a)[8], const u32 (&x)[8], const u64 *constants, const MontQ &q) {
+    typedef __attribute__((address_space(4))) const u64 scalar_u64;
+    asm volatile("" : "+s"(constants));        // loaded where it is used, as in tw_first
+    scalar_u64 *c = (scalar_u64 *)reinterpret_cast<uintptr_t>(constants);
+#define GALA_WORDS(C) "s"((u32)(C)), "s"((u32)((C) >> 32))
+    const u64 x0 = (u64)x[0] + BIAS;
+    u64 e0 = mont_small<WIDE>(x[4], make_ulonglong2(c[0], 0), q, x0), e1 = (x0 << 1) - e0;
+    u64 L, H, M, I;
+    asm("v_mad_i64_i32 %0, vcc, %4, %6, 0\n\t"
+        "v_mad_i64_i32 %2, vcc, %4, %8, 0\n\t"
+        "v_mad_i64_i32 %1, vcc, %4, %7, 0\n\t"
+        "v_mad_i64_i32 %3, vcc, %4, %9, 0\n\t"
+        "v_mad_i64_i32 %0, vcc, %5, %10, %0\n\t"
+        "v_mad_i64_i32 %2, vcc, %5, %12, %2\n\t"
+        "v_mad_i64_i32 %1, vcc, %5, %11, %1\n\t"
+        "v_mad_i64_i32 %3, vcc, %5, %13, %3"
+        : "=&v"(L), "=&v"(H), "=&v"(M), "=&v"(I)
+        : "v"(x[2]), "v"(x[6]), GALA_WORDS(c[1]), GALA_WORDS(c[2]), GALA_WORDS(c[3]), GALA_WORDS(c[4])
+        : "vcc");
+    mont_reduce2<WIDE>(L, H, M, I, q);
+    const u64 p[4] = {e0 + H, e0 - H, e1 + I, e1 - I};
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        scalar_u64 *d = c + 6 + 8 * h;
+        asm("v_mad_i64_i32 %0, vcc, %4, %8, 0\n\t"
+            "v_mad_i64_i32 %2, vcc, %4, %10, 0\n\t"
+            "v_mad_i64_i32 %1, vcc, %4, %9, 0\n\t"
+            "v_mad_i64_i32 %3, vcc, %4, %11, 0\n\t"
+            "v_mad_i64_i32 %0, vcc, %5, %12, %0\n\t"
+            "v_mad_i64_i32 %2, vcc, %5, %14, %2\n\t"
+            "v_mad_i64_i32 %1, vcc, %5, %13, %1\n\t"
+            "v_mad_i64_i32 %3, vcc, %5, %15, %3\n\t"
+            "v_mad_i64_i32 %0, vcc, %6, %16, %0\n\t"
+            "v_mad_i64_i32 %2, vcc, %6, %18, %2\n\t"
+            "v_mad_i64_i32 %1, vcc, %6, %17, %1\n\t"
+            "v_mad_i64_i32 %3, vcc, %6, %19, %3\n\t"
+            "v_mad_i64_i32 %0, vcc, %7, %20, %0\n\t"
+            "v_mad_i64_i32 %2, vcc, %7, %22, %2\n\t"
+            "v_mad_i64_i32 %1, vcc, %7, %21, %1\n\t"
+            "v_mad_i64_i32 %3, vcc, %7, %23, %3"
+            : "=&v"(L), "=&v"(H), "=&v"(M), "=&v"(I)
+            : "v"(x[1]), "v"(x[5]), "v"(x[3]), "v"(x[7]), GALA_WORDS(d[0]), GALA_WORDS(d[1]), GALA_WORDS(d[2]), GALA_WORDS(d[3]),
+              GALA_WORDS(d[4]), GALA_WORDS(d[5]), GALA_WORDS(d[6]), GALA_WORDS(d[7])
+            : "vcc");
+        mont_reduce2<WIDE>(L, H, M, I, q);
+        a[4 * h] = p[2 * h] + H;
+        a[4 * h + 1] = p[2 * h] - H;
+        a[4 * h + 2] = p[2 * h + 1] + I;
+        a[4 * h + 3] = p[2 * h + 1] - I;
+    }
+#undef GALA_WORDS
 }
 // Inverse transform.  The values sit in bit-reversed order, which is what a decimation-in-time transform starts from:
 // it evaluates the plain cyclic sum over the powers of psi^-2, and a multiplication of coefficient j by psi^-j / n at
@@ -435,6 +485,7 @@ __device__ __forceinline__ void exchange(u64 (&a)[8], u64 *buf, int tid) {
 
 struct RingTables {
     const ulonglong2 *tw, *itw;   // MontPairs, forward (see tw_level) and inverse (see inv_level)
+    const u64 *digits;            // constants of digit_pass; null: its sums might not fit their words
     ulonglong2 w8[3];             // w8, w8^2, w8^3 of the inverse transform's first pass
     ulonglong2 one;               // the constant 1
     Modulus mod;
@@ -496,7 +547,8 @@ struct TableCopy {
 // Forward transform of the 8 registers (ownership t + (n/8) k); the result is left in LDS buffer `res` (natural index,
 // padded), biased, below 7.3 (5.4 at n = 2048).  LDS phases: other, res, other, res; at n = 8192, where a
 // fifth phase would start and end on the same buffer, res, other, res, other, res behind a barrier.
-// IN: what the registers hold on entry.  Digits are below 2^31.  Bounds from |a| < m: 1.8, 2.6, 3.5 | 4.3, 5.2, 6.1 |
+// IN: what the registers hold on entry.  digit: the transform of the gadget digits digit(0) .. digit(7) instead, whatever the registers hold.
+// Bounds from |a| < m: 1.8, 2.6, 3.5 | 4.3, 5.2, 6.1 |
 // shrunk, 2.0, 2.8, 3.6 | 4.5, 5.4, 6.3 | 7.2.
 // `ahead` runs before the last pass: loads of what is multiplied with the result can be issued there.
 struct NothingAhead {
@@ -510,21 +562,15 @@ enum Entry { PLAIN, BIASED };
 // the start, the exchanges' in their order, the one at the end.
 constexpr int FORWARD_BARRIERS = (LOGN == 13) + crosses(LOGN - 3, LOGN - 6) + crosses(LOGN - 6, LOGN - 9) +
                                  crosses(LOGN - 9, LOGN < 12 ? 0 : LOGN - 12) + (LOGN == 13 && crosses(LOGN - 12, 0)) + 1;
-template <bool WIDE, int S, Entry IN = PLAIN, bool ALONE = false, class Copy = NoCopy, class Ahead = NothingAhead>
+struct WholeWords {};
+template <bool WIDE, int S, Entry IN = PLAIN, bool ALONE = false, class Digit = WholeWords, class Copy = NoCopy, class Ahead = NothingAhead>
 __device__ __forceinline__ void forward_to_lds(u64 (&a)[8], u64 *res, u64 *other, const RingTables &T, int tid_,
-                                               bool digits = false, Copy copy = Copy{}, Ahead ahead = Ahead{}) {
+                                               Digit digit = Digit{}, Copy copy = Copy{}, Ahead ahead = Ahead{}) {
     const int tid = fresh(tid_);
     const MontQ q = T.mont;
     constexpr int B1 = LOGN - 3, B2 = LOGN - 6, B3 = LOGN - 9, B4 = LOGN >= 12 ? LOGN - 12 : 0;
     u64 *first = LOGN == 13 ? res : other, *second = LOGN == 13 ? other : res;
     if (LOGN == 13) __syncthreads();
-    if (IN == PLAIN) {
-#pragma unroll
-        for (int k = 0; k < 4; ++k) a[k] += BIAS;
-        if (!digits)
-#pragma unroll
-            for (int k = 4; k < 8; ++k) a[k] += BIAS;
-    }
     Tw7 w8, w64, w512, last;        // levels 8, 64, 512 (from n = 4096 on) and n/8 (but at n = 4096, where it is level 512)
     auto get8 = [&] {
         if (Copy::LEVELS >= 1) w8 = copy.template get<8>(copy.f8, (unsigned)tid >> B2);
@@ -543,7 +589,26 @@ __device__ __forceinline__ void forward_to_lds(u64 (&a)[8], u64 *res, u64 *other
         if (LOGN != 12) get_last();
         pin_loads();
     }
-    fwd_pass<WIDE, 0, false, true>(a, tw_first(T.tw), q, digits);                        // stages 1-3
+    // stages 1-3
+    auto whole = [&] {
+        if (IN == PLAIN) {
+#pragma unroll
+            for (int k = 0; k < 8; ++k) a[k] += BIAS;
+        }
+        fwd_pass<WIDE, 0, false, true>(a, tw_first(T.tw), q);
+    };
+    if constexpr (std::is_same_v<Digit, WholeWords>) {
+        whole();
+    } else if (T.digits) {
+        u32 x[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) x[k] = (u32)digit(k);
+        digit_pass<WIDE>(a, x, T.digits, q);
+    } else {
+#pragma unroll
+        for (int k = 0; k < 8; ++k) a[k] = digit(k);
+        whole();
+    }
     if (!ALONE) get8();
     exchange<S, B1, B2>(a, first, tid);
     if (!ALONE && Copy::LEVELS < 2) {
@@ -1136,6 +1201,10 @@ __device__ __forceinline__ void item_and_chunk(const PermJob &job, int &item, in
 // From wire to wire, three digits: he_fc 128x1024 at batch 64 209 -> 162 us, 1000x2048 2669 -> 2195 us (the share of the
 // import and export transforms in that is 12 us); two digits and a special prime, 100x784 at batch 7: 92 -> 80 us.
 
+// the word at a byte offset of an image
+__device__ __forceinline__ u64 word_at(const u64 *image, u32 offset) {
+    return *reinterpret_cast<const u64 *>(reinterpret_cast<const char *>(image) + offset);
+}
 // a pair of a polynomial of which the start is uniform: a scalar base and 32 bits of offset, no address arithmetic
 __device__ __forceinline__ ulonglong2 pair_at(const ulonglong2 *base, int tid) {
     typedef __attribute__((address_space(1))) const char global_char;
@@ -1255,7 +1324,7 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
         const unsigned turn = turn_of(tid);
         // ScMult of the thread's own eight coefficients.  c1 (.) w stays in registers for the inverse transform.
         u64 a[PER];
-        // Where the automorphism takes the eight outputs from: word indices into an image, two to a register.  At n = 8192 they
+        // Where the automorphism takes the eight outputs from: byte offsets into an image, two to a register.  At n = 8192 they
         // are worked out again for each digit: kept, they were spilled with what they displaced (700 rotations 173 us, 151 now;
         // he_fc 100x784 at batch 64 250 us, 217 now).
         u32 from[PARK ? 4 : 1];
@@ -1305,10 +1374,10 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
                 const int src = source(turn, k);
                 u64 d;
                 if (PARK) {
-                    const int at = pad<PERM_S>(src);
-                    from[PARK ? k & 3 : 0] = k < 4 ? (u32)at : from[PARK ? k & 3 : 0] | (u32)at << 16;
+                    const u32 at = (u32)pad<PERM_S>(src) * 8;
+                    from[PARK ? k & 3 : 0] = k < 4 ? at : from[PARK ? k & 3 : 0] | at << 16;
                     sum0[k] += stash[pad<5>(src)];
-                    d = bufB[at];
+                    d = word_at(bufB, at);
                 } else if (HAS_W) {
                     const ulonglong2 ww = w[src];
                     sum0[k] = mont<WIDE, true>(plain_words(c0[src]), ww, q, sum0[k]);
@@ -1334,11 +1403,10 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
 
         int pending = 2;   // products added to sum0 since it was last shrunk
         for (int j = 0; j < ndigits - 1; ++j) {
-#pragma unroll
-            for (int k = 0; k < PER; ++k) a[k] = ((PARK ? stash[tid + k * NT] : coef[PARK ? 0 : k]) >> (j * gadget_bits)) & digit_mask;
+            auto digit = [&](int k) { return ((PARK ? stash[tid + k * NT] : coef[PARK ? 0 : k]) >> (j * gadget_bits)) & digit_mask; };
             const ulonglong2 *kb = key + (size_t)(2 * j) * N, *ka = kb + N;
             ulonglong2 kbv[AHEAD ? AHEAD : 1], kav[AHEAD ? AHEAD : 1];
-            forward_to_lds<WIDE, PERM_S, PLAIN, FEW>(a, bufA, bufB, T, tid, gadget_bits <= 31, copy, [&] {
+            forward_to_lds<WIDE, PERM_S, PLAIN, FEW>(a, bufA, bufB, T, tid, digit, copy, [&] {
 #pragma unroll
                 for (int k = 0; k < AHEAD; ++k) {
                     kbv[k] = pair_at(kb + k * NT, tid);
@@ -1358,8 +1426,8 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
             const unsigned turn_j = PARK ? 0 : turn_of(fresh(tid));
 #pragma unroll
             for (int k = 0; k < PER; ++k) {
-                const u32 at = !PARK ? (u32)pad<PERM_S>(source(turn_j, k)) : from[PARK ? k & 3 : 0] >> (k < 4 ? 0 : 16) & 0xffff;
-                const Words d = biased_words(bufA[at]);
+                const u32 at = !PARK ? (u32)pad<PERM_S>(source(turn_j, k)) * 8 : from[PARK ? k & 3 : 0] >> (k < 4 ? 0 : 16) & 0xffff;
+                const Words d = biased_words(word_at(bufA, at));
                 const ulonglong2 b = k < AHEAD ? kbv[k < AHEAD ? k : 0] : pair_at(kb + k * NT, tid),
                                  aa = k < AHEAD ? kav[k < AHEAD ? k : 0] : pair_at(ka + k * NT, tid);
                 mont2<WIDE, false, IN_PLACE>(sum0[k], sum1[k], d, b, d, aa, q);       // the sums ride on the products
@@ -1406,9 +1474,8 @@ __global__ __launch_bounds__(NT) void decperm_ring(const u64 *ct_in, u64 *digits
     }
     inverse_in_regs<WIDE, ALONE_S, false, FEW>(a, bufA, bufB, T, tid);      // LDS phases A B A
     const u64 digit_mask = (1ull << gadget_bits) - 1;
-#pragma unroll
-    for (int k = 0; k < PER; ++k) a[k] = (a[k] >> (j * gadget_bits)) & digit_mask;
-    forward_to_lds<WIDE, ALONE_S, PLAIN, FEW>(a, bufA, bufB, T, tid, gadget_bits <= 31);       // LDS phases B A B A, ends on a barrier
+    auto digit = [&](int k) { return (a[k] >> (j * gadget_bits)) & digit_mask; };
+    forward_to_lds<WIDE, ALONE_S, PLAIN, FEW>(a, bufA, bufB, T, tid, digit);       // LDS phases B A B A, ends on a barrier
     u64 *out = digits + ((size_t)ct * stored + j) * N;
 #pragma unroll
     for (int k = 0; k < PER; ++k) out[tid + k * NT] = bufA[pad<ALONE_S>(tid + k * NT)];
@@ -1848,10 +1915,10 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
 #pragma unroll
             for (int k = 0; k < PER; ++k) {
                 const int k3 = ((k & 1) << 2) | (k & 2) | (k >> 2);
-                const int at = pad<PS>((int)(__brev(turn + (unsigned)(k3 * gal)) >> (32 - LOGN)));
-                from[k & 3] = k < 4 ? (u32)at : from[k & 3] | (u32)at << 16;
-                const u64 x = stash[at];
-                const Words y = plain_words(bufB[at]);
+                const u32 at = (u32)pad<PS>((int)(__brev(turn + (unsigned)(k3 * gal)) >> (32 - LOGN))) * 8;
+                from[k & 3] = k < 4 ? at : from[k & 3] | at << 16;
+                const u64 x = word_at(stash, at);
+                const Words y = plain_words(word_at(bufB, at));
                 const ulonglong2 b = pair_at(kb + k * NT, tid), aa = pair_at(ka + k * NT, tid);
                 sum0[k] = mont<WIDE, true, true>(plain_words(x), S.Pq, q, sum0[k]);
                 mont2<WIDE, false, IN_PLACE>(sum0[k], sum1[k], y, b, y, aa, q);
@@ -1866,9 +1933,8 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
         for (int k = 0; k < PER; ++k) tp0[k] = tp1[k] = 0;
         for (int j = 0; j < ndigits; ++j) {
             const ulonglong2 *kb = key + (size_t)(4 * j) * N, *ka = kb + N;
+            auto digit = [&](int k) { return (stash[tid + k * NT] >> (j * gadget_bits)) & digit_mask; };
             if (j + 1 < ndigits) {
-#pragma unroll
-                for (int k = 0; k < PER; ++k) a[k] = (stash[tid + k * NT] >> (j * gadget_bits)) & digit_mask;
                 ulonglong2 kbv[AHEAD], kav[AHEAD];
                 auto ahead = [&] {
 #pragma unroll
@@ -1878,7 +1944,7 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
                     }
                     pin_loads();
                 };
-                forward_to_lds<WIDE, PS>(a, bufA, bufB, T, tid, gadget_bits <= 31, NoCopy{}, ahead);
+                forward_to_lds<WIDE, PS>(a, bufA, bufB, T, tid, digit, NoCopy{}, ahead);
                 if (pending == 4) {
                     asm volatile("");
 #pragma unroll
@@ -1890,7 +1956,7 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
                 }
 #pragma unroll
                 for (int k = 0; k < PER; ++k) {
-                    const Words d = biased_words(bufA[k < 4 ? from[k] & 0xffff : from[k & 3] >> 16]);
+                    const Words d = biased_words(word_at(bufA, k < 4 ? from[k] & 0xffff : from[k & 3] >> 16));
                     const ulonglong2 b = k < AHEAD ? kbv[k < AHEAD ? k : 0] : pair_at(kb + k * NT, tid),
                                      aa = k < AHEAD ? kav[k < AHEAD ? k : 0] : pair_at(ka + k * NT, tid);
                     mont2<WIDE, false, IN_PLACE>(sum0[k], sum1[k], d, b, d, aa, q);
@@ -1898,8 +1964,6 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
                 ++pending;
             }
             // the same digit modulo P
-#pragma unroll
-            for (int k = 0; k < PER; ++k) a[k] = (stash[tid + k * NT] >> (j * gadget_bits)) & digit_mask;
             const ulonglong2 *kbP = kb + 2 * (size_t)N, *kaP = kbP + N;
             ulonglong2 kbv[AHEAD], kav[AHEAD];
             auto ahead = [&] {
@@ -1910,7 +1974,7 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
                 }
                 pin_loads();
             };
-            forward_to_lds<WIDE, PS>(a, bufA, bufB, S.TP, tid, gadget_bits <= 31, NoCopy{}, ahead);
+            forward_to_lds<WIDE, PS>(a, bufA, bufB, S.TP, tid, digit, NoCopy{}, ahead);
             if (pendingP == 4) {
                 asm volatile("");
 #pragma unroll
@@ -1922,7 +1986,7 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
             }
 #pragma unroll
             for (int k = 0; k < PER; ++k) {
-                const Words d = biased_words(bufA[k < 4 ? from[k] & 0xffff : from[k & 3] >> 16]);
+                const Words d = biased_words(word_at(bufA, k < 4 ? from[k] & 0xffff : from[k & 3] >> 16));
                 const ulonglong2 b = k < AHEAD ? kbv[k < AHEAD ? k : 0] : pair_at(kbP + k * NT, tid),
                                  aa = k < AHEAD ? kav[k < AHEAD ? k : 0] : pair_at(kaP + k * NT, tid);
                 mont2<WIDE, false, IN_PLACE>(tp0[k], tp1[k], d, b, d, aa, qP);
@@ -2003,10 +2067,9 @@ __global__ __launch_bounds__(NT) void decperm_special_ring(const u64 *ct_in, u64
     }
     inverse_in_regs<WIDE, ALONE_S>(a, bufA, bufB, T, tid);
     const u64 digit_mask = (1ull << gadget_bits) - 1;
-#pragma unroll
-    for (int k = 0; k < PER; ++k) a[k] = (a[k] >> (j * gadget_bits)) & digit_mask;
-    if (m) forward_to_lds<WIDE, ALONE_S>(a, bufA, bufB, TP, tid, gadget_bits <= 31);
-    else forward_to_lds<WIDE, ALONE_S>(a, bufA, bufB, T, tid, gadget_bits <= 31);
+    auto digit = [&](int k) { return (a[k] >> (j * gadget_bits)) & digit_mask; };
+    if (m) forward_to_lds<WIDE, ALONE_S>(a, bufA, bufB, TP, tid, digit);
+    else forward_to_lds<WIDE, ALONE_S>(a, bufA, bufB, T, tid, digit);
     u64 *out = digits + (((size_t)ct * ndigits + j) * 2 + m) * N;
 #pragma unroll
     for (int k = 0; k < PER; ++k) out[tid + k * NT] = bufA[pad<ALONE_S>(tid + k * NT)];
@@ -2129,6 +2192,7 @@ static RingTables make_tables(const MontPair *pairs, const NttHost &h) {
     RingTables T;
     T.tw = reinterpret_cast<const ulonglong2 *>(pairs);
     T.itw = T.tw + FWD_PAIRS;
+    T.digits = h.digit_sums ? reinterpret_cast<const u64 *>(T.itw + INV_TWIST + N) : nullptr;
     for (int e = 0; e < 3; ++e) T.w8[e] = as_words(h.w8m[e]);
     T.one = as_words(h.one_m);
     T.mod = h.mod;
