@@ -1205,6 +1205,22 @@ __device__ __forceinline__ void item_and_chunk(const PermJob &job, int &item, in
 __device__ __forceinline__ u64 word_at(const u64 *image, u32 offset) {
     return *reinterpret_cast<const u64 *>(reinterpret_cast<const char *>(image) + offset);
 }
+// Brings the constants of digit_pass into the scalar cache while something else is waited for: its own three loads, one after the other,
+// each wait for memory otherwise.  he_fc 1000x512 on one input 32.3 -> 31.7 us from wire to wire.  Not for a second entry of a sum (32.0
+// with the first two), nor where registers are short (with the special prime 58.9 -> 59.8, 100x784 at batch 7).
+struct DigitLines {
+    u64 w[4];
+    __device__ __forceinline__ void request(const u64 *digits) {
+        typedef __attribute__((address_space(4))) const u64 scalar_u64;
+        scalar_u64 *c = (scalar_u64 *)reinterpret_cast<uintptr_t>(digits);
+#pragma unroll
+        for (int l = 0; l < 4; ++l) w[l] = c[7 * l];        // a word of every line
+    }
+    __device__ __forceinline__ void wait() const {
+#pragma unroll
+        for (int l = 0; l < 4; ++l) asm volatile("" : : "s"(w[l]));
+    }
+};
 // a pair of a polynomial of which the start is uniform: a scalar base and 32 bits of offset, no address arithmetic
 __device__ __forceinline__ ulonglong2 pair_at(const ulonglong2 *base, int tid) {
     typedef __attribute__((address_space(1))) const char global_char;
@@ -1311,6 +1327,9 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
             }
             continue;
         }
+        DigitLines lines;
+        const bool lone = FEW && T.digits && g == g0;
+        if (lone) lines.request(T.digits);
         // LDS phases of one rotation: the stash and B (gathers), A B A (inverse), then B A B A per digit.  Consecutive phases
         // use different buffers, which is what lets each exchange do with one barrier.
         const ulonglong2 *key = reinterpret_cast<const ulonglong2 *>(job.keys2) + (size_t)job.key_idx[g] * key_pairs;
@@ -1365,6 +1384,7 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
             kal[k] = pair_at(ka_last + k * NT, tid);
         }
         if (EARLY) pin_loads();
+        if (lone) lines.wait();
         __syncthreads();
         // the c0 part, permuted c0 (.) w, and the last digit's products: with the folded keys
         // (key_pack_kernel) they are products of the rotated c1 (.) w itself
