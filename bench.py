@@ -42,20 +42,23 @@ OPS_CONST_MUL = 8       # y*w mod q, a signed Montgomery product: 4 + 2 multiply
 OPS_QUOTIENT_MUL = 13   # the same with a precomputed quotient: 6 for the high product, 6 + 1 for y*w - h*q
 OPS_CSUB = 4            # a value brought near or below the modulus
 OPS_BF = OPS_CONST_MUL + 3                     # lazy butterfly: x + w y rides on the product, x - w y = 2x - (x + w y)
+OPS_DIGIT_PASS = 91     # the first three stages on eight gadget digits: a product with 2 multiply-adds, 2 sums of two and 4 of four such
+                        # products, each reduced once (4), and the sums and differences; twelve butterflies would take 132
 OPS_MAC128 = 10         # 64x64 product added into a 128-bit sum: 4 multiply-adds and 6 carry additions
 OPS_REDUCE128 = 2 * OPS_QUOTIENT_MUL + 2 * OPS_CSUB + 1
 # (2) 32x32-bit multiplies only, 7 per modular multiplication (four of the operand's words, one for the quotient
 #     modulo 2^32, two by the modulus), against the measured multiply issue rate.
 MUL32_PER_MODMUL = 7
+DIGIT_PASS_MODMULS = 9  # 42 multiply-adds and seven reductions of three multiplies
 
 
-def transform_ops(n, logn):
+def transform_ops(n, logn, digits=True):
     """Both directions are decimation-in-time transforms of lazy butterflies.  The inverse's first pass has seven constants
     of one in twelve butterflies and corrects eight of a thread's values twice, then twists and scales every word; the
-    forward transform corrects half of its words once."""
+    forward transform, of gadget digits or of whole words, corrects half of its words once."""
     half = n // 2
     inverse = half * logn * OPS_BF - n // 8 * 7 * OPS_CONST_MUL + n * OPS_CSUB + n * (OPS_CONST_MUL + OPS_CSUB)
-    forward = half * logn * OPS_BF + half * OPS_CSUB
+    forward = half * (logn - 3) * OPS_BF + (n // 8 * OPS_DIGIT_PASS if digits else half * 3 * OPS_BF) + half * OPS_CSUB
     return inverse, forward
 
 
@@ -74,7 +77,8 @@ def ops_per_fused_perm(n, logn, ndigits):
 def modmuls_per_fused_perm(n, logn, ndigits, scmult=True):
     """Modular multiplications of the same unit: butterflies of ndigits transforms, the inverse's twist, the key inner
     product and (scmult) the three products with the encoded weight."""
-    return ndigits * (n // 2) * logn - n // 8 * 7 + n + 2 * ndigits * n + (3 * n if scmult else 0)
+    return (ndigits * (n // 2) * logn - (ndigits - 1) * (n // 8) * (12 - DIGIT_PASS_MODMULS) - n // 8 * 7 + n + 2 * ndigits * n +
+            (3 * n if scmult else 0))
 
 
 def ops_per_fused_perm_special(n, logn, ndigits):
@@ -92,7 +96,8 @@ def ops_per_fused_perm_special(n, logn, ndigits):
 
 
 def modmuls_per_fused_perm_special(n, logn, ndigits):
-    return (2 + 2 * ndigits) * (n // 2) * logn - 3 * (n // 8 * 7) + 3 * n + 4 * ndigits * n + 3 * n + 4 * n
+    return ((2 + 2 * ndigits) * (n // 2) * logn - (2 * ndigits - 1) * (n // 8) * (12 - DIGIT_PASS_MODMULS) - 3 * (n // 8 * 7) + 3 * n +
+            4 * ndigits * n + 3 * n + 4 * n)
 
 
 def ops_decperm(n, logn, ndigits):
@@ -242,7 +247,7 @@ def fc_config(ctx, sk, D, torch, par, shape, steps, prewarm_s, cpu_sample, cpu_r
                             traffic_file=f"perm_accumulate_{shape.name}_hbm_traffic.txt" if not special else None)
     else:
         # no rotation at all: one ScMult and the mask's encoding (a transform mod p and one mod q) per input
-        inverse, forward = transform_ops(par.n, 11)
+        inverse, forward = transform_ops(par.n, 11, digits=False)
         roof = alu_roofline("scmult_masked_ring", kms, batch, 2 * par.n * OPS_CONST_MUL + inverse + forward + par.n * OPS_CONST_MUL,
                             11 * par.n + 3 * par.n,
                             note="latency-bound: one input is one workgroup of work; the figure is the launch's duration")
