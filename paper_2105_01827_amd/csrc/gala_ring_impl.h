@@ -1103,14 +1103,30 @@ __device__ __forceinline__ void mask_behind(const RingTables &T, const MaskJob &
     __syncthreads();        // the images may still be read
     mask_role<WIDE, S, ALONE>(T, mj, item, bufA, bufB, [&](int, int i, u64 m) { out[i] = sub_mod(out[i], m, q); });
 }
+// The kernel's arguments, read again where this is called; Args lists them as the kernel does (the segment holds them in order, each
+// at its natural alignment, as a struct does).  What a mask behind the rotations takes from them was otherwise loaded at the kernel's
+// start and kept through the rotations, in scalar registers that spilled to lanes of vector registers: 84 instead of 20 with weights, 23
+// now, and rotations up to a tenth slower: he_fc 1000x4096 at batch 8 (32 rotations a chunk) 611 us, 574 with
+// masks in workgroups of their own, 570 now; 500x1024 at batch 8 (four) 78.5, 84.8 and 73.9.
+template <class Args>
+__device__ __forceinline__ const Args &arguments_again() {
+    typedef __attribute__((address_space(4))) const char kernarg;
+    kernarg *p = (kernarg *)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));
+    return *(const Args *)(const char *)p;
+}
+struct PermArgs {
+    PermJob job;
+    RingTables T;
+    MaskJob mj;
+};
 // At n = 4096 a workgroup has a CU to itself and sums are cut into whole rounds of the 256 CUs.  In a launch of one round the masks
 // wait for the first workgroups to end, and then start from the beginning.  Where the G - 1 rotations do not divide by the number of
 // chunks the first chunk is one of the shorter ones, and a mask takes less than a rotation: there its workgroup builds the mask.
-// he_fc 500x1024 at batch 8 86.4 -> 80.4 us, 16x2048 at batch 64 55.2 -> 46.1, with the special prime 102.6 -> 91.5, 100x1000 at
-// batch 23 (253 chunks) 70.3 -> 63.8.  Not where CUs are left for a good part of the masks (9x600 at batch 100, 200 chunks: 43.6 us, 46.9
+// The layer alone: he_fc 500x1024 at batch 8 84.8 -> 73.9 us, 16x2048 at batch 64 54.4 -> 42.4, with the special prime 101.2 -> 90.0, 100x1000
+// at batch 23 (253 chunks) 70.3 -> 63.8; a convolution of 64 channels of 16x16 to 64, 3x3, at batch 16 181 -> 170, with the special
+// prime 338 -> 324.  Not where CUs are left for a good part of the masks (9x600 at batch 100, 200 chunks: 43.6 us, 46.9
 // behind first chunks), nor in launches of several rounds, whose tail the masks fill (16x2048 at batch 300 209 us and 220).
-// Instantiations of their own (MASK_BEHIND): the rotations of a kernel that has a mask behind them are up to a tenth slower (60x4000 at
-// batch 20 109 -> 119 us).
 static bool mask_in_first_chunk(const PermJob &job) {
     const long chunks = (long)job.items * job.nchunks, idle = 256 - chunks;
     return LOGN == 12 && (job.G - 1) % job.nchunks != 0 && idle >= 0 && idle < job.items && 4 * idle <= job.items;
@@ -1283,7 +1299,7 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
     // two wavefronts per SIMD, six: 103.2 us instead of 104.5 with three or eight.
     constexpr int AHEAD = FEW ? PER : LOGN == 12 ? 6 : LOGN == 13 ? 0 : 4, EARLY = LOGN == 13 ? 0 : PER;
     const int tid = threadIdx.x;
-    if ((int)blockIdx.x >= job.items * job.nchunks) {   // only launched when mj.enabled
+    if (!MASK_BEHIND && (int)blockIdx.x >= job.items * job.nchunks) {   // only launched when mj.enabled
         mask_partial<WIDE, PERM_S, FEW>(job, T, mj, (int)blockIdx.x - job.items * job.nchunks, bufA, bufB);
         return;
     }
@@ -1467,7 +1483,10 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
         out[i] = canonical<WIDE>(plain_words(sum0[k]), T);
         out[N + i] = canonical<WIDE>(plain_words(sum1[k]), T);
     }
-    if (MASK_BEHIND && chunk == 0) mask_behind<WIDE, PERM_S, FEW>(T, mj, item, bufA, bufB, out);
+    if (MASK_BEHIND && chunk == 0) {
+        const PermArgs &again = arguments_again<PermArgs>();
+        mask_behind<WIDE, PERM_S, FEW>(again.T, again.mj, item, bufA, bufB, out);
+    }
 }
 
 // Hoisted rotations of the input ciphertexts (Sec. III-B: one DecPerm shared by all the taps of a kernel,
@@ -1852,6 +1871,12 @@ struct SpecialJob {
     RingTables TP;          // transform tables of P
     ulonglong2 Pq, minus_Pinv;    // P and -P^-1 mod q, MontPairs
 };
+struct SpecialArgs {        // as PermArgs
+    PermJob job;
+    RingTables T;
+    SpecialJob S;
+    MaskJob mj;
+};
 
 // IN8: the inputs lie in blocks of eight coefficients (PermJob::in8_S), as the matrix-core product leaves them.
 template <bool WIDE, bool HAS_W, bool IN8 = false, bool MASK_BEHIND = false>
@@ -1864,7 +1889,7 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
     // words live in LDS slots of its own (no barrier), which is what two workgroups per CU leave room for.
     __shared__ u64 Rl[15 * NT];
     const int tid = threadIdx.x;
-    if ((int)blockIdx.x >= job.items * job.nchunks) {   // only launched when mj.enabled
+    if (!MASK_BEHIND && (int)blockIdx.x >= job.items * job.nchunks) {   // only launched when mj.enabled
         mask_partial<WIDE, PS>(job, T, mj, (int)blockIdx.x - job.items * job.nchunks, bufA, bufB);
         return;
     }
@@ -2075,7 +2100,10 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
             out[h * N + i] = unsign(mont<WIDE, false, true>(biased_words(minus), S.minus_Pinv, q), T.mod.q);
         }
     }
-    if (MASK_BEHIND && chunk == 0) mask_behind<WIDE, PS, false>(T, mj, item, bufA, bufB, out);
+    if (MASK_BEHIND && chunk == 0) {
+        const SpecialArgs &again = arguments_again<SpecialArgs>();
+        mask_behind<WIDE, PS, false>(again.T, again.mj, item, bufA, bufB, out);
+    }
 }
 
 // ---- hoisted input rotations with a special prime ----------------------------------------------------------

@@ -74,3 +74,22 @@ def test_large_layers_without_rotations_leave_room_for_four_wavefronts(kernels, 
     fits = {"ILb1E" in name for (m, name), k in kernels.items() if m == n and "scmult_masked_ring" in name and
             k[".vgpr_count"] <= 128 and k[".private_segment_fixed_size"] <= (60 if n == 8192 else 0)}
     assert fits == ({True, False} if n < 4096 else {True})
+
+
+@pytest.mark.parametrize("weights,blocks", [(1, 0), (0, 1), (0, 0)])
+@pytest.mark.parametrize("kernel,few", [("perm_accumulate_ring", "Lb0E"), ("perm_accumulate_special_ring", "")])
+def test_masks_behind_rotations_leave_their_scalars_alone(kernels, kernel, few, weights, blocks):
+    """What a mask needs of the arguments is read behind the rotations.  Kept through them it took 46 to 64 more
+    scalar registers than there are, in lanes of vector registers."""
+    form = f"{kernel}ILb1ELb{weights}ELb{blocks}E{few}"
+    plain, behind = ([k for (n, name), k in kernels.items() if n == 4096 and f"{form}Lb{mask}E" in name] for mask in (0, 1))
+    assert len(plain) == len(behind) == 1
+    assert behind[0][".sgpr_spill_count"] <= plain[0][".sgpr_spill_count"] + 12
+    # they are read as a struct of the arguments: in order, structs at multiples of 16 bytes
+    end = 0
+    for arg in behind[0][".args"]:
+        if arg[".value_kind"] != "by_value":
+            break
+        align = 4 if arg[".size"] == 4 else 16
+        assert arg[".offset"] == -(-end // align) * align
+        end = arg[".offset"] + arg[".size"]
