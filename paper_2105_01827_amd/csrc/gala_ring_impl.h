@@ -1124,12 +1124,18 @@ struct PermArgs {
 // wait for the first workgroups to end, and then start from the beginning.  Where the G - 1 rotations do not divide by the number of
 // chunks the first chunk is one of the shorter ones, and a mask takes less than a rotation: there its workgroup builds the mask.
 // The layer alone: he_fc 500x1024 at batch 8 84.8 -> 73.9 us, 16x2048 at batch 64 54.4 -> 42.4, with the special prime 101.2 -> 90.0, 100x1000
-// at batch 23 (253 chunks) 70.3 -> 63.8; a convolution of 64 channels of 16x16 to 64, 3x3, at batch 16 181 -> 170, with the special
-// prime 338 -> 324.  Not where CUs are left for a good part of the masks (9x600 at batch 100, 200 chunks: 43.6 us, 46.9
-// behind first chunks), nor in launches of several rounds, whose tail the masks fill (16x2048 at batch 300 209 us and 220).
+// at batch 23 (253 chunks) 69.2 -> 58.1; a convolution of 64 channels of 16x16 to 64, 3x3, at batch 16 181 -> 170, with the special
+// prime 338 -> 324.  What it saves is one mask, so it fades with the rotations of a chunk: of the longest chunk's 8 rotations
+// 147 -> 135 us (500x1024 at batch 16), of 32 518 -> 507 (120x4000 at batch 64), of 64 1017 -> 1006 (250x4000 at
+// batch 64) and with the special prime 2301 -> 2293; of 103 (1000x4096 at batch 25) 1734 -> 1739 and with it 4086 -> 4098, of 256 (batch 64)
+// 4241 -> 4264.  So up to 64.
+// Not where CUs are left for a good part of the masks (9x600 at batch 100, 200 chunks), nor in launches of several rounds, whose
+// tail the masks fill: measured before the arguments were read again, 43.6 and 46.9 us, 16x2048 at batch 300 209 and 220.
+// Since then 42.7 and 42.1, 205 and 191, with the special prime 87.7 and 87.3, 424 and 424: no longer a loss, and not taken up here.
 static bool mask_in_first_chunk(const PermJob &job) {
     const long chunks = (long)job.items * job.nchunks, idle = 256 - chunks;
-    return LOGN == 12 && (job.G - 1) % job.nchunks != 0 && idle >= 0 && idle < job.items && 4 * idle <= job.items;
+    const int longest = (job.G - 2) / job.nchunks + 1;
+    return LOGN == 12 && (job.G - 1) % job.nchunks != 0 && longest <= 64 && idle >= 0 && 4 * idle <= job.items;
 }
 // A layer without rotations (he_fc with G = 1: a matrix that fits one ciphertext; a convolution always has two kernel
 // orders at least) is one product and the mask: the workgroup that builds an item's mask forms its output at once, in one
@@ -2341,7 +2347,7 @@ static int launch_perm(const gala_ctx *c, void *stream, const PermJob &job, cons
             hipLaunchKernelGGL(kernel, grid, dim3(NT), 0, st, job, T, mj, c->gadget_bits, c->ndigits);
         };
 #if GALA_LOGN == 12
-        if (mj.first_chunk) {        // with all constants at the start 500x1024 at batch 8 takes 84.2 us, 80.4 without
+        if (mj.first_chunk) {        // with all constants at the start the layer 500x1024 at batch 8 takes 76.7 us, 74.4 without
             if (job.w) go(perm_accumulate_ring<WIDE, true, false, false, true>);
             else if (job.in8_S) go(perm_accumulate_ring<WIDE, false, true, false, true>);
             else go(perm_accumulate_ring<WIDE, false, false, false, true>);
