@@ -1369,6 +1369,7 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
         // are worked out again for each digit: kept, they were spilled with what they displaced (700 rotations 173 us, 151 now;
         // he_fc 100x784 at batch 64 250 us, 217 now).
         u32 from[PARK ? 4 : 1];
+        static_assert(!PARK || 8 * lds_words(PERM_S) <= 1 << 16);
         {
             const ulonglong2 *c0v = reinterpret_cast<const ulonglong2 *>(IN8 ? c0 + (size_t)tid * S : c0 + 8 * tid),
                              *c1v = reinterpret_cast<const ulonglong2 *>(IN8 ? c1 + (size_t)tid * S : c1 + 8 * tid);
@@ -1946,7 +1947,8 @@ __global__ __launch_bounds__(NT, 2) void perm_accumulate_special_ring(PermJob jo
         const ulonglong2 *key = reinterpret_cast<const ulonglong2 *>(job.keys2) + (size_t)job.key_idx[g] * key_pairs;
         const unsigned turn = (unsigned)((2 * bitrev(tid) + 1) * gal) >> 1;
         u64 a[PER];
-        u32 from[4];
+        u32 from[4];      // byte offsets into an image, two to a register
+        static_assert(8 * lds_words(PS) <= 1 << 16);
         {
             const ulonglong2 *c0v = reinterpret_cast<const ulonglong2 *>(IN8 ? c0 + (size_t)tid * S8 : c0 + 8 * tid),
                              *c1v = reinterpret_cast<const ulonglong2 *>(IN8 ? c1 + (size_t)tid * S8 : c1 + 8 * tid);
