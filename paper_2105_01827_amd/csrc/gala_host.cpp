@@ -120,6 +120,29 @@ void NttHost::init(int n_, u64 q, u64 psi_) {
     }
     one_m = mont_pair(1, mont);
 }
+// Constants of the first pass on eight gadget digits (digit_pass in gala_ring_impl.h), words w 2^32 mod m.  t[0] .. t[6] are the
+// first block's.  In this order: t0 of x4; by twos, what the sums for stage 2 and stage 3 of two blocks multiply x2 and x6, x1, x5, x3 and
+// x7 with.  Returns whether a sum's low words leave 64 bits room for the reduction.
+bool digit_pass_constants(const NttHost &h, int gadget_bits, u64 *a) {
+    const u64 m = h.mod.q, *t = h.tw.data() + 1;
+    const MontMaker mont = make_mont(m);
+    auto mul = [&](u64 x, u64 y) { return mul_mod(x, y, h.mod); };
+    auto neg = [&](u64 x) { return x ? m - x : 0; };
+    const u64 t10 = mul(t[1], t[0]), t20 = mul(t[2], t[0]);
+    std::vector<u64> w = {t[0], t[1], t[2], t10, neg(t20), 0};
+    const u64 odd[2][3] = {{t[0], t[1], t10}, {neg(t[0]), t[2], neg(t20)}};       // of x5, x3, x7
+    for (int b = 0; b < 2; ++b) {
+        const u64 u = t[3 + 2 * b], v = t[4 + 2 * b];
+        w.insert(w.end(), {u, v, mul(u, odd[b][0]), mul(v, odd[b][0]), mul(u, odd[b][1]), neg(mul(v, odd[b][1])), mul(u, odd[b][2]),
+                           neg(mul(v, odd[b][2]))});
+    }
+    for (int k = 0; k < kDigitPassWords; ++k) a[k] = mont_pair(w[k], mont).a;
+    auto low = [&](int k) { return (u128)std::llabs((long long)(int)(u32)a[k]); };
+    u128 most = std::max(low(0), std::max(low(1) + low(3), low(2) + low(4)));
+    for (int k = 6; k < kDigitPassWords; k += 8)
+        for (int e = k; e < k + 2; ++e) most = std::max(most, low(e) + low(e + 2) + low(e + 4) + low(e + 6));
+    return gadget_bits <= 31 && (most << gadget_bits) + ((u128)1 << 59) < ((u128)1 << 63);
+}
 void NttHost::forward(u64 *a) const {
     const u64 q = mod.q, q2 = mod.q2;
     for (int m = 1, t = n >> 1; m < n; m <<= 1, t >>= 1)
@@ -421,30 +444,11 @@ extern "C" int gala_ctx_create(const gala_params *par, gala_ctx **out) {
             for (size_t k = 0; k < w.size(); ++k) out[k] = mont_pair(w[k], mont);
             return out;
         };
-        // Behind a modulus' tables: the constants of the first pass on eight gadget digits (digit_pass in gala_ring_impl.h), words
-        // w 2^32 mod m, two to a pair.  t[0] .. t[6] are the first block's.  In this order: t0 of x4; by twos, what the sums for stage 2 and
-        // stage 3 of two blocks multiply x2 and x6, x1, x5, x3 and x7 with.  A sum's low words must leave 64 bits room for the reduction.
+        // behind a modulus' tables
         auto append_digit_sums = [&](std::vector<MontPair> &out, NttHost &h) {
-            const u64 m = h.mod.q, *t = h.tw.data() + 1;
-            const MontMaker mont = make_mont(m);
-            auto mul = [&](u64 x, u64 y) { return mul_mod(x, y, h.mod); };
-            auto neg = [&](u64 x) { return x ? m - x : 0; };
-            const u64 t10 = mul(t[1], t[0]), t20 = mul(t[2], t[0]);
-            std::vector<u64> w = {t[0], t[1], t[2], t10, neg(t20), 0};
-            const u64 odd[2][3] = {{t[0], t[1], t10}, {neg(t[0]), t[2], neg(t20)}};       // of x5, x3, x7
-            for (int b = 0; b < 2; ++b) {
-                const u64 u = t[3 + 2 * b], v = t[4 + 2 * b];
-                w.insert(w.end(), {u, v, mul(u, odd[b][0]), mul(v, odd[b][0]), mul(u, odd[b][1]), neg(mul(v, odd[b][1])), mul(u, odd[b][2]),
-                                   neg(mul(v, odd[b][2]))});
-            }
-            u64 a[22];
-            for (int k = 0; k < 22; ++k) a[k] = mont_pair(w[k], mont).a;
-            for (int k = 0; k < 22; k += 2) out.push_back({a[k], a[k + 1]});
-            auto low = [&](int k) { return (u128)std::llabs((long long)(int)(u32)a[k]); };
-            u128 most = std::max(low(0), std::max(low(1) + low(3), low(2) + low(4)));
-            for (int k = 6; k < 22; k += 8)
-                for (int e = k; e < k + 2; ++e) most = std::max(most, low(e) + low(e + 2) + low(e + 4) + low(e + 6));
-            h.digit_sums = c->gadget_bits <= 31 && (most << c->gadget_bits) + ((u128)1 << 59) < ((u128)1 << 63);
+            u64 a[kDigitPassWords];
+            h.digit_sums = digit_pass_constants(h, c->gadget_bits, a);
+            for (int k = 0; k < kDigitPassWords; k += 2) out.push_back({a[k], a[k + 1]});
         };
         pairs = pack(build(c->ntt_q), q);
         append_digit_sums(pairs, c->ntt_q);

@@ -56,7 +56,7 @@ struct NttHost {
     u64 ninv = 0, ninvs = 0, itw1n = 0, itw1ns = 0;
     u64 w8[3] = {0, 0, 0};                       // powers 1, 2, 3 of psi^(-2n/8)
     MontPair w8m[3] = {}, one_m{};               // ... and the constant 1 for the ring kernels
-    bool digit_sums = false;                     // the context's gadget digits fit the ring kernels' sums of products (append_digit_sums)
+    bool digit_sums = false;                     // the context's gadget digits fit the ring kernels' sums of products (digit_pass_constants)
 
     void init(int n, u64 q, u64 psi);
     void forward(u64 *a) const;   // in place, canonical in -> canonical out
@@ -69,6 +69,9 @@ struct NttDev {
     u64 ninv, ninvs, itw1n, itw1ns;
     Modulus mod;
 };
+
+constexpr int kDigitPassWords = 22;
+bool digit_pass_constants(const NttHost &h, int gadget_bits, u64 *words);
 
 u64 pow_mod(u64 b, u64 e, u64 m);
 u64 inv_mod(u64 a, u64 m);

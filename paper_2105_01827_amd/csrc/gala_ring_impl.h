@@ -340,8 +340,8 @@ __device__ __forceinline__ void fwd_pass(u64 (&a)[8], const Tw7 &w, const MontQ 
 // The first pass on eight gadget digits x_0 .. x_7, not biased; a biased.  Digits are short, so products of several of them by
 // constants add up in the words of one product and are reduced together: three of stages 1 and 2 for x_0, x_2, x_4, x_6, and what stage 3
 // adds to and takes from those, sums of four products of x_1, x_3, x_5, x_7 each.  91 instructions instead of 144, or 132 with
-// a first stage of small factors.  Constants (see append_digit_sums): words w 2^32 mod m alone, the other half of a pair has nothing to
-// multiply.  Bounds with digits of 30 bits: 0.63 | 1.4 | 2.4.
+// a first stage of small factors.  Constants (see digit_pass_constants): words w 2^32 mod m alone, the other half of a pair has nothing to
+// multiply.  Bounds with digits of 30 bits: 0.63 | 1.4 | 2.4; of 31, taken where the low words leave room: 0.75 | 1.75 | 3.25.
 // With offsets of bytes for the gathers (Perm kernels), from wire to wire: he_fc 1000x2048 at batch 64 1711 -> 1676 us, 128x1024 135.2 -> 133.1,
 // the 16x16x128 convolution at batch 16 245.0 -> 241.9.
 template <bool WIDE>

@@ -14,11 +14,10 @@ from tests.test_gpu_parity import both
 
 pytestmark = pytest.mark.gpu
 
+RINGS, BITS = [1024, 2048, 4096, 8192], [12, 20, 28, 29, 30, 31, 32]
 
-@pytest.mark.parametrize("special", [False, True])
-@pytest.mark.parametrize("bits", [12, 20, 28, 29, 30, 31, 32])
-@pytest.mark.parametrize("n", [1024, 2048, 4096, 8192])
-def test_rotations(n, bits, special):
+
+def parameters(n, bits, special):
     if special and (n == 8192 or bits == 32):
         pytest.skip("no kernels of its own, or as without a special prime")
     par = small_params(n, gadget_bits=bits)
@@ -26,6 +25,15 @@ def test_rotations(n, bits, special):
         par = dataclasses.replace(wl.DEFAULT, gadget_bits=bits)      # a short low word
     if special:
         par = dataclasses.replace(par, special=wl.find_prime_below(1 << 60, 2 * n))
+    return par
+
+
+# which of them take the sums of products: test_digit_pass_host.py
+@pytest.mark.parametrize("special", [False, True])
+@pytest.mark.parametrize("bits", BITS)
+@pytest.mark.parametrize("n", RINGS)
+def test_rotations(n, bits, special):
+    par = parameters(n, bits, special)
     ctx, o = both(par)
     sk, osk = ctx.keygen(3), o.keygen(3)
     rng = np.random.default_rng(n + bits)
