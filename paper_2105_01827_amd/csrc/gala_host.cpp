@@ -137,11 +137,21 @@ bool digit_pass_constants(const NttHost &h, int gadget_bits, u64 *a) {
                            neg(mul(v, odd[b][2]))});
     }
     for (int k = 0; k < kDigitPassWords; ++k) a[k] = mont_pair(w[k], mont).a;
-    auto low = [&](int k) { return (u128)std::llabs((long long)(int)(u32)a[k]); };
-    u128 most = std::max(low(0), std::max(low(1) + low(3), low(2) + low(4)));
+    // digits are not negative: what a sum's positive low words reach and what its negative ones do are never there together
+    long long most = 0;
+    auto sum = [&](std::initializer_list<int> terms) {
+        long long up = 0, down = 0;
+        for (int k : terms) {
+            const int low = (int)(u32)a[k];
+            (low > 0 ? up : down) += low;
+        }
+        most = std::max({most, up, -down});
+    };
+    sum({0});
+    for (int e = 1; e < 3; ++e) sum({e, e + 2});
     for (int k = 6; k < kDigitPassWords; k += 8)
-        for (int e = k; e < k + 2; ++e) most = std::max(most, low(e) + low(e + 2) + low(e + 4) + low(e + 6));
-    return gadget_bits <= 31 && (most << gadget_bits) + ((u128)1 << 59) < ((u128)1 << 63);
+        for (int e = k; e < k + 2; ++e) sum({e, e + 2, e + 4, e + 6});
+    return gadget_bits <= 31 && ((u128)most << gadget_bits) + ((u128)1 << 59) < ((u128)1 << 63);
 }
 void NttHost::forward(u64 *a) const {
     const u64 q = mod.q, q2 = mod.q2;

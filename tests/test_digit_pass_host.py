@@ -26,6 +26,9 @@ extern "C" int read_transform(const gala_ctx *c, int special, unsigned long long
 # results of the three stages in multiples of the modulus, as stated beside the kernel; the general pass has 3.5 after the third
 BOUNDS = {30: (0.63, 1.4, 2.4), 31: (0.75, 1.75, 3.25)}
 
+# the constants whose products are added up: of x4; x2 and x6; x1, x5, x3 and x7
+SUMS = [(0,), (1, 3), (2, 4)] + [(c, c + 2, c + 4, c + 6) for c in (6, 7, 14, 15)]
+
 
 @pytest.fixture(scope="module")
 def read_transform(tmp_path_factory):
@@ -103,11 +106,13 @@ def test_sums_of_products(read_transform, n, bits, special):
     for modulus in range(2 if special else 1):
         taken, m, tw, words = read_transform(par, modulus)
         assert m == (par.special if modulus else par.q)
-        if not taken:
+        the_pass = Pass(m, words)
+        if not taken:        # not for nothing: digits of zeros and ones fill the words, but for what the reduction may add
             assert bits > 30
+            low = [[the_pass.words[k][0] for k in terms] for terms in SUMS]
+            assert bits > 31 or max(abs(sum(w for w in s if w * sign > 0)) for s in low for sign in (1, -1)) << bits >= (1 << 63) - (1 << 59)
             continue
         assert bits <= 31
-        the_pass = Pass(m, words)
         for x in itertools.chain(itertools.product((0, top), repeat=8), [(1, top, 2, top - 1, 3, top // 2, 4, top // 3)]):
             stages = the_pass.run(x)
             assert [v % m for v in stages[2]] == three_stages(x, tw, m)
