@@ -342,8 +342,9 @@ __device__ __forceinline__ void fwd_pass(u64 (&a)[8], const Tw7 &w, const MontQ 
 // adds to and takes from those, sums of four products of x_1, x_3, x_5, x_7 each.  91 instructions instead of 144, or 132 with
 // a first stage of small factors.  Constants (see digit_pass_constants): words w 2^32 mod m alone, the other half of a pair has nothing to
 // multiply.  Bounds with digits of 30 bits: 0.63 | 1.4 | 2.4; of 31, taken where the low words leave room: 0.75 | 1.75 | 3.25.
-// With offsets of bytes for the gathers (Perm kernels), from wire to wire: he_fc 1000x2048 at batch 64 1711 -> 1676 us, 128x1024 135.2 -> 133.1,
-// the 16x16x128 convolution at batch 16 245.0 -> 241.9.
+// A launch of the Perm kernel has 3.5 % fewer instructions, the byte offsets of its gathers included.  From wire to wire he_fc 1000x2048 at batch 64
+// 1711 -> 1676 us, 128x1024 135.2 -> 133.1, the 16x16x128 convolution at batch 16 245.0 -> 241.9: 1 to 2 %, within what runs timed
+// in turn differ by.  The byte offsets alone 1670 -> 1664, 131.9 -> 131.3 and 235.7 -> 235.0, 500x1024 at n = 4096 90.0 -> 90.6: nothing.
 template <bool WIDE>
 __device__ __forceinline__ void digit_pass(u64 (&a)[8], const u32 (&x)[8], const u64 *constants, const MontQ &q) {
     typedef __attribute__((address_space(4))) const u64 scalar_u64;
@@ -1252,7 +1253,7 @@ __device__ __forceinline__ ulonglong2 pair_at(const ulonglong2 *base, int tid) {
     global_u64 *at = (global_u64 *)(p + (unsigned)tid * 16u);
     return make_ulonglong2(at[0], at[1]);
 }
-// What bounds the Perm kernel, in clocks of a CU per wavefront and rotation at n = 2048 with weights: the vector ALU, some 2730
+// What bounds the Perm kernel, in clocks of a CU per wavefront and rotation at n = 2048 with weights: the vector ALU, some 2625
 // instructions at one a clock, and behind it the vector cache, 113 loads at 16 clocks (178 before the first pass's
 // constants came through the scalar cache, the small levels through LDS, and c0 and c1 were read once, by the threads that own
 // them, instead of being gathered from memory), and the LDS, about 1250.  Most of what it waited for was the L2, where constants of 94 KiB a workgroup
@@ -1293,7 +1294,7 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
     __shared__ ulonglong2 tables[PERM_LEVELS ? TableCopy<PERM_LEVELS>::PAIRS : 1];
     // each thread parks its 8 coefficients here between digits (private slots, no barrier); at n = 8192 there is no LDS
     // left for them and they are variables: the workgroup's four wavefronts per SIMD leave 128 registers, and the
-    // compiler spills 62 with weights, 75 on blocks of eight and 55 on whole ciphertexts (188, 264 and 216 bytes of
+    // compiler spills 62 with weights, 74 on blocks of eight and 54 on whole ciphertexts (188, 260 and 212 bytes of
     // scratch a lane).  Against the any-n kernel he_fc 200x8192 at batch 40 takes 2345 us instead of 5562 all the same.
     // Before that a rotation's c0 (.) w waits here, and c1 (.) w in bufB, for the threads that gather them.
     constexpr bool PARK = LOGN < 13;
@@ -2147,7 +2148,8 @@ __global__ __launch_bounds__(NT) void decperm_special_ring(const u64 *ct_in, u64
 // sum modulo P back to coefficients, lifted, reduced modulo q and transformed forward again, then
 // out = (P c0(X^g) + t_b - NTT(r_b)) / P or (t_a - NTT(r_a)) / P.  Output: xrot[ct][tap][c0|c1][i], canonical.
 // A polynomial a workgroup instead of both, one after the other: 118 registers instead of 146, so four wavefronts per SIMD instead
-// of three, and half the chain of steps: the 16x16x128 convolution at batch 16 (2048 rotations) 421 -> 413 us.  The vector ALU
+// of three, and half the chain of steps: the 16x16x128 convolution at batch 16 (2048 rotations) 421 -> 413 us,
+// which is within what runs timed in turn differ by.  The vector ALU
 // (1700 instructions a wavefront) and the vector cache (some 100 loads at 16 clocks) are busy for about 50 of its 90 us each.
 template <bool WIDE>
 __global__ __launch_bounds__(NT, 4) void hstperm_special_ring(const u64 *ct_in, const u64 *digits, TermList terms,
