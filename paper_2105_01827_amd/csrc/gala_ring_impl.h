@@ -1230,7 +1230,9 @@ __device__ __forceinline__ u64 word_at(const u64 *image, u32 offset) {
 }
 // Brings the constants of digit_pass into the scalar cache while something else is waited for: its own three loads, one after the other,
 // each wait for memory otherwise.  he_fc 1000x512 on one input 32.3 -> 31.7 us from wire to wire.  Not for a second entry of a sum (32.0
-// with the first two), nor where registers are short (with the special prime 58.9 -> 59.8, 100x784 at batch 7).
+// with the first two), nor where registers are short: with the special prime 58.9 -> 59.8 (100x784 at batch 7), on blocks of eight four
+// spilled at n = 4096 (a convolution of 7x7x17 to 48 channels at batch 6 111.9 -> 114.1 us, 112.2 before the digit pass) and nothing was gained
+// at 2048 (13x11x24 to 40 at batch 5 64.3 and 64.2, 32x32x23 to 13, 1x1, at batch 2 39.9 -> 41.8).
 struct DigitLines {
     u64 w[4];
     __device__ __forceinline__ void request(const u64 *digits) {
@@ -1351,7 +1353,7 @@ __global__ __launch_bounds__(NT, FEW ? 2 : PERM_WAVES) void perm_accumulate_ring
             continue;
         }
         DigitLines lines;
-        const bool lone = FEW && T.digits && g == g0;
+        const bool lone = FEW && !IN8 && T.digits && g == g0;
         if (lone) lines.request(T.digits);
         // LDS phases of one rotation: the stash and B (gathers), A B A (inverse), then B A B A per digit.  Consecutive phases
         // use different buffers, which is what lets each exchange do with one barrier.

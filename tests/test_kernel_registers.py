@@ -93,3 +93,10 @@ def test_masks_behind_rotations_leave_their_scalars_alone(kernels, kernel, few, 
         align = 4 if arg[".size"] == 4 else 16
         assert arg[".offset"] == -(-end // align) * align
         end = arg[".offset"] + arg[".size"]
+
+
+@pytest.mark.parametrize("weights,blocks", [(1, 0), (0, 1), (0, 0)])
+def test_small_launches_of_rotations_spill_nothing(kernels, weights, blocks):
+    found = {n: k for (n, name), k in kernels.items() if n < 8192 and f"perm_accumulate_ringILb1ELb{weights}ELb{blocks}ELb1ELb0E" in name}
+    assert set(found) == {1024, 2048, 4096}
+    assert all(k[".private_segment_fixed_size"] == 0 for k in found.values()), {n: k[".vgpr_spill_count"] for n, k in found.items()}
